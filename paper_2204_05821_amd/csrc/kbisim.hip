@@ -729,7 +729,6 @@ int build_schedule_device(kbisim_ctx *c, const int64_t *ptr, Schedule &s, int ra
 int build_schedule(kbisim_ctx *c, const int64_t *ptr, Schedule &s, int range_edges, int64_t row_max,
                    int64_t staged_max) {
   const int64_t n = c->g.n;
-  const Tuning &t = c->tune;
   s = Schedule{};
   s.range_edges = range_edges;
   // (the device walk needs 80 bytes of scratch per chunk in the 4n bytes of vlist)
