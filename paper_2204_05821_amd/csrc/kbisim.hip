@@ -291,6 +291,9 @@ int hip_fail(hipError_t e) {
 
 inline unsigned blocks_for(int64_t items, int per) { return (unsigned)((items + per - 1) / per); }
 
+// Workgroups of the radix kernels (see radix_tile).
+unsigned radix_grid(int64_t ntiles) { return (unsigned)((ntiles + XCDS - 1) / XCDS * XCDS); }
+
 // Range check of cnt int32 values on stream s (see k_validate_vals).
 void validate_vals(hipStream_t s, int64_t cnt, const int32_t *vals, int64_t upper, u32 *err, u32 bit) {
   if (cnt <= 0) return;
@@ -898,14 +901,14 @@ int build_rank(kbisim_ctx *c) {
   // stable LSD passes of 8 bits over key bits [32, 32 + bits)
   auto radix_passes = [&](int bits) -> int {
     for (int shift = 32; shift < 32 + bits; shift += 8) {
-      k_radix_hist<<<(unsigned)rtiles, 256, 0, c->stream>>>(n, ka, shift, rtiles, hist);
+      k_radix_hist<<<radix_grid(rtiles), RADIX_THREADS, 0, c->stream>>>(n, ka, shift, rtiles, hist);
       LAUNCH_CHECK();
       const int64_t nt = (hist_n + SCAN_TILE - 1) / SCAN_TILE;
       k_sum_tiles64<<<(unsigned)nt, 256, 0, c->stream>>>(hist_n, hist, tiles);
       k_scan_tiles64<<<1, 256, 0, c->stream>>>(nt, tiles);
       k_write_ptr64<<<(unsigned)nt, 256, 0, c->stream>>>(hist_n, hist, tiles, offs, nullptr);
       LAUNCH_CHECK();
-      k_radix_scatter<<<(unsigned)rtiles, 256, 0, c->stream>>>(n, ka, shift, rtiles, offs, hist, kb);
+      k_radix_scatter<<<radix_grid(rtiles), RADIX_THREADS, 0, c->stream>>>(n, ka, shift, rtiles, offs, kb);
       LAUNCH_CHECK();
       std::swap(ka, kb);
     }
@@ -2656,10 +2659,10 @@ int kbisim_quotient(kbisim_ctx *c, const int32_t *src_pid, const int32_t *dst_pi
                          tgt, q, ka);
   if (rc) return rc;
   for (int shift = 0; shift < total_bits; shift += 8) {
-    k_radix_hist<<<(unsigned)p.rtiles, 256, 0, s>>>(m, ka, shift, p.rtiles, hist);
+    k_radix_hist<<<radix_grid(p.rtiles), RADIX_THREADS, 0, s>>>(m, ka, shift, p.rtiles, hist);
     HIP_TRY(hipGetLastError());
     if ((rc = scan64(s, p.hist_n, hist, tiles, offs))) return rc;
-    k_radix_scatter<<<(unsigned)p.rtiles, 256, 0, s>>>(m, ka, shift, p.rtiles, offs, hist, kb);
+    k_radix_scatter<<<radix_grid(p.rtiles), RADIX_THREADS, 0, s>>>(m, ka, shift, p.rtiles, offs, kb);
     HIP_TRY(hipGetLastError());
     std::swap(ka, kb);
   }

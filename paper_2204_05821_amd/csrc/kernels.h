@@ -1676,13 +1676,33 @@ __device__ inline int64_t block_exclusive_scan64(int64_t mine, int64_t *sh_w, in
   return base + x - mine;
 }
 
+// The SCAN_ITEMS counts from base on (zeros past n), 16 bytes per load where
+// the array allows.
+__device__ inline void scan_items(int64_t n, const int *__restrict__ cnt, int64_t base, int (&c)[SCAN_ITEMS]) {
+  if (base + SCAN_ITEMS <= n && (reinterpret_cast<uintptr_t>(cnt) & 15) == 0) {
+    const int4 *p4 = reinterpret_cast<const int4 *>(cnt + base);
+#pragma unroll
+    for (int q = 0; q < SCAN_ITEMS / 4; ++q) {
+      const int4 x = p4[q];
+      c[4 * q] = x.x;
+      c[4 * q + 1] = x.y;
+      c[4 * q + 2] = x.z;
+      c[4 * q + 3] = x.w;
+    }
+  } else {
+#pragma unroll
+    for (int j = 0; j < SCAN_ITEMS; ++j) c[j] = base + j < n ? cnt[base + j] : 0;
+  }
+}
+
 __global__ void __launch_bounds__(256) k_sum_tiles64(int64_t n, const int *__restrict__ cnt, int64_t *tile_sum) {
   __shared__ int64_t sh_w[4];
   const int64_t base = (int64_t)blockIdx.x * SCAN_TILE + (int64_t)threadIdx.x * SCAN_ITEMS;
+  int c[SCAN_ITEMS];
+  scan_items(n, cnt, base, c);
   int64_t mine = 0;
 #pragma unroll
-  for (int j = 0; j < SCAN_ITEMS; ++j)
-    if (base + j < n) mine += cnt[base + j];
+  for (int j = 0; j < SCAN_ITEMS; ++j) mine += c[j];
   int64_t total;
   block_exclusive_scan64(mine, sh_w, &total);
   if (threadIdx.x == 0) tile_sum[blockIdx.x] = total;
@@ -1694,12 +1714,23 @@ __global__ void __launch_bounds__(256) k_scan_tiles64(int64_t ntiles, int64_t *t
   __shared__ int64_t carry;
   if (threadIdx.x == 0) carry = 0;
   __syncthreads();
-  for (int64_t b0 = 0; b0 < ntiles; b0 += 256) {
-    const int64_t i = b0 + threadIdx.x;
-    const int64_t mine = i < ntiles ? tile_sum[i] : 0;
+  constexpr int PER = 8;  // consecutive sums per thread and round
+  for (int64_t b0 = 0; b0 < ntiles; b0 += 256 * PER) {
+    const int64_t i0 = b0 + (int64_t)threadIdx.x * PER;
+    int64_t c[PER];
+    int64_t mine = 0;
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+      c[j] = i0 + j < ntiles ? tile_sum[i0 + j] : 0;
+      mine += c[j];
+    }
     int64_t total;
-    const int64_t ex = block_exclusive_scan64(mine, sh_w, &total);
-    if (i < ntiles) tile_sum[i] = carry + ex;
+    int64_t at = carry + block_exclusive_scan64(mine, sh_w, &total);
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+      if (i0 + j < ntiles) tile_sum[i0 + j] = at;
+      at += c[j];
+    }
     __syncthreads();
     if (threadIdx.x == 0) carry += total;
     __syncthreads();
@@ -1712,15 +1743,25 @@ __global__ void __launch_bounds__(256) k_write_ptr64(int64_t n, const int *__res
                                                      unsigned long long *cursor) {
   __shared__ int64_t sh_w[4];
   const int64_t base = (int64_t)blockIdx.x * SCAN_TILE + (int64_t)threadIdx.x * SCAN_ITEMS;
-  int64_t c[SCAN_ITEMS];
+  int c[SCAN_ITEMS];
+  scan_items(n, cnt, base, c);
   int64_t mine = 0;
 #pragma unroll
-  for (int j = 0; j < SCAN_ITEMS; ++j) {
-    c[j] = base + j < n ? cnt[base + j] : 0;
-    mine += c[j];
-  }
+  for (int j = 0; j < SCAN_ITEMS; ++j) mine += c[j];
   int64_t total;
   int64_t off = tile_pre[blockIdx.x] + block_exclusive_scan64(mine, sh_w, &total);
+  const bool vec = base + SCAN_ITEMS < n && ((reinterpret_cast<uintptr_t>(out_ptr) |
+                                              reinterpret_cast<uintptr_t>(cursor)) & 15) == 0;
+  if (vec) {
+#pragma unroll
+    for (int j = 0; j < SCAN_ITEMS; j += 2) {
+      const longlong2 two = make_longlong2(off, off + c[j]);
+      reinterpret_cast<longlong2 *>(out_ptr + base)[j / 2] = two;
+      if (cursor) reinterpret_cast<longlong2 *>(cursor + base)[j / 2] = two;
+      off += c[j] + (int64_t)c[j + 1];
+    }
+    return;
+  }
 #pragma unroll
   for (int j = 0; j < SCAN_ITEMS; ++j) {
     if (base + j < n) {
@@ -2068,94 +2109,138 @@ __global__ void __launch_bounds__(256) k_quotient_hubs(Src src, const Chunk *__r
   for (int64_t e = row + c.b + threadIdx.x; e < row + c.e; e += 256) keys[e] = quotient_key(src, tgt, q, sb, e);
 }
 
-constexpr int RADIX_ITEMS = 16;                  // keys per thread per tile
-constexpr int RADIX_TILE = 256 * RADIX_ITEMS;    // keys per tile
+// Tiles of 8192 keys: the 32 keys a digit gets on average leave as whole
+// lines.  A summary graph of 125M entries (7 passes): 8.5 ms with 8192-key
+// tiles against 9.25 with 4096; 16384 leave one workgroup per CU (8.6
+// against 7.6 ms, both with the mapping below).
+constexpr int RADIX_ITEMS = 16;  // keys per thread per tile
+constexpr int RADIX_THREADS = 512;
+constexpr int RADIX_TILE = RADIX_THREADS * RADIX_ITEMS;
+constexpr int XCDS = 8;  // workgroups go to the XCDs in turn
+// Tile of this workgroup (>= ntiles: none; grids are padded to a multiple of
+// XCDS): each XCD takes a contiguous share of the tiles in order, so that the
+// runs that neighbouring tiles write side by side meet in one L2 and leave it
+// as whole lines (9.25 -> 7.6 ms per summary graph of 125M entries).
+__device__ inline int64_t radix_tile(int64_t ntiles) {
+  return (int64_t)(blockIdx.x % XCDS) * ((ntiles + XCDS - 1) / XCDS) + blockIdx.x / XCDS;
+}
 
 // Digit histogram of each tile: hist[digit * ntiles + tile].
-__global__ void __launch_bounds__(256) k_radix_hist(int64_t m, const u64 *__restrict__ keys, int shift, int64_t ntiles,
+template <class K>
+__global__ void __launch_bounds__(RADIX_THREADS) k_radix_hist(int64_t m, const K *__restrict__ keys, int shift, int64_t ntiles,
                                                     int *__restrict__ hist) {
   __shared__ int h[256];
-  h[threadIdx.x] = 0;
+  const int64_t tile = radix_tile(ntiles);
+  if (tile >= ntiles) return;
+  if (threadIdx.x < 256) h[threadIdx.x] = 0;
   __syncthreads();
-  const int64_t base = (int64_t)blockIdx.x * RADIX_TILE;
+  const int64_t base = tile * RADIX_TILE;
   // every key of the thread is requested before the first count
-  u64 kk[RADIX_ITEMS];
+  K kk[RADIX_ITEMS];
 #pragma unroll
   for (int j = 0; j < RADIX_ITEMS; ++j) {
-    const int64_t i = base + j * 256 + threadIdx.x;
-    kk[j] = i < m ? __builtin_nontemporal_load(&keys[i]) : 0ULL;
+    const int64_t i = base + j * RADIX_THREADS + threadIdx.x;
+    kk[j] = i < m ? __builtin_nontemporal_load(&keys[i]) : (K)0;
   }
 #pragma unroll
   for (int j = 0; j < RADIX_ITEMS; ++j)
-    if (base + j * 256 + threadIdx.x < m) atomicAdd(&h[(kk[j] >> shift) & 255], 1);
+    if (base + j * RADIX_THREADS + threadIdx.x < m) atomicAdd(&h[(u32)(kk[j] >> shift) & 255u], 1);
   __syncthreads();
-  hist[(int64_t)threadIdx.x * ntiles + blockIdx.x] = h[threadIdx.x];
+  if (threadIdx.x < 256) hist[(int64_t)threadIdx.x * ntiles + tile] = h[threadIdx.x];
 }
 
-// Stable scatter of a tile.  Keys are ranked chunk by chunk (256 keys, in
-// index order); inside a chunk, lanes with equal digits are found with one
-// ballot per digit bit, and waves are ordered through per-digit counts.  Each
-// key first goes to its digit-sorted place inside the tile, in LDS; then the
-// tile is written out in that order, so the keys of one digit leave as one
-// run of consecutive addresses (whole lines) instead of one scattered key
-// per lane.  hist holds the tile's digit counts (k_radix_hist).
-__global__ void __launch_bounds__(256) k_radix_scatter(int64_t m, const u64 *__restrict__ keys, int shift,
+// Stable scatter of a tile.  Each wave ranks its own 1024 consecutive keys by
+// itself: per 64 keys, the lanes with equal digits are found with one ballot
+// per digit bit, and a wave-private count per digit carries on (LDS accesses
+// of one wave stay in order, so the loop has no workgroup barrier; ranking
+// the tile in chunks of 256 keys took three barriers per chunk).  A scan over
+// digits and waves then gives every key its place in the tile, the tile is
+// put in digit order in LDS and written out in that order, so the keys of one
+// digit leave as one run of consecutive addresses (whole lines).
+// Bound by the ranking's LDS round trips and HBM (16 bytes per 64-bit key).
+template <class K>
+__global__ void __launch_bounds__(RADIX_THREADS) k_radix_scatter(int64_t m, const K *__restrict__ keys, int shift,
                                                        int64_t ntiles, const int64_t *__restrict__ offs,
-                                                       const int *__restrict__ hist, u64 *__restrict__ out) {
-  __shared__ u64 sk[RADIX_TILE];     // the tile in digit order
-  __shared__ int64_t base[256];      // global position of the tile's first key of each digit
-  __shared__ int tstart[256];        // tile position of the first key of each digit
-  __shared__ int run[256];           // keys of each digit placed so far
-  __shared__ int wcnt[4][256];       // per-wave digit counts of the current chunk
+                                                       K *__restrict__ out) {
+  __shared__ K sk[RADIX_TILE];       // the tile in digit order
+  __shared__ int64_t gpos[256];      // global position minus tile position of each digit's keys
+  __shared__ int wcnt[RADIX_THREADS / WAVE][256];       // per wave: keys of each digit so far, then their first tile position
   __shared__ u32 sh_w[4];
+  const int64_t tile = radix_tile(ntiles);
+  if (tile >= ntiles) return;
   const int t = threadIdx.x, lane = t & 63, w = t >> 6;
-  base[t] = offs[(int64_t)t * ntiles + blockIdx.x];
-  {
-    u32 total;
-    tstart[t] = (int)block_exclusive_scan((u32)hist[(int64_t)t * ntiles + blockIdx.x], sh_w, &total);
-  }
-  run[t] = 0;
-  const int64_t tile0 = (int64_t)blockIdx.x * RADIX_TILE;
+  const int64_t goff = t < 256 ? offs[(int64_t)t * ntiles + tile] : 0;
+  const int64_t tile0 = tile * RADIX_TILE;
   const int cnt = (int)min<int64_t>(m - tile0, RADIX_TILE);
   const u64 lt = (1ULL << lane) - 1ULL;
   // the whole tile is requested at once, so its load latency is paid once
-  // instead of once per chunk
-  u64 kk[RADIX_ITEMS];
+  K kk[RADIX_ITEMS];
+  const int i0 = w * (WAVE * RADIX_ITEMS) + lane;
 #pragma unroll
   for (int j = 0; j < RADIX_ITEMS; ++j) {
-    const int i = j * 256 + t;
-    kk[j] = i < cnt ? __builtin_nontemporal_load(&keys[tile0 + i]) : 0ULL;
+    const int i = i0 + j * WAVE;
+    kk[j] = i < cnt ? __builtin_nontemporal_load(&keys[tile0 + i]) : (K)0;
   }
 #pragma unroll
+  for (int q = 0; q < 256 / WAVE; ++q) wcnt[w][q * WAVE + lane] = 0;
+  __builtin_amdgcn_wave_barrier();
+  int rank[RADIX_ITEMS];
+#pragma unroll
   for (int j = 0; j < RADIX_ITEMS; ++j) {
-    for (int q = 0; q < 4; ++q) wcnt[q][t] = 0;
-    __syncthreads();
-    const int i = j * 256 + t;
-    const bool valid = i < cnt;
-    const u64 key = kk[j];
-    const u32 d = (u32)(key >> shift) & 255u;
+    const bool valid = i0 + j * WAVE < cnt;
+    const u32 d = (u32)(kk[j] >> shift) & 255u;
     u64 peers = __ballot(valid);
 #pragma unroll
     for (int b = 0; b < 8; ++b) {
-      const u64 ones = __ballot(valid && ((d >> b) & 1u));
+      const u64 ones = __ballot((d >> b) & 1u);
       peers &= ((d >> b) & 1u) ? ones : ~ones;
     }
-    const int rank = __popcll(peers & lt);
-    if (valid && rank == 0) wcnt[w][d] = __popcll(peers);
-    __syncthreads();
-    if (valid) {
-      int before = 0;
-      for (int q = 0; q < w; ++q) before += wcnt[q][d];
-      sk[tstart[d] + run[d] + before + rank] = key;
-    }
-    __syncthreads();
-    run[t] += wcnt[0][t] + wcnt[1][t] + wcnt[2][t] + wcnt[3][t];
+    const int below = __popcll(peers & lt);
+    const int before = wcnt[w][d];
+    __builtin_amdgcn_wave_barrier();
+    if (valid && below == 0) wcnt[w][d] = before + __popcll(peers);
+    __builtin_amdgcn_wave_barrier();
+    rank[j] = before + below;
   }
   __syncthreads();
-  for (int i = t; i < cnt; i += 256) {
-    const u64 key = sk[i];
-    const u32 d = (u32)(key >> shift) & 255u;
-    out[base[d] + (i - tstart[d])] = key;
+  // exclusive scan over digits (thread t: digit t), then over the waves of a digit
+  {
+    u32 c = 0;
+    if (t < 256)
+#pragma unroll
+      for (int q = 0; q < RADIX_THREADS / WAVE; ++q) c += (u32)wcnt[q][t];
+    u32 x = c;
+#pragma unroll
+    for (int o = 1; o < WAVE; o <<= 1) {
+      const u32 y = __shfl_up(x, o, WAVE);
+      if (lane >= o) x += y;
+    }
+    if (t < 256 && lane == WAVE - 1) sh_w[w] = x;
+    __syncthreads();
+    if (t < 256) {
+      int at = (int)(x - c);
+      for (int i = 0; i < w; ++i) at += (int)sh_w[i];
+      gpos[t] = goff - at;
+#pragma unroll
+      for (int q = 0; q < RADIX_THREADS / WAVE; ++q) {
+        const int n = wcnt[q][t];
+        wcnt[q][t] = at;
+        at += n;
+      }
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < RADIX_ITEMS; ++j)
+    if (i0 + j * WAVE < cnt) sk[wcnt[w][(u32)(kk[j] >> shift) & 255u] + rank[j]] = kk[j];
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < RADIX_ITEMS; ++j) {
+    const int i = j * RADIX_THREADS + t;
+    if (i < cnt) {
+      const K key = sk[i];
+      out[gpos[(u32)(key >> shift) & 255u] + i] = key;
+    }
   }
 }
 
