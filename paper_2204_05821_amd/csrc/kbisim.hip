@@ -294,11 +294,14 @@ inline unsigned blocks_for(int64_t items, int per) { return (unsigned)((items + 
 // Workgroups of the radix kernels (see radix_tile).
 unsigned radix_grid(int64_t ntiles) { return (unsigned)((ntiles + XCDS - 1) / XCDS * XCDS); }
 
-// Range check of cnt int32 values on stream s (see k_validate_vals).
-void validate_vals(hipStream_t s, int64_t cnt, const int32_t *vals, int64_t upper, u32 *err, u32 bit) {
+// Range check of cnt int32 values on stream s, and their maximum into
+// *max_out unless null (see k_validate_vals).
+void validate_vals(hipStream_t s, int64_t cnt, const int32_t *vals, int64_t upper, u32 *err, u32 bit,
+                   u32 *max_out = nullptr) {
   if (cnt <= 0) return;
   const unsigned g = (unsigned)std::min<int64_t>(VALIDATE_GRID, blocks_for(cnt / 4 + 1, 256));
-  k_validate_vals<<<g, 256, 0, s>>>(cnt, vals, upper, err, bit);
+  if (max_out) k_validate_vals<true><<<g, 256, 0, s>>>(cnt, vals, upper, err, bit, max_out);
+  else k_validate_vals<false><<<g, 256, 0, s>>>(cnt, vals, upper, err, bit, nullptr);
 }
 
 // ---- per-kernel profiling: events around each launch, resolved after syncs.
@@ -2030,7 +2033,7 @@ int create_impl(const kbisim_graph *g, int kmax, const kbisim_tuning *tuning, vo
   }
   if (m > 0) {
     validate_vals(c->stream, m, g->col, n, c->err, ERR_GRAPH_COL);
-    if (g->elabel) validate_vals(c->stream, m, g->elabel, -1, c->err, ERR_GRAPH_ELABEL);
+    if (g->elabel) validate_vals(c->stream, m, g->elabel, -1, c->err, ERR_GRAPH_ELABEL, c->err + 2);
   }
   if (g->vlabel_ptr) {
     k_validate_rows<<<blocks_for(n + 1, 256), 256, 0, c->stream>>>(n, nl, g->vlabel_ptr, c->err, ERR_GRAPH_VPTR);
@@ -2039,9 +2042,12 @@ int create_impl(const kbisim_graph *g, int kmax, const kbisim_tuning *tuning, vo
     validate_vals(c->stream, n, g->vlabel, -1, c->err, ERR_GRAPH_VLABEL);
   }
   if (hipGetLastError() != hipSuccess) return fail(KBISIM_EHIP);
+  u32 ew[4] = {0, 0, 0, 0};  // error bits, -, largest edge label
+  if (hipMemcpyAsync(ew, c->err, sizeof ew, hipMemcpyDeviceToHost, c->stream) != hipSuccess ||
+      hipStreamSynchronize(c->stream) != hipSuccess)
+    return fail(KBISIM_EHIP);
+  if (ew[0]) return fail(KBISIM_EGRAPH);
   u32 err = 0;
-  if ((rc = read_err(c, &err))) return fail(rc);
-  if (err) return fail(KBISIM_EGRAPH);
 
   // Pairs keep block ids modulo 2^pb, pb = bit width of the largest graph's
   // vertex count (the block ids of one graph form an interval no longer than
@@ -2053,14 +2059,7 @@ int create_impl(const kbisim_graph *g, int kmax, const kbisim_tuning *tuning, vo
       gmax = 0;
       for (int64_t i = 0; i < num_graphs; ++i) gmax = std::max<int64_t>(gmax, vert_off[i + 1] - vert_off[i]);
     }
-    u32 max_label = 0;
-    if (g->elabel && m > 0) {
-      k_max_i32<<<(unsigned)std::min<int64_t>(blocks_for(m, 256), 4096), 256, 0, c->stream>>>(m, g->elabel, c->err + 2);
-      if (hipGetLastError() != hipSuccess) return fail(KBISIM_EHIP);
-      if (hipMemcpyAsync(&max_label, c->err + 2, sizeof(u32), hipMemcpyDeviceToHost, c->stream) != hipSuccess ||
-          hipStreamSynchronize(c->stream) != hipSuccess)
-        return fail(KBISIM_EHIP);
-    }
+    const u32 max_label = ew[2];
     u32 pb = 1, lb = 0;
     while (pb < 31 && (int64_t(1) << pb) < gmax) ++pb;
     while (lb < 32 && (max_label >> lb) != 0) ++lb;
@@ -2092,10 +2091,12 @@ int create_impl(const kbisim_graph *g, int kmax, const kbisim_tuning *tuning, vo
             hipSuccess ||
         hipMemcpyAsync(c->next, nxt.data(), 8 * (size_t)num_graphs, hipMemcpyHostToDevice, c->stream) != hipSuccess)
       return fail(KBISIM_EHIP);
-    k_graph_ids<<<(unsigned)num_graphs, 256, 0, c->stream>>>((int)num_graphs, c->first, c->gid);
-    if (hipGetLastError() != hipSuccess) return fail(KBISIM_EHIP);
     if (n > 0) {
-      k_validate_batch<<<blocks_for(n, 256), 256, 0, c->stream>>>((int)n, g->row_ptr, g->col, c->gid, c->err);
+      // workgroups per graph: all of them for few graphs, no more than there is work for
+      const int share = (int)std::max<int64_t>(
+          1, std::min<int64_t>(GRAPH_GRID / num_graphs, blocks_for(std::max(n, m), 1024)));
+      k_graph_ids<<<(unsigned)(share * std::min<int64_t>(num_graphs, GRAPH_GRID)), 256, 0, c->stream>>>(
+          num_graphs, share, c->first, g->row_ptr, g->col, c->gid, c->err);
       if (hipGetLastError() != hipSuccess) return fail(KBISIM_EHIP);
     }
     if ((rc = read_err(c, &err))) return fail(rc);
@@ -2633,10 +2634,8 @@ int kbisim_quotient(kbisim_ctx *c, const int32_t *src_pid, const int32_t *dst_pi
   int rc = 0;
   // both partitions must hold ids in [0, n)
   k_fill_i32<<<1, 64, 0, s>>>((int *)word, 4, 0);
-  validate_vals(s, n, src_pid, n, word, ERR_BAD_PID);
-  validate_vals(s, n, dst_pid, n, word, ERR_BAD_PID);
-  k_max_i32<<<(unsigned)std::min<int64_t>(blocks_for(n, 256), 4096), 256, 0, s>>>(n, src_pid, word + 1);
-  k_max_i32<<<(unsigned)std::min<int64_t>(blocks_for(n, 256), 4096), 256, 0, s>>>(n, dst_pid, word + 2);
+  validate_vals(s, n, src_pid, n, word, ERR_BAD_PID, word + 1);
+  validate_vals(s, n, dst_pid, n, word, ERR_BAD_PID, word + 2);
   HIP_TRY(hipGetLastError());
   u32 hw[3] = {0, 0, 0};
   HIP_TRY(hipMemcpyAsync(hw, word, sizeof hw, hipMemcpyDeviceToHost, s));

@@ -484,24 +484,19 @@ __global__ void k_validate_rows(int64_t n, int64_t m, const int64_t *__restrict_
   if (bad) atomicOr(err, bit);
 }
 
-// Largest value of a non-negative array (atomicMax into *out, which starts at 0).
-__global__ void k_max_i32(int64_t cnt, const int32_t *__restrict__ vals, u32 *out) {
-  u32 mx = 0;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < cnt; i += (int64_t)gridDim.x * blockDim.x)
-    mx = max(mx, (u32)vals[i]);
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) mx = max(mx, (u32)__shfl_xor(mx, o, WAVE));
-  if ((threadIdx.x & (WAVE - 1)) == 0 && mx) atomicMax(out, mx);
-}
-
 // Range check of cnt values: any value < 0, or >= upper when upper >= 0, sets
 // `bit` in *err.  Grid-stride over the 16-byte-aligned body of the array (the
 // few values before and after it one by one), 4 groups of 4 values in flight
-// per thread, one atomic per wave that found a bad value.
+// per thread, one atomic per wave that found a bad value.  MAX: the largest
+// value too (as unsigned, into *max_out, which starts at 0) from the same
+// read: one candidate per workgroup, and a workgroup whose candidate is not
+// above the current maximum issues no atomic (one per wave, on one address,
+// took 0.2 ms whatever the array's length).
 constexpr int VALIDATE_GRID = 4096;
 typedef u32 u32x4 __attribute__((ext_vector_type(4)));
+template <bool MAX>
 __global__ void __launch_bounds__(256) k_validate_vals(int64_t cnt, const int32_t *__restrict__ vals, int64_t upper,
-                                                       u32 *err, u32 bit) {
+                                                       u32 *err, u32 bit, u32 *max_out) {
   // negative values become >= 2^31 as unsigned: one compare covers both ends
   const u32 lim = (upper >= 0 && upper < 0x80000000ll) ? (u32)upper : 0x80000000u;
   const uintptr_t a = reinterpret_cast<uintptr_t>(vals);
@@ -511,21 +506,42 @@ __global__ void __launch_bounds__(256) k_validate_vals(int64_t cnt, const int32_
   const int64_t stride = (int64_t)gridDim.x * 256;
   const int64_t gt = (int64_t)blockIdx.x * 256 + threadIdx.x;
   bool bad = false;
+  u32 mx = 0;
   int64_t i = gt;
   for (; i + 3 * stride < ng; i += 4 * stride) {
     u32x4 q[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) q[j] = __builtin_nontemporal_load(&g4[i + j * stride]);
 #pragma unroll
-    for (int j = 0; j < 4; ++j) bad |= (q[j].x >= lim) | (q[j].y >= lim) | (q[j].z >= lim) | (q[j].w >= lim);
+    for (int j = 0; j < 4; ++j) {
+      bad |= (q[j].x >= lim) | (q[j].y >= lim) | (q[j].z >= lim) | (q[j].w >= lim);
+      if constexpr (MAX) mx = max(max(max(mx, q[j].x), max(q[j].y, q[j].z)), q[j].w);
+    }
   }
   for (; i < ng; i += stride) {
     const u32x4 q = __builtin_nontemporal_load(&g4[i]);
     bad |= (q.x >= lim) | (q.y >= lim) | (q.z >= lim) | (q.w >= lim);
+    if constexpr (MAX) mx = max(max(max(mx, q.x), max(q.y, q.z)), q.w);
   }
-  for (int64_t t = gt; t < head; t += stride) bad |= (u32)vals[t] >= lim;
-  for (int64_t t = head + (ng << 2) + gt; t < cnt; t += stride) bad |= (u32)vals[t] >= lim;
+  auto one = [&](int64_t t) {
+    const u32 x = (u32)vals[t];
+    bad |= x >= lim;
+    if constexpr (MAX) mx = max(mx, x);
+  };
+  for (int64_t t = gt; t < head; t += stride) one(t);
+  for (int64_t t = head + (ng << 2) + gt; t < cnt; t += stride) one(t);
   if (__ballot(bad) && (threadIdx.x & (WAVE - 1)) == 0) atomicOr(err, bit);
+  if constexpr (MAX) {
+    __shared__ u32 sh_m[4];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) mx = max(mx, (u32)__shfl_xor(mx, o, WAVE));
+    if ((threadIdx.x & (WAVE - 1)) == 0) sh_m[threadIdx.x >> 6] = mx;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      mx = max(max(sh_m[0], sh_m[1]), max(sh_m[2], sh_m[3]));
+      if (mx > __hip_atomic_load(max_out, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(max_out, mx);
+    }
+  }
 }
 
 // ---------------------------------------------------------------- signature tiers
@@ -1974,20 +1990,27 @@ __global__ void k_scatter_rank(int n, const int *__restrict__ pid, const int *__
 // first[g+1])).  Blocks never span graphs, so each graph's first vertex heads
 // a block and its global id is the number of blocks in earlier graphs:
 // per-graph ids are global ids minus that base.
-__global__ void k_graph_ids(int G, const int64_t *__restrict__ first, int *__restrict__ gid) {
-  const int g = blockIdx.x;
-  if (g >= G) return;
-  for (int64_t v = first[g] + threadIdx.x; v < first[g + 1]; v += blockDim.x) gid[v] = g;
-}
-
-// Every CSR entry must stay inside its row's graph.
-__global__ void k_validate_batch(int n, const int64_t *__restrict__ row_ptr, const int32_t *__restrict__ col,
-                                 const int *__restrict__ gid, u32 *err) {
-  const int v = blockIdx.x * blockDim.x + threadIdx.x;
-  if (v >= n) return;
-  const int g = gid[v];
-  for (int64_t e = row_ptr[v]; e < row_ptr[v + 1]; ++e)
-    if (gid[col[e]] != g) { atomicOr(err, ERR_GRAPH_COL); return; }
+constexpr int GRAPH_GRID = 8192;  // workgroups over all graphs of a batch
+// Every CSR entry must stay inside its row's graph.  A graph owns the vertices
+// [first[g], first[g+1]) and, rows being in vertex order, the entries from
+// row_ptr[first[g]] to row_ptr[first[g+1]]: `share` workgroups stride over
+// them, with no look at single rows (one thread per vertex walking its row
+// took 0.6 ms on 64 small graphs, the length of the longest row).  They also
+// write the graph id of its vertices.
+__global__ void __launch_bounds__(256) k_graph_ids(int64_t G, int share, const int64_t *__restrict__ first,
+                                                   const int64_t *__restrict__ row_ptr,
+                                                   const int32_t *__restrict__ col, int *__restrict__ gid, u32 *err) {
+  bool bad = false;
+  const int part = blockIdx.x % share;
+  const int64_t t0 = (int64_t)part * 256 + threadIdx.x, stride = (int64_t)share * 256;
+  for (int64_t g = blockIdx.x / share; g < G; g += gridDim.x / share) {
+    const int64_t v0 = first[g], v1 = first[g + 1];
+    if (v0 == v1) continue;
+    for (int64_t v = v0 + t0; v < v1; v += stride) gid[v] = (int)g;
+    const int64_t e1 = row_ptr[v1];
+    for (int64_t e = row_ptr[v0] + t0; e < e1; e += stride) bad |= col[e] < v0 || col[e] >= v1;
+  }
+  if (__ballot(bad) && (threadIdx.x & (WAVE - 1)) == 0) atomicOr(err, ERR_GRAPH_COL);
 }
 
 __global__ void k_rebase(int n, const int *__restrict__ gid, const int64_t *__restrict__ first,
