@@ -224,7 +224,10 @@ int kbisim_batch_destroy(kbisim_batch *b);
  *   out_row_ptr  device int64 [n+1]
  *   out_col      device int32 [m]
  *   out_elabel   device int32 [m] or NULL (zeros when elabel is NULL)
- *   workspace    device, kbisim_transpose_workspace_bytes(n, m) bytes
+ *   workspace    device, kbisim_transpose_workspace_bytes(n, m) bytes (the
+ *                entries are then sorted, 16 bytes of keys each), or at least
+ *                kbisim_transpose_workspace_bytes(n, 0): scattered one by one,
+ *                several times slower
  * The order of entries inside an output row is unspecified; refinement does
  * not depend on it.  Validates the input first; synchronises `stream`.
  * Errors: EINVAL, ERANGE, ENOSPACE, EGRAPH (invalid input), EHIP.           */

@@ -436,10 +436,15 @@ def transpose(row_ptr: torch.Tensor, col: torch.Tensor, elabel: Optional[torch.T
     if rc:
         raise KbisimError(rc, "kbisim_transpose_workspace_bytes")
     with torch.cuda.device(dev):
-        ws = torch.empty(int(nbytes.value), dtype=torch.uint8, device=dev)
         out_rp = torch.empty(n + 1, dtype=torch.int64, device=dev)
         out_col = torch.empty(max(m, 0), dtype=torch.int32, device=dev)
         out_el = torch.empty(max(m, 0), dtype=torch.int32, device=dev) if elabel is not None else None
+        try:
+            ws = torch.empty(int(nbytes.value), dtype=torch.uint8, device=dev)
+        except torch.cuda.OutOfMemoryError:
+            # no room for sort keys: the smaller workspace of the entry-by-entry scatter
+            lib.kbisim_transpose_workspace_bytes(n, 0, ctypes.byref(nbytes))
+            ws = torch.empty(int(nbytes.value), dtype=torch.uint8, device=dev)
         torch.cuda.current_stream().synchronize()
         rc = lib.kbisim_transpose(n, m, _ptr(row_ptr), _ptr(col), _ptr(elabel), _ptr(out_rp), _ptr(out_col),
                                   _ptr(out_el), _ptr(ws), int(nbytes.value), _stream_handle(stream))

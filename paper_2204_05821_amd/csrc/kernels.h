@@ -2267,6 +2267,107 @@ __global__ void __launch_bounds__(RADIX_THREADS) k_radix_scatter(int64_t m, cons
   }
 }
 
+// ---------------------------------------------------------------- transpose by sorting
+// Largest r in [lo, hi) with ptr[r] <= x, for a non-decreasing ptr with
+// ptr[lo] <= x; the whole wave searches, 64 probes at a time.
+__device__ inline int64_t wave_last_le(const int64_t *__restrict__ ptr, int64_t lo, int64_t hi, int64_t x) {
+  const int lane = threadIdx.x & (WAVE - 1);
+  while (hi - lo > 1) {
+    const int64_t step = (hi - lo + WAVE - 1) / WAVE;
+    const int64_t at = lo + lane * step;
+    const int ok = __popcll(__ballot(at < hi && ptr[at] <= x));  // a prefix of the lanes, lane 0 among them
+    lo += (ok - 1) * step;
+    hi = min(hi, lo + step);
+  }
+  return lo;
+}
+
+// One key per CSR entry: target << (lb + sb) | label << sb | source, so that a
+// stable sort by target gives the rows of the transposed graph.  A workgroup
+// takes TKEY_CHUNK consecutive entries; their rows come from two searches in
+// the row offsets and a max-scan over row-start marks (or, where the chunk
+// spans more than TKEY_ROWS rows, most of them empty, a search per entry).
+constexpr int TKEY_CHUNK = 2048, TKEY_ROWS = 8192;
+__global__ void __launch_bounds__(256) k_transpose_keys(int64_t n, int64_t m, const int64_t *__restrict__ row_ptr,
+                                                        const int32_t *__restrict__ col,
+                                                        const int32_t *__restrict__ elabel, u32 sb, u32 lb,
+                                                        u64 *__restrict__ keys) {
+  constexpr int PER = TKEY_CHUNK / 256;
+  __shared__ u32 own[TKEY_CHUNK];
+  __shared__ int64_t ends[2];
+  __shared__ u32 wmax[4];
+  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+  const int64_t e0 = (int64_t)blockIdx.x * TKEY_CHUNK;
+  const int cnt = (int)min<int64_t>(m - e0, TKEY_CHUNK);
+  for (int i = t; i < TKEY_CHUNK; i += 256) own[i] = 0;
+  if (w < 2) {
+    const int64_t r = wave_last_le(row_ptr, 0, n, w == 0 ? e0 : e0 + cnt - 1);
+    if (lane == 0) ends[w] = r;
+  }
+  __syncthreads();
+  const int64_t r0 = ends[0], rows = ends[1] - r0 + 1;
+  if (rows <= TKEY_ROWS) {
+    // rows that start inside the chunk; of those at one position the last is not empty
+    for (int i = 1 + t; i < (int)rows; i += 256) atomicMax(&own[row_ptr[r0 + i] - e0], (u32)i);
+    __syncthreads();
+    u32 run = 0;
+#pragma unroll
+    for (int k = 0; k < PER; ++k) run = max(run, own[t * PER + k]);
+    u32 x = run;
+#pragma unroll
+    for (int o = 1; o < WAVE; o <<= 1) {
+      const u32 y = __shfl_up(x, o, WAVE);
+      if (lane >= o) x = max(x, y);
+    }
+    if (lane == WAVE - 1) wmax[w] = x;
+    u32 carry = __shfl_up(x, 1, WAVE);
+    if (lane == 0) carry = 0;
+    __syncthreads();
+    for (int i = 0; i < w; ++i) carry = max(carry, wmax[i]);
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+      carry = max(carry, own[t * PER + k]);
+      own[t * PER + k] = carry;
+    }
+    __syncthreads();
+  }
+  for (int i = t; i < cnt; i += 256) {
+    const int64_t e = e0 + i;
+    int64_t r;
+    if (rows <= TKEY_ROWS) {
+      r = r0 + own[i];
+    } else {
+      int64_t lo = r0, hi = ends[1] + 1;
+      while (hi - lo > 1) {
+        const int64_t mid = (lo + hi) >> 1;
+        if (row_ptr[mid] <= e) lo = mid;
+        else hi = mid;
+      }
+      r = lo;
+    }
+    u64 k = (u64)(u32)__builtin_nontemporal_load(&col[e]) << (lb + sb) | (u64)r;
+    if (elabel) k |= (u64)(u32)__builtin_nontemporal_load(&elabel[e]) << sb;
+    keys[e] = k;
+  }
+}
+
+// The sorted keys back into (source, label) per entry, and the entries per
+// target into cnt (zero on entry, modulo 2^32): the first entry of a target
+// subtracts its position and the last one adds its end, two atomics per
+// named target instead of one per entry.
+__global__ void __launch_bounds__(256) k_transpose_unpack(int64_t m, const u64 *__restrict__ keys, u32 sb, u32 lb,
+                                                          int32_t *__restrict__ out_col,
+                                                          int32_t *__restrict__ out_elabel, int *cnt) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i >= m) return;
+  const u64 k = keys[i];
+  const u64 d = k >> (lb + sb);
+  out_col[i] = (int32_t)(k & ((1ull << sb) - 1ull));
+  if (out_elabel) out_elabel[i] = (int32_t)((k >> sb) & ((1ull << lb) - 1ull));
+  if (i == 0 || (keys[i - 1] >> (lb + sb)) != d) atomicSub(&cnt[d], (int)(u32)i);
+  if (i == m - 1 || (keys[i + 1] >> (lb + sb)) != d) atomicAdd(&cnt[d], (int)(u32)(i + 1));
+}
+
 // ---------------------------------------------------------------- degree schedule
 // Rows are packed greedily into ranges of consecutive vertices: a range
 // closes before a row that would overflow it (range_edges entries), after
