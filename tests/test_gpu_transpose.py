@@ -21,10 +21,11 @@ def _rows(n, rp, col, el):
     return np.stack([row, np.asarray(lab)[at], np.asarray(col)[at]])
 
 
-# chunks of 2048 entries; rows per chunk past the marked limit (8192) most of them empty; one hub
-# target; labels so wide that the sort key does not fit and the entries are scattered instead
-CASES = [(1, 1, 1), (2, 2047, 0), (300, 2048, 7), (300, 2049, 0), (100_003, 5_000, 3), (1_000_003, 2_050, 1 << 31),
-         (100_003, 70_001, 1 << 31), (70_001, 300_007, 40)]
+# sorted from 2^20 entries on: whole and ragged chunks of 2048; rows per chunk past the marked limit
+# (8192), most of them empty; one hub target; labels so wide that the sort key does not fit
+M = 1 << 20
+CASES = [(1, 1, 1), (300, 2049, 0), (1, M, 0), (2, M + 1, 3), (70_001, M - 1, 40), (70_001, M + 2047, 40),
+         (5_000_011, M + 2049, 3), (100_003, M, 1 << 31), (1_000_003, M, 0)]
 
 
 @pytest.mark.parametrize("n,m,labels", CASES)
