@@ -876,6 +876,89 @@ int bit_width(uint64_t x) {
   return b;
 }
 
+// Exclusive scan of cnt[0..len) into out[0..len] (64-bit), on `s`.
+int scan64(hipStream_t s, int64_t len, const int *cnt, int64_t *tiles, int64_t *out) {
+  const int64_t nt = (len + SCAN_TILE - 1) / SCAN_TILE;
+  k_sum_tiles64<<<(unsigned)nt, 256, 0, s>>>(len, cnt, tiles);
+  k_scan_tiles64<<<1, 256, 0, s>>>(nt, tiles);
+  k_write_ptr64<<<(unsigned)nt, 256, 0, s>>>(len, cnt, tiles, out, nullptr);
+  HIP_TRY(hipGetLastError());
+  return 0;
+}
+
+// Stable sort of m keys by their bits [lo, hi), 8 bits per pass, between ka and
+// kb; on return ka points to the sorted keys.
+template <class K>
+int radix_sort(hipStream_t s, int64_t m, K *&ka, K *&kb, int lo, int hi, int64_t rtiles, int *hist, int64_t *tiles,
+               int64_t *offs) {
+  int rc = 0;
+  for (int shift = lo; shift < hi; shift += 8) {
+    k_radix_hist<<<radix_grid(rtiles), RADIX_THREADS, 0, s>>>(m, ka, shift, rtiles, hist);
+    HIP_TRY(hipGetLastError());
+    if ((rc = scan64(s, 256 * rtiles, hist, tiles, offs))) return rc;
+    k_radix_scatter<<<radix_grid(rtiles), RADIX_THREADS, 0, s>>>(m, ka, shift, rtiles, offs, kb);
+    HIP_TRY(hipGetLastError());
+    std::swap(ka, kb);
+  }
+  return 0;
+}
+// Entries per target of the context's graph into indeg.  Graphs of at least
+// INDEG_SORT_MIN entries partition the targets first (k_bucket_count): 24M
+// entries 0.95 -> 0.17 ms, 40M 1.65 -> 0.27.  Scratch: the hub-set space, not yet in use.
+constexpr int64_t INDEG_SORT_MIN = (int64_t)1 << 21;
+int in_degrees(kbisim_ctx *c, int *indeg) {
+  const int64_t n = c->g.n, m = c->g.m;
+  hipStream_t s = c->stream;
+  int rc = 0;
+  if (m < INDEG_SORT_MIN) {
+    if ((rc = fill_i32(c, indeg, n, 0))) return rc;
+    if (m > 0) {
+      k_indegree<<<(unsigned)std::min<int64_t>(blocks_for(m, INDEG_CHUNK), 1 << 16), 256, 0, s>>>(m, c->g.col, indeg);
+      LAUNCH_CHECK();
+    }
+    return 0;
+  }
+  // buckets of 2^shift targets: 8 high bits (one pass) while 2^15 counters
+  // hold a bucket, else 16 (two passes)
+  const int bits = std::max(9, bit_width((uint64_t)(n - 1)));
+  const int passes = bits <= 23 ? 1 : 2;
+  const int shift = bits - 8 * passes;
+  const int64_t nb = ((n - 1) >> shift) + 1;
+  const int64_t rtiles = (m + RADIX_TILE - 1) / RADIX_TILE, hist_n = 256 * rtiles;
+  char *w = (char *)c->hubsets;
+  size_t at = 0;
+  auto take = [&](size_t bytes) {
+    char *p = w + at;
+    at = align_up(at + bytes);
+    return p;
+  };
+  u32 *ka = (u32 *)take(4 * (size_t)m), *kb = (u32 *)take(4 * (size_t)m);
+  int *hist = (int *)take(4 * (size_t)hist_n);
+  int64_t *offs = (int64_t *)take(8 * (size_t)(hist_n + 1));
+  int64_t *tiles = (int64_t *)take(8 * (size_t)(hist_n / SCAN_TILE + 1));
+  int64_t *starts = (int64_t *)take(8 * (size_t)nb);
+  int *rest = (int *)take(4);
+  if (at > 8 * (size_t)c->plan.hubset_slots) return KBISIM_EINTERNAL;
+  u32 *from = reinterpret_cast<u32 *>(const_cast<int32_t *>(c->g.col)), *to = ka;  // the caller's array is only read
+  for (int p = 0; p < passes; ++p) {
+    u32 *next = to == ka ? kb : ka;
+    if ((rc = radix_sort(s, m, from, to, shift + 8 * p, shift + 8 * p + 8, rtiles, hist, tiles, offs))) return rc;
+    to = next;  // radix_sort left the result in `from`
+  }
+  if ((rc = fill_i32(c, rest, 1, 0))) return rc;
+  // a bucket of several times the mean is finished by the whole grid
+  const int64_t cap = std::max<int64_t>(1 << 16, 8 * (m / nb));
+  if (shift <= 13)
+    k_bucket_count<13><<<(unsigned)nb, BUCKET_THREADS, 0, s>>>(m, n, from, (u32)shift, cap, indeg, starts, rest);
+  else
+    k_bucket_count<15><<<(unsigned)nb, BUCKET_THREADS, 0, s>>>(m, n, from, (u32)shift, cap, indeg, starts, rest);
+  LAUNCH_CHECK();
+  k_indegree_rest<<<(unsigned)std::min<int64_t>(blocks_for(m, INDEG_CHUNK), 8192), 256, 0, s>>>(m, from, (u32)shift,
+                                                                                            cap, starts, rest, indeg);
+  LAUNCH_CHECK();
+  return 0;
+}
+
 // Rank vertices by decreasing in-degree (ties by vertex id) and renumber the
 // targets of every CSR entry: gcol[e] = rank[col[e]].  Vertices no entry
 // names get rank -1: they are never gathered.  A stable LSD radix sort of
@@ -885,13 +968,8 @@ int build_rank(kbisim_ctx *c) {
   const int64_t n = c->g.n, m = c->g.m;
   if (n == 0) return 0;
   int *indeg = c->vlist;  // scratch
-  int rc = fill_i32(c, indeg, n, 0);
+  int rc = in_degrees(c, indeg);
   if (rc) return rc;
-  if (m > 0) {
-    k_indegree<<<(unsigned)std::min<int64_t>(blocks_for(m, INDEG_CHUNK), 1 << 16), 256, 0, c->stream>>>(m, c->g.col,
-                                                                                                       indeg);
-    LAUNCH_CHECK();
-  }
   u64 *ka = c->table, *kb = c->table + n;  // 8 * tslots >= 16 n bytes
   const int64_t rtiles = (n + RADIX_TILE - 1) / RADIX_TILE, hist_n = 256 * rtiles;
   int *hist = (int *)c->ctable;
@@ -901,22 +979,8 @@ int build_rank(kbisim_ctx *c) {
     return KBISIM_EINTERNAL;
   k_rank_keys<<<(unsigned)std::min<int64_t>(blocks_for(n, 256), 1 << 16), 256, 0, c->stream>>>(n, indeg, ka);
   LAUNCH_CHECK();
-  // stable LSD passes of 8 bits over key bits [32, 32 + bits)
-  auto radix_passes = [&](int bits) -> int {
-    for (int shift = 32; shift < 32 + bits; shift += 8) {
-      k_radix_hist<<<radix_grid(rtiles), RADIX_THREADS, 0, c->stream>>>(n, ka, shift, rtiles, hist);
-      LAUNCH_CHECK();
-      const int64_t nt = (hist_n + SCAN_TILE - 1) / SCAN_TILE;
-      k_sum_tiles64<<<(unsigned)nt, 256, 0, c->stream>>>(hist_n, hist, tiles);
-      k_scan_tiles64<<<1, 256, 0, c->stream>>>(nt, tiles);
-      k_write_ptr64<<<(unsigned)nt, 256, 0, c->stream>>>(hist_n, hist, tiles, offs, nullptr);
-      LAUNCH_CHECK();
-      k_radix_scatter<<<radix_grid(rtiles), RADIX_THREADS, 0, c->stream>>>(n, ka, shift, rtiles, offs, kb);
-      LAUNCH_CHECK();
-      std::swap(ka, kb);
-    }
-    return 0;
-  };
+  // stable passes over key bits [32, 32 + bits)
+  auto radix_passes = [&](int bits) { return radix_sort(c->stream, n, ka, kb, 32, 32 + bits, rtiles, hist, tiles, offs); };
   if ((rc = radix_passes(RANK_KEYBITS))) return rc;
   if (c->num_graphs > 1) {
     // In a batch, ranks stay inside each graph's vertex range (ordered by
@@ -2504,33 +2568,6 @@ TransposePlan transpose_plan(int64_t n, int64_t m) {
     p.sort_total = at;
   }
   return p;
-}
-
-// Exclusive scan of cnt[0..len) into out[0..len] (64-bit), on `s`.
-int scan64(hipStream_t s, int64_t len, const int *cnt, int64_t *tiles, int64_t *out) {
-  const int64_t nt = (len + SCAN_TILE - 1) / SCAN_TILE;
-  k_sum_tiles64<<<(unsigned)nt, 256, 0, s>>>(len, cnt, tiles);
-  k_scan_tiles64<<<1, 256, 0, s>>>(nt, tiles);
-  k_write_ptr64<<<(unsigned)nt, 256, 0, s>>>(len, cnt, tiles, out, nullptr);
-  HIP_TRY(hipGetLastError());
-  return 0;
-}
-
-// Stable sort of m keys by their bits [lo, hi), 8 bits per pass, between ka and
-// kb; on return ka points to the sorted keys.
-extern "C++" template <class K>
-int radix_sort(hipStream_t s, int64_t m, K *&ka, K *&kb, int lo, int hi, int64_t rtiles, int *hist, int64_t *tiles,
-               int64_t *offs) {
-  int rc = 0;
-  for (int shift = lo; shift < hi; shift += 8) {
-    k_radix_hist<<<radix_grid(rtiles), RADIX_THREADS, 0, s>>>(m, ka, shift, rtiles, hist);
-    HIP_TRY(hipGetLastError());
-    if ((rc = scan64(s, 256 * rtiles, hist, tiles, offs))) return rc;
-    k_radix_scatter<<<radix_grid(rtiles), RADIX_THREADS, 0, s>>>(m, ka, shift, rtiles, offs, kb);
-    HIP_TRY(hipGetLastError());
-    std::swap(ka, kb);
-  }
-  return 0;
 }
 }  // namespace
 

@@ -2267,6 +2267,105 @@ __global__ void __launch_bounds__(RADIX_THREADS) k_radix_scatter(int64_t m, cons
   }
 }
 
+// ---------------------------------------------------------------- in-degrees by partition
+// Entries per target without an atomic per entry (device-wide atomics reach
+// about 25 G/s here): targets are first partitioned by their high bits (one
+// or two radix passes), so that a bucket's counters fit one workgroup's LDS;
+// then one workgroup counts each bucket and writes its counters whole.
+// First i in [0, m) with keys[i] >> shift >= b (m if none), for keys in bucket
+// order; the whole wave searches.
+__device__ inline int64_t wave_bucket_start(const u32 *__restrict__ keys, int64_t m, u32 shift, u32 b) {
+  const int lane = threadIdx.x & (WAVE - 1);
+  int64_t lo = -1, hi = m;  // keys[lo] is below the bucket, keys[hi] is not
+  while (hi - lo > 1) {
+    const int64_t step = (hi - lo + WAVE - 1) / WAVE;
+    const int64_t at = lo + lane * step;
+    const int below = __popcll(__ballot(lane == 0 || (at < hi && (keys[at] >> shift) < b)));
+    lo += (below - 1) * step;
+    hi = min(hi, lo + step);
+  }
+  return hi;
+}
+
+constexpr int BUCKET_THREADS = 1024;
+// Counters of bucket b (targets [b << shift, (b + 1) << shift), shift <= WB)
+// from its first `cap` entries; a bucket with more sets *rest, and the starts
+// are kept for k_indegree_rest.
+template <int WB>
+__global__ void __launch_bounds__(BUCKET_THREADS) k_bucket_count(int64_t m, int64_t n, const u32 *__restrict__ keys,
+                                                                 u32 shift, int64_t cap, int *__restrict__ indeg,
+                                                                 int64_t *__restrict__ starts, int *rest) {
+  __shared__ int cnt[1 << WB];
+  __shared__ int64_t range[2];
+  const int w = threadIdx.x >> 6;
+  const u32 b = blockIdx.x, width = 1u << shift;
+  for (u32 i = threadIdx.x; i < width; i += BUCKET_THREADS) cnt[i] = 0;
+  if (w < 2) {
+    const int64_t at = wave_bucket_start(keys, m, shift, b + w);
+    if ((threadIdx.x & (WAVE - 1)) == 0) range[w] = at;
+  }
+  __syncthreads();
+  const int64_t i0 = range[0], i1 = min(range[1], i0 + cap);
+  if (threadIdx.x == 0) {
+    starts[b] = i0;
+    if (range[1] > i1) *rest = 1;
+  }
+  constexpr int U = 8;  // entries in flight per thread
+  int64_t i = i0 + threadIdx.x;
+  for (; i + (U - 1) * BUCKET_THREADS < i1; i += U * BUCKET_THREADS) {
+    u32 k[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) k[u] = __builtin_nontemporal_load(&keys[i + u * BUCKET_THREADS]);
+#pragma unroll
+    for (int u = 0; u < U; ++u) atomicAdd(&cnt[k[u] & (width - 1u)], 1);
+  }
+  for (; i < i1; i += BUCKET_THREADS) atomicAdd(&cnt[keys[i] & (width - 1u)], 1);
+  __syncthreads();
+  const int64_t v0 = (int64_t)b << shift;
+  for (u32 j = threadIdx.x; j < width; j += BUCKET_THREADS)
+    if (v0 + j < n) indeg[v0 + j] = cnt[j];
+}
+
+// The entries past the first `cap` of their bucket (graphs where a few targets
+// take most entries): chunks counted in LDS, one device atomic per distinct
+// target of a chunk, as k_indegree.  Exits at once when no bucket was that long.
+__global__ void __launch_bounds__(256) k_indegree_rest(int64_t m, const u32 *__restrict__ keys, u32 shift, int64_t cap,
+                                                       const int64_t *__restrict__ starts,
+                                                       const int *__restrict__ rest, int *indeg) {
+  if (*rest == 0) return;
+  __shared__ int key[INDEG_SLOTS];
+  __shared__ int val[INDEG_SLOTS];
+  for (int64_t base = (int64_t)blockIdx.x * INDEG_CHUNK; base < m; base += (int64_t)gridDim.x * INDEG_CHUNK) {
+    const int cnt = (int)min<int64_t>(m - base, INDEG_CHUNK);
+    // a chunk whose last entry is among the first of its bucket can still hold
+    // late entries of the bucket before; its first entry's bucket tells
+    const bool any = base + cnt > starts[keys[base] >> shift] + cap;
+    if (!any) continue;  // uniform in the workgroup
+    for (int i = threadIdx.x; i < INDEG_SLOTS; i += 256) {
+      key[i] = -1;
+      val[i] = 0;
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < cnt; i += 256) {
+      const u32 c = keys[base + i];
+      if (base + i < starts[c >> shift] + cap) continue;
+      u32 sl = (c * 0x9E3779B1u) >> 20;  // 12 bits: INDEG_SLOTS
+      while (true) {
+        const int old = atomicCAS(&key[sl], -1, (int)c);
+        if (old == -1 || old == (int)c) {
+          atomicAdd(&val[sl], 1);
+          break;
+        }
+        sl = (sl + 1) & (INDEG_SLOTS - 1);
+      }
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < INDEG_SLOTS; i += 256)
+      if (key[i] >= 0) atomicAdd(&indeg[key[i]], val[i]);
+    __syncthreads();
+  }
+}
+
 // ---------------------------------------------------------------- transpose by sorting
 // Largest r in [lo, hi) with ptr[r] <= x, for a non-decreasing ptr with
 // ptr[lo] <= x; the whole wave searches, 64 probes at a time.
