@@ -19,7 +19,6 @@
 #include <map>
 #include <mutex>
 #include <new>
-#include <thread>
 #include <type_traits>
 #include <utility>
 #include <vector>
@@ -41,14 +40,6 @@ constexpr int CLEAR_GRID = 2048;
 constexpr int MIN_RANGE_EDGES = 1024;  // smallest tunable range capacity
 constexpr int MIN_HUB_CHUNK = 2048;    // smallest tunable hub chunk
 constexpr int MAX_GRAPH_CACHE = 8;
-constexpr int SCHED_CHUNKS = 16;  // host-built schedules: this many vertex chunks packed in parallel
-// Graphs of at least this many vertices get their schedule built on the
-// device.  A chunk walk is sequential, so the two walks take about 8 ms
-// whatever the graph; the host copy of the row offsets and the packing cost
-// about 1 ns per vertex, and win below this size (an 8.4M-vertex graph
-// creates in 17.5 ms instead of 21.4; serving, which creates many small
-// contexts, keeps its latency).
-constexpr int64_t SCHED_DEVICE_MIN = (int64_t)1 << 24;
 
 inline size_t align_up(size_t x) { return (x + ALIGN - 1) / ALIGN * ALIGN; }
 
@@ -86,7 +77,7 @@ Plan make_plan(int64_t n, int64_t m, int64_t nl, int kmax, int64_t num_graphs) {
   // "next" once), when full of vertices, or at the end; rows above the
   // capacity form ranges of their own.  Bounds use the smallest capacity.
   p.max_ranges = big / (RANGE_DMAX + 1) + 2 * big / (MIN_RANGE_EDGES + 1) + 2 * big / MIN_RANGE_EDGES +
-                 (int64_t)N / RANGE_VERTS + 8 + SCHED_CHUNKS + (int64_t)N / SCHED_CHUNK_V + 1;
+                 (int64_t)N / RANGE_VERTS + 24 + (int64_t)N / SCHED_CHUNK_V + 1;
   p.max_lists = big / (RANGE_DMAX + 1) + 8;
   p.nhub_max = big / (BLOCK_MAX + 1) + 1;
   p.nchunk_max = big / MIN_HUB_CHUNK + p.nhub_max + 1;
@@ -139,7 +130,7 @@ Plan make_plan(int64_t n, int64_t m, int64_t nl, int kmax, int64_t num_graphs) {
 }
 
 // Static degree schedule of one row structure (graph rows or label-set rows),
-// built on the host at create time; degrees never change across iterations.
+// built at create time (k_sched_chunks); degrees never change across iterations.
 struct Schedule {
   int range_edges = RANGE_EDGES;  // range capacity of this schedule (1024 or 2048)
   int nranges = 0;  // multi-vertex ranges (at most range_edges entries)
@@ -160,7 +151,6 @@ struct Tuning {
   int hub_part_target = HUB_PART_TARGET;
   int key_bits = 0;  // LDS set keys: 0 = 32-bit (exact where pairs fit, else hashed), 32 = hashed, 64 = 64-bit
   int hub_parts_cap = HUB_PMAX;  // most partitions per staged hub (a smaller cap is a test knob)
-  bool device_schedule = false;  // test knob: build the schedule on the device at any size
   int scan_items = SCAN_ITEMS;   // vertices per thread in the numbering scan: 8 or 16
   int gfilter_min = GFILTER_MIN_DIRTY;  // dirty vertices from which update steps use the global filter
 };
@@ -203,7 +193,6 @@ struct kbisim_ctx {
   unsigned char *single[2] = {nullptr, nullptr};  // singleton flags of the last two partitions
   u32 *multi = nullptr;  // stamps of heads that have a non-head member
   u32 prof_mask = ~0u;   // kernel kinds timed by the profiler
-  bool pinned_ok = true;  // schedule building may take pinned host buffers
   bool narrow = false;  // 32-bit LDS keys
   bool hashed = false;  // ... that hash the pair (it does not fit 31 bits, or 32-bit keys were asked for)
   u32 pb = 31;
@@ -401,23 +390,6 @@ bool separate_labels(const kbisim_ctx *c) { return !c->packed && c->g.elabel != 
 // The separate labels the kernels read: the rank-sorted copy, if made.
 const int32_t *sep_labels(const kbisim_ctx *c) { return c->glab ? c->glab : c->g.elabel; }
 
-// Dense ids numbered by first vertex: out[v] = number of heads (rep[v] == v)
-// before v for heads, -1 for the others; the head count into *count_dev.
-int numbering_scan(kbisim_ctx *c, int n, int *out, int64_t *count_dev) {
-  const int items = c->tune.scan_items;
-  const int ntiles = (int)blocks_for(n, 256 * items);
-  const int aligned = ((uintptr_t)out & 15) == 0;
-  if (items == 8) k_tile_count<8><<<(unsigned)ntiles, 256, 0, c->stream>>>(n, c->rep, c->tiles);
-  else k_tile_count<16><<<(unsigned)ntiles, 256, 0, c->stream>>>(n, c->rep, c->tiles);
-  LAUNCH_CHECK();
-  k_tile_scan<<<1, 1024, 0, c->stream>>>(ntiles, c->tiles, count_dev);
-  LAUNCH_CHECK();
-  if (items == 8) k_scan_write<8><<<(unsigned)ntiles, 256, 0, c->stream>>>(n, c->rep, c->tiles, out, aligned);
-  else k_scan_write<16><<<(unsigned)ntiles, 256, 0, c->stream>>>(n, c->rep, c->tiles, out, aligned);
-  LAUNCH_CHECK();
-  return 0;
-}
-
 // A step's numbering: head words and the tile prefixes of the heads in
 // vertex order (k_head_words, k_tile_scan); the block count to count_dev.
 // The assign kernels then read every vertex's dense id through the result.
@@ -430,22 +402,6 @@ int numbering_words(kbisim_ctx *c, int n, int64_t *count_dev, HeadIds *ids) {
   k_tile_scan<<<1, 1024, 0, c->stream>>>(ntiles, c->tiles, count_dev);
   LAUNCH_CHECK();
   *ids = HeadIds{c->hw, c->tiles, items == 8 ? 11 : 12};
-  return 0;
-}
-
-// The vertices with at least one entry, in order, into c->nzv (s.nzv then
-// points there): flags, the head scan of the numbering, and a scatter.  Uses
-// rep and vlist as scratch.
-int build_nonempty_list(kbisim_ctx *c, Schedule &s) {
-  const int n = (int)c->g.n;
-  if (n == 0) return 0;
-  k_mark_rows<<<blocks_for(n, 256), 256, 0, c->stream>>>(n, c->g.row_ptr, c->rep);
-  LAUNCH_CHECK();
-  int rc = numbering_scan(c, n, c->vlist, c->dcounts + (c->plan.ncounter_steps - 1));
-  if (rc) return rc;
-  k_list_from_ids<<<blocks_for(n, 256), 256, 0, c->stream>>>(n, c->vlist, c->nzv);
-  LAUNCH_CHECK();
-  s.nzv = c->nzv;
   return 0;
 }
 
@@ -502,84 +458,12 @@ int sort_long_rows(kbisim_ctx *c, const Schedule &s) {
   return sort_rows_impl<true>(c, s, reinterpret_cast<u32 *>(lab));
 }
 
-// Host copies of row-offset arrays for schedule building.  Fresh host pages
-// cost more to map than the copy itself, so buffers (pinned when possible)
-// go back to a process-wide pool and serve later creates.  The pool holds at
-// most as many buffers as schedules were built at once; it is never freed.
-struct HostRows {
-  int64_t *p = nullptr;
-  size_t cap = 0;
-  bool pinned = false;
-};
-std::mutex &host_rows_mu() {
-  static std::mutex *m = new std::mutex();
-  return *m;
-}
-std::vector<HostRows> &host_rows_pool() {
-  static std::vector<HostRows> *v = new std::vector<HostRows>();
-  return *v;
-}
-void host_rows_free(HostRows &b) {
-  if (!b.p) return;
-  if (b.pinned) (void)hipHostFree(b.p);
-  else delete[] b.p;
-  b = HostRows{};
-}
-// A buffer of at least cnt entries (p null if none could be had).
-HostRows host_rows_take(size_t cnt) {
-  HostRows old{};
-  {
-    std::lock_guard<std::mutex> lk(host_rows_mu());
-    auto &pool = host_rows_pool();
-    size_t best = pool.size();
-    for (size_t i = 0; i < pool.size(); ++i)
-      if (pool[i].cap >= cnt && (best == pool.size() || pool[i].cap < pool[best].cap)) best = i;
-    if (best < pool.size()) {
-      HostRows b = pool[best];
-      pool.erase(pool.begin() + (std::ptrdiff_t)best);
-      return b;
-    }
-    if (!pool.empty()) {  // replace the largest (too small) buffer
-      size_t big = 0;
-      for (size_t i = 1; i < pool.size(); ++i)
-        if (pool[i].cap > pool[big].cap) big = i;
-      old = pool[big];
-      pool.erase(pool.begin() + (std::ptrdiff_t)big);
-    }
-  }
-  host_rows_free(old);
-  HostRows b;
-  void *q = nullptr;
-  if (hipHostMalloc(&q, 8 * cnt, hipHostMallocDefault) == hipSuccess) {
-    b.p = static_cast<int64_t *>(q);
-    b.pinned = true;
-  } else {
-    (void)hipGetLastError();
-    b.p = new (std::nothrow) int64_t[cnt];
-  }
-  b.cap = b.p ? cnt : 0;
-  return b;
-}
-struct HostRowsLease {
-  HostRows b;
-  ~HostRowsLease() {
-    if (!b.p) return;
-    std::lock_guard<std::mutex> lk(host_rows_mu());
-    host_rows_pool().push_back(b);
-  }
-};
-
-// Build the static schedule of the rows of `ptr` (NULL: every row has one
-// item) on the host: runs of consecutive low-degree vertices, single-row
-// ranges, and hub chunks, partitions and staging areas.  Synchronises.
-// row_max: longest row with a workgroup of its own (longer rows are hubs);
-// staged_max: longest hub staged in partitions (longer hubs use a global set).
 // Hub plan (staged chunks and partitions, global-set chunks) of a schedule
-// whose range lists are already counted in s, and the uploads: the range
-// lists and the hub list when they were built on the host (host_ranges),
-// then the hub plan.  Synchronises.
+// whose range lists are on the device and counted in s.
+// staged_max: longest hub staged in partitions (longer hubs use a global set).
+// Synchronises when there are hubs.
 int plan_hubs(kbisim_ctx *c, Schedule &s, const std::vector<int> &hubs, const std::vector<int64_t> &hub_deg,
-              int64_t staged_max, const std::vector<Range> *host_ranges) {
+              int64_t staged_max) {
   const Tuning &t = c->tune;
   const int64_t nranges_total = (int64_t)s.nranges + s.nbig + s.nrow8 + s.nrow20;
   // hubs: staged (partitioned) unless very large or out of offset space
@@ -650,11 +534,6 @@ int plan_hubs(kbisim_ctx *c, Schedule &s, const std::vector<int> &hubs, const st
   s.nchunks = (int)chunks.size();
   s.nparts = (int)parts.size();
   s.ngchunks = (int)gchunks.size();
-  if (host_ranges && !host_ranges->empty())
-    HIP_TRY(hipMemcpyAsync(c->ranges, host_ranges->data(), sizeof(Range) * host_ranges->size(), hipMemcpyHostToDevice,
-                           c->stream));
-  if (host_ranges && !hubs.empty())
-    HIP_TRY(hipMemcpyAsync(c->lists, hubs.data(), 4 * hubs.size(), hipMemcpyHostToDevice, c->stream));
   if (!chunks.empty())
     HIP_TRY(hipMemcpyAsync(c->chunks, chunks.data(), sizeof(HubChunk) * chunks.size(), hipMemcpyHostToDevice,
                            c->stream));
@@ -664,59 +543,46 @@ int plan_hubs(kbisim_ctx *c, Schedule &s, const std::vector<int> &hubs, const st
     HIP_TRY(hipMemcpyAsync(c->gchunks, gchunks.data(), sizeof(HubGChunk) * gchunks.size(), hipMemcpyHostToDevice,
                            c->stream));
   int rc = 0;
-  if (s.nhub) {
-    if ((rc = fill_u64(c, c->hacc, s.nhub, 0))) return rc;
-    if ((rc = fill_i32(c, (int *)c->hcnt, s.nhub, 0))) return rc;
-    if ((rc = fill_u64(c, c->hubsets + s.gset_begin, s.gset_end - s.gset_begin, 0))) return rc;
-  }
+  if (!s.nhub) return 0;
+  if ((rc = fill_u64(c, c->hacc, s.nhub, 0))) return rc;
+  if ((rc = fill_i32(c, (int *)c->hcnt, s.nhub, 0))) return rc;
+  if ((rc = fill_u64(c, c->hubsets + s.gset_begin, s.gset_end - s.gset_begin, 0))) return rc;
   HIP_TRY(hipStreamSynchronize(c->stream));
   return 0;
 }
 
-// The schedule of graph rows built on the device (k_sched_walk): two walks
-// over fixed vertex chunks, a host scan of the per-chunk counts in between;
-// only the counts, the hub list and the hubs' degrees come back to the host.
-// Scratch: c->vlist (4n bytes; n >= 64).
-int build_schedule_device(kbisim_ctx *c, const int64_t *ptr, Schedule &s, int range_edges, int64_t row_max,
-                          int64_t staged_max) {
+// Static schedule of the rows of `ptr`, built on the device in two parts.
+// sched_enqueue launches the kernels (range lists, hub list and, with nzv, the
+// list of non-empty vertices) and leaves the totals on the device;
+// sched_finish takes the totals, once copied to the host, and plans the hubs.
+// row_max: longest row with a workgroup of its own (longer rows are hubs).
+// Scratch: c->vlist (224 bytes at least, 80 per chunk); the totals go to
+// `totals` (SCHED_TOTALS words).
+int sched_enqueue(kbisim_ctx *c, const int64_t *ptr, int range_edges, int64_t row_max, int64_t *totals, int *nzv) {
   const int64_t n = c->g.n;
   const int nch = (int)((n + SCHED_CHUNK_V - 1) / SCHED_CHUNK_V);
-  int *cnt = c->vlist, *off = cnt + 5 * (size_t)nch, *base = off + 5 * (size_t)nch;
-  int64_t *sums = reinterpret_cast<int64_t *>(c->vlist) + (10 * (size_t)nch + 4 + 1) / 2 + 1;
-  if ((size_t)((char *)(sums + 5 * (size_t)nch) - (char *)c->vlist) > 4 * (size_t)n) return KBISIM_EINTERNAL;
-  const unsigned grid = blocks_for(nch, 64);
-  k_sched_walk<false><<<grid, 64, 0, c->stream>>>(ptr, n, nch, range_edges, row_max, cnt, sums, nullptr, nullptr,
-                                                  nullptr, nullptr);
+  int64_t *sums = reinterpret_cast<int64_t *>(c->vlist);
+  int *cnt = reinterpret_cast<int *>(sums + 5 * (size_t)nch);
+  k_sched_chunks<false><<<(unsigned)nch, SCHED_THREADS, 0, c->stream>>>(ptr, n, nch, range_edges, row_max, cnt, sums,
+                                                                        totals, nullptr, nullptr, nullptr);
+  k_sched_scan<<<1, 256, 0, c->stream>>>(nch, cnt, sums, totals);
+  k_sched_chunks<true><<<(unsigned)nch, SCHED_THREADS, 0, c->stream>>>(ptr, n, nch, range_edges, row_max, cnt, sums,
+                                                                       totals, c->ranges, c->lists, nzv);
   LAUNCH_CHECK();
-  std::vector<int> hc(5 * (size_t)nch);
-  std::vector<int64_t> hs(5 * (size_t)nch);
-  HIP_TRY(hipMemcpyAsync(hc.data(), cnt, 4 * hc.size(), hipMemcpyDeviceToHost, c->stream));
-  HIP_TRY(hipMemcpyAsync(hs.data(), sums, 8 * hs.size(), hipMemcpyDeviceToHost, c->stream));
-  HIP_TRY(hipStreamSynchronize(c->stream));
-  int64_t tot[5] = {0, 0, 0, 0, 0};
-  std::vector<int> ho(5 * (size_t)nch);
-  for (int l = 0; l < 5; ++l)
-    for (int ci = 0; ci < nch; ++ci) {
-      ho[(size_t)l * nch + ci] = (int)tot[l];
-      tot[l] += hc[(size_t)l * nch + ci];
-    }
-  for (int ci = 0; ci < nch; ++ci) {
-    for (int i = 0; i < 4; ++i) s.info[i] += hs[5 * (size_t)ci + i];
-    s.nonempty += hs[5 * (size_t)ci + 4];
-  }
-  if (tot[0] + tot[1] + tot[2] + tot[3] > c->plan.max_ranges || tot[4] > c->plan.nhub_max ||
-      tot[4] > c->plan.max_lists)
-    return KBISIM_EINTERNAL;
+  return 0;
+}
+
+int sched_finish(kbisim_ctx *c, const int64_t *ptr, Schedule &s, int range_edges, int64_t staged_max,
+                 const int64_t *tot, const int *nzv) {
+  s = Schedule{};
+  s.range_edges = range_edges;
   s.nranges = (int)tot[0];
   s.nbig = (int)tot[1];
   s.nrow8 = (int)tot[2];
   s.nrow20 = (int)tot[3];
-  const int hb[4] = {0, (int)tot[0], (int)(tot[0] + tot[1]), (int)(tot[0] + tot[1] + tot[2])};
-  HIP_TRY(hipMemcpyAsync(off, ho.data(), 4 * ho.size(), hipMemcpyHostToDevice, c->stream));
-  HIP_TRY(hipMemcpyAsync(base, hb, sizeof hb, hipMemcpyHostToDevice, c->stream));
-  k_sched_walk<true><<<grid, 64, 0, c->stream>>>(ptr, n, nch, range_edges, row_max, nullptr, nullptr, off, base,
-                                                 c->ranges, c->lists);
-  LAUNCH_CHECK();
+  for (int i = 0; i < 4; ++i) s.info[i] = tot[5 + i];
+  s.nonempty = tot[9];
+  s.nzv = nzv;
   const int nh = (int)tot[4];
   std::vector<int> hubs((size_t)nh);
   std::vector<int64_t> hub_deg((size_t)nh);
@@ -729,144 +595,7 @@ int build_schedule_device(kbisim_ctx *c, const int64_t *ptr, Schedule &s, int ra
     HIP_TRY(hipMemcpyAsync(hub_deg.data(), deg, 8 * (size_t)nh, hipMemcpyDeviceToHost, c->stream));
     HIP_TRY(hipStreamSynchronize(c->stream));
   }
-  return plan_hubs(c, s, hubs, hub_deg, staged_max, nullptr);
-}
-
-int build_schedule(kbisim_ctx *c, const int64_t *ptr, Schedule &s, int range_edges, int64_t row_max,
-                   int64_t staged_max) {
-  const int64_t n = c->g.n;
-  s = Schedule{};
-  s.range_edges = range_edges;
-  // (the device walk needs 80 bytes of scratch per chunk in the 4n bytes of vlist)
-  if (ptr && (n >= SCHED_DEVICE_MIN || (c->tune.device_schedule && n >= 64)))
-    return build_schedule_device(c, ptr, s, range_edges, row_max, staged_max);
-  HostRowsLease lease;
-  std::vector<int64_t> pageable;  // when no pinned host memory may be taken
-  const int64_t *rp = nullptr;
-  if (ptr && n > 0) {
-    int64_t *dst = nullptr;
-    if (c->pinned_ok) {
-      lease.b = host_rows_take((size_t)n + 1);
-      dst = lease.b.p;
-    } else {
-      try {
-        pageable.resize((size_t)n + 1);
-      } catch (...) {
-        return KBISIM_EINTERNAL;
-      }
-      dst = pageable.data();
-    }
-    if (!dst) return KBISIM_EINTERNAL;
-    HIP_TRY(hipMemcpyAsync(dst, ptr, 8 * (size_t)(n + 1), hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(hipStreamSynchronize(c->stream));
-    rp = dst;
-  }
-  // Degree tiers.  Rows are packed greedily into ranges of consecutive
-  // vertices; the vertex sequence is cut into SCHED_CHUNKS fixed chunks that
-  // are packed in parallel (a range never crosses a chunk boundary), so the
-  // schedule is the same on every machine.
-  struct Part {
-    std::vector<Range> ranges, big, row8, row20;
-    std::vector<int> hubs;
-    int64_t info[4] = {0, 0, 0, 0};
-    int64_t nonempty = 0;
-  };
-  std::vector<Part> parts_((size_t)SCHED_CHUNKS);
-  auto pack = [&](int ci) {
-    Part &P = parts_[(size_t)ci];
-    const int64_t v_begin = n * ci / SCHED_CHUNKS, v_end = n * (ci + 1) / SCHED_CHUNKS;
-    if (!ptr) {
-      // one label per vertex: every row has one item, ranges of RANGE_VERTS vertices
-      for (int64_t v0 = v_begin; v0 < v_end; v0 += RANGE_VERTS)
-      {
-        const int64_t v1 = std::min<int64_t>(v_end, v0 + RANGE_VERTS);
-        P.ranges.push_back(Range{(int)v0, (int)v1, (int)(v1 - v0), 0, v0});
-      }
-      P.info[0] = P.info[1] = P.nonempty = v_end - v_begin;
-      return;
-    }
-    int64_t cur0 = -1, cur_e = 0;
-    auto close = [&](int64_t vend) {
-      if (cur0 >= 0) P.ranges.push_back(Range{(int)cur0, (int)vend, (int)cur_e, 0, rp[(size_t)cur0]});
-      cur0 = -1;
-      cur_e = 0;
-    };
-    for (int64_t v = v_begin; v < v_end; ++v) {
-      const int64_t d = rp[(size_t)v + 1] - rp[(size_t)v];
-      P.nonempty += d > 0;
-      if (d > row_max) {
-        close(v);
-        P.hubs.push_back((int)v);
-        continue;
-      }
-      if (d > ROW_MAX) {
-        close(v);
-        P.row20.push_back(Range{(int)v, (int)v + 1, (int)d, 0, rp[(size_t)v]});
-        P.info[2] += 1;
-        P.info[3] += d;
-        continue;
-      }
-      if (d > RANGE_DMAX) {
-        close(v);
-        P.row8.push_back(Range{(int)v, (int)v + 1, (int)d, 0, rp[(size_t)v]});
-        P.info[2] += 1;
-        P.info[3] += d;
-        continue;
-      }
-      if (d > range_edges) {
-        close(v);
-        P.big.push_back(Range{(int)v, (int)v + 1, (int)d, 0, rp[(size_t)v]});
-        P.info[2] += 1;
-        P.info[3] += d;
-        continue;
-      }
-      if (cur0 >= 0 && (cur_e + d > range_edges || v - cur0 == RANGE_VERTS)) close(v);
-      if (cur0 < 0) cur0 = v;
-      cur_e += d;
-      P.info[0] += 1;
-      P.info[1] += d;
-    }
-    close(v_end);
-  };
-  // Chunks run on threads when there is enough work; a chunk whose thread
-  // cannot be started is packed here (no exception leaves the library).
-  std::vector<std::thread> th;
-  std::vector<char> started((size_t)SCHED_CHUNKS, 0);
-  if (n >= (int64_t)1 << 16) {
-    for (int ci = 0; ci < SCHED_CHUNKS; ++ci) {
-      try {
-        th.emplace_back(pack, ci);
-        started[(size_t)ci] = 1;
-      } catch (...) {
-        break;
-      }
-    }
-  }
-  for (int ci = 0; ci < SCHED_CHUNKS; ++ci)
-    if (!started[(size_t)ci]) pack(ci);
-  for (auto &x : th) x.join();
-  std::vector<Range> ranges, big_ranges, row8_ranges, row20_ranges;
-  std::vector<int> hubs;
-  for (const Part &P : parts_) {
-    row20_ranges.insert(row20_ranges.end(), P.row20.begin(), P.row20.end());
-    ranges.insert(ranges.end(), P.ranges.begin(), P.ranges.end());
-    big_ranges.insert(big_ranges.end(), P.big.begin(), P.big.end());
-    row8_ranges.insert(row8_ranges.end(), P.row8.begin(), P.row8.end());
-    hubs.insert(hubs.end(), P.hubs.begin(), P.hubs.end());
-    for (int i = 0; i < 4; ++i) s.info[i] += P.info[i];
-    s.nonempty += P.nonempty;
-  }
-  auto deg = [&](int64_t v) -> int64_t { return ptr ? rp[(size_t)v + 1] - rp[(size_t)v] : 1; };
-  s.nranges = (int)ranges.size();
-  s.nbig = (int)big_ranges.size();
-  s.nrow8 = (int)row8_ranges.size();
-  s.nrow20 = (int)row20_ranges.size();
-  ranges.insert(ranges.end(), big_ranges.begin(), big_ranges.end());
-  ranges.insert(ranges.end(), row8_ranges.begin(), row8_ranges.end());
-  ranges.insert(ranges.end(), row20_ranges.begin(), row20_ranges.end());
-  std::vector<int64_t> hub_deg(hubs.size());
-  for (size_t i = 0; i < hubs.size(); ++i) hub_deg[i] = deg(hubs[i]);
-  return plan_hubs(c, s, hubs, hub_deg, staged_max, &ranges);
+  return plan_hubs(c, s, hubs, hub_deg, staged_max);
 }
 
 // Bits needed for x (0 for 0).
@@ -963,7 +692,7 @@ int in_degrees(kbisim_ctx *c, int *indeg) {
 // targets of every CSR entry: gcol[e] = rank[col[e]].  Vertices no entry
 // names get rank -1: they are never gathered.  A stable LSD radix sort of
 // (in-degree key, vertex) on the device; the grouping tables serve as
-// scratch, so this runs before they are cleared.  Synchronises.
+// scratch, so this runs before they are cleared.
 int build_rank(kbisim_ctx *c) {
   const int64_t n = c->g.n, m = c->g.m;
   if (n == 0) return 0;
@@ -1000,7 +729,6 @@ int build_rank(kbisim_ctx *c) {
         m, c->g.col, c->rank, c->gcol, c->packed ? c->g.elabel : nullptr, c->rbits);
     LAUNCH_CHECK();
   }
-  HIP_TRY(hipStreamSynchronize(c->stream));
   return 0;
 }
 
@@ -1130,6 +858,15 @@ int launch_signatures(kbisim_ctx *c, const Src &src, const Schedule &s, bool zfr
                       bool range_tier = true) {
   const u64 tmask = table_mask<Src>(c);
   int rc = 0;
+  if constexpr (!Src::GRAPH) {
+    if (!src.ptr) {  // one label per vertex
+      ProfScope ps(c, KBISIM_K_SIG_RANGE);
+      k_sig_one<Src><<<blocks_for(c->g.n, 256), 256, 0, c->stream>>>(src, (int)c->g.n, c->H, c->DC, c->table, tmask,
+                                                                    c->dep, c->hmask);
+      LAUNCH_CHECK();
+      return 0;
+    }
+  }
   if ((rc = launch_ranges(c, src, s, zfresh ? 1 : 0, skip_in, range_tier))) return rc;
   if (s.nhub) {
     const int *hubs = c->lists + s.hub_off;
@@ -1978,8 +1715,7 @@ int read_tuning(const kbisim_tuning *t, Tuning &out) {
 // Shared by kbisim_create and kbisim_batch_create.  With vert_off (host,
 // num_graphs + 1) the graph is a batch of disjoint graphs.
 int create_impl(const kbisim_graph *g, int kmax, const kbisim_tuning *tuning, void *workspace, size_t ws_bytes,
-                void *stream, int64_t num_graphs, const int64_t *vert_off, kbisim_ctx **out,
-                bool pinned_ok = true) {
+                void *stream, int64_t num_graphs, const int64_t *vert_off, kbisim_ctx **out) {
   int rc = check_sizes(g);
   if (rc) return rc;
   if (!out || kmax < 0 || kmax > (1 << 20)) return KBISIM_EINVAL;
@@ -2005,7 +1741,6 @@ int create_impl(const kbisim_graph *g, int kmax, const kbisim_tuning *tuning, vo
   if (!c) return KBISIM_EINTERNAL;
   c->g = *g;
   c->kmax = kmax;
-  c->pinned_ok = pinned_ok;
   c->stream = (hipStream_t)stream;
   c->plan = plan;
   c->tune = tune;
@@ -2065,9 +1800,6 @@ int create_impl(const kbisim_graph *g, int kmax, const kbisim_tuning *tuning, vo
     int q = atoi(pdbg);
     if (q >= 1 && q <= HUB_PMAX && (q & (q - 1)) == 0) c->tune.hub_parts_cap = q;
   }
-  // Test knob: build the degree schedule on the device for small graphs too.
-  const char *sdbg = getenv("KBISIM_DEBUG_DEVICE_SCHEDULE");
-  if (sdbg && *sdbg == '1') c->tune.device_schedule = true;
   // Test knob: keep only this many bits of hashed set keys, so that keys
   // collide inside rows (the exact check must still separate the pair sets).
   const char *kdbg = getenv("KBISIM_DEBUG_KEY_BITS");
@@ -2106,6 +1838,28 @@ int create_impl(const kbisim_graph *g, int kmax, const kbisim_tuning *tuning, vo
     validate_vals(c->stream, n, g->vlabel, -1, c->err, ERR_GRAPH_VLABEL);
   }
   if (hipGetLastError() != hipSuccess) return fail(KBISIM_EHIP);
+  std::vector<int64_t> nxt;
+  if (num_graphs > 0) {
+    // graph of every vertex; first vertex of the next non-empty graph
+    nxt.assign((size_t)num_graphs, -1);
+    int64_t after = -1;
+    for (int64_t i = num_graphs - 1; i >= 0; --i) {
+      nxt[(size_t)i] = after;
+      if (vert_off[i + 1] > vert_off[i]) after = vert_off[i];
+    }
+    if (hipMemcpyAsync(c->first, vert_off, 8 * (size_t)(num_graphs + 1), hipMemcpyHostToDevice, c->stream) !=
+            hipSuccess ||
+        hipMemcpyAsync(c->next, nxt.data(), 8 * (size_t)num_graphs, hipMemcpyHostToDevice, c->stream) != hipSuccess)
+      return fail(KBISIM_EHIP);
+    if (n > 0) {
+      // workgroups per graph: all of them for few graphs, no more than there is work for
+      const int share = (int)std::max<int64_t>(
+          1, std::min<int64_t>(GRAPH_GRID / num_graphs, blocks_for(std::max(n, m), 1024)));
+      k_graph_ids<<<(unsigned)(share * std::min<int64_t>(num_graphs, GRAPH_GRID)), 256, 0, c->stream>>>(
+          num_graphs, share, m, c->first, g->row_ptr, g->col, c->gid, c->err);
+      if (hipGetLastError() != hipSuccess) return fail(KBISIM_EHIP);
+    }
+  }
   u32 ew[4] = {0, 0, 0, 0};  // error bits, -, largest edge label
   if (hipMemcpyAsync(ew, c->err, sizeof ew, hipMemcpyDeviceToHost, c->stream) != hipSuccess ||
       hipStreamSynchronize(c->stream) != hipSuccess)
@@ -2143,30 +1897,6 @@ int create_impl(const kbisim_graph *g, int kmax, const kbisim_tuning *tuning, vo
     c->hashed = c->narrow && (c->tune.key_bits == 32 || pb + lb > 31);
   }
 
-  if (num_graphs > 0) {
-    // graph of every vertex; first vertex of the next non-empty graph
-    std::vector<int64_t> nxt((size_t)num_graphs, -1);
-    int64_t after = -1;
-    for (int64_t i = num_graphs - 1; i >= 0; --i) {
-      nxt[(size_t)i] = after;
-      if (vert_off[i + 1] > vert_off[i]) after = vert_off[i];
-    }
-    if (hipMemcpyAsync(c->first, vert_off, 8 * (size_t)(num_graphs + 1), hipMemcpyHostToDevice, c->stream) !=
-            hipSuccess ||
-        hipMemcpyAsync(c->next, nxt.data(), 8 * (size_t)num_graphs, hipMemcpyHostToDevice, c->stream) != hipSuccess)
-      return fail(KBISIM_EHIP);
-    if (n > 0) {
-      // workgroups per graph: all of them for few graphs, no more than there is work for
-      const int share = (int)std::max<int64_t>(
-          1, std::min<int64_t>(GRAPH_GRID / num_graphs, blocks_for(std::max(n, m), 1024)));
-      k_graph_ids<<<(unsigned)(share * std::min<int64_t>(num_graphs, GRAPH_GRID)), 256, 0, c->stream>>>(
-          num_graphs, share, c->first, g->row_ptr, g->col, c->gid, c->err);
-      if (hipGetLastError() != hipSuccess) return fail(KBISIM_EHIP);
-    }
-    if ((rc = read_err(c, &err))) return fail(rc);
-    if (err) return fail(KBISIM_EGRAPH);
-  }
-
   // Gather renumbering: rank vertices by decreasing in-degree (ties by id).
   // Uses the grouping tables as scratch, before they are cleared below.
   if ((rc = build_rank(c))) return fail(rc);
@@ -2177,29 +1907,56 @@ int create_impl(const kbisim_graph *g, int kmax, const kbisim_tuning *tuning, vo
   if ((rc = fill_i32(c, (int *)c->multi, std::max<int64_t>(n, 1), 0))) return fail(rc);
 
   // P0: blocks of equal vertex label sets, numbered by first vertex; in a
-  // batch the graph id joins the key, so no block spans two graphs.
+  // batch the graph id joins the key, so no block spans two graphs.  Then the
+  // static schedule of the graph rows.  What the host has to know of both
+  // comes back in one copy: the schedule's totals in the counter rows kmax
+  // and kmax + 1, P0's counters after them, its count and the error bits.
+  static_assert((SCHED_TOTALS + 2) * sizeof(int64_t) <= 2 * CNT_STRIDE * sizeof(int), "two counter rows");
+  const int gcap = range_cap(c, !c->narrow);
+  const int64_t grow_max = c->narrow ? ROW_MAX_NARROW : ROW_MAX;
+  int *back = c->counters + (size_t)CNT_STRIDE * kmax, *cnt = back + 2 * CNT_STRIDE;
+  int64_t *totals = reinterpret_cast<int64_t *>(back);
+  int64_t host[3 * CNT_STRIDE * sizeof(int) / sizeof(int64_t)] = {};
   if (!g->vlabel && num_graphs == 0) {
     if ((rc = fill_i32(c, c->p0, n, 0))) return fail(rc);
     c->p0_count = n > 0 ? 1 : 0;
-  } else if (n > 0) {
+  }
+  if (n > 0) {
     Schedule ls;
     LabelSrc src{g->vlabel_ptr, g->vlabel, c->gid};
     if (!g->vlabel) src = LabelSrc{nullptr, c->gid, nullptr};  // batch without labels: one block per graph
-    if ((rc = build_schedule(c, src.ptr, ls, range_cap(c, true), ROW_MAX, HUB_STAGED_MAX_WIDE))) return fail(rc);
-    int *cnt = c->counters + CNT_STRIDE * (plan.ncounter_steps - 2);
-    if ((rc = fill_i32(c, cnt, CNT_STRIDE, 0))) return fail(rc);
-    int64_t *dcount = c->dcounts + (plan.ncounter_steps - 2);
-    if ((rc = run_step(c, src, ls, c->p0, dcount, cnt, true, nullptr, true))) return fail(rc);
-    if (hipMemcpyAsync(&c->p0_count, dcount, 8, hipMemcpyDeviceToHost, c->stream) != hipSuccess)
-      return fail(KBISIM_EHIP);
-    if ((rc = read_err(c, &err))) return fail(rc);
+    const bool labelled = g->vlabel || num_graphs > 0;
+    auto copy_back = [&]() -> int {
+      HIP_TRY(hipMemcpyAsync(host, back, sizeof host, hipMemcpyDeviceToHost, c->stream));
+      HIP_TRY(hipStreamSynchronize(c->stream));
+      return 0;
+    };
+    // A hash collision that P0's one peeling round did not settle: all again,
+    // with host-driven rounds (the label rows' schedule shares the range lists).
+    for (bool careful = false;; careful = true) {
+      if (labelled && src.ptr) {
+        const int lcap = range_cap(c, true);
+        if ((rc = sched_enqueue(c, src.ptr, lcap, ROW_MAX, totals, nullptr))) return fail(rc);
+        if ((rc = copy_back())) return fail(rc);
+        if ((rc = sched_finish(c, src.ptr, ls, lcap, HUB_STAGED_MAX_WIDE, host, nullptr))) return fail(rc);
+      }
+      if ((rc = fill_i32(c, back, 3 * CNT_STRIDE, 0))) return fail(rc);
+      if (labelled &&
+          (rc = run_step(c, src, ls, c->p0, &totals[SCHED_TOTALS], cnt, careful, nullptr, true)))
+        return fail(rc);
+      if ((rc = sched_enqueue(c, g->row_ptr, gcap, grow_max, totals, c->nzv))) return fail(rc);
+      k_copy_i32<<<1, 1, 0, c->stream>>>((int *)&totals[SCHED_TOTALS + 1], (const int *)c->err, 1);
+      if (hipGetLastError() != hipSuccess) return fail(KBISIM_EHIP);
+      if ((rc = copy_back())) return fail(rc);
+      err = (u32)host[SCHED_TOTALS + 1];
+      if (labelled) c->p0_count = host[SCHED_TOTALS];
+      if (careful || err || !labelled || reinterpret_cast<const int *>(host)[2 * CNT_STRIDE + 2] == 0) break;
+    }
     if (err) return fail(KBISIM_EINTERNAL);
+    if ((rc = sched_finish(c, g->row_ptr, c->sched, gcap, c->narrow ? HUB_STAGED_MAX : HUB_STAGED_MAX_WIDE, host,
+                           c->nzv)))
+      return fail(rc);
   }
-  // Static schedule of the graph rows.
-  if ((rc = build_schedule(c, g->row_ptr, c->sched, range_cap(c, !c->narrow),
-                           c->narrow ? ROW_MAX_NARROW : ROW_MAX, c->narrow ? HUB_STAGED_MAX : HUB_STAGED_MAX_WIDE)))
-    return fail(rc);
-  if ((rc = build_nonempty_list(c, c->sched))) return fail(rc);
   if ((rc = sort_long_rows(c, c->sched))) return fail(rc);
   // a load of at most 1/4 (within the planned table): shorter probe runs measured
   // faster than a smaller, more cache-resident span
@@ -2811,7 +2568,7 @@ int kbisim_refine_noalloc(const kbisim_graph *g, int k, int32_t *const *out_bloc
   void *ws = nullptr;
   if ((rc = scratch_address(&ws))) return rc;
   kbisim_ctx *c = nullptr;
-  if ((rc = create_impl(g, k, nullptr, ws, NOALLOC_SCRATCH_BYTES, stream, 0, nullptr, &c, false))) return rc;
+  if ((rc = create_impl(g, k, nullptr, ws, NOALLOC_SCRATCH_BYTES, stream, 0, nullptr, &c))) return rc;
   rc = refine_impl(c, nullptr, k, out_block_ids, out_counts);
   kbisim_destroy(c);
   return rc;

@@ -826,6 +826,22 @@ __global__ void __launch_bounds__(256) k_sig_range(Src src, const Range *__restr
   zero_insert_wave(slots, zrep, zero, own, (u32)v, zep);
 }
 
+// Rows of exactly one item (P0 with one label per vertex): no set, no row
+// offsets, one vertex per thread.
+template <class Src>
+__global__ void __launch_bounds__(256) k_sig_one(Src src, int n, u64 *__restrict__ H, u32 *__restrict__ DC, u64 *table,
+                                                 u64 tmask, const u32 *__restrict__ dep, u64 hmask) {
+  __shared__ u32 slots[4][FIRST_SLOTS];
+  const int v = blockIdx.x * 256 + threadIdx.x;
+  u64 h = 0;
+  if (v < n) {
+    h = finalize_key(mix_pair(src.pair(v)), 1u, src.own(v)) & hmask;
+    H[v] = h;
+    DC[v] = 1u;
+  }
+  if (wave_first_of_key(slots[threadIdx.x >> 6], v < n, h)) table_insert(table, tmask, h, (u32)v, dep[EP_TABLE]);
+}
+
 // Row tier: one workgroup of NT threads per row of more entries than the
 // range capacity and at most EMAX.  All entries are gathered at once (EMAX / NT per thread), then
 // inserted into an LDS hash set of 2 * deg slots; first insertions add to
@@ -1448,11 +1464,9 @@ __global__ void __launch_bounds__(256) k_res_verify(Src src, const int *__restri
 }
 
 // ---------------------------------------------------------------- numbering
-// Reduce-then-scan over the flags "rep[v] == v" in vertex order (tiles of
-// 256 * ITEMS vertices, ITEMS = 8 or 16 per thread): per-tile head counts, one workgroup scans the tile
-// counts, then every tile numbers its heads.  A head's exclusive prefix is its
-// dense id, so blocks are numbered by their first vertex.  Non-heads get -1
-// (k_scan_write lists the heads; the steps number through head words).
+// Flags "rep[v] == v" in vertex order (tiles of 256 * ITEMS vertices, ITEMS =
+// 8 or 16 per thread).  A head's exclusive prefix is its dense id, so blocks
+// are numbered by their first vertex.
 template <int ITEMS>
 __device__ inline u32 tile_flags(int n, const int *__restrict__ rep, int64_t base) {
   int r[ITEMS];
@@ -1477,16 +1491,6 @@ __device__ inline u32 tile_flags(int n, const int *__restrict__ rep, int64_t bas
   return bits;
 }
 
-
-template <int ITEMS>
-__global__ void __launch_bounds__(256) k_tile_count(int n, const int *__restrict__ rep, u32 *__restrict__ tile_sum) {
-  __shared__ u32 sh_w[4];
-  const int64_t base = (int64_t)blockIdx.x * (256 * ITEMS) + (int64_t)threadIdx.x * ITEMS;
-  const u32 mine = __popc(tile_flags<ITEMS>(n, rep, base));
-  u32 total;
-  block_exclusive_scan(mine, sh_w, &total);
-  if (threadIdx.x == 0) tile_sum[blockIdx.x] = total;
-}
 
 // One workgroup of 1024 threads: in-place exclusive scan of ntiles counts.
 __global__ void __launch_bounds__(1024) k_tile_scan(int ntiles, u32 *tile_sum, int64_t *count_out) {
@@ -1529,39 +1533,13 @@ __global__ void __launch_bounds__(1024) k_tile_scan(int ntiles, u32 *tile_sum, i
   if (t == 0) *count_out = (int64_t)carry;
 }
 
-template <int ITEMS>
-__global__ void __launch_bounds__(256) k_scan_write(int n, const int *__restrict__ rep, const u32 *__restrict__ tile_pre,
-                                                    int *__restrict__ out, int out_aligned) {
-  __shared__ u32 sh_w[4];
-  const int64_t base = (int64_t)blockIdx.x * (256 * ITEMS) + (int64_t)threadIdx.x * ITEMS;
-  const u32 bits = tile_flags<ITEMS>(n, rep, base);
-  u32 total;
-  u32 id = tile_pre[blockIdx.x] + block_exclusive_scan(__popc(bits), sh_w, &total);
-  int o[ITEMS];
-#pragma unroll
-  for (int j = 0; j < ITEMS; ++j) {
-    o[j] = (bits & (1u << j)) ? (int)id : -1;
-    id += (bits >> j) & 1u;
-  }
-  if (out_aligned && base + ITEMS <= n) {
-    int4 *q4 = reinterpret_cast<int4 *>(out + base);
-#pragma unroll
-    for (int q = 0; q < ITEMS / 4; ++q) q4[q] = make_int4(o[4 * q], o[4 * q + 1], o[4 * q + 2], o[4 * q + 3]);
-  } else {
-#pragma unroll
-    for (int j = 0; j < ITEMS; ++j)
-      if (base + j < n) out[base + j] = o[j];
-  }
-}
-
 // Head words: the numbering of a step without the scattered write of every
 // head's id.  Word w holds one bit per vertex 64w..64w+63 (set for a head,
-// rep[v] == v) and the number of heads before the word in its tile (tiles of
-// 256 * ITEMS vertices, as k_tile_count; the tile counts go to tile_sum for
-// k_tile_scan).  A vertex then reads its dense id from its representative's
-// word: tile prefix + word prefix + heads below it in the word.  The words
-// (n / 4 bytes) and tile prefixes stay in the caches, unlike a gather of
-// every representative's id from the output (n * 4 bytes).
+// rep[v] == v) and the number of heads before the word in its tile (the
+// tile counts go to tile_sum for k_tile_scan).  A vertex then reads its dense
+// id from its representative's word: tile prefix + word prefix + heads below
+// it in the word.  The words (n / 4 bytes) and tile prefixes stay in the
+// caches, unlike a gather of every representative's id from the output.
 struct HeadWord {
   u64 bits;
   u32 pre;
@@ -1595,19 +1573,6 @@ __global__ void __launch_bounds__(256) k_head_words(int n, const int *__restrict
   if ((threadIdx.x % TPW) == 0 && base < n)
     *reinterpret_cast<u32x4 *>(&hw[base >> 6]) = u32x4{(u32)word, (u32)(word >> 32), pre, 0u};
   if (threadIdx.x == 0) tile_sum[blockIdx.x] = total;
-}
-
-// rep[v] = v for vertices with at least one entry, else -1 (heads of the
-// numbering scan, which then lists them in order).
-__global__ void k_mark_rows(int n, const int64_t *__restrict__ row_ptr, int *__restrict__ rep) {
-  const int v = blockIdx.x * blockDim.x + threadIdx.x;
-  if (v < n) rep[v] = row_ptr[v + 1] > row_ptr[v] ? v : -1;
-}
-
-// list[pos[v]] = v for every v with pos[v] >= 0.
-__global__ void k_list_from_ids(int n, const int *__restrict__ pos, int *__restrict__ list) {
-  const int v = blockIdx.x * blockDim.x + threadIdx.x;
-  if (v < n && pos[v] >= 0) list[pos[v]] = v;
 }
 
 // Every vertex takes its representative's dense id (head words), and the
@@ -1997,7 +1962,7 @@ constexpr int GRAPH_GRID = 8192;  // workgroups over all graphs of a batch
 // them, with no look at single rows (one thread per vertex walking its row
 // took 0.6 ms on 64 small graphs, the length of the longest row).  They also
 // write the graph id of its vertices.
-__global__ void __launch_bounds__(256) k_graph_ids(int64_t G, int share, const int64_t *__restrict__ first,
+__global__ void __launch_bounds__(256) k_graph_ids(int64_t G, int share, int64_t m, const int64_t *__restrict__ first,
                                                    const int64_t *__restrict__ row_ptr,
                                                    const int32_t *__restrict__ col, int *__restrict__ gid, u32 *err) {
   bool bad = false;
@@ -2007,8 +1972,9 @@ __global__ void __launch_bounds__(256) k_graph_ids(int64_t G, int share, const i
     const int64_t v0 = first[g], v1 = first[g + 1];
     if (v0 == v1) continue;
     for (int64_t v = v0 + t0; v < v1; v += stride) gid[v] = (int)g;
-    const int64_t e1 = row_ptr[v1];
-    for (int64_t e = row_ptr[v0] + t0; e < e1; e += stride) bad |= col[e] < v0 || col[e] >= v1;
+    // (the row offsets may be invalid themselves, which k_validate_rows reports)
+    const int64_t e0 = max<int64_t>(row_ptr[v0], 0), e1 = min<int64_t>(row_ptr[v1], m);
+    for (int64_t e = e0 + t0; e < e1; e += stride) bad |= col[e] < v0 || col[e] >= v1;
   }
   if (__ballot(bad) && (threadIdx.x & (WAVE - 1)) == 0) atomicOr(err, ERR_GRAPH_COL);
 }
@@ -2472,86 +2438,214 @@ __global__ void __launch_bounds__(256) k_transpose_unpack(int64_t m, const u64 *
 // closes before a row that would overflow it (range_edges entries), after
 // RANGE_VERTS vertices, before a longer row and at the end of its chunk of
 // SCHED_CHUNK_V vertices; longer rows go to the row tiers (up to RANGE_DMAX,
-// ROW_MAX and row_max entries) or are hubs.  One thread walks one chunk, so
-// the schedule depends on n and the degrees only.  The first walk counts per
-// chunk (cnt[list * nchunks + chunk], lists: ranges, up to RANGE_DMAX, up to
-// ROW_MAX, up to row_max, hubs; sums[5 * chunk + i]: range vertices and
-// entries, row-tier rows and entries, non-empty rows); the second writes at
-// the scanned offsets off[list * nchunks + chunk], the range lists one after
-// another in `ranges` (list starts in base[0..3]) and the hubs in `hubs`.
+// ROW_MAX and row_max entries) or are hubs.  The schedule depends on n and the
+// degrees only.  One workgroup takes one chunk, twice: the first launch
+// counts per chunk (cnt[list * nchunks + chunk], lists: ranges, up to
+// RANGE_DMAX, up to ROW_MAX, up to row_max, hubs; sums[5 * chunk + i]: range
+// vertices and entries, row-tier rows and entries, non-empty rows);
+// k_sched_scan turns the counts into offsets; the second launch writes the
+// range lists one after another in `ranges`, the hubs in `hubs` and the
+// non-empty vertices in `nzv` (unless null).
+//
+// Where a range that starts at row s would close depends on s alone, so all
+// the closing points of a chunk are found in parallel (a binary search over
+// the row offsets in LDS) and one thread then only follows them from the
+// chunk's start, one LDS read per range.  A thread that walked a chunk row by
+// row took 4 ms a launch at any size, and a host copy of the offsets with the
+// packing there 1 ns per vertex and a synchronisation.
 constexpr int SCHED_CHUNK_V = 16384;
+constexpr int SCHED_THREADS = 1024;
+constexpr int SCHED_PER = SCHED_CHUNK_V / SCHED_THREADS;
+
+// Totals of a schedule, written by k_sched_scan: rows per list, then the sums.
+constexpr int SCHED_TOTALS = 10;
 
 template <bool WRITE>
-__global__ void k_sched_walk(const int64_t *__restrict__ ptr, int64_t n, int nchunks, int range_edges,
-                             int64_t row_max, int *__restrict__ cnt, int64_t *__restrict__ sums,
-                             const int *__restrict__ off, const int *__restrict__ base, Range *__restrict__ ranges,
-                             int *__restrict__ hubs) {
-  const int ci = blockIdx.x * blockDim.x + threadIdx.x;
-  if (ci >= nchunks) return;
-  const int64_t v0 = (int64_t)ci * SCHED_CHUNK_V, v1 = min(n, v0 + (int64_t)SCHED_CHUNK_V);
-  int c[5] = {0, 0, 0, 0, 0};
-  int o[5] = {0, 0, 0, 0, 0};
-  int b4[4] = {0, 0, 0, 0};
-  if constexpr (WRITE) {
+__global__ void __launch_bounds__(SCHED_THREADS) k_sched_chunks(const int64_t *__restrict__ ptr, int64_t n,
+                                                                int nchunks, int range_edges, int64_t row_max,
+                                                                int *__restrict__ cnt, int64_t *__restrict__ sums,
+                                                                const int64_t *__restrict__ totals,
+                                                                Range *__restrict__ ranges, int *__restrict__ hubs,
+                                                                int *__restrict__ nzv) {
+  static_assert(SCHED_CHUNK_V <= 65536 && SCHED_PER == 16, "16-bit closing points, one start bit per row of a thread");
+  __shared__ u32 off[SCHED_CHUNK_V + 1];              // low words: differences inside a range are exact
+  __shared__ unsigned short close_at[SCHED_CHUNK_V];  // end - 1 of the range that starts at a row
+  __shared__ unsigned short starts[SCHED_THREADS];    // bit j of word t: row 16 t + j starts a range (or is long)
+  __shared__ int wl[SCHED_THREADS / WAVE];
+  __shared__ int64_t wsum[5][SCHED_THREADS / WAVE];
+  __shared__ int wcnt[6][SCHED_THREADS / WAVE];
+  const int t = threadIdx.x, lane = t & 63, w = t >> 6, ci = blockIdx.x;
+  const int64_t v0 = (int64_t)ci * SCHED_CHUNK_V;
+  const int V = (int)min<int64_t>(n - v0, SCHED_CHUNK_V);
+  for (int i = t; i <= V; i += SCHED_THREADS) off[i] = (u32)ptr[v0 + i];
+  // this thread's rows: 16 t .. 16 t + 15
+  const int r0 = t * SCHED_PER;
+  int64_t d[SCHED_PER], eb = 0;
+  {
+    int64_t prev = r0 <= V ? ptr[v0 + r0] : 0;
+    eb = prev;
 #pragma unroll
-    for (int l = 0; l < 5; ++l) o[l] = off[(int64_t)l * nchunks + ci];
-#pragma unroll
-    for (int l = 0; l < 4; ++l) b4[l] = base[l];
-  }
-  int64_t rv = 0, re = 0, rowv = 0, rowe = 0, nonempty = 0;
-  int64_t cur0 = -1, cur_e = 0, cur_b = 0;
-  auto emit = [&](int list, int64_t a, int64_t z, int64_t ne, int64_t e0) {
-    if constexpr (WRITE) ranges[b4[list] + o[list] + c[list]] = Range{(int)a, (int)z, (int)ne, 0, e0};
-    ++c[list];
-  };
-  auto close = [&](int64_t vend) {
-    if (cur0 >= 0) emit(0, cur0, vend, cur_e, cur_b);
-    cur0 = -1;
-    cur_e = 0;
-  };
-  constexpr int PF = 16;  // row ends requested together
-  int64_t prev = ptr[v0];
-  for (int64_t vb = v0; vb < v1; vb += PF) {
-    int64_t nx[PF];
-#pragma unroll
-    for (int j = 0; j < PF; ++j) nx[j] = vb + j < v1 ? ptr[vb + j + 1] : 0;
-#pragma unroll
-    for (int j = 0; j < PF; ++j) {
-      const int64_t v = vb + j;
-      if (v >= v1) break;
-      const int64_t b = prev, d = nx[j] - prev;
-      prev = nx[j];
-      nonempty += d > 0;
-      if (d > row_max) {
-        close(v);
-        if constexpr (WRITE) hubs[o[4] + c[4]] = (int)v;
-        ++c[4];
-      } else if (d > range_edges) {
-        close(v);
-        emit(d > ROW_MAX ? 3 : d > RANGE_DMAX ? 2 : 1, v, v + 1, d, b);
-        rowv += 1;
-        rowe += d;
-      } else {
-        if (cur0 >= 0 && (cur_e + d > range_edges || v - cur0 == RANGE_VERTS)) close(v);
-        if (cur0 < 0) {
-          cur0 = v;
-          cur_b = b;
-        }
-        cur_e += d;
-        rv += 1;
-        re += d;
-      }
+    for (int j = 0; j < SCHED_PER; ++j) {
+      const int64_t nx = r0 + j < V ? ptr[v0 + r0 + j + 1] : prev;
+      d[j] = nx - prev;
+      prev = nx;
     }
   }
-  close(v1);
+  u32 lmask = 0;  // long rows
+#pragma unroll
+  for (int j = 0; j < SCHED_PER; ++j) lmask |= (r0 + j < V && d[j] > range_edges ? 1u : 0u) << j;
+  starts[t] = 0;
+  // first long row after this thread's rows
+  int nl = lmask ? r0 + __ffs(lmask) - 1 : V;
+#pragma unroll
+  for (int o = 1; o < WAVE; o <<= 1) {
+    const int y = __shfl_down(nl, o, WAVE);
+    if (lane + o < WAVE) nl = min(nl, y);
+  }
+  if (lane == 0) wl[w] = nl;
+  __syncthreads();
+  int next_long = __shfl_down(nl, 1, WAVE);
+  if (lane == WAVE - 1) next_long = V;
+  for (int i = w + 1; i < SCHED_THREADS / WAVE; ++i) next_long = min(next_long, wl[i]);
+#pragma unroll
+  for (int j = SCHED_PER - 1; j >= 0; --j) {
+    const int s = r0 + j;
+    if (s >= V) continue;
+    if ((lmask >> j) & 1u) {
+      next_long = s;
+      close_at[s] = (unsigned short)s;
+      continue;
+    }
+    // largest e <= lim with off[e] - off[s] <= range_edges (a row that is not long fits)
+    int lo = s + 1, hi = min(s + RANGE_VERTS, next_long);
+    while (lo < hi) {
+      const int mid = (lo + hi + 1) >> 1;
+      if (off[mid] - off[s] <= (u32)range_edges) lo = mid;
+      else hi = mid - 1;
+    }
+    close_at[s] = (unsigned short)(lo - 1);
+  }
+  __syncthreads();
+  if (t == 0)
+    for (int s = 0; s < V;) {
+      starts[s >> 4] |= (unsigned short)(1u << (s & 15));
+      s = (int)close_at[s] + 1;
+    }
+  __syncthreads();
+  // lists of this thread's starts
+  const u32 st = starts[t];
+  int c[6] = {0, 0, 0, 0, 0, 0};  // the five lists, then non-empty rows
+  int64_t sm[5] = {0, 0, 0, 0, 0};
+#pragma unroll
+  for (int j = 0; j < SCHED_PER; ++j) {
+    if (r0 + j >= V) continue;
+    c[5] += d[j] > 0;
+    const bool lg = (lmask >> j) & 1u;
+    const int list = !lg ? 0 : d[j] > row_max ? 4 : d[j] > ROW_MAX ? 3 : d[j] > RANGE_DMAX ? 2 : 1;
+    if (!lg) {
+      sm[0] += 1;
+      sm[1] += d[j];
+    } else if (list < 4) {
+      sm[2] += 1;
+      sm[3] += d[j];
+    }
+    const bool s = (st >> j) & 1u;
+#pragma unroll
+    for (int l = 0; l < 5; ++l) c[l] += s && list == l;
+  }
+  sm[4] = c[5];
   if constexpr (!WRITE) {
 #pragma unroll
-    for (int l = 0; l < 5; ++l) cnt[(int64_t)l * nchunks + ci] = c[l];
-    sums[5 * (int64_t)ci + 0] = rv;
-    sums[5 * (int64_t)ci + 1] = re;
-    sums[5 * (int64_t)ci + 2] = rowv;
-    sums[5 * (int64_t)ci + 3] = rowe;
-    sums[5 * (int64_t)ci + 4] = nonempty;
+    for (int l = 0; l < 5; ++l) {
+      const u32 x = wave_sum_u32((u32)c[l]);
+      const u64 y = wave_sum_u64((u64)sm[l]);
+      if (lane == 0) {
+        wcnt[l][w] = (int)x;
+        wsum[l][w] = (int64_t)y;
+      }
+    }
+    __syncthreads();
+    if (t < 5) {
+      int x = 0;
+      int64_t y = 0;
+      for (int i = 0; i < SCHED_THREADS / WAVE; ++i) {
+        x += wcnt[t][i];
+        y += wsum[t][i];
+      }
+      cnt[(int64_t)t * nchunks + ci] = x;
+      sums[(int64_t)t * nchunks + ci] = y;
+    }
+  } else {
+    // exclusive positions inside the chunk, per list
+    int at[6];
+#pragma unroll
+    for (int l = 0; l < 6; ++l) {
+      int x = c[l];
+#pragma unroll
+      for (int o = 1; o < WAVE; o <<= 1) {
+        const int y = __shfl_up(x, o, WAVE);
+        if (lane >= o) x += y;
+      }
+      if (lane == WAVE - 1) wcnt[l][w] = x;
+      at[l] = x - c[l];
+    }
+    __syncthreads();
+    int64_t base = 0;
+#pragma unroll
+    for (int l = 0; l < 6; ++l) {
+      for (int i = 0; i < w; ++i) at[l] += wcnt[l][i];
+      // the scanned offsets: counts of the lists, sums[4] of the non-empty rows
+      at[l] += l < 5 ? cnt[(int64_t)l * nchunks + ci] : (int)sums[(int64_t)4 * nchunks + ci];
+      if (l < 4) {
+        at[l] += (int)base;
+        base += totals[l];
+      }
+    }
+    int64_t e = eb;
+#pragma unroll
+    for (int j = 0; j < SCHED_PER; ++j) {
+      if (r0 + j >= V) continue;
+      const int s = r0 + j;
+      const int v = (int)(v0 + s);
+      if (nzv && d[j] > 0) nzv[at[5]++] = v;
+      if ((st >> j) & 1u) {
+        if (!((lmask >> j) & 1u)) {
+          const int z = (int)close_at[s] + 1;
+          ranges[at[0]++] = Range{v, (int)(v0 + z), (int)(off[z] - off[s]), 0, e};
+        } else if (d[j] > row_max) {
+          hubs[at[4]++] = v;
+        } else {
+          const Range one{v, v + 1, (int)d[j], 0, e};
+          if (d[j] > ROW_MAX) ranges[at[3]++] = one;
+          else if (d[j] > RANGE_DMAX) ranges[at[2]++] = one;
+          else ranges[at[1]++] = one;
+        }
+      }
+      e += d[j];
+    }
+  }
+}
+
+// One workgroup: in-place exclusive scan of every list's chunk counts and of
+// the non-empty rows (sums[4]), and the totals of all ten.
+__global__ void __launch_bounds__(256) k_sched_scan(int nchunks, int *__restrict__ cnt, int64_t *__restrict__ sums,
+                                                    int64_t *__restrict__ totals) {
+  __shared__ int64_t sh_w[4];
+  for (int l = 0; l < SCHED_TOTALS; ++l) {
+    int64_t carry = 0;
+    for (int b0 = 0; b0 < nchunks; b0 += 256) {
+      const int i = b0 + threadIdx.x;
+      const int64_t at = (int64_t)(l % 5) * nchunks + i;
+      const int64_t mine = i < nchunks ? (l < 5 ? (int64_t)cnt[at] : sums[at]) : 0;
+      int64_t total;
+      const int64_t ex = carry + block_exclusive_scan64(mine, sh_w, &total);
+      if (i < nchunks) {
+        if (l < 5) cnt[at] = (int)ex;
+        else if (l == 9) sums[at] = ex;
+      }
+      carry += total;
+    }
+    if (threadIdx.x == 0) totals[l] = carry;
   }
 }
 
