@@ -33,13 +33,14 @@ namespace {
 thread_local char g_hip_msg[256] = "";
 
 constexpr size_t ALIGN = 256;
-constexpr int CNT_STRIDE = 16;  // device counters per step
+constexpr int CNT_STRIDE = STEP_ROW;  // device counters per step
 constexpr int PERSIST_GRID = 2048;
 constexpr int RES_GRID = 256;
 constexpr int CLEAR_GRID = 2048;
 constexpr int MIN_RANGE_EDGES = 1024;  // smallest tunable range capacity
 constexpr int MIN_HUB_CHUNK = 2048;    // smallest tunable hub chunk
 constexpr int MAX_GRAPH_CACHE = 8;
+constexpr size_t READBACK_MAX = 1 << 16;  // bytes of counters and counts copied back at once
 
 inline size_t align_up(size_t x) { return (x + ALIGN - 1) / ALIGN * ALIGN; }
 
@@ -141,6 +142,7 @@ struct Schedule {
   int nchunks = 0, nparts = 0, ngchunks = 0;
   int64_t gset_begin = 0, gset_end = 0;  // global hash sets of very large hubs
   int64_t nonempty = 0;                   // rows with at least one entry
+  int64_t nlong = 0;                      // rows of more than SMALL_MAX entries
   const int *nzv = nullptr;               // their vertices in order (graph rows), or null
   int64_t info[8] = {0, 0, 0, 0, 0, 0, 0, 0};  // vertices, entries per tier
 };
@@ -177,6 +179,7 @@ struct kbisim_ctx {
   char *ws;
   u64 *H, *table, *ctable, *hacc, *hubsets, *zrep;
   u32 *DC, *hcnt, *err, *tiles, *dep;
+  const u32 *cur = nullptr;  // the epochs of the step being enqueued: dep, or its row (k_prepare_steps)
   HeadWord *hw;
   int *rep, *p0, *vlist, *clA, *clB, *lists, *counters, *poff, *gcol, *rank, *gpid[2], *nzv;
   int64_t *dcounts;
@@ -393,15 +396,21 @@ const int32_t *sep_labels(const kbisim_ctx *c) { return c->glab ? c->glab : c->g
 // A step's numbering: head words and the tile prefixes of the heads in
 // vertex order (k_head_words, k_tile_scan); the block count to count_dev.
 // The assign kernels then read every vertex's dense id through the result.
-int numbering_words(kbisim_ctx *c, int n, int64_t *count_dev, HeadIds *ids) {
+// With scan_tiles, up to 256 tiles are left unscanned and their number put
+// there, for k_assign.
+int numbering_words(kbisim_ctx *c, int n, int64_t *count_dev, HeadIds *ids, int *scan_tiles = nullptr) {
   const int items = c->tune.scan_items;
   const int ntiles = (int)blocks_for(n, 256 * items);
   if (items == 8) k_head_words<8><<<(unsigned)ntiles, 256, 0, c->stream>>>(n, c->rep, c->hw, c->tiles);
   else k_head_words<16><<<(unsigned)ntiles, 256, 0, c->stream>>>(n, c->rep, c->hw, c->tiles);
   LAUNCH_CHECK();
+  *ids = HeadIds{c->hw, c->tiles, items == 8 ? 11 : 12};
+  if (scan_tiles && ntiles <= 256) {
+    *scan_tiles = ntiles;
+    return 0;
+  }
   k_tile_scan<<<1, 1024, 0, c->stream>>>(ntiles, c->tiles, count_dev);
   LAUNCH_CHECK();
-  *ids = HeadIds{c->hw, c->tiles, items == 8 ? 11 : 12};
   return 0;
 }
 
@@ -556,13 +565,13 @@ int plan_hubs(kbisim_ctx *c, Schedule &s, const std::vector<int> &hubs, const st
 // list of non-empty vertices) and leaves the totals on the device;
 // sched_finish takes the totals, once copied to the host, and plans the hubs.
 // row_max: longest row with a workgroup of its own (longer rows are hubs).
-// Scratch: c->vlist (224 bytes at least, 80 per chunk); the totals go to
+// Scratch: c->vlist (68 bytes per chunk); the totals go to
 // `totals` (SCHED_TOTALS words).
 int sched_enqueue(kbisim_ctx *c, const int64_t *ptr, int range_edges, int64_t row_max, int64_t *totals, int *nzv) {
   const int64_t n = c->g.n;
   const int nch = (int)((n + SCHED_CHUNK_V - 1) / SCHED_CHUNK_V);
   int64_t *sums = reinterpret_cast<int64_t *>(c->vlist);
-  int *cnt = reinterpret_cast<int *>(sums + 5 * (size_t)nch);
+  int *cnt = reinterpret_cast<int *>(sums + 6 * (size_t)nch);
   k_sched_chunks<false><<<(unsigned)nch, SCHED_THREADS, 0, c->stream>>>(ptr, n, nch, range_edges, row_max, cnt, sums,
                                                                         totals, nullptr, nullptr, nullptr);
   k_sched_scan<<<1, 256, 0, c->stream>>>(nch, cnt, sums, totals);
@@ -582,6 +591,7 @@ int sched_finish(kbisim_ctx *c, const int64_t *ptr, Schedule &s, int range_edges
   s.nrow20 = (int)tot[3];
   for (int i = 0; i < 4; ++i) s.info[i] = tot[5 + i];
   s.nonempty = tot[9];
+  s.nlong = tot[10];
   s.nzv = nzv;
   const int nh = (int)tot[4];
   std::vector<int> hubs((size_t)nh);
@@ -736,10 +746,10 @@ int build_rank(kbisim_ctx *c) {
 template <class Src>
 int peel_round(kbisim_ctx *c, const Src &src, int *in_cnt, int *in_list, int *out_cnt, int *out_list) {
   ProfScope ps(c, KBISIM_K_PEEL);
-  k_res_insert<<<RES_GRID, 256, 0, c->stream>>>(in_cnt, in_list, c->H, c->ctable, c->plan.tslots - 1, c->dep);
+  k_res_insert<<<RES_GRID, 256, 0, c->stream>>>(in_cnt, in_list, c->H, c->ctable, c->plan.tslots - 1, c->cur);
   LAUNCH_CHECK();
   k_res_verify<Src><<<RES_GRID, 256, 0, c->stream>>>(src, in_cnt, in_list, c->H, c->DC, c->ctable,
-                                                     c->plan.tslots - 1, c->dep, c->rep, out_cnt, out_list, c->err);
+                                                     c->plan.tslots - 1, c->cur, c->rep, out_cnt, out_list, c->err);
   LAUNCH_CHECK();
   return 0;
 }
@@ -758,10 +768,10 @@ int launch_range_kernel(kbisim_ctx *c, const Src &src, const Schedule &s, u64 tm
   ProfScope ps(c, KBISIM_K_SIG_RANGE);
   if (s.range_edges == 1024)
     k_sig_range<Src, 1024, K, SKIP><<<(unsigned)s.nranges, 256, 0, c->stream>>>(
-        src, c->ranges, c->H, c->DC, c->table, tmask, c->dep, c->hmask, c->zrep, zfresh, skip);
+        src, c->ranges, c->H, c->DC, c->table, tmask, c->cur, c->hmask, c->zrep, zfresh, skip);
   else
     k_sig_range<Src, 2048, K, SKIP><<<(unsigned)s.nranges, 256, 0, c->stream>>>(
-        src, c->ranges, c->H, c->DC, c->table, tmask, c->dep, c->hmask, c->zrep, zfresh, skip);
+        src, c->ranges, c->H, c->DC, c->table, tmask, c->cur, c->hmask, c->zrep, zfresh, skip);
   LAUNCH_CHECK();
   return 0;
 }
@@ -785,18 +795,18 @@ int launch_ranges_k(kbisim_ctx *c, const Src &src, const Schedule &s, int zfresh
     ProfScope ps(c, KBISIM_K_SIG_BLOCK);
     if (s.nbig) {
       k_sig_row<Src, RANGE_DMAX, 512, K><<<(unsigned)s.nbig, 512, 0, c->stream>>>(
-          src, c->ranges + s.nranges, c->H, c->DC, c->table, tmask, c->dep, c->hmask, c->zrep, skip);
+          src, c->ranges + s.nranges, c->H, c->DC, c->table, tmask, c->cur, c->hmask, c->zrep, skip);
       LAUNCH_CHECK();
     }
     if (s.nrow8) {
       k_sig_row<Src, ROW_MAX, 1024, K><<<(unsigned)s.nrow8, 1024, 0, c->stream>>>(
-          src, c->ranges + s.nranges + s.nbig, c->H, c->DC, c->table, tmask, c->dep, c->hmask, c->zrep, skip);
+          src, c->ranges + s.nranges + s.nbig, c->H, c->DC, c->table, tmask, c->cur, c->hmask, c->zrep, skip);
       LAUNCH_CHECK();
     }
     if constexpr (std::is_same<K, u32>::value) {
       if (s.nrow20) {
         k_sig_row<Src, ROW_MAX_NARROW, 1024, u32><<<(unsigned)s.nrow20, 1024, 0, c->stream>>>(
-            src, c->ranges + s.nranges + s.nbig + s.nrow8, c->H, c->DC, c->table, tmask, c->dep, c->hmask, c->zrep,
+            src, c->ranges + s.nranges + s.nbig + s.nrow8, c->H, c->DC, c->table, tmask, c->cur, c->hmask, c->zrep,
             skip);
         LAUNCH_CHECK();
       }
@@ -862,7 +872,7 @@ int launch_signatures(kbisim_ctx *c, const Src &src, const Schedule &s, bool zfr
     if (!src.ptr) {  // one label per vertex
       ProfScope ps(c, KBISIM_K_SIG_RANGE);
       k_sig_one<Src><<<blocks_for(c->g.n, 256), 256, 0, c->stream>>>(src, (int)c->g.n, c->H, c->DC, c->table, tmask,
-                                                                    c->dep, c->hmask);
+                                                                    c->cur, c->hmask);
       LAUNCH_CHECK();
       return 0;
     }
@@ -884,33 +894,37 @@ int launch_signatures(kbisim_ctx *c, const Src &src, const Schedule &s, bool zfr
     if (s.ngchunks) {
       ProfScope ps(c, KBISIM_K_HUB_STAGE);
       k_sig_hub_global<Src><<<(unsigned)s.ngchunks, 256, 0, c->stream>>>(src, c->gchunks, hubs, c->hubsets, c->hacc,
-                                                                         c->hcnt, c->dep, skip_in);
+                                                                         c->hcnt, c->cur, skip_in);
       LAUNCH_CHECK();
     }
     ProfScope ps(c, KBISIM_K_HUB_FINAL);
     k_hub_final<Src><<<blocks_for(s.nhub, 256), 256, 0, c->stream>>>(src, hubs, s.nhub, c->hacc, c->hcnt, c->H, c->DC,
-                                                                     c->table, tmask, c->dep, c->hmask, c->zrep,
+                                                                     c->table, tmask, c->cur, c->hmask, c->zrep,
                                                                      skip_in);
     LAUNCH_CHECK();
   }
   return 0;
 }
 
-// After the lookup: exact checks of longer rows, one peeling round and, when
-// careful, host-driven peeling rounds until no collision is left.
+// After the lookup: exact checks of longer rows (any_long: the schedule has
+// some), one peeling round and, when careful, host-driven peeling rounds until
+// no collision is left.
 template <class Src>
-int settle_collisions(kbisim_ctx *c, const Src &src, const Schedule &s, int *cnt, bool careful) {
+int settle_collisions(kbisim_ctx *c, const Src &src, const Schedule &s, int *cnt, bool careful, bool any_long = true) {
   const int n = (int)c->g.n;
   int rc = 0;
-  {
+  if (any_long) {
     ProfScope ps(c, KBISIM_K_VERIFY);
     k_verify<Src><<<PERSIST_GRID, 256, 0, c->stream>>>(src, &cnt[0], c->vlist, c->DC, c->rep, &cnt[1], c->clA,
                                                        c->err);
     LAUNCH_CHECK();
   }
-  rc = peel_round(c, src, &cnt[1], c->clA, &cnt[2], c->clB);
-  if (rc) return rc;
-  if (careful) {
+  if (!careful) {
+    ProfScope ps(c, KBISIM_K_PEEL);
+    k_peel_few<Src><<<1, 256, 0, c->stream>>>(src, &cnt[1], c->clA, c->H, c->DC, c->rep, &cnt[2], c->clB, c->err);
+    LAUNCH_CHECK();
+  } else {
+    if ((rc = peel_round(c, src, &cnt[1], c->clA, &cnt[2], c->clB))) return rc;
     int *in_cnt = &cnt[2], *out_cnt = &cnt[3];
     int *in_list = c->clB, *out_list = c->clA;
     for (int round = 0;; ++round) {
@@ -937,8 +951,9 @@ int run_step(kbisim_ctx *c, const Src &src, const Schedule &s, int *out, int64_t
   const int n = (int)c->g.n;
   if (n == 0) return 0;
   const u64 tmask = table_mask<Src>(c);
-  int rc = advance(c, ADV_TABLE | ADV_CTABLE | ADV_ZERO | (s.ngchunks ? ADV_HUB : 0u), s);
-  if (rc) return rc;
+  int rc = 0;
+  if (c->cur == c->dep && (rc = advance(c, ADV_TABLE | ADV_CTABLE | ADV_ZERO | (s.ngchunks ? ADV_HUB : 0u), s)))
+    return rc;
   if ((rc = launch_signatures(c, src, s, zfresh, skip_in))) return rc;
   {
     ProfScope ps(c, KBISIM_K_LOOKUP);
@@ -947,16 +962,17 @@ int run_step(kbisim_ctx *c, const Src &src, const Schedule &s, int *out, int64_t
     const bool listed = !zfresh && s.nzv != nullptr;
     const int count = listed ? (int)s.nonempty : n;
     k_lookup<Src><<<blocks_for(std::max(count, 1), 256), 256, 0, c->stream>>>(
-        src, count, listed ? s.nzv : nullptr, c->H, c->DC, c->table, tmask, c->dep, c->rep,
+        src, count, listed ? s.nzv : nullptr, c->H, c->DC, c->table, tmask, c->cur, c->rep,
                                                              &cnt[0], c->vlist, &cnt[1], c->clA, c->err, c->zrep,
                                                              zfresh ? 1 : 0, skip_in, nullptr, nullptr);
     LAUNCH_CHECK();
   }
-  if ((rc = settle_collisions(c, src, s, cnt, careful))) return rc;
+  if ((rc = settle_collisions(c, src, s, cnt, careful, careful || s.nlong > 0))) return rc;
   HeadIds ids{};
+  int scan_tiles = 0;  // tile counts that k_assign scans itself
   {
     ProfScope ps(c, KBISIM_K_SCAN);
-    if ((rc = numbering_words(c, n, count_dev, &ids))) return rc;
+    if ((rc = numbering_words(c, n, count_dev, &ids, names_out ? nullptr : &scan_tiles))) return rc;
   }
   {
     ProfScope ps(c, KBISIM_K_ASSIGN);
@@ -965,12 +981,18 @@ int run_step(kbisim_ctx *c, const Src &src, const Schedule &s, int *out, int64_t
                                                                 gpid_next ? c->rank : nullptr, gpid_next, nullptr,
                                                                 nullptr, nullptr, nullptr, nullptr);
     } else {
-      k_assign<<<blocks_for((n + ASSIGN_V - 1) / ASSIGN_V, 256), 256, 0, c->stream>>>(
-          n, c->rep, ids, out, gpid_next ? c->rank : nullptr, gpid_next, single_out ? c->multi : nullptr, c->dep);
+      const unsigned ag = blocks_for((n + ASSIGN_V - 1) / ASSIGN_V, 256);
+      const int *rank = gpid_next ? c->rank : nullptr;
+      u32 *multi = single_out ? c->multi : nullptr;
+      if (scan_tiles)
+        k_assign<true><<<ag, 256, 0, c->stream>>>(n, c->rep, ids, out, rank, gpid_next, multi, c->cur, scan_tiles,
+                                                  count_dev);
+      else
+        k_assign<false><<<ag, 256, 0, c->stream>>>(n, c->rep, ids, out, rank, gpid_next, multi, c->cur, 0, nullptr);
     }
     LAUNCH_CHECK();
     if (single_out) {
-      k_singletons<<<blocks_for(n, 256), 256, 0, c->stream>>>(n, c->rep, c->multi, c->dep, single_out);
+      k_singletons<<<blocks_for(n, 256), 256, 0, c->stream>>>(n, c->rep, c->multi, c->cur, single_out);
       LAUNCH_CHECK();
     }
   }
@@ -984,16 +1006,39 @@ int run_step(kbisim_ctx *c, const Src &src, const Schedule &s, int *out, int64_t
 // copy prev into the rank-ordered buffer first (false only when the previous
 // step of this context already left it there).
 int enqueue_steps(kbisim_ctx *c, const int32_t *prev, int i0, int k, int32_t *const *out, bool careful,
-                  int cstride, bool scatter = true) {
+                  int cstride, bool scatter = true, bool reset_err = false) {
   const int n = (int)c->g.n;
   const bool batch = c->num_graphs > 0;
+  // Counters and epochs are laid out ahead, for up to STEP_SEGMENT steps in one
+  // launch; not where the host drives peeling rounds (they advance the epochs
+  // too) or global hub sets need clearing every third step.
+  const bool ahead = !careful && !c->sched.ngchunks;
+  struct Restore {  // whatever way this returns, later calls use the context's epochs
+    kbisim_ctx *c;
+    ~Restore() { c->cur = c->dep; }
+  } restore{c};
   int rc = 0;
+  if (!ahead) {
+    if (reset_err && (rc = fill_i32(c, (int *)c->err, 1, 0))) return rc;
+    if ((rc = fill_i32(c, c->counters + CNT_STRIDE * (size_t)i0, CNT_STRIDE * (int64_t)(k - i0), 0))) return rc;
+  }
   if (scatter) {
     k_scatter_rank<<<blocks_for(n, 256), 256, 0, c->stream>>>(n, prev, c->rank, c->gpid[i0 & 1]);
     LAUNCH_CHECK();
   }
   for (int i = i0; i < k; ++i) {
-    if (careful && (rc = fill_i32(c, c->counters + CNT_STRIDE * i, CNT_STRIDE, 0))) return rc;
+    if (ahead) {
+      if ((i - i0) % STEP_SEGMENT == 0) {
+        ProfScope ps(c, KBISIM_K_FILL);
+        k_prepare_steps<<<1, 64, 0, c->stream>>>(c->dep, c->counters, i, std::min(STEP_SEGMENT, k - i), c->err,
+                                                 reset_err && i == i0 ? 1 : 0);
+        LAUNCH_CHECK();
+        k_clear_if<<<CLEAR_GRID, 256, 0, c->stream>>>(c->dep, c->table, (int64_t)c->plan.tslots, c->ctable,
+                                                      c->hubsets, 0);
+        LAUNCH_CHECK();
+      }
+      c->cur = reinterpret_cast<const u32 *>(c->counters + CNT_STRIDE * (size_t)i) + STEP_EPOCHS;
+    }
     int *dst = batch ? c->ibuf[i & 1] : out[i];
     // work-efficient mode: singletons of P_i (flags of step i-1) are not refined
     const unsigned char *skip_in = (c->work_eff && i > 0) ? c->single[(i - 1) & 1] : nullptr;
@@ -1053,12 +1098,10 @@ int refine_we(kbisim_ctx *c, const int32_t *start, int k, int32_t *const *out, i
   const int32_t *p0 = start ? start : c->p0;
   int64_t prev_count = start ? -1 : c->p0_count;
   int rc = 0;
-  if ((rc = fill_i32(c, c->counters, (int64_t)CNT_STRIDE * k, 0))) return rc;
-  if ((rc = fill_i32(c, (int *)c->err, 1, 0))) return rc;
   int done = k;
   for (int i = 0; i < k; ++i) {
     const int32_t *prev = i == 0 ? p0 : (batch ? c->ibuf[(i - 1) & 1] : out[i - 1]);
-    if ((rc = enqueue_steps(c, prev, i, i + 1, out, false, k, i == 0))) return rc;
+    if ((rc = enqueue_steps(c, prev, i, i + 1, out, false, k, i == 0, i == 0))) return rc;
     int left = 0;
     u32 err = 0;
     int64_t cnt = 0;
@@ -1127,9 +1170,7 @@ int refine_impl(kbisim_ctx *c, const int32_t *start, int k, int32_t *const *out,
         c->graphs.erase(c->graphs.begin());
       }
       HIP_TRY(hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal));
-      int rc1 = fill_i32(c, c->counters, (int64_t)CNT_STRIDE * k, 0);
-      if (!rc1) rc1 = fill_i32(c, (int *)c->err, 1, 0);
-      if (!rc1) rc1 = enqueue_steps(c, p0, 0, k, out, false, k);
+      const int rc1 = enqueue_steps(c, p0, 0, k, out, false, k, true, true);
       hipGraph_t graph = nullptr;
       hipError_t e = hipStreamEndCapture(c->stream, &graph);
       if (rc1) {
@@ -1145,16 +1186,20 @@ int refine_impl(kbisim_ctx *c, const int32_t *start, int k, int32_t *const *out,
     }
     HIP_TRY(hipGraphLaunch(it->second, c->stream));
   } else {
-    if ((rc = fill_i32(c, c->counters, (int64_t)CNT_STRIDE * k, 0))) return rc;
-    if ((rc = fill_i32(c, (int *)c->err, 1, 0))) return rc;
-    if ((rc = enqueue_steps(c, p0, 0, k, out, false, k))) return rc;
+    if ((rc = enqueue_steps(c, p0, 0, k, out, false, k, true, true))) return rc;
   }
-  std::vector<int> hc((size_t)CNT_STRIDE * k);
+  // Counters, block counts and the error word are one stretch of the
+  // workspace: one copy brings them back, as long as it is short.
+  const size_t span = c->plan.off_err + sizeof(u32) - c->plan.off_counters;
+  const bool whole = span <= READBACK_MAX;
+  std::vector<int> hc(whole ? (span + 3) / 4 : (size_t)CNT_STRIDE * k);
   u32 err = 0;
-  HIP_TRY(hipMemcpyAsync(hc.data(), c->counters, 4 * hc.size(), hipMemcpyDeviceToHost, c->stream));
-  HIP_TRY(hipMemcpyAsync(&err, c->err, sizeof err, hipMemcpyDeviceToHost, c->stream));
+  HIP_TRY(hipMemcpyAsync(hc.data(), c->counters, whole ? span : 4 * hc.size(), hipMemcpyDeviceToHost, c->stream));
+  if (!whole) HIP_TRY(hipMemcpyAsync(&err, c->err, sizeof err, hipMemcpyDeviceToHost, c->stream));
+  if (batch) HIP_TRY(hipMemcpyAsync(counts, c->bcounts, 8 * (size_t)ncounts, hipMemcpyDeviceToHost, c->stream));
   HIP_TRY(hipStreamSynchronize(c->stream));
   prof_collect(c);
+  if (whole) memcpy(&err, (const char *)hc.data() + (c->plan.off_err - c->plan.off_counters), sizeof err);
   if (err) return KBISIM_EINTERNAL;
   int first_bad = -1;
   for (int i = 0; i < k; ++i)
@@ -1171,12 +1216,13 @@ int refine_impl(kbisim_ctx *c, const int32_t *start, int k, int32_t *const *out,
     prof_collect(c);
     if (err) return KBISIM_EINTERNAL;
   }
-  if (batch) {
-    HIP_TRY(hipMemcpyAsync(counts, c->bcounts, 8 * (size_t)ncounts, hipMemcpyDeviceToHost, c->stream));
-  } else {
-    HIP_TRY(hipMemcpyAsync(counts, c->dcounts, 8 * (size_t)k, hipMemcpyDeviceToHost, c->stream));
+  if (!batch && whole && first_bad < 0) {
+    memcpy(counts, (const char *)hc.data() + (c->plan.off_dcounts - c->plan.off_counters), 8 * (size_t)k);
+  } else if (!batch || first_bad >= 0) {
+    HIP_TRY(hipMemcpyAsync(counts, batch ? c->bcounts : c->dcounts, 8 * (size_t)ncounts, hipMemcpyDeviceToHost,
+                           c->stream));
+    HIP_TRY(hipStreamSynchronize(c->stream));
   }
-  HIP_TRY(hipStreamSynchronize(c->stream));
   if (c->incr && !batch) c->incr_k = start ? 0 : k;  // the cache holds a chain from P0
   return KBISIM_OK;
 }
@@ -1273,10 +1319,10 @@ int update_step(kbisim_ctx *c, const TierSrc &tsrc, const ListSrc &lsrc, int i, 
   if (rc) return rc;
   auto lists = [&](int *count, int *small, int *large) -> int {
     k_sig_list_small<ListSrc, K><<<LIST_GRID_SMALL, 256, 0, c->stream>>>(lsrc, count, small, c->H, c->DC, c->table,
-                                                                         tmask, c->dep, c->hmask, c->zrep);
+                                                                         tmask, c->cur, c->hmask, c->zrep);
     LAUNCH_CHECK();
     k_sig_list_large<ListSrc, K><<<LIST_GRID_LARGE, 256, 0, c->stream>>>(lsrc, count + 1, large, c->H, c->DC,
-                                                                         c->table, tmask, c->dep, c->hmask, c->zrep,
+                                                                         c->table, tmask, c->cur, c->hmask, c->zrep,
                                                                          c->err);
     LAUNCH_CHECK();
     return 0;
@@ -1293,13 +1339,13 @@ int update_step(kbisim_ctx *c, const TierSrc &tsrc, const ListSrc &lsrc, int i, 
   if ((rc = lists(&S.cnt[0], S.small, S.large))) return rc;
   if (S.nerows8) {
     k_sig_row<ListSrc, ROW_MAX, 1024, K><<<(unsigned)S.nerows8, 1024, 0, c->stream>>>(
-        lsrc, S.erows, c->H, c->DC, c->table, tmask, c->dep, c->hmask, c->zrep, nullptr);
+        lsrc, S.erows, c->H, c->DC, c->table, tmask, c->cur, c->hmask, c->zrep, nullptr);
     LAUNCH_CHECK();
   }
   if constexpr (std::is_same<K, u32>::value) {
     if (S.nerows20) {
       k_sig_row<ListSrc, ROW_MAX_NARROW, 1024, u32><<<(unsigned)S.nerows20, 1024, 0, c->stream>>>(
-          lsrc, S.erows + S.nerows8, c->H, c->DC, c->table, tmask, c->dep, c->hmask, c->zrep, nullptr);
+          lsrc, S.erows + S.nerows8, c->H, c->DC, c->table, tmask, c->cur, c->hmask, c->zrep, nullptr);
       LAUNCH_CHECK();
     }
   }
@@ -1307,11 +1353,11 @@ int update_step(kbisim_ctx *c, const TierSrc &tsrc, const ListSrc &lsrc, int i, 
     // edited rows too long for one workgroup: global hash sets in the spare hub-set space
     if ((rc = fill_u64(c, c->hubsets + S.huge_set_begin, S.huge_set_slots, 0))) return rc;
     k_sig_hub_global<ListSrc><<<(unsigned)S.nhuge_chunks, 256, 0, c->stream>>>(
-        lsrc, S.huge_chunks, S.huge, c->hubsets + S.huge_set_begin, S.huge_acc, S.huge_cnt, c->dep, nullptr);
+        lsrc, S.huge_chunks, S.huge, c->hubsets + S.huge_set_begin, S.huge_acc, S.huge_cnt, c->cur, nullptr);
     LAUNCH_CHECK();
     k_hub_final<ListSrc><<<blocks_for(S.nhuge, 256), 256, 0, c->stream>>>(lsrc, S.huge, S.nhuge, S.huge_acc,
                                                                           S.huge_cnt, c->H, c->DC, c->table, tmask,
-                                                                          c->dep, c->hmask, c->zrep, nullptr);
+                                                                          c->cur, c->hmask, c->zrep, nullptr);
     LAUNCH_CHECK();
   }
   int nlk = 0;
@@ -1329,7 +1375,7 @@ int update_step(kbisim_ctx *c, const TierSrc &tsrc, const ListSrc &lsrc, int i, 
     }
     k_classify<<<(unsigned)std::min<int64_t>(CLASSIFY_GRID, blocks_for(n, 256)), 256, 0, c->stream>>>(
         n, S.MVc + at, S.dirty, S.touch, S.FKc + at, S.Hc + at, S.DCc + at, names_prev, S.filter, gfilter, c->table,
-        tmask, c->dep, c->zrep, c->H, c->DC, c->rep, S.names[i & 1], &cnt[11], S.lk);
+        tmask, c->cur, c->zrep, c->H, c->DC, c->rep, S.names[i & 1], &cnt[11], S.lk);
     LAUNCH_CHECK();
     HIP_TRY(hipMemcpyAsync(&nlk, &cnt[11], sizeof nlk, hipMemcpyDeviceToHost, c->stream));
     HIP_TRY(hipStreamSynchronize(c->stream));
@@ -1340,19 +1386,19 @@ int update_step(kbisim_ctx *c, const TierSrc &tsrc, const ListSrc &lsrc, int i, 
     }
     if (nlk) {
       k_insert_list<<<blocks_for(nlk, 256), 256, 0, c->stream>>>(nlk, S.lk, c->H, c->DC, names_prev, c->table, tmask,
-                                                                  c->dep, c->zrep);
+                                                                  c->cur, c->zrep);
       k_lookup<ListSrc><<<blocks_for(nlk, 256), 256, 0, c->stream>>>(
-          lsrc, nlk, S.lk, c->H, c->DC, c->table, tmask, c->dep, c->rep, &cnt[0], c->vlist, &cnt[1], c->clA, c->err,
+          lsrc, nlk, S.lk, c->H, c->DC, c->table, tmask, c->cur, c->rep, &cnt[0], c->vlist, &cnt[1], c->clA, c->err,
           c->zrep, 1, nullptr, S.dirty, S.MVc + at);
       LAUNCH_CHECK();
     }
   } else {
     k_insert_cached<<<blocks_for(n, 256), 256, 0, c->stream>>>(n, S.dirty, S.Hc + at, S.DCc + at, S.MVc + at,
-                                                                names_prev, c->H, c->DC, c->table, tmask, c->dep,
+                                                                names_prev, c->H, c->DC, c->table, tmask, c->cur,
                                                                 c->zrep);
     LAUNCH_CHECK();
     k_lookup<ListSrc><<<blocks_for(n, 256), 256, 0, c->stream>>>(lsrc, n, nullptr, c->H, c->DC, c->table, tmask,
-                                                                 c->dep, c->rep, &cnt[0], c->vlist, &cnt[1], c->clA,
+                                                                 c->cur, c->rep, &cnt[0], c->vlist, &cnt[1], c->clA,
                                                                  c->err, c->zrep, 1, nullptr, S.dirty, S.MVc + at);
     LAUNCH_CHECK();
   }
@@ -1774,6 +1820,7 @@ int create_impl(const kbisim_graph *g, int kmax, const kbisim_tuning *tuning, vo
   c->dcounts = (int64_t *)(w + plan.off_dcounts);
   c->err = (u32 *)(w + plan.off_err);
   c->dep = (u32 *)(w + plan.off_dep);
+  c->cur = c->dep;
   c->hubsets = (u64 *)(w + plan.off_hubsets);
   c->single[0] = (unsigned char *)(w + plan.off_single);
   c->single[1] = c->single[0] + std::max<int64_t>(n, 1);
@@ -2029,10 +2076,8 @@ int step_async_impl(kbisim_ctx *c, int i, const int32_t *prev, int32_t *out) {
   const int32_t *p = i == 0 ? c->p0 : (batch ? c->ibuf[(i - 1) & 1] : prev);
   int rc = 0;
   if (c->incr) c->incr_k = 0;  // single steps do not keep a chain for updates
-  if (i == 0 && (rc = fill_i32(c, (int *)c->err, 1, 0))) return rc;
-  if ((rc = fill_i32(c, c->counters + CNT_STRIDE * i, CNT_STRIDE, 0))) return rc;
   std::vector<int32_t *> o((size_t)i + 1, out);  // indexed by step number
-  return enqueue_steps(c, p, i, i + 1, o.data(), false, c->kmax, i == 0);
+  return enqueue_steps(c, p, i, i + 1, o.data(), false, c->kmax, i == 0, i == 0);
 }
 
 int step_result_impl(kbisim_ctx *c, int i, const int32_t *prev, int32_t *out) {

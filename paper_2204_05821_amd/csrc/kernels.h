@@ -1463,6 +1463,49 @@ __global__ void __launch_bounds__(256) k_res_verify(Src src, const int *__restri
   }
 }
 
+// The one peeling round inside a step, by one workgroup: collided vertices are
+// few (the tags and home slots of 10^8 keys leave a handful), so the minimum
+// vertex of each hash is found by comparing all pairs in LDS.  More than
+// PEEL_MAX of them are passed on whole; the host then redoes the step with
+// k_res_insert and k_res_verify rounds over the whole grid.
+constexpr int PEEL_MAX = 512;
+template <class Src>
+__global__ void __launch_bounds__(256) k_peel_few(Src src, const int *__restrict__ count, const int *__restrict__ list,
+                                                  const u64 *__restrict__ H, const u32 *__restrict__ DC,
+                                                  int *__restrict__ rep, int *next_count, int *next_list, u32 *err) {
+  const int total = *count;
+  if (total == 0) return;
+  if (total > PEEL_MAX) {
+    for (int i = threadIdx.x; i < total; i += 256) next_list[i] = list[i];
+    if (threadIdx.x == 0) *next_count = total;
+    return;
+  }
+  __shared__ u64 set[BLOCK_SLOTS];
+  __shared__ int sh_flag[2];
+  __shared__ int vs[PEEL_MAX];
+  __shared__ u64 hs[PEEL_MAX];
+  for (int i = threadIdx.x; i < total; i += 256) {
+    vs[i] = list[i];
+    hs[i] = H[vs[i]];
+  }
+  __syncthreads();
+  for (int item = 0; item < total; ++item) {
+    const int v = vs[item];
+    int r = v;
+    for (int i = 0; i < total; ++i) r = hs[i] == hs[item] ? min(r, vs[i]) : r;
+    bool ok;
+    if (r == v) ok = true;
+    else if (src.own(v) != src.own(r) || DC[v] != DC[r]) ok = false;
+    else if (DC[v] == 0) ok = true;
+    else ok = wg_subset(src, v, r, DC[r], set, sh_flag, err);
+    if (threadIdx.x == 0) {
+      if (ok) rep[v] = r;
+      else next_list[(*next_count)++] = v;
+    }
+    __syncthreads();
+  }
+}
+
 // ---------------------------------------------------------------- numbering
 // Flags "rep[v] == v" in vertex order (tiles of 256 * ITEMS vertices, ITEMS =
 // 8 or 16 per thread).  A head's exclusive prefix is its dense id, so blocks
@@ -1582,11 +1625,25 @@ __global__ void __launch_bounds__(256) k_head_words(int n, const int *__restrict
 // step's stamp, so a head left unmarked is a singleton block (k_singletons).
 // ASSIGN_V consecutive vertices per thread: representatives, ranks and ids
 // move 16 bytes at a time where the arrays' starts allow.
+// SCAN (at most 256 tiles): the tile counts are still to be scanned, which
+// every workgroup does for itself (one launch less; with more tiles the loads
+// of every workgroup would cost more than it); the total goes to *count_out.
 constexpr int ASSIGN_V = 4;
+template <bool SCAN>
 __global__ void __launch_bounds__(256) k_assign(int n, const int *__restrict__ rep, HeadIds ids,
                                                 int *__restrict__ out, const int *__restrict__ rank,
                                                 int *__restrict__ gpid_next, u32 *multi,
-                                                const u32 *__restrict__ dep) {
+                                                const u32 *__restrict__ dep, int ntiles, int64_t *count_out) {
+  __shared__ u32 tp[SCAN ? 256 : 1];
+  if constexpr (SCAN) {
+    __shared__ u32 sh_w[4];
+    u32 total;
+    const u32 mine = (int)threadIdx.x < ntiles ? ids.tile_pre[threadIdx.x] : 0u;
+    tp[threadIdx.x] = block_exclusive_scan(mine, sh_w, &total);
+    if (blockIdx.x == 0 && threadIdx.x == 0) *count_out = (int64_t)total;
+    __syncthreads();
+    ids.tile_pre = tp;
+  }
   const int64_t v0 = ((int64_t)blockIdx.x * 256 + threadIdx.x) * ASSIGN_V;
   if (v0 >= n) return;
   const bool vec = v0 + ASSIGN_V <= n && ((reinterpret_cast<uintptr_t>(rep) | reinterpret_cast<uintptr_t>(out) |
@@ -2441,8 +2498,8 @@ __global__ void __launch_bounds__(256) k_transpose_unpack(int64_t m, const u64 *
 // ROW_MAX and row_max entries) or are hubs.  The schedule depends on n and the
 // degrees only.  One workgroup takes one chunk, twice: the first launch
 // counts per chunk (cnt[list * nchunks + chunk], lists: ranges, up to
-// RANGE_DMAX, up to ROW_MAX, up to row_max, hubs; sums[5 * chunk + i]: range
-// vertices and entries, row-tier rows and entries, non-empty rows);
+// RANGE_DMAX, up to ROW_MAX, up to row_max, hubs; sums[i * nchunks + chunk]: range
+// vertices and entries, row-tier rows and entries, non-empty rows, rows past SMALL_MAX);
 // k_sched_scan turns the counts into offsets; the second launch writes the
 // range lists one after another in `ranges`, the hubs in `hubs` and the
 // non-empty vertices in `nzv` (unless null).
@@ -2458,7 +2515,7 @@ constexpr int SCHED_THREADS = 1024;
 constexpr int SCHED_PER = SCHED_CHUNK_V / SCHED_THREADS;
 
 // Totals of a schedule, written by k_sched_scan: rows per list, then the sums.
-constexpr int SCHED_TOTALS = 10;
+constexpr int SCHED_TOTALS = 11;
 
 template <bool WRITE>
 __global__ void __launch_bounds__(SCHED_THREADS) k_sched_chunks(const int64_t *__restrict__ ptr, int64_t n,
@@ -2472,7 +2529,7 @@ __global__ void __launch_bounds__(SCHED_THREADS) k_sched_chunks(const int64_t *_
   __shared__ unsigned short close_at[SCHED_CHUNK_V];  // end - 1 of the range that starts at a row
   __shared__ unsigned short starts[SCHED_THREADS];    // bit j of word t: row 16 t + j starts a range (or is long)
   __shared__ int wl[SCHED_THREADS / WAVE];
-  __shared__ int64_t wsum[5][SCHED_THREADS / WAVE];
+  __shared__ int64_t wsum[6][SCHED_THREADS / WAVE];
   __shared__ int wcnt[6][SCHED_THREADS / WAVE];
   const int t = threadIdx.x, lane = t & 63, w = t >> 6, ci = blockIdx.x;
   const int64_t v0 = (int64_t)ci * SCHED_CHUNK_V;
@@ -2535,11 +2592,12 @@ __global__ void __launch_bounds__(SCHED_THREADS) k_sched_chunks(const int64_t *_
   // lists of this thread's starts
   const u32 st = starts[t];
   int c[6] = {0, 0, 0, 0, 0, 0};  // the five lists, then non-empty rows
-  int64_t sm[5] = {0, 0, 0, 0, 0};
+  int64_t sm[6] = {0, 0, 0, 0, 0, 0};
 #pragma unroll
   for (int j = 0; j < SCHED_PER; ++j) {
     if (r0 + j >= V) continue;
     c[5] += d[j] > 0;
+    sm[5] += d[j] > SMALL_MAX;
     const bool lg = (lmask >> j) & 1u;
     const int list = !lg ? 0 : d[j] > row_max ? 4 : d[j] > ROW_MAX ? 3 : d[j] > RANGE_DMAX ? 2 : 1;
     if (!lg) {
@@ -2556,7 +2614,7 @@ __global__ void __launch_bounds__(SCHED_THREADS) k_sched_chunks(const int64_t *_
   sm[4] = c[5];
   if constexpr (!WRITE) {
 #pragma unroll
-    for (int l = 0; l < 5; ++l) {
+    for (int l = 0; l < 6; ++l) {
       const u32 x = wave_sum_u32((u32)c[l]);
       const u64 y = wave_sum_u64((u64)sm[l]);
       if (lane == 0) {
@@ -2565,14 +2623,14 @@ __global__ void __launch_bounds__(SCHED_THREADS) k_sched_chunks(const int64_t *_
       }
     }
     __syncthreads();
-    if (t < 5) {
+    if (t < 6) {
       int x = 0;
       int64_t y = 0;
       for (int i = 0; i < SCHED_THREADS / WAVE; ++i) {
         x += wcnt[t][i];
         y += wsum[t][i];
       }
-      cnt[(int64_t)t * nchunks + ci] = x;
+      if (t < 5) cnt[(int64_t)t * nchunks + ci] = x;
       sums[(int64_t)t * nchunks + ci] = y;
     }
   } else {
@@ -2627,7 +2685,7 @@ __global__ void __launch_bounds__(SCHED_THREADS) k_sched_chunks(const int64_t *_
 }
 
 // One workgroup: in-place exclusive scan of every list's chunk counts and of
-// the non-empty rows (sums[4]), and the totals of all ten.
+// the non-empty rows (sums[4]), and the totals of all.
 __global__ void __launch_bounds__(256) k_sched_scan(int nchunks, int *__restrict__ cnt, int64_t *__restrict__ sums,
                                                     int64_t *__restrict__ totals) {
   __shared__ int64_t sh_w[4];
@@ -2635,7 +2693,7 @@ __global__ void __launch_bounds__(256) k_sched_scan(int nchunks, int *__restrict
     int64_t carry = 0;
     for (int b0 = 0; b0 < nchunks; b0 += 256) {
       const int i = b0 + threadIdx.x;
-      const int64_t at = (int64_t)(l % 5) * nchunks + i;
+      const int64_t at = (int64_t)(l < 5 ? l : l - 5) * nchunks + i;
       const int64_t mine = i < nchunks ? (l < 5 ? (int64_t)cnt[at] : sums[at]) : 0;
       int64_t total;
       const int64_t ex = carry + block_exclusive_scan64(mine, sh_w, &total);
@@ -3451,6 +3509,40 @@ __global__ void k_advance(u32 *dep, u32 mask) {
     dep[EP_CLR_HUB] = dep[EP_HUB] == 1u;
   } else {
     dep[EP_CLR_HUB] = 0;
+  }
+}
+
+// Counters and epochs of steps [i0, i0 + cnt) of a call (cnt <= 14), ahead of
+// all of them: row i of `rows` (STEP_ROW words) gets zeroed counters and, from
+// STEP_EPOCHS on, the step's own epochs, so a step launches nothing for them.
+// Epochs that would wrap inside the segment start again from 1, and the table
+// is cleared before it (k_clear_if).  reset_err: also clear the error word.
+constexpr int STEP_ROW = 16, STEP_EPOCHS = 8, STEP_SEGMENT = 14;
+__global__ void k_prepare_steps(u32 *dep, int *rows, int i0, int cnt, u32 *err, int reset_err) {
+  const int t = threadIdx.x;
+  u32 e = dep[EP_TABLE], ec = dep[EP_CTABLE];
+  const u32 z = dep[EP_ZERO], hub = dep[EP_HUB];
+  const bool wrap = e + (u32)cnt > 15u, cwrap = ec + (u32)cnt > 15u;
+  if (wrap) e = 0;
+  if (cwrap) ec = 0;
+  if (t < cnt) {
+    int *row = rows + (int64_t)(i0 + t) * STEP_ROW;
+    for (int j = 0; j < STEP_EPOCHS; ++j) row[j] = 0;
+    u32 *d = reinterpret_cast<u32 *>(row) + STEP_EPOCHS;
+    d[EP_TABLE] = e + (u32)t + 1u;
+    d[EP_CTABLE] = ec + (u32)t + 1u;
+    d[EP_ZERO] = z + (u32)t + 1u;
+    d[EP_HUB] = hub;
+  }
+  __syncthreads();  // every thread has read dep
+  if (t == 0) {
+    dep[EP_TABLE] = e + (u32)cnt;
+    dep[EP_CTABLE] = ec + (u32)cnt;
+    dep[EP_ZERO] = z + (u32)cnt;
+    dep[EP_CLR_TABLE] = wrap;
+    dep[EP_CLR_CTABLE] = cwrap;
+    dep[EP_CLR_HUB] = 0;
+    if (reset_err) *err = 0;
   }
 }
 
