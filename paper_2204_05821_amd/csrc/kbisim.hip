@@ -178,6 +178,8 @@ struct kbisim_ctx {
   Tuning tune;
   char *ws;
   u64 *H, *table, *ctable, *hacc, *hubsets, *zrep;
+  int64_t cslots = 0;    // slots of the peeling table: half of its space, nzrow has the rest
+  u32 *nzrow = nullptr;  // low word of the offset of every non-empty row (in the order of nzv)
   u32 *DC, *hcnt, *err, *tiles, *dep;
   const u32 *cur = nullptr;  // the epochs of the step being enqueued: dep, or its row (k_prepare_steps)
   HeadWord *hw;
@@ -363,7 +365,7 @@ int advance(kbisim_ctx *c, u32 mask, const Schedule &s) {
   ProfScope ps(c, KBISIM_K_FILL);
   k_advance<<<1, 64, 0, c->stream>>>(c->dep, mask);
   LAUNCH_CHECK();
-  k_clear_if<<<CLEAR_GRID, 256, 0, c->stream>>>(c->dep, c->table, (int64_t)c->plan.tslots, c->ctable,
+  k_clear_if<<<CLEAR_GRID, 256, 0, c->stream>>>(c->dep, c->table, (int64_t)c->plan.tslots, c->ctable, c->cslots,
                                                 c->hubsets + s.gset_begin, s.gset_end - s.gset_begin);
   LAUNCH_CHECK();
   return 0;
@@ -423,13 +425,10 @@ template <bool PAY>
 int sort_rows_impl(kbisim_ctx *c, const Schedule &s, u32 *lab) {
   u32 *g = reinterpret_cast<u32 *>(c->gcol);
   if (s.nranges) {
-    const GraphSrcT<false> src{c->g.row_ptr, c->gcol, nullptr, nullptr, nullptr, c->pb, c->rbits};
     if (s.range_edges == 1024)
-      k_sort_ranges<GraphSrcT<false>, 1024, PAY><<<(unsigned)s.nranges, 256, 0, c->stream>>>(src, g, lab, c->ranges,
-                                                                                           c->rbits);
+      k_sort_ranges<1024, PAY><<<(unsigned)s.nranges, 256, 0, c->stream>>>(g, lab, c->ranges, c->nzrow, c->rbits);
     else
-      k_sort_ranges<GraphSrcT<false>, 2048, PAY><<<(unsigned)s.nranges, 256, 0, c->stream>>>(src, g, lab, c->ranges,
-                                                                                           c->rbits);
+      k_sort_ranges<2048, PAY><<<(unsigned)s.nranges, 256, 0, c->stream>>>(g, lab, c->ranges, c->nzrow, c->rbits);
     LAUNCH_CHECK();
   }
   const Range *rows = c->ranges + s.nranges;
@@ -561,22 +560,21 @@ int plan_hubs(kbisim_ctx *c, Schedule &s, const std::vector<int> &hubs, const st
 }
 
 // Static schedule of the rows of `ptr`, built on the device in two parts.
-// sched_enqueue launches the kernels (range lists, hub list and, with nzv, the
-// list of non-empty vertices) and leaves the totals on the device;
+// sched_enqueue launches the kernels (range lists, hub list, non-empty rows) and leaves the totals on the device;
 // sched_finish takes the totals, once copied to the host, and plans the hubs.
 // row_max: longest row with a workgroup of its own (longer rows are hubs).
 // Scratch: c->vlist (68 bytes per chunk); the totals go to
 // `totals` (SCHED_TOTALS words).
-int sched_enqueue(kbisim_ctx *c, const int64_t *ptr, int range_edges, int64_t row_max, int64_t *totals, int *nzv) {
+int sched_enqueue(kbisim_ctx *c, const int64_t *ptr, int range_edges, int64_t row_max, int64_t *totals) {
   const int64_t n = c->g.n;
   const int nch = (int)((n + SCHED_CHUNK_V - 1) / SCHED_CHUNK_V);
   int64_t *sums = reinterpret_cast<int64_t *>(c->vlist);
   int *cnt = reinterpret_cast<int *>(sums + 6 * (size_t)nch);
   k_sched_chunks<false><<<(unsigned)nch, SCHED_THREADS, 0, c->stream>>>(ptr, n, nch, range_edges, row_max, cnt, sums,
-                                                                        totals, nullptr, nullptr, nullptr);
+                                                                        totals, nullptr, nullptr, nullptr, nullptr);
   k_sched_scan<<<1, 256, 0, c->stream>>>(nch, cnt, sums, totals);
   k_sched_chunks<true><<<(unsigned)nch, SCHED_THREADS, 0, c->stream>>>(ptr, n, nch, range_edges, row_max, cnt, sums,
-                                                                       totals, c->ranges, c->lists, nzv);
+                                                                       totals, c->ranges, c->lists, c->nzv, c->nzrow);
   LAUNCH_CHECK();
   return 0;
 }
@@ -746,10 +744,10 @@ int build_rank(kbisim_ctx *c) {
 template <class Src>
 int peel_round(kbisim_ctx *c, const Src &src, int *in_cnt, int *in_list, int *out_cnt, int *out_list) {
   ProfScope ps(c, KBISIM_K_PEEL);
-  k_res_insert<<<RES_GRID, 256, 0, c->stream>>>(in_cnt, in_list, c->H, c->ctable, c->plan.tslots - 1, c->cur);
+  k_res_insert<<<RES_GRID, 256, 0, c->stream>>>(in_cnt, in_list, c->H, c->ctable, (u64)c->cslots - 1, c->cur);
   LAUNCH_CHECK();
   k_res_verify<Src><<<RES_GRID, 256, 0, c->stream>>>(src, in_cnt, in_list, c->H, c->DC, c->ctable,
-                                                     c->plan.tslots - 1, c->cur, c->rep, out_cnt, out_list, c->err);
+                                                     (u64)c->cslots - 1, c->cur, c->rep, out_cnt, out_list, c->err);
   LAUNCH_CHECK();
   return 0;
 }
@@ -763,31 +761,29 @@ u64 table_mask(const kbisim_ctx *c) {
 }
 
 template <class Src, class K, bool SKIP>
-int launch_range_kernel(kbisim_ctx *c, const Src &src, const Schedule &s, u64 tmask, int zfresh,
-                        const unsigned char *skip) {
+int launch_range_kernel(kbisim_ctx *c, const Src &src, const Schedule &s, u64 tmask, const unsigned char *skip) {
   ProfScope ps(c, KBISIM_K_SIG_RANGE);
   if (s.range_edges == 1024)
     k_sig_range<Src, 1024, K, SKIP><<<(unsigned)s.nranges, 256, 0, c->stream>>>(
-        src, c->ranges, c->H, c->DC, c->table, tmask, c->cur, c->hmask, c->zrep, zfresh, skip);
+        src, c->ranges, c->H, c->DC, c->table, tmask, c->cur, c->hmask, c->nzv, c->nzrow, skip);
   else
     k_sig_range<Src, 2048, K, SKIP><<<(unsigned)s.nranges, 256, 0, c->stream>>>(
-        src, c->ranges, c->H, c->DC, c->table, tmask, c->cur, c->hmask, c->zrep, zfresh, skip);
+        src, c->ranges, c->H, c->DC, c->table, tmask, c->cur, c->hmask, c->nzv, c->nzrow, skip);
   LAUNCH_CHECK();
   return 0;
 }
 
 // skip: singleton flags of the previous partition (work-efficient mode), or NULL.
 template <class Src, class K>
-int launch_ranges_k(kbisim_ctx *c, const Src &src, const Schedule &s, int zfresh, const unsigned char *skip,
-                    bool range_tier = true) {
+int launch_ranges_k(kbisim_ctx *c, const Src &src, const Schedule &s, const unsigned char *skip, bool range_tier) {
   const u64 tmask = table_mask<Src>(c);
   if (s.nranges && range_tier) {
     int rc = 0;
     if constexpr (Src::GRAPH) {
-      rc = skip ? launch_range_kernel<Src, K, true>(c, src, s, tmask, zfresh, skip)
-                : launch_range_kernel<Src, K, false>(c, src, s, tmask, zfresh, nullptr);
+      rc = skip ? launch_range_kernel<Src, K, true>(c, src, s, tmask, skip)
+                : launch_range_kernel<Src, K, false>(c, src, s, tmask, nullptr);
     } else {
-      rc = launch_range_kernel<Src, K, false>(c, src, s, tmask, zfresh, nullptr);
+      rc = launch_range_kernel<Src, K, false>(c, src, s, tmask, nullptr);
     }
     if (rc) return rc;
   }
@@ -816,15 +812,14 @@ int launch_ranges_k(kbisim_ctx *c, const Src &src, const Schedule &s, int zfresh
 }
 
 template <class Src>
-int launch_ranges(kbisim_ctx *c, const Src &src, const Schedule &s, int zfresh, const unsigned char *skip,
-                  bool range_tier = true) {
+int launch_ranges(kbisim_ctx *c, const Src &src, const Schedule &s, const unsigned char *skip, bool range_tier) {
   if constexpr (Src::HASHED) {
-    return launch_ranges_k<Src, u32>(c, src, s, zfresh, skip, range_tier);
+    return launch_ranges_k<Src, u32>(c, src, s, skip, range_tier);
   } else {
     if constexpr (Src::GRAPH) {
-      if (c->narrow) return launch_ranges_k<Src, u32>(c, src, s, zfresh, skip, range_tier);
+      if (c->narrow) return launch_ranges_k<Src, u32>(c, src, s, skip, range_tier);
     }
-    return launch_ranges_k<Src, u64>(c, src, s, zfresh, skip, range_tier);
+    return launch_ranges_k<Src, u64>(c, src, s, skip, range_tier);
   }
 }
 
@@ -877,7 +872,12 @@ int launch_signatures(kbisim_ctx *c, const Src &src, const Schedule &s, bool zfr
       return 0;
     }
   }
-  if ((rc = launch_ranges(c, src, s, zfresh ? 1 : 0, skip_in, range_tier))) return rc;
+  if (zfresh && range_tier && s.nonempty < c->g.n) {
+    ProfScope ps(c, KBISIM_K_SIG_RANGE);
+    k_sig_empty<Src><<<blocks_for(c->g.n, 256), 256, 0, c->stream>>>(src, (int)c->g.n, c->DC, c->zrep, c->cur, skip_in);
+    LAUNCH_CHECK();
+  }
+  if ((rc = launch_ranges(c, src, s, skip_in, range_tier))) return rc;
   if (s.nhub) {
     const int *hubs = c->lists + s.hub_off;
     if (s.nchunks) {
@@ -1033,7 +1033,7 @@ int enqueue_steps(kbisim_ctx *c, const int32_t *prev, int i0, int k, int32_t *co
         k_prepare_steps<<<1, 64, 0, c->stream>>>(c->dep, c->counters, i, std::min(STEP_SEGMENT, k - i), c->err,
                                                  reset_err && i == i0 ? 1 : 0);
         LAUNCH_CHECK();
-        k_clear_if<<<CLEAR_GRID, 256, 0, c->stream>>>(c->dep, c->table, (int64_t)c->plan.tslots, c->ctable,
+        k_clear_if<<<CLEAR_GRID, 256, 0, c->stream>>>(c->dep, c->table, (int64_t)c->plan.tslots, c->ctable, c->cslots,
                                                       c->hubsets, 0);
         LAUNCH_CHECK();
       }
@@ -1803,6 +1803,8 @@ int create_impl(const kbisim_graph *g, int kmax, const kbisim_tuning *tuning, vo
   c->lists = (int *)(w + plan.off_lists);
   c->table = (u64 *)(w + plan.off_table);
   c->ctable = (u64 *)(w + plan.off_ctable);
+  c->cslots = (int64_t)(plan.tslots / 2);  // still at least n
+  c->nzrow = reinterpret_cast<u32 *>(c->ctable + c->cslots);
   c->hacc = (u64 *)(w + plan.off_hacc);
   c->hcnt = (u32 *)(w + plan.off_hcnt);
   c->chunks = (HubChunk *)(w + plan.off_chunks);
@@ -1949,7 +1951,7 @@ int create_impl(const kbisim_graph *g, int kmax, const kbisim_tuning *tuning, vo
   if ((rc = build_rank(c))) return fail(rc);
   // Fresh state: tables start empty; empty-signature slots start above any entry.
   if ((rc = fill_u64(c, c->table, (int64_t)plan.tslots, 0))) return fail(rc);
-  if ((rc = fill_u64(c, c->ctable, (int64_t)plan.tslots, 0))) return fail(rc);
+  if ((rc = fill_u64(c, c->ctable, c->cslots, 0))) return fail(rc);
   if ((rc = fill_u64(c, c->zrep, std::max<int64_t>(n, 1), ~0ULL))) return fail(rc);
   if ((rc = fill_i32(c, (int *)c->multi, std::max<int64_t>(n, 1), 0))) return fail(rc);
 
@@ -1983,7 +1985,7 @@ int create_impl(const kbisim_graph *g, int kmax, const kbisim_tuning *tuning, vo
     for (bool careful = false;; careful = true) {
       if (labelled && src.ptr) {
         const int lcap = range_cap(c, true);
-        if ((rc = sched_enqueue(c, src.ptr, lcap, ROW_MAX, totals, nullptr))) return fail(rc);
+        if ((rc = sched_enqueue(c, src.ptr, lcap, ROW_MAX, totals))) return fail(rc);
         if ((rc = copy_back())) return fail(rc);
         if ((rc = sched_finish(c, src.ptr, ls, lcap, HUB_STAGED_MAX_WIDE, host, nullptr))) return fail(rc);
       }
@@ -1991,7 +1993,7 @@ int create_impl(const kbisim_graph *g, int kmax, const kbisim_tuning *tuning, vo
       if (labelled &&
           (rc = run_step(c, src, ls, c->p0, &totals[SCHED_TOTALS], cnt, careful, nullptr, true)))
         return fail(rc);
-      if ((rc = sched_enqueue(c, g->row_ptr, gcap, grow_max, totals, c->nzv))) return fail(rc);
+      if ((rc = sched_enqueue(c, g->row_ptr, gcap, grow_max, totals))) return fail(rc);
       k_copy_i32<<<1, 1, 0, c->stream>>>((int *)&totals[SCHED_TOTALS + 1], (const int *)c->err, 1);
       if (hipGetLastError() != hipSuccess) return fail(KBISIM_EHIP);
       if ((rc = copy_back())) return fail(rc);
@@ -2482,9 +2484,11 @@ int quotient_keys(kbisim_ctx *c, const Src &src, const int32_t *src_pid, const i
   hipStream_t st = c->stream;
   if (S.nranges) {
     if (S.range_edges == 1024)
-      k_quotient_range<Src, 1024><<<(unsigned)S.nranges, 256, 0, st>>>(src, c->ranges, src_pid, tgt, q, keys);
+      k_quotient_range<Src, 1024><<<(unsigned)S.nranges, 256, 0, st>>>(src, c->ranges, c->nzv, c->nzrow, src_pid, tgt, q,
+                                                                      keys);
     else
-      k_quotient_range<Src, 2048><<<(unsigned)S.nranges, 256, 0, st>>>(src, c->ranges, src_pid, tgt, q, keys);
+      k_quotient_range<Src, 2048><<<(unsigned)S.nranges, 256, 0, st>>>(src, c->ranges, c->nzv, c->nzrow, src_pid, tgt, q,
+                                                                      keys);
   }
   const int nrows = S.nbig + S.nrow8 + S.nrow20;
   if (nrows) k_quotient_rows<Src><<<(unsigned)nrows, 256, 0, st>>>(src, c->ranges + S.nranges, src_pid, tgt, q, keys);

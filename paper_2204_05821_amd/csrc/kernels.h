@@ -142,8 +142,6 @@ struct GraphSrcT {
   const int32_t *pid;     // previous partition in vertex order
   __device__ inline int64_t begin(int v) const { return row_ptr[v]; }
   __device__ inline int64_t end(int v) const { return row_ptr[v + 1]; }
-  // low word of begin(v): enough for offsets within a range (little endian)
-  __device__ inline u32 begin_lo(int v) const { return reinterpret_cast<const u32 *>(row_ptr)[2 * (int64_t)v]; }
   // A pair keeps the target's block id modulo 2^pb.  The targets of one row
   // lie in one graph, whose block ids form an interval of at most 2^pb ids
   // (pb covers the largest graph; a single graph: all ids), so the reduction
@@ -231,9 +229,6 @@ struct LabelSrc {
   const int32_t *gid;  // may be null; in a batch, the graph of each vertex (P0 never joins graphs)
   __device__ inline int64_t begin(int v) const { return ptr ? ptr[v] : (int64_t)v; }
   __device__ inline int64_t end(int v) const { return ptr ? ptr[v + 1] : (int64_t)v + 1; }
-  __device__ inline u32 begin_lo(int v) const {
-    return ptr ? reinterpret_cast<const u32 *>(ptr)[2 * (int64_t)v] : (u32)v;
-  }
   __device__ inline u64 pair(int64_t e) const { return (u64)(u32)lab[e]; }
   __device__ inline void entry(int64_t e, u32 &l, u32 &r) const {
     l = (u32)lab[e];
@@ -545,9 +540,10 @@ __global__ void __launch_bounds__(256) k_validate_vals(int64_t cnt, const int32_
 }
 
 // ---------------------------------------------------------------- signature tiers
-// A run of consecutive vertices [v0, v1) handled by one workgroup, with the
-// run's first entry e0 and its entry count ne, so that a workgroup requests
-// its entries without waiting for the row offsets.
+// A run of consecutive non-empty rows [v0, v1) (indices into the list of
+// non-empty rows; vertices in a single-row range of the row tiers) handled by
+// one workgroup, with the run's first entry e0 and its entry count ne, so that
+// a workgroup requests its entries without waiting for the row offsets.
 struct Range {
   int v0, v1;
   int ne, pad;
@@ -589,8 +585,8 @@ __device__ inline void block_reduce_2(u64 &acc, u32 &cnt, u64 *sh_acc, u32 *sh_c
   }
 }
 
-// Range tier: a workgroup takes a run of consecutive vertices holding at most
-// EMAX entries (the range capacity, 1024 or 2048) and RANGE_VERTS vertices;
+// Range tier: a workgroup takes a run of consecutive non-empty rows holding at
+// most EMAX entries (the range capacity, 1024 or 2048), RANGE_VERTS rows;
 // longer rows go to the row tier.  All entries are gathered at once (EMAX/256
 // per thread, loads issued before dependent work, consecutive entries on
 // consecutive lanes), then inserted into their vertex's region of an LDS hash
@@ -601,11 +597,12 @@ __device__ inline void block_reduce_2(u64 &acc, u32 &cnt, u64 *sh_acc, u32 *sh_c
 template <class Src, int EMAX, class K = u64, bool SKIP = false>
 __global__ void __launch_bounds__(256) k_sig_range(Src src, const Range *__restrict__ ranges, u64 *__restrict__ H,
                                                    u32 *__restrict__ DC, u64 *table, u64 tmask,
-                                                   const u32 *__restrict__ dep, u64 hmask, u64 *zrep, int zfresh,
+                                                   const u32 *__restrict__ dep, u64 hmask,
+                                                   const int *__restrict__ nzv, const u32 *__restrict__ nzrow,
                                                    const unsigned char *__restrict__ skip) {
   typedef Keys<K> KO;
   constexpr int U = EMAX / 256;
-  const u32 epoch = dep[EP_TABLE], zep = dep[EP_ZERO];
+  const u32 epoch = dep[EP_TABLE];
   __shared__ K set[2 * EMAX];
   __shared__ u64 acc[RANGE_VERTS];
   __shared__ u32 cnt[RANGE_VERTS];
@@ -620,29 +617,25 @@ __global__ void __launch_bounds__(256) k_sig_range(Src src, const Range *__restr
   const int V = rg.v1 - rg.v0;
   const bool single = V == 1;
   const int64_t eb = rg.e0;
-  // The addresses of the row offsets, this thread's previous block (V <=
-  // blockDim) and the streamed words need only the range, so all three are
-  // requested together; the gathers follow, and the offsets reach LDS last.
-  const u32 b0 = t <= V ? src.begin_lo(rg.v0 + t) : 0u;
-  const u32 b1 = t + 256 <= V ? src.begin_lo(rg.v0 + t + 256) : 0u;
-  const u32 own_t = t < V ? src.own(rg.v0 + t) : 0u;
+  // The addresses of the row offsets, this thread's vertex (V <= blockDim)
+  // and the streamed words need only the range, so all three are requested
+  // together; the gathers follow (the vertex's previous block among them), and
+  // the offsets reach LDS last.
+  const u32 b0 = t < V ? nzrow[rg.v0 + t] : 0u;
+  const int v = t < V ? nzv[rg.v0 + t] : 0;
   u32 el[U], er[U];
-  if constexpr (!SKIP)
-    if (rg.ne > 0) src.template entries<U, 256>(eb, t, rg.ne, el, er);
+  if constexpr (!SKIP) src.template entries<U, 256>(eb, t, rg.ne, el, er);
   K pr[U];
-#pragma unroll
-  for (int u = 0; u < U; ++u) pr[u] = KO::EMPTY;
   if constexpr (!SKIP) {
-    if (rg.ne > 0) {
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const K p = KO::from(src, el[u], er[u]);
-        pr[u] = t + u * 256 < rg.ne ? p : KO::EMPTY;
-      }
+    for (int u = 0; u < U; ++u) {
+      const K p = KO::from(src, el[u], er[u]);
+      pr[u] = t + u * 256 < rg.ne ? p : KO::EMPTY;
     }
   }
-  if (t <= V) roff[t] = (int)(b0 - (u32)eb);
-  if (t + 256 <= V) roff[t + 256] = (int)(b1 - (u32)eb);
+  const u32 own_t = t < V ? src.own(v) : 0u;
+  if (t < V) roff[t] = (int)(b0 - (u32)eb);
+  if (t == 0) roff[V] = rg.ne;
   for (int i = t; i < V; i += 256) {
     acc[i] = 0;
     cnt[i] = 0;
@@ -653,7 +646,7 @@ __global__ void __launch_bounds__(256) k_sig_range(Src src, const Range *__restr
   const int *off = roff;  // offsets that place entries and set regions
   bool skipped = false;   // this thread's vertex (t < V) is left out
   if constexpr (SKIP) {
-    skipped = t < V && skip[rg.v0 + t];
+    skipped = t < V && skip[v];
     const u32 d = (t < V && !skipped) ? (u32)(roff[t + 1] - roff[t]) : 0u;
     u32 total;
     const u32 ex = block_exclusive_scan(d, wmax, &total);
@@ -730,15 +723,11 @@ __global__ void __launch_bounds__(256) k_sig_range(Src src, const Range *__restr
       }
     }
     block_reduce_2(a, c, sh_acc, sh_cnt);
-    bool out = t == 0 && (c || zfresh);
-    if constexpr (SKIP) out = out && !skip[rg.v0];
-    if (out) {
-      const int v = rg.v0;
-      const u32 own = own_t;
-      const u64 h = finalize_key(a, c, own) & hmask;
+    if (t == 0 && !skipped) {
+      const u64 h = finalize_key(a, c, own_t) & hmask;
       H[v] = h;
       DC[v] = c;
-      key_insert(table, tmask, zrep, h, c, own, (u32)v, epoch, zep);
+      table_insert(table, tmask, h, (u32)v, epoch);
     }
     return;
   }
@@ -800,30 +789,39 @@ __global__ void __launch_bounds__(256) k_sig_range(Src src, const Range *__restr
     }
   }
   __syncthreads();
-  // V <= RANGE_VERTS = blockDim: one vertex per thread.  Vertices with an
-  // empty signature keep their representative from the call's first step
-  // unless zfresh (their classes never change within a call).
-  bool zero = false, keyed = false;
-  u32 own = 0;
+  // V <= RANGE_VERTS = blockDim: one vertex per thread.
+  const bool keyed = t < V && !skipped;
   u64 h = 0;
-  const int v = rg.v0 + t;
-  if (t < V && !skipped) {
+  if (keyed) {
     const u32 c = cnt[t];
-    own = own_t;
-    if (c) {
-      h = finalize_key(acc[t], c, own) & hmask;
-      H[v] = h;
-      keyed = true;
-    } else if (zfresh) {
-      zero = true;
-    }
+    h = finalize_key(acc[t], c, own_t) & hmask;
+    H[v] = h;
     DC[v] = c;
   }
   // (the set is no longer read: its space holds the waves' key slots)
-  static_assert(sizeof(set) >= 8 * FIRST_SLOTS * sizeof(u32), "key slots of four waves");
-  u32 *slots = reinterpret_cast<u32 *>(set) + w * 2 * FIRST_SLOTS;
-  if (wave_first_of_key(slots, keyed, h)) table_insert(table, tmask, h, (u32)v, epoch);
-  zero_insert_wave(slots, zrep, zero, own, (u32)v, zep);
+  static_assert(sizeof(set) >= 4 * FIRST_SLOTS * sizeof(u32), "key slots of four waves");
+  if (wave_first_of_key(reinterpret_cast<u32 *>(set) + w * FIRST_SLOTS, keyed, h))
+    table_insert(table, tmask, h, (u32)v, epoch);
+}
+
+// Vertices with an empty signature, which are in no range: no distinct pair,
+// and grouped by their previous block alone.  Launched where representatives
+// of empty signatures are formed: the first step of a call (their classes
+// never change within a call), P0, and updates (skip: all but the flagged).
+template <class Src>
+__global__ void __launch_bounds__(256) k_sig_empty(Src src, int n, u32 *__restrict__ DC, u64 *zrep,
+                                                   const u32 *__restrict__ dep,
+                                                   const unsigned char *__restrict__ skip) {
+  __shared__ u32 slots[4][2 * FIRST_SLOTS];
+  const u32 zep = dep[EP_ZERO];
+  const int v = blockIdx.x * 256 + threadIdx.x;
+  const bool zero = v < n && src.begin(v) == src.end(v) && !(skip && skip[v]);
+  u32 own = 0;
+  if (zero) {
+    DC[v] = 0;
+    own = src.own(v);
+  }
+  zero_insert_wave(slots[threadIdx.x >> 6], zrep, zero, own, (u32)v, zep);
 }
 
 // Rows of exactly one item (P0 with one label per vertex): no set, no row
@@ -1925,9 +1923,9 @@ static_assert(RANGE_DMAX <= 4096 && ROW_MAX <= 8192 && ROW_MAX_NARROW <= 32768 &
 // the range sorted by rank_first in place.  Keys (row << 32 | rank_first) in
 // a bitonic network over N LDS slots; the row of an entry is found by
 // binary search over the range's row offsets.
-template <class Src, int N, bool PAY>
-__global__ void __launch_bounds__(256) k_sort_ranges(Src src, u32 *gcol, u32 *labels, const Range *__restrict__ ranges,
-                                                     u32 rbits) {
+template <int N, bool PAY>
+__global__ void __launch_bounds__(256) k_sort_ranges(u32 *gcol, u32 *labels, const Range *__restrict__ ranges,
+                                                     const u32 *__restrict__ nzrow, u32 rbits) {
   __shared__ u64 sh[N];
   __shared__ u32 shl[PAY ? N : 1];
   __shared__ int roff[RANGE_VERTS + 1];
@@ -1935,7 +1933,7 @@ __global__ void __launch_bounds__(256) k_sort_ranges(Src src, u32 *gcol, u32 *la
   const int V = rg.v1 - rg.v0, E = rg.ne;
   u32 *words = gcol + rg.e0;
   u32 *labs = PAY ? labels + rg.e0 : nullptr;
-  for (int i = threadIdx.x; i <= V; i += 256) roff[i] = (int)(src.begin_lo(rg.v0 + i) - (u32)rg.e0);
+  for (int i = threadIdx.x; i < V; i += 256) roff[i] = (int)(nzrow[rg.v0 + i] - (u32)rg.e0);
   __syncthreads();
   for (int i = threadIdx.x; i < N; i += 256) {
     u64 key = ~0ULL;
@@ -2089,6 +2087,7 @@ __device__ inline u64 quotient_key(const Src &src, const int32_t *__restrict__ t
 
 template <class Src, int EMAX>
 __global__ void __launch_bounds__(256) k_quotient_range(Src src, const Range *__restrict__ ranges,
+                                                        const int *__restrict__ nzv, const u32 *__restrict__ nzrow,
                                                         const int32_t *__restrict__ src_pid,
                                                         const int32_t *__restrict__ tgt, QKey q, u64 *keys) {
   __shared__ int roff[RANGE_VERTS + 1];
@@ -2098,8 +2097,11 @@ __global__ void __launch_bounds__(256) k_quotient_range(Src src, const Range *__
   const int t = threadIdx.x, lane = t & 63, w = t >> 6;
   const Range rg = ranges[blockIdx.x];
   const int V = rg.v1 - rg.v0;
-  for (int i = t; i <= V; i += 256) roff[i] = (int)(src.begin_lo(rg.v0 + i) - (u32)rg.e0);  // V may be 256
-  if (t < V) sbk[t] = (u64)(u32)src_pid[rg.v0 + t] << (q.lb + q.db);
+  if (t < V) {
+    roff[t] = (int)(nzrow[rg.v0 + t] - (u32)rg.e0);
+    sbk[t] = (u64)(u32)src_pid[nzv[rg.v0 + t]] << (q.lb + q.db);
+  }
+  if (t == 0) roff[V] = rg.ne;
   for (int i = t; i < EMAX; i += 256) owner[i] = 0;
   __syncthreads();
   for (int i = t; i < V; i += 256)
@@ -2491,18 +2493,22 @@ __global__ void __launch_bounds__(256) k_transpose_unpack(int64_t m, const u64 *
 }
 
 // ---------------------------------------------------------------- degree schedule
-// Rows are packed greedily into ranges of consecutive vertices: a range
+// Non-empty rows are packed greedily into ranges of consecutive ones: a range
 // closes before a row that would overflow it (range_edges entries), after
-// RANGE_VERTS vertices, before a longer row and at the end of its chunk of
+// RANGE_VERTS rows, before a longer row and at the end of its chunk of
 // SCHED_CHUNK_V vertices; longer rows go to the row tiers (up to RANGE_DMAX,
-// ROW_MAX and row_max entries) or are hubs.  The schedule depends on n and the
-// degrees only.  One workgroup takes one chunk, twice: the first launch
-// counts per chunk (cnt[list * nchunks + chunk], lists: ranges, up to
-// RANGE_DMAX, up to ROW_MAX, up to row_max, hubs; sums[i * nchunks + chunk]: range
-// vertices and entries, row-tier rows and entries, non-empty rows, rows past SMALL_MAX);
-// k_sched_scan turns the counts into offsets; the second launch writes the
-// range lists one after another in `ranges`, the hubs in `hubs` and the
-// non-empty vertices in `nzv` (unless null).
+// ROW_MAX and row_max entries) or are hubs.  Empty rows are in no range: where
+// most vertices have none (70% on the 1B-edge graph) they would fill ranges
+// that carry few entries.  The schedule depends on n and the degrees only.
+// One workgroup takes one chunk, twice: the first launch counts per chunk
+// (cnt[list * nchunks + chunk], lists: ranges, up to RANGE_DMAX, up to
+// ROW_MAX, up to row_max, hubs; sums[i * nchunks + chunk]: vertices and
+// entries of rows up to range_edges, of row-tier rows, non-empty rows, rows
+// past SMALL_MAX); k_sched_scan turns the counts into offsets; the second
+// launch writes the range lists one after another in `ranges`, the hubs in
+// `hubs`, and every non-empty row's vertex and the low word of its offset in
+// nzv and nzrow (a multi-row Range counts rows there, a single-row one
+// vertices).
 //
 // Where a range that starts at row s would close depends on s alone, so all
 // the closing points of a chunk are found in parallel (a binary search over
@@ -2523,37 +2529,71 @@ __global__ void __launch_bounds__(SCHED_THREADS) k_sched_chunks(const int64_t *_
                                                                 int *__restrict__ cnt, int64_t *__restrict__ sums,
                                                                 const int64_t *__restrict__ totals,
                                                                 Range *__restrict__ ranges, int *__restrict__ hubs,
-                                                                int *__restrict__ nzv) {
-  static_assert(SCHED_CHUNK_V <= 65536 && SCHED_PER == 16, "16-bit closing points, one start bit per row of a thread");
-  __shared__ u32 off[SCHED_CHUNK_V + 1];              // low words: differences inside a range are exact
-  __shared__ unsigned short close_at[SCHED_CHUNK_V];  // end - 1 of the range that starts at a row
+                                                                int *__restrict__ nzv, u32 *__restrict__ nzrow) {
+  static_assert(SCHED_CHUNK_V <= 65536 && SCHED_PER == 16, "16-bit rows, one start bit per row of a thread");
+  __shared__ u32 off[SCHED_CHUNK_V];                  // low word of each non-empty row's offset
+  __shared__ unsigned short row[SCHED_CHUNK_V];       // its vertex in the chunk
+  __shared__ unsigned short close_at[SCHED_CHUNK_V];  // last row of the range that starts at a row
+  __shared__ unsigned char kind[SCHED_CHUNK_V];       // its list (0: a range)
   __shared__ unsigned short starts[SCHED_THREADS];    // bit j of word t: row 16 t + j starts a range (or is long)
   __shared__ int wl[SCHED_THREADS / WAVE];
   __shared__ int64_t wsum[6][SCHED_THREADS / WAVE];
-  __shared__ int wcnt[6][SCHED_THREADS / WAVE];
+  __shared__ int wcnt[5][SCHED_THREADS / WAVE];
   const int t = threadIdx.x, lane = t & 63, w = t >> 6, ci = blockIdx.x;
   const int64_t v0 = (int64_t)ci * SCHED_CHUNK_V;
   const int V = (int)min<int64_t>(n - v0, SCHED_CHUNK_V);
-  for (int i = t; i <= V; i += SCHED_THREADS) off[i] = (u32)ptr[v0 + i];
-  // this thread's rows: 16 t .. 16 t + 15
+  // this thread's vertices 16 t .. 16 t + 15: degrees, sums, and the non-empty
+  // ones of the chunk packed into LDS
   const int r0 = t * SCHED_PER;
-  int64_t d[SCHED_PER], eb = 0;
+  int64_t sm[6] = {0, 0, 0, 0, 0, 0};
   {
-    int64_t prev = r0 <= V ? ptr[v0 + r0] : 0;
-    eb = prev;
+    int64_t e[SCHED_PER + 1];
+    e[0] = r0 <= V ? ptr[v0 + r0] : 0;
+#pragma unroll
+    for (int j = 0; j < SCHED_PER; ++j) e[j + 1] = r0 + j < V ? ptr[v0 + r0 + j + 1] : e[j];
 #pragma unroll
     for (int j = 0; j < SCHED_PER; ++j) {
-      const int64_t nx = r0 + j < V ? ptr[v0 + r0 + j + 1] : prev;
-      d[j] = nx - prev;
-      prev = nx;
+      const int64_t d = e[j + 1] - e[j];
+      if (r0 + j < V && d <= range_edges) {
+        sm[0] += 1;
+        sm[1] += d;
+      } else if (d > 0 && d <= row_max) {
+        sm[2] += 1;
+        sm[3] += d;
+      }
+      sm[4] += d > 0;
+      sm[5] += d > SMALL_MAX;
+    }
+    int x = (int)sm[4];
+#pragma unroll
+    for (int o = 1; o < WAVE; o <<= 1) {
+      const int y = __shfl_up(x, o, WAVE);
+      if (lane >= o) x += y;
+    }
+    if (lane == WAVE - 1) wl[w] = x;
+    starts[t] = 0;
+    __syncthreads();
+    int at = x - (int)sm[4];
+    for (int i = 0; i < w; ++i) at += wl[i];
+#pragma unroll
+    for (int j = 0; j < SCHED_PER; ++j) {
+      const int64_t d = e[j + 1] - e[j];
+      if (d == 0) continue;
+      off[at] = (u32)e[j];
+      row[at] = (unsigned short)(r0 + j);
+      kind[at] = d <= range_edges ? 0 : d > row_max ? 4 : d > ROW_MAX ? 3 : d > RANGE_DMAX ? 2 : 1;
+      ++at;
     }
   }
-  u32 lmask = 0;  // long rows
+  int R = 0;  // non-empty rows of the chunk
+  for (int i = 0; i < SCHED_THREADS / WAVE; ++i) R += wl[i];
+  __syncthreads();
+  const u32 chunk_end = (u32)ptr[v0 + V];
+  // first long row at or after each row, then where its range closes
+  u32 lmask = 0;
 #pragma unroll
-  for (int j = 0; j < SCHED_PER; ++j) lmask |= (r0 + j < V && d[j] > range_edges ? 1u : 0u) << j;
-  starts[t] = 0;
-  // first long row after this thread's rows
-  int nl = lmask ? r0 + __ffs(lmask) - 1 : V;
+  for (int j = 0; j < SCHED_PER; ++j) lmask |= (r0 + j < R && kind[r0 + j] != 0 ? 1u : 0u) << j;
+  int nl = lmask ? r0 + __ffs(lmask) - 1 : R;
 #pragma unroll
   for (int o = 1; o < WAVE; o <<= 1) {
     const int y = __shfl_down(nl, o, WAVE);
@@ -2562,63 +2602,53 @@ __global__ void __launch_bounds__(SCHED_THREADS) k_sched_chunks(const int64_t *_
   if (lane == 0) wl[w] = nl;
   __syncthreads();
   int next_long = __shfl_down(nl, 1, WAVE);
-  if (lane == WAVE - 1) next_long = V;
+  if (lane == WAVE - 1) next_long = R;
   for (int i = w + 1; i < SCHED_THREADS / WAVE; ++i) next_long = min(next_long, wl[i]);
+  // end of row e - 1: the next non-empty row's start (rows between are empty)
+  auto end_of = [&](int e) { return e < R ? off[e] : chunk_end; };
 #pragma unroll
   for (int j = SCHED_PER - 1; j >= 0; --j) {
     const int s = r0 + j;
-    if (s >= V) continue;
+    if (s >= R) continue;
     if ((lmask >> j) & 1u) {
       next_long = s;
       close_at[s] = (unsigned short)s;
       continue;
     }
-    // largest e <= lim with off[e] - off[s] <= range_edges (a row that is not long fits)
+    // largest e <= lim whose rows [s, e) fit (one row that is not long does);
+    // low words differ exactly, no long row being among them
     int lo = s + 1, hi = min(s + RANGE_VERTS, next_long);
     while (lo < hi) {
       const int mid = (lo + hi + 1) >> 1;
-      if (off[mid] - off[s] <= (u32)range_edges) lo = mid;
+      if (end_of(mid) - off[s] <= (u32)range_edges) lo = mid;
       else hi = mid - 1;
     }
     close_at[s] = (unsigned short)(lo - 1);
   }
   __syncthreads();
   if (t == 0)
-    for (int s = 0; s < V;) {
+    for (int s = 0; s < R;) {
       starts[s >> 4] |= (unsigned short)(1u << (s & 15));
       s = (int)close_at[s] + 1;
     }
   __syncthreads();
   // lists of this thread's starts
   const u32 st = starts[t];
-  int c[6] = {0, 0, 0, 0, 0, 0};  // the five lists, then non-empty rows
-  int64_t sm[6] = {0, 0, 0, 0, 0, 0};
+  int c[5] = {0, 0, 0, 0, 0};
 #pragma unroll
   for (int j = 0; j < SCHED_PER; ++j) {
-    if (r0 + j >= V) continue;
-    c[5] += d[j] > 0;
-    sm[5] += d[j] > SMALL_MAX;
-    const bool lg = (lmask >> j) & 1u;
-    const int list = !lg ? 0 : d[j] > row_max ? 4 : d[j] > ROW_MAX ? 3 : d[j] > RANGE_DMAX ? 2 : 1;
-    if (!lg) {
-      sm[0] += 1;
-      sm[1] += d[j];
-    } else if (list < 4) {
-      sm[2] += 1;
-      sm[3] += d[j];
-    }
-    const bool s = (st >> j) & 1u;
+    if (!((st >> j) & 1u)) continue;
+    const int list = kind[r0 + j];
 #pragma unroll
-    for (int l = 0; l < 5; ++l) c[l] += s && list == l;
+    for (int l = 0; l < 5; ++l) c[l] += list == l;
   }
-  sm[4] = c[5];
   if constexpr (!WRITE) {
 #pragma unroll
     for (int l = 0; l < 6; ++l) {
-      const u32 x = wave_sum_u32((u32)c[l]);
+      const u32 x = wave_sum_u32(l < 5 ? (u32)c[l < 5 ? l : 0] : 0u);
       const u64 y = wave_sum_u64((u64)sm[l]);
       if (lane == 0) {
-        wcnt[l][w] = (int)x;
+        if (l < 5) wcnt[l][w] = (int)x;
         wsum[l][w] = (int64_t)y;
       }
     }
@@ -2627,7 +2657,7 @@ __global__ void __launch_bounds__(SCHED_THREADS) k_sched_chunks(const int64_t *_
       int x = 0;
       int64_t y = 0;
       for (int i = 0; i < SCHED_THREADS / WAVE; ++i) {
-        x += wcnt[t][i];
+        if (t < 5) x += wcnt[t][i];
         y += wsum[t][i];
       }
       if (t < 5) cnt[(int64_t)t * nchunks + ci] = x;
@@ -2635,9 +2665,9 @@ __global__ void __launch_bounds__(SCHED_THREADS) k_sched_chunks(const int64_t *_
     }
   } else {
     // exclusive positions inside the chunk, per list
-    int at[6];
+    int at[5];
 #pragma unroll
-    for (int l = 0; l < 6; ++l) {
+    for (int l = 0; l < 5; ++l) {
       int x = c[l];
 #pragma unroll
       for (int o = 1; o < WAVE; o <<= 1) {
@@ -2648,38 +2678,38 @@ __global__ void __launch_bounds__(SCHED_THREADS) k_sched_chunks(const int64_t *_
       at[l] = x - c[l];
     }
     __syncthreads();
+    // the scanned offsets: counts of the lists, sums[4] of the non-empty rows
     int64_t base = 0;
 #pragma unroll
-    for (int l = 0; l < 6; ++l) {
+    for (int l = 0; l < 5; ++l) {
       for (int i = 0; i < w; ++i) at[l] += wcnt[l][i];
-      // the scanned offsets: counts of the lists, sums[4] of the non-empty rows
-      at[l] += l < 5 ? cnt[(int64_t)l * nchunks + ci] : (int)sums[(int64_t)4 * nchunks + ci];
+      at[l] += cnt[(int64_t)l * nchunks + ci];
       if (l < 4) {
         at[l] += (int)base;
         base += totals[l];
       }
     }
-    int64_t e = eb;
+    const int z0 = (int)sums[(int64_t)4 * nchunks + ci];
+    for (int i = t; i < R; i += SCHED_THREADS) {
+      nzv[z0 + i] = (int)(v0 + row[i]);
+      nzrow[z0 + i] = off[i];
+    }
 #pragma unroll
     for (int j = 0; j < SCHED_PER; ++j) {
-      if (r0 + j >= V) continue;
-      const int s = r0 + j;
-      const int v = (int)(v0 + s);
-      if (nzv && d[j] > 0) nzv[at[5]++] = v;
-      if ((st >> j) & 1u) {
-        if (!((lmask >> j) & 1u)) {
-          const int z = (int)close_at[s] + 1;
-          ranges[at[0]++] = Range{v, (int)(v0 + z), (int)(off[z] - off[s]), 0, e};
-        } else if (d[j] > row_max) {
-          hubs[at[4]++] = v;
-        } else {
-          const Range one{v, v + 1, (int)d[j], 0, e};
-          if (d[j] > ROW_MAX) ranges[at[3]++] = one;
-          else if (d[j] > RANGE_DMAX) ranges[at[2]++] = one;
-          else ranges[at[1]++] = one;
-        }
+      if (!((st >> j) & 1u)) continue;
+      const int s = r0 + j, list = kind[s];
+      const int v = (int)(v0 + row[s]);
+      if (list == 4) {
+        hubs[at[4]++] = v;
+      } else if (list == 0) {
+        const int z = (int)close_at[s] + 1;
+        ranges[at[0]++] = Range{z0 + s, z0 + z, (int)(end_of(z) - off[s]), 0, ptr[v]};
+      } else {
+        const Range one{v, v + 1, (int)(end_of(s + 1) - off[s]), 0, ptr[v]};
+        if (list == 3) ranges[at[3]++] = one;
+        else if (list == 2) ranges[at[2]++] = one;
+        else ranges[at[1]++] = one;
       }
-      e += d[j];
     }
   }
 }
@@ -3548,8 +3578,8 @@ __global__ void k_prepare_steps(u32 *dep, int *rows, int i0, int cnt, u32 *err, 
 
 // Clears the tables whose epoch just wrapped (one launch; exits at once when
 // nothing wrapped).
-__global__ void k_clear_if(const u32 *__restrict__ dep, u64 *table, int64_t tslots, u64 *ctable, u64 *hub_sets,
-                           int64_t hub_slots) {
+__global__ void k_clear_if(const u32 *__restrict__ dep, u64 *table, int64_t tslots, u64 *ctable, int64_t cslots,
+                           u64 *hub_sets, int64_t hub_slots) {
   const bool ct = dep[EP_CLR_TABLE] != 0, cc = dep[EP_CLR_CTABLE] != 0, ch = dep[EP_CLR_HUB] != 0;
   if (!ct && !cc && !ch) return;
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
@@ -3557,7 +3587,7 @@ __global__ void k_clear_if(const u32 *__restrict__ dep, u64 *table, int64_t tslo
   if (ct)
     for (int64_t i = i0; i < tslots; i += stride) table[i] = 0;
   if (cc)
-    for (int64_t i = i0; i < tslots; i += stride) ctable[i] = 0;
+    for (int64_t i = i0; i < cslots; i += stride) ctable[i] = 0;
   if (ch)
     for (int64_t i = i0; i < hub_slots; i += stride) hub_sets[i] = 0;
 }
