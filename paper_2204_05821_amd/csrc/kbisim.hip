@@ -893,8 +893,18 @@ int launch_signatures(kbisim_ctx *c, const Src &src, const Schedule &s, bool zfr
     }
     if (s.ngchunks) {
       ProfScope ps(c, KBISIM_K_HUB_STAGE);
-      k_sig_hub_global<Src><<<(unsigned)s.ngchunks, 256, 0, c->stream>>>(src, c->gchunks, hubs, c->hubsets, c->hacc,
-                                                                         c->hcnt, c->cur, skip_in);
+      auto global_sets = [&](auto key) {
+        k_sig_hub_global<Src, decltype(key)><<<(unsigned)s.ngchunks, 256, 0, c->stream>>>(
+            src, c->gchunks, hubs, c->hubsets, c->hacc, c->hcnt, c->cur, skip_in);
+      };
+      if constexpr (Src::HASHED) {
+        global_sets(u32{});
+      } else if constexpr (Src::GRAPH) {
+        if (c->narrow) global_sets(u32{});
+        else global_sets(u64{});
+      } else {
+        global_sets(u64{});
+      }
       LAUNCH_CHECK();
     }
     ProfScope ps(c, KBISIM_K_HUB_FINAL);
@@ -1352,7 +1362,7 @@ int update_step(kbisim_ctx *c, const TierSrc &tsrc, const ListSrc &lsrc, int i, 
   if (S.nhuge) {
     // edited rows too long for one workgroup: global hash sets in the spare hub-set space
     if ((rc = fill_u64(c, c->hubsets + S.huge_set_begin, S.huge_set_slots, 0))) return rc;
-    k_sig_hub_global<ListSrc><<<(unsigned)S.nhuge_chunks, 256, 0, c->stream>>>(
+    k_sig_hub_global<ListSrc, K><<<(unsigned)S.nhuge_chunks, 256, 0, c->stream>>>(
         lsrc, S.huge_chunks, S.huge, c->hubsets + S.huge_set_begin, S.huge_acc, S.huge_cnt, c->cur, nullptr);
     LAUNCH_CHECK();
     k_hub_final<ListSrc><<<blocks_for(S.nhuge, 256), 256, 0, c->stream>>>(lsrc, S.huge, S.nhuge, S.huge_acc,

@@ -85,12 +85,13 @@ constexpr u32 ERR_GRAPH_VLABEL = 256u;
 constexpr u32 ERR_BAD_PID = 512u;
 
 // ---------------------------------------------------------------- hashing
-// Murmur3's 64-bit finalizer (Appleby, MurmurHash3, public domain) as the
-// mixing function.  The key hash of a vertex is
-//   H = fmix64( sum_{p distinct} fmix64(p ^ C1)  +  fmix64((own << 32 | dc) ^ C2) )
-// with own = the vertex's previous block and dc = the number of distinct
-// pairs.  The sum over distinct pairs makes the hash independent of the order
-// in which a row's pairs are met, so no sort is needed to canonicalise.
+// Murmur3's finalizers (Appleby, MurmurHash3, public domain) as the mixing
+// functions.  The key hash of a vertex is
+//   H = fmix64( sum_{k distinct} mix(k)  +  (own << 32 | dc) * odd )
+// over the distinct set keys k of its pairs, with own = the vertex's previous
+// block and dc = the number of distinct keys.  The sum makes the hash
+// independent of the order in which a row's pairs are met, so no sort is
+// needed to canonicalise.
 __host__ __device__ inline u64 fmix64(u64 k) {
   k ^= k >> 33;
   k *= 0xff51afd7ed558ccdULL;
@@ -99,26 +100,55 @@ __host__ __device__ inline u64 fmix64(u64 k) {
   k ^= k >> 33;
   return k;
 }
+__host__ __device__ inline u32 fmix32(u32 k) {
+  k ^= k >> 16;
+  k *= 0x85ebca6bu;
+  k ^= k >> 13;
+  k *= 0xc2b2ae35u;
+  k ^= k >> 16;
+  return k;
+}
+// What a distinct key adds to the sum.  64-bit keys are pairs and are mixed
+// here; 32-bit keys are mixed already (fmix32), and one wide product of the
+// key with a second form of itself spreads them over 64 bits without being
+// linear in it.  Integer multiplies run at a quarter of the vector rate, and
+// two 64-bit finalizers per entry (one of them on empty slots half the time)
+// took a quarter of the range kernel.
 __device__ inline u64 mix_pair(u64 p) { return fmix64(p ^ 0x9ae16a3b2f90404fULL); }
-// Slot position inside LDS hash sets: two 32-bit multiplies and a shift
-// (the sets need spread, not collision resistance; equality is exact).
+__device__ inline u64 mix_key32(u32 x) { return (u64)x * (u64)(x ^ 0x9E3779B9u) + ((u64)x << 32); }
+// Slot position of 64-bit keys inside LDS hash sets: two 32-bit multiplies and
+// a shift (the sets need spread, not collision resistance; equality is exact).
 __device__ inline u32 set_hash(u64 p) {
   const u32 h = (u32)p * 0x9E3779B1u ^ ((u32)(p >> 32) + 0x7F4A7C15u) * 0x85EBCA77u;
   return h ^ (h >> 15);
 }
 __device__ inline u32 part_hash(u64 p) { return (u32)fmix64(p ^ 0x6a09e667f3bcc909ULL); }
 __device__ inline u32 sub_hash(u64 p) { return (u32)(fmix64(p ^ 0xa0761d6478bd642fULL) >> 32); }
-// Hashed 32-bit set key of a 64-bit pair (bits 16..47 of a Murmur3 fmix64);
-// never the empty marker 0xFFFFFFFF.
-__device__ inline u32 pair_key32(u64 p) {
-  const u32 k = (u32)(fmix64(p ^ 0x3c6ef372fe94f82bULL) >> 16);
-  return k == 0xFFFFFFFFu ? 0xFFFFFFFEu : k;
-}
 __device__ inline u64 finalize_key(u64 acc, u32 dc, u32 own) {
-  return fmix64(acc + fmix64((((u64)own) << 32 | (u64)dc) ^ 0xc2b2ae3d27d4eb4fULL));
+  return fmix64(acc + (((u64)own << 32) | (u64)dc) * 0x9E3779B97F4A7C15ULL);
 }
 
 // ---------------------------------------------------------------- sources
+// 32-bit set key of a pair (label l, reduced block b).  When every edge label
+// and reduced block id fit together in 31 bits it is exact: fmix32 is one to
+// one, and the one word it takes to 0xFFFFFFFF, the empty marker (0x331DA083),
+// has the top bit clear, which is set here.  Otherwise (HK) it is a 32-bit hash of the pair.  Deduplicating and
+// summing hashed keys gives a function of the signature (equal pair sets give
+// equal key sets), so equal signatures still get equal key hashes; the
+// distinct count is then the number of distinct keys, and the exact check
+// compares pair sets in both directions (a key collision inside a row could
+// otherwise make a proper subset look equal).  kmask: the bits kept of hashed
+// keys (all but for tests that make key collisions routine).
+template <bool HK>
+__device__ inline u32 narrow_key(u32 l, u32 b, u32 pb, u32 kmask) {
+  if constexpr (HK) {
+    const u32 k = fmix32(b ^ ((l << 22) | (l >> 10))) & kmask;
+    return k == 0xFFFFFFFFu ? 0xFFFFFFFEu : k;
+  } else {
+    return fmix32(0x80000000u | (l << pb) | b);
+  }
+}
+
 // A source describes, for each vertex, a row of items and how an item maps
 // to a 64-bit pair.  GraphSrc is one refinement step: item = CSR entry,
 // pair = (edge label << 31) | previous block of the target.  LabelSrc builds
@@ -153,7 +183,6 @@ struct GraphSrcT {
   u32 rbits;
   // bits kept of hashed keys (all but for tests that make key collisions routine)
   u32 kmask = 0xFFFFFFFFu;
-  __device__ inline u32 hkey(u64 p) const { return pair_key32(p) & kmask; }
   __device__ inline u32 pmask() const { return pb >= 31 ? 0x7FFFFFFFu : (1u << pb) - 1u; }
   // (label, rank of the target) of entry e; streamed arrays are read
   // non-temporally so they do not evict the gather targets from the L2
@@ -195,29 +224,14 @@ struct GraphSrcT {
     return pair_of(l, r);
   }
   __device__ inline u32 own(int v) const { return (u32)pid[v]; }
-  // Narrow form of a pair, used inside LDS sets.  When every edge label and
-  // reduced block id fit together in 31 bits it is exact: (label << pb) |
-  // block.  Otherwise (HK) it is a 32-bit hash of the pair.  Deduplicating
-  // and summing hashed keys gives a function of the signature (equal pair
-  // sets give equal key sets), so equal signatures still get equal key
-  // hashes; the distinct count is then the number of distinct keys, and the
-  // exact check compares pair sets in both directions (a key collision
-  // inside a row could otherwise make a proper subset look equal).
+  // Narrow form of a pair, used inside LDS sets (narrow_key).
   __device__ inline u32 key32_of(u32 l, u32 r) const {
-    if constexpr (HK) return hkey(pair_of(l, r));
-    else return (l << pb) | ((u32)gpid[r] & pmask());
+    return narrow_key<HK>(l, (u32)gpid[r] & pmask(), pb, kmask);
   }
   __device__ inline u32 key32(int64_t e) const {
     u32 l, r;
     entry(e, l, r);
     return key32_of(l, r);
-  }
-  // The value a distinct narrow key contributes to the key-hash sum: the
-  // pair itself for exact keys (so every tier mixes the same values), the
-  // key for hashed ones.
-  __device__ inline u64 mixin(u32 q) const {
-    if constexpr (HK) return (u64)q;
-    else return ((u64)(q >> pb) << 31) | (u64)(q & pmask());
   }
 };
 
@@ -256,8 +270,7 @@ struct Keys<u64> {
   __device__ static inline u64 load(const Src &s, int64_t e) { return s.pair(e); }
   template <class Src>
   __device__ static inline u64 from(const Src &s, u32 l, u32 r) { return s.pair_of(l, r); }
-  template <class Src>
-  __device__ static inline u64 mixin(const Src &, u64 p) { return p; }
+  __device__ static inline u64 mix(u64 p) { return mix_pair(p); }
   __device__ static inline u32 hash(u64 p) { return set_hash(p); }
 };
 template <>
@@ -267,12 +280,8 @@ struct Keys<u32> {
   __device__ static inline u32 load(const Src &s, int64_t e) { return s.key32(e); }
   template <class Src>
   __device__ static inline u32 from(const Src &s, u32 l, u32 r) { return s.key32_of(l, r); }
-  template <class Src>
-  __device__ static inline u64 mixin(const Src &s, u32 q) { return s.mixin(q); }
-  __device__ static inline u32 hash(u32 q) {
-    const u32 h = q * 0x9E3779B1u;
-    return h ^ (h >> 15);
-  }
+  __device__ static inline u64 mix(u32 x) { return mix_key32(x); }
+  __device__ static inline u32 hash(u32 x) { return x; }
 };
 
 // Load the keys of entries first + j*STRIDE (j = 0..U-1, only those below
@@ -550,7 +559,9 @@ struct Range {
   int64_t e0;
 };
 
+// a scaled to [0, n)
 __device__ inline u64 scale_to(u32 a, u64 n) { return __umul64hi(((u64)a) << 32, n); }
+__device__ inline u32 scale_to(u32 a, u32 n) { return __umulhi(a, n); }
 
 // Exclusive block scan (256 threads) of one u32 per thread; returns the
 // thread's prefix and writes the block total to *total.
@@ -714,10 +725,10 @@ __global__ void __launch_bounds__(256) k_sig_range(Src src, const Range *__restr
     for (int u = 0; u < U; ++u) {
       const K p = pr[u];
       if (p == KO::EMPTY) continue;
-      u32 sl = (u32)scale_to(KO::hash(p), sz);
+      u32 sl = scale_to(KO::hash(p), sz);
       while (true) {
         const K old = atomicCAS(&set[sl], KO::EMPTY, p);
-        if (old == KO::EMPTY) { a += mix_pair(KO::mixin(src, p)); ++c; break; }
+        if (old == KO::EMPTY) { a += KO::mix(p); ++c; break; }
         if (old == p) break;
         sl = (sl + 1 == sz) ? 0u : sl + 1;
       }
@@ -739,7 +750,7 @@ __global__ void __launch_bounds__(256) k_sig_range(Src src, const Range *__restr
       const K p = pr[u];
       const int base = 2 * off[lo];
       const u32 sz = 2u * (u32)(off[lo + 1] - off[lo]);
-      u32 sl = (u32)scale_to(KO::hash(p), sz);
+      u32 sl = scale_to(KO::hash(p), sz);
       while (true) {
         const K old = atomicCAS(&set[base + sl], KO::EMPTY, p);
         if (old == KO::EMPTY || old == p) break;
@@ -778,7 +789,7 @@ __global__ void __launch_bounds__(256) k_sig_range(Src src, const Range *__restr
         }
         const K p = set[sidx];
         if (p != KO::EMPTY) {
-          a += mix_pair(KO::mixin(src, p));
+          a += KO::mix(p);
           ++c;
         }
       }
@@ -877,10 +888,10 @@ __global__ void __launch_bounds__(NT) k_sig_row(Src src, const Range *__restrict
   for (int u = 0; u < U; ++u) {
     const K p = pr[u];
     if (p == KO::EMPTY) continue;
-    u32 sl = (u32)scale_to(KO::hash(p), sz);
+    u32 sl = scale_to(KO::hash(p), sz);
     while (true) {
       const K old = atomicCAS(&set[sl], KO::EMPTY, p);
-      if (old == KO::EMPTY) { a += mix_pair(KO::mixin(src, p)); ++c; break; }
+      if (old == KO::EMPTY) { a += KO::mix(p); ++c; break; }
       if (old == p) break;
       sl = (sl + 1 == sz) ? 0u : sl + 1;
     }
@@ -1105,7 +1116,7 @@ __global__ void __launch_bounds__(256) k_hub_reduce(Src src, const HubPart *__re
             if (sh_fill[1]) break;
             const K old = atomicCAS(&set[sl], KO::EMPTY, p);
             if (old == KO::EMPTY) {
-              pacc += mix_pair(KO::mixin(src, p));
+              pacc += KO::mix(p);
               ++pcnt;
               if (atomicAdd(&sh_fill[0], 1u) + 1u >= (u32)(PS / 4 * 3)) sh_fill[1] = 1u;
               break;
@@ -1160,7 +1171,7 @@ struct HubGChunk {
 // the current one, so dep[EP_HUB] must be 1..3 (advanced at least once; a
 // zeroed set with epoch 0 would have no empty slot) and each set must hold
 // more slots than its row has entries.
-template <class Src>
+template <class Src, class K>
 __global__ void __launch_bounds__(256) k_sig_hub_global(Src src, const HubGChunk *__restrict__ chunks,
                                                         const int *__restrict__ hubs, u64 *sets, u64 *hub_acc,
                                                         u32 *hub_cnt, const u32 *__restrict__ dep,
@@ -1176,16 +1187,15 @@ __global__ void __launch_bounds__(256) k_sig_hub_global(Src src, const HubGChunk
   u64 acc = 0;
   u32 cnt = 0;
   for (int64_t i = row + c.b + threadIdx.x; i < row + c.e; i += 256) {
-    u64 p = src.pair(i);
-    if constexpr (Src::HASHED) p = (u64)src.hkey(p);  // the tiers of one graph dedupe the same keys
-    const u64 want = p | ((u64)hepoch << 62);
-    u64 sl = scale_to(set_hash(p), size);
+    const K key = Keys<K>::load(src, i);  // the tiers of one graph dedupe the same keys
+    const u64 want = (u64)key | ((u64)hepoch << 62);
+    u64 sl = scale_to(set_hash((u64)key), size);
     while (true) {
       u64 cur = __hip_atomic_load(&set[sl], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       bool done = false;
       while ((cur >> 62) != (u64)hepoch) {
         const u64 old = atomicCAS(&set[sl], cur, want);
-        if (old == cur) { acc += mix_pair(p); ++cnt; done = true; break; }
+        if (old == cur) { acc += Keys<K>::mix(key); ++cnt; done = true; break; }
         cur = old;
       }
       if (done || cur == want) break;
@@ -2816,12 +2826,8 @@ struct PlainSrcT {
     return ((u64)label(e) << 31) | (u64)((u32)names[col[e]] & pmask());
   }
   __device__ inline u32 own(int v) const { return (u32)names[v]; }
-  __device__ inline u32 hkey(u64 p) const { return pair_key32(p) & kmask; }
-  // the same key forms as GraphSrcT: exact (label << pb) | block, or a hash of the pair
-  __device__ inline u32 key32(int64_t e) const {
-    if constexpr (HK) return hkey(pair(e));
-    else return (label(e) << pb) | ((u32)names[col[e]] & pmask());
-  }
+  // the same key forms as GraphSrcT
+  __device__ inline u32 key32(int64_t e) const { return key32_of(label(e), (u32)col[e]); }
   // the row kernels' interface (as GraphSrcT, with targets in vertex order):
   // (label, target) of entries first + min(t + u*STRIDE, count - 1)
   template <int U, int STRIDE>
@@ -2835,12 +2841,7 @@ struct PlainSrcT {
   }
   __device__ inline u64 pair_of(u32 l, u32 r) const { return ((u64)l << 31) | (u64)((u32)names[r] & pmask()); }
   __device__ inline u32 key32_of(u32 l, u32 r) const {
-    if constexpr (HK) return hkey(pair_of(l, r));
-    else return (l << pb) | ((u32)names[r] & pmask());
-  }
-  __device__ inline u64 mixin(u32 q) const {
-    if constexpr (HK) return (u64)q;
-    else return ((u64)(q >> pb) << 31) | (u64)(q & pmask());
+    return narrow_key<HK>(l, (u32)names[r] & pmask(), pb, kmask);
   }
 };
 
@@ -2893,7 +2894,7 @@ __global__ void __launch_bounds__(256) k_sig_list_small(Src src, const int *__re
       u32 sl = KO::hash(p) & (SL - 1);
       while (true) {
         const K old = atomicCAS(&set[w][sl], KO::EMPTY, p);
-        if (old == KO::EMPTY) { a = mix_pair(KO::mixin(src, p)); c = 1; break; }
+        if (old == KO::EMPTY) { a = KO::mix(p); c = 1; break; }
         if (old == p) break;
         sl = (sl + 1) & (SL - 1);
       }
@@ -2954,7 +2955,7 @@ __global__ void __launch_bounds__(256) k_sig_list_large(Src src, const int *__re
             if (sh_fill[1]) break;  // overflowed: the pass is redone with more sub-partitions
             const K old = atomicCAS(&set[sl], KO::EMPTY, p);
             if (old == KO::EMPTY) {
-              pacc += mix_pair(KO::mixin(src, p));
+              pacc += KO::mix(p);
               ++pcnt;
               if (atomicAdd(&sh_fill[0], 1u) + 1u >= (u32)(PS / 4 * 3)) sh_fill[1] = 1u;
               break;
