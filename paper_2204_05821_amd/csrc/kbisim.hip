@@ -39,6 +39,13 @@ constexpr int RES_GRID = 256;
 constexpr int CLEAR_GRID = 2048;
 constexpr int MIN_RANGE_EDGES = 1024;  // smallest tunable range capacity
 constexpr int MIN_HUB_CHUNK = 2048;    // smallest tunable hub chunk
+// Non-empty rows from which a full step groups by partition (9 launches more,
+// no device-wide atomics) instead of through the table.  k = 10 calls, table
+// against partition: 0.5M rows of 8 entries 0.95 / 1.09 ms, 1.7M rows of 23
+// entries 4.28 / 4.32, 2.0M rows of 8 entries 3.29 / 2.73, the 100M-edge graph
+// (3.5M rows) 9.29 / 8.75, a 1,024-graph batch (27M rows) 34.5 / 25.2, the
+// 1B-edge graph (40M rows) 146.6 / 130.8.
+constexpr int64_t GROUP_MIN = 1800000;
 constexpr int MAX_GRAPH_CACHE = 8;
 constexpr size_t READBACK_MAX = 1 << 16;  // bytes of counters and counts copied back at once
 
@@ -154,6 +161,7 @@ struct Tuning {
   int key_bits = 0;  // LDS set keys: 0 = 32-bit (exact where pairs fit, else hashed), 32 = hashed, 64 = 64-bit
   int hub_parts_cap = HUB_PMAX;  // most partitions per staged hub (a smaller cap is a test knob)
   int scan_items = SCAN_ITEMS;   // vertices per thread in the numbering scan: 8 or 16
+  int64_t group_min = GROUP_MIN;  // non-empty rows from which full steps group by partition
   int gfilter_min = GFILTER_MIN_DIRTY;  // dirty vertices from which update steps use the global filter
 };
 
@@ -193,6 +201,7 @@ struct kbisim_ctx {
   u64 hmask = ~0ULL;
   u32 kmask = 0xFFFFFFFFu;  // bits kept of hashed set keys (test knob)
   u64 tmask_steps = 0;   // grouping-table mask of refinement steps (sized by vertices with edges)
+  bool table_dirty = false;  // the grouping table's space was used by partitioned steps
   bool work_eff = false;  // skip singleton blocks, stop at the fixpoint
   int we_steps = 0;       // steps computed by the last work-efficient call
   unsigned char *single[2] = {nullptr, nullptr};  // singleton flags of the last two partitions
@@ -617,8 +626,12 @@ int bit_width(uint64_t x) {
 int scan64(hipStream_t s, int64_t len, const int *cnt, int64_t *tiles, int64_t *out) {
   const int64_t nt = (len + SCAN_TILE - 1) / SCAN_TILE;
   k_sum_tiles64<<<(unsigned)nt, 256, 0, s>>>(len, cnt, tiles);
-  k_scan_tiles64<<<1, 256, 0, s>>>(nt, tiles);
-  k_write_ptr64<<<(unsigned)nt, 256, 0, s>>>(len, cnt, tiles, out, nullptr);
+  if (nt <= 256) {
+    k_write_ptr64<true><<<(unsigned)nt, 256, 0, s>>>(len, cnt, tiles, out, nullptr);
+  } else {
+    k_scan_tiles64<<<1, 256, 0, s>>>(nt, tiles);
+    k_write_ptr64<false><<<(unsigned)nt, 256, 0, s>>>(len, cnt, tiles, out, nullptr);
+  }
   HIP_TRY(hipGetLastError());
   return 0;
 }
@@ -761,29 +774,29 @@ u64 table_mask(const kbisim_ctx *c) {
 }
 
 template <class Src, class K, bool SKIP>
-int launch_range_kernel(kbisim_ctx *c, const Src &src, const Schedule &s, u64 tmask, const unsigned char *skip) {
+int launch_range_kernel(kbisim_ctx *c, const Src &src, const Schedule &s, KeySink sink, const unsigned char *skip) {
   ProfScope ps(c, KBISIM_K_SIG_RANGE);
   if (s.range_edges == 1024)
     k_sig_range<Src, 1024, K, SKIP><<<(unsigned)s.nranges, 256, 0, c->stream>>>(
-        src, c->ranges, c->H, c->DC, c->table, tmask, c->cur, c->hmask, c->nzv, c->nzrow, skip);
+        src, c->ranges, c->H, c->DC, sink, c->cur, c->hmask, c->nzv, c->nzrow, skip);
   else
     k_sig_range<Src, 2048, K, SKIP><<<(unsigned)s.nranges, 256, 0, c->stream>>>(
-        src, c->ranges, c->H, c->DC, c->table, tmask, c->cur, c->hmask, c->nzv, c->nzrow, skip);
+        src, c->ranges, c->H, c->DC, sink, c->cur, c->hmask, c->nzv, c->nzrow, skip);
   LAUNCH_CHECK();
   return 0;
 }
 
 // skip: singleton flags of the previous partition (work-efficient mode), or NULL.
 template <class Src, class K>
-int launch_ranges_k(kbisim_ctx *c, const Src &src, const Schedule &s, const unsigned char *skip, bool range_tier) {
-  const u64 tmask = table_mask<Src>(c);
+int launch_ranges_k(kbisim_ctx *c, const Src &src, const Schedule &s, KeySink sink, const unsigned char *skip,
+                    bool range_tier) {
   if (s.nranges && range_tier) {
     int rc = 0;
     if constexpr (Src::GRAPH) {
-      rc = skip ? launch_range_kernel<Src, K, true>(c, src, s, tmask, skip)
-                : launch_range_kernel<Src, K, false>(c, src, s, tmask, nullptr);
+      rc = skip ? launch_range_kernel<Src, K, true>(c, src, s, sink, skip)
+                : launch_range_kernel<Src, K, false>(c, src, s, sink, nullptr);
     } else {
-      rc = launch_range_kernel<Src, K, false>(c, src, s, tmask, nullptr);
+      rc = launch_range_kernel<Src, K, false>(c, src, s, sink, nullptr);
     }
     if (rc) return rc;
   }
@@ -791,18 +804,18 @@ int launch_ranges_k(kbisim_ctx *c, const Src &src, const Schedule &s, const unsi
     ProfScope ps(c, KBISIM_K_SIG_BLOCK);
     if (s.nbig) {
       k_sig_row<Src, RANGE_DMAX, 512, K><<<(unsigned)s.nbig, 512, 0, c->stream>>>(
-          src, c->ranges + s.nranges, c->H, c->DC, c->table, tmask, c->cur, c->hmask, c->zrep, skip);
+          src, c->ranges + s.nranges, c->H, c->DC, sink, c->cur, c->hmask, c->zrep, skip);
       LAUNCH_CHECK();
     }
     if (s.nrow8) {
       k_sig_row<Src, ROW_MAX, 1024, K><<<(unsigned)s.nrow8, 1024, 0, c->stream>>>(
-          src, c->ranges + s.nranges + s.nbig, c->H, c->DC, c->table, tmask, c->cur, c->hmask, c->zrep, skip);
+          src, c->ranges + s.nranges + s.nbig, c->H, c->DC, sink, c->cur, c->hmask, c->zrep, skip);
       LAUNCH_CHECK();
     }
     if constexpr (std::is_same<K, u32>::value) {
       if (s.nrow20) {
         k_sig_row<Src, ROW_MAX_NARROW, 1024, u32><<<(unsigned)s.nrow20, 1024, 0, c->stream>>>(
-            src, c->ranges + s.nranges + s.nbig + s.nrow8, c->H, c->DC, c->table, tmask, c->cur, c->hmask, c->zrep,
+            src, c->ranges + s.nranges + s.nbig + s.nrow8, c->H, c->DC, sink, c->cur, c->hmask, c->zrep,
             skip);
         LAUNCH_CHECK();
       }
@@ -812,14 +825,15 @@ int launch_ranges_k(kbisim_ctx *c, const Src &src, const Schedule &s, const unsi
 }
 
 template <class Src>
-int launch_ranges(kbisim_ctx *c, const Src &src, const Schedule &s, const unsigned char *skip, bool range_tier) {
+int launch_ranges(kbisim_ctx *c, const Src &src, const Schedule &s, KeySink sink, const unsigned char *skip,
+                  bool range_tier) {
   if constexpr (Src::HASHED) {
-    return launch_ranges_k<Src, u32>(c, src, s, skip, range_tier);
+    return launch_ranges_k<Src, u32>(c, src, s, sink, skip, range_tier);
   } else {
     if constexpr (Src::GRAPH) {
-      if (c->narrow) return launch_ranges_k<Src, u32>(c, src, s, skip, range_tier);
+      if (c->narrow) return launch_ranges_k<Src, u32>(c, src, s, sink, skip, range_tier);
     }
-    return launch_ranges_k<Src, u64>(c, src, s, skip, range_tier);
+    return launch_ranges_k<Src, u64>(c, src, s, sink, skip, range_tier);
   }
 }
 
@@ -860,8 +874,10 @@ int launch_hub_staged(kbisim_ctx *c, const Src &src, const Schedule &s, const in
 // distinct count and the insertion into the grouping table.
 template <class Src>
 int launch_signatures(kbisim_ctx *c, const Src &src, const Schedule &s, bool zfresh, const unsigned char *skip_in,
-                      bool range_tier = true) {
+                      bool range_tier = true, bool partition = false) {
   const u64 tmask = table_mask<Src>(c);
+  // (the partition's keys lie where the table is otherwise)
+  const KeySink sink{partition ? nullptr : c->table, tmask, c->rep, partition ? c->table : nullptr};
   int rc = 0;
   if constexpr (!Src::GRAPH) {
     if (!src.ptr) {  // one label per vertex
@@ -877,7 +893,7 @@ int launch_signatures(kbisim_ctx *c, const Src &src, const Schedule &s, bool zfr
     k_sig_empty<Src><<<blocks_for(c->g.n, 256), 256, 0, c->stream>>>(src, (int)c->g.n, c->DC, c->zrep, c->cur, skip_in);
     LAUNCH_CHECK();
   }
-  if ((rc = launch_ranges(c, src, s, skip_in, range_tier))) return rc;
+  if ((rc = launch_ranges(c, src, s, sink, skip_in, range_tier))) return rc;
   if (s.nhub) {
     const int *hubs = c->lists + s.hub_off;
     if (s.nchunks) {
@@ -909,11 +925,64 @@ int launch_signatures(kbisim_ctx *c, const Src &src, const Schedule &s, bool zfr
     }
     ProfScope ps(c, KBISIM_K_HUB_FINAL);
     k_hub_final<Src><<<blocks_for(s.nhub, 256), 256, 0, c->stream>>>(src, hubs, s.nhub, c->hacc, c->hcnt, c->H, c->DC,
-                                                                     c->table, tmask, c->cur, c->hmask, c->zrep,
-                                                                     skip_in);
+                                                                     sink, c->cur, c->hmask, c->zrep, skip_in, s.nzv, (int)s.nonempty);
     LAUNCH_CHECK();
   }
   return 0;
+}
+
+// Candidate representatives of the non-empty vertices by partition (see
+// k_group_hist).  The signature kernels left the keys at the start of the
+// grouping table's space; pairs go to the list space (vlist, clA, clB: 12 n
+// bytes, free until the lookup), then back to the table's space, which also
+// holds the histograms.  It is cleared before the table is next used
+// (table_dirty).
+int group_by_partition(kbisim_ctx *c, const Schedule &s) {
+  ProfScope ps(c, KBISIM_K_LOOKUP);
+  hipStream_t st = c->stream;
+  const int64_t N = s.nonempty, nt = (N + GROUP_TILE - 1) / GROUP_TILE, hist_n = 256 * nt;
+  char *w = (char *)c->table;
+  size_t at = 0;
+  auto take = [&](size_t bytes) {
+    char *p = w + at;
+    at = align_up(at + bytes);
+    return p;
+  };
+  u64 *ka = (u64 *)take(8 * (size_t)N);
+  int *va = (int *)take(4 * (size_t)N);
+  int *hist = (int *)take(4 * (size_t)hist_n);
+  int64_t *offs[2] = {(int64_t *)take(8 * (size_t)(hist_n + 1)), (int64_t *)take(8 * (size_t)(hist_n + 1))};
+  int64_t *tiles = (int64_t *)take(8 * (size_t)(hist_n / SCAN_TILE + 1));
+  if (at > 8 * c->plan.tslots) return KBISIM_EINTERNAL;
+  u64 *kb = (u64 *)c->vlist;
+  int *vb = (int *)(kb + N);
+  const int64_t *total = offs[0] + hist_n;  // pairs after the first pass
+  const unsigned grid = radix_grid(nt);
+  int rc = 0;
+  c->table_dirty = true;
+  k_group_hist<true><<<grid, GROUP_THREADS, 0, st>>>(N, nullptr, s.nzv, c->rep, ka, 0, nt, hist);
+  LAUNCH_CHECK();
+  if ((rc = scan64(st, hist_n, hist, tiles, offs[0]))) return rc;
+  k_group_scatter<true><<<grid, GROUP_THREADS, 0, st>>>(N, nullptr, ka, s.nzv, 0, nt, offs[0], kb, vb);
+  k_group_hist<false><<<grid, GROUP_THREADS, 0, st>>>(N, total, nullptr, nullptr, kb, 8, nt, hist);
+  LAUNCH_CHECK();
+  if ((rc = scan64(st, hist_n, hist, tiles, offs[1]))) return rc;
+  k_group_scatter<false><<<grid, GROUP_THREADS, 0, st>>>(N, total, kb, vb, 8, nt, offs[1], ka, va);
+  k_group_buckets<<<blocks_for(N, GROUP_CHUNK), BUCKET_GROUP, 0, st>>>(total, ka, va, c->rep, c->err);
+  LAUNCH_CHECK();
+  return 0;
+}
+
+// The grouping table empty again after partitioned steps used its space.
+int clean_table(kbisim_ctx *c) {
+  if (!c->table_dirty) return 0;
+  c->table_dirty = false;
+  return fill_u64(c, c->table, (int64_t)c->plan.tslots, 0);
+}
+
+// Whether full steps of this schedule group by partition.
+bool by_partition(const kbisim_ctx *c, const Schedule &s) {
+  return s.nzv && s.nonempty >= c->tune.group_min && 14 * (u64)s.nonempty + 16384 <= 8 * c->plan.tslots;
 }
 
 // After the lookup: exact checks of longer rows (any_long: the schedule has
@@ -964,17 +1033,30 @@ int run_step(kbisim_ctx *c, const Src &src, const Schedule &s, int *out, int64_t
   int rc = 0;
   if (c->cur == c->dep && (rc = advance(c, ADV_TABLE | ADV_CTABLE | ADV_ZERO | (s.ngchunks ? ADV_HUB : 0u), s)))
     return rc;
-  if ((rc = launch_signatures(c, src, s, zfresh, skip_in))) return rc;
+  bool partition = false;
+  if constexpr (Src::GRAPH) partition = !c->work_eff && by_partition(c, s);
+  if (!partition && (rc = clean_table(c))) return rc;
+  if ((rc = launch_signatures(c, src, s, zfresh, skip_in, true, partition))) return rc;
+  if (partition && (rc = group_by_partition(c, s))) return rc;
   {
     ProfScope ps(c, KBISIM_K_LOOKUP);
-    // after a call's first step only vertices with edges can change their
-    // representative (the others keep the one of that step)
-    const bool listed = !zfresh && s.nzv != nullptr;
-    const int count = listed ? (int)s.nonempty : n;
-    k_lookup<Src><<<blocks_for(std::max(count, 1), 256), 256, 0, c->stream>>>(
-        src, count, listed ? s.nzv : nullptr, c->H, c->DC, c->table, tmask, c->cur, c->rep,
-                                                             &cnt[0], c->vlist, &cnt[1], c->clA, c->err, c->zrep,
-                                                             zfresh ? 1 : 0, skip_in, nullptr, nullptr);
+    // Vertices without edges keep the representative of a call's first step;
+    // the others are looked up through the list (label rows have none: every
+    // vertex, empty ones included).
+    if (s.nzv && zfresh && s.nonempty < n) {
+      k_rep_empty<Src><<<blocks_for(n, 256), 256, 0, c->stream>>>(src, n, c->DC, c->zrep, c->cur, c->rep, c->err,
+                                                                  skip_in);
+      LAUNCH_CHECK();
+    }
+    const int count = s.nzv ? (int)s.nonempty : n;
+    if (partition) {
+      k_resolve<Src><<<blocks_for(blocks_for(count, RESOLVE_V), 256), 256, 0, c->stream>>>(
+          src, count, s.nzv, c->DC, c->rep, &cnt[0], c->vlist, &cnt[1], c->clA);
+    } else if (count) {
+      k_lookup<Src><<<blocks_for(count, 256), 256, 0, c->stream>>>(
+          src, count, s.nzv, c->H, c->DC, c->table, tmask, c->cur, c->rep, &cnt[0], c->vlist, &cnt[1], c->clA, c->err,
+          c->zrep, zfresh ? 1 : 0, skip_in, nullptr, nullptr);
+    }
     LAUNCH_CHECK();
   }
   if ((rc = settle_collisions(c, src, s, cnt, careful, careful || s.nlong > 0))) return rc;
@@ -1043,9 +1125,11 @@ int enqueue_steps(kbisim_ctx *c, const int32_t *prev, int i0, int k, int32_t *co
         k_prepare_steps<<<1, 64, 0, c->stream>>>(c->dep, c->counters, i, std::min(STEP_SEGMENT, k - i), c->err,
                                                  reset_err && i == i0 ? 1 : 0);
         LAUNCH_CHECK();
-        k_clear_if<<<CLEAR_GRID, 256, 0, c->stream>>>(c->dep, c->table, (int64_t)c->plan.tslots, c->ctable, c->cslots,
-                                                      c->hubsets, 0);
-        LAUNCH_CHECK();
+        if (c->work_eff || !by_partition(c, c->sched)) {
+          k_clear_if<<<CLEAR_GRID, 256, 0, c->stream>>>(c->dep, c->table, (int64_t)c->plan.tslots, nullptr, 0, nullptr,
+                                                        0);
+          LAUNCH_CHECK();
+        }
       }
       c->cur = reinterpret_cast<const u32 *>(c->counters + CNT_STRIDE * (size_t)i) + STEP_EPOCHS;
     }
@@ -1194,6 +1278,7 @@ int refine_impl(kbisim_ctx *c, const int32_t *start, int k, int32_t *const *out,
       if (e != hipSuccess) return hip_fail(e);
       it = c->graphs.emplace(key, exec).first;
     }
+    if (by_partition(c, c->sched)) c->table_dirty = true;  // as the captured steps leave it
     HIP_TRY(hipGraphLaunch(it->second, c->stream));
   } else {
     if ((rc = enqueue_steps(c, p0, 0, k, out, false, k, true, true))) return rc;
@@ -1347,15 +1432,16 @@ int update_step(kbisim_ctx *c, const TierSrc &tsrc, const ListSrc &lsrc, int i, 
     if ((rc = launch_signatures(c, tsrc, s, true, S.skip))) return rc;
   }
   if ((rc = lists(&S.cnt[0], S.small, S.large))) return rc;
+  const KeySink sink{c->table, tmask, nullptr, nullptr};
   if (S.nerows8) {
     k_sig_row<ListSrc, ROW_MAX, 1024, K><<<(unsigned)S.nerows8, 1024, 0, c->stream>>>(
-        lsrc, S.erows, c->H, c->DC, c->table, tmask, c->cur, c->hmask, c->zrep, nullptr);
+        lsrc, S.erows, c->H, c->DC, sink, c->cur, c->hmask, c->zrep, nullptr);
     LAUNCH_CHECK();
   }
   if constexpr (std::is_same<K, u32>::value) {
     if (S.nerows20) {
       k_sig_row<ListSrc, ROW_MAX_NARROW, 1024, u32><<<(unsigned)S.nerows20, 1024, 0, c->stream>>>(
-          lsrc, S.erows + S.nerows8, c->H, c->DC, c->table, tmask, c->cur, c->hmask, c->zrep, nullptr);
+          lsrc, S.erows + S.nerows8, c->H, c->DC, sink, c->cur, c->hmask, c->zrep, nullptr);
       LAUNCH_CHECK();
     }
   }
@@ -1366,8 +1452,8 @@ int update_step(kbisim_ctx *c, const TierSrc &tsrc, const ListSrc &lsrc, int i, 
         lsrc, S.huge_chunks, S.huge, c->hubsets + S.huge_set_begin, S.huge_acc, S.huge_cnt, c->cur, nullptr);
     LAUNCH_CHECK();
     k_hub_final<ListSrc><<<blocks_for(S.nhuge, 256), 256, 0, c->stream>>>(lsrc, S.huge, S.nhuge, S.huge_acc,
-                                                                          S.huge_cnt, c->H, c->DC, c->table, tmask,
-                                                                          c->cur, c->hmask, c->zrep, nullptr);
+                                                                          S.huge_cnt, c->H, c->DC, sink, c->cur,
+                                                                          c->hmask, c->zrep, nullptr, nullptr, 0);
     LAUNCH_CHECK();
   }
   int nlk = 0;
@@ -1630,6 +1716,7 @@ int update_impl(kbisim_ctx *c, const kbisim_graph *gn, const int32_t *rows, int6
       }
     }
   }
+  if ((rc = clean_table(c))) return rc;
   // every vertex may carry a key in an update (edited rows can gain entries),
   // and empty signatures are grouped by block names below 2n
   const u64 tmask_saved = c->tmask_steps;
@@ -1706,7 +1793,7 @@ int incr_enable_impl(kbisim_ctx *c, void *state, size_t bytes) {
                                                                                                        cnt);
     k_sum_tiles64<<<(unsigned)nt, 256, 0, c->stream>>>(n, cnt, tiles);
     k_scan_tiles64<<<1, 256, 0, c->stream>>>(nt, tiles);
-    k_write_ptr64<<<(unsigned)nt, 256, 0, c->stream>>>(n, cnt, tiles, S.tptr, cursor);
+    k_write_ptr64<false><<<(unsigned)nt, 256, 0, c->stream>>>(n, cnt, tiles, S.tptr, cursor);
     if (m > 0)
       k_transpose_scatter<<<(unsigned)std::min<int64_t>(blocks_for(n * WAVE, 256), 65536), 256, 0, c->stream>>>(
           n, c->g.row_ptr, c->g.col, nullptr, cursor, S.tcol, nullptr);
@@ -1865,6 +1952,12 @@ int create_impl(const kbisim_graph *g, int kmax, const kbisim_tuning *tuning, vo
   if (kdbg && *kdbg) {
     int b = atoi(kdbg);
     if (b >= 1 && b < 32) c->kmask = (1u << b) - 1u;
+  }
+  // Test knob: group by partition from this many non-empty rows on (at least 1).
+  const char *qdbg = getenv("KBISIM_DEBUG_GROUP_MIN");
+  if (qdbg && *qdbg) {
+    const long q = atol(qdbg);
+    if (q >= 1) c->tune.group_min = q;
   }
   // Test knob: update steps use the global dirty-key filter from this many
   // dirty vertices on (at least 1), so that small graphs take that path.
@@ -2447,7 +2540,7 @@ int kbisim_transpose(int64_t n, int64_t m, const int64_t *row_ptr, const int32_t
   if (m > 0) k_indegree<<<(unsigned)std::min<int64_t>(blocks_for(m, INDEG_CHUNK), 65536), 256, 0, s>>>(m, col, cnt);
   k_sum_tiles64<<<(unsigned)p.ntiles, 256, 0, s>>>(n, cnt, tiles);
   k_scan_tiles64<<<1, 256, 0, s>>>(p.ntiles, tiles);
-  k_write_ptr64<<<(unsigned)p.ntiles, 256, 0, s>>>(n, cnt, tiles, out_row_ptr, cursor);
+  k_write_ptr64<false><<<(unsigned)p.ntiles, 256, 0, s>>>(n, cnt, tiles, out_row_ptr, cursor);
   if (m > 0)
     k_transpose_scatter<<<(unsigned)std::min<int64_t>(blocks_for(n * WAVE, 256), 65536), 256, 0, s>>>(
         n, row_ptr, col, elabel, cursor, out_col, out_elabel);

@@ -128,6 +128,16 @@ __device__ inline u64 finalize_key(u64 acc, u32 dc, u32 own) {
   return fmix64(acc + (((u64)own << 32) | (u64)dc) * 0x9E3779B97F4A7C15ULL);
 }
 
+// Where a key goes: into the grouping table, or (table NULL) to the partition
+// (k_group_*): keys[i] for non-empty row i, EMPTY64 where another vertex of the
+// wave speaks for this one, and rep[v] = that vertex (or v itself).
+struct KeySink {
+  u64 *table;
+  u64 tmask;
+  int *rep;
+  u64 *keys;
+};
+
 // ---------------------------------------------------------------- sources
 // 32-bit set key of a pair (label l, reduced block b).  When every edge label
 // and reduced block id fit together in 31 bits it is exact: fmix32 is one to
@@ -302,6 +312,12 @@ __device__ inline void load_keys(const Src &src, int64_t first, int t, int count
 }
 
 // ---------------------------------------------------------------- wave helpers
+__device__ inline u64 sink_form(u64 h) { return h == EMPTY64 ? EMPTY64 - 1ULL : h; }
+__device__ inline void sink_key(const KeySink &s, int row, int v, u64 h) {
+  s.rep[v] = v;
+  s.keys[row] = sink_form(h);
+}
+
 __device__ inline u64 wave_sum_u64(u64 x) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, WAVE);
@@ -428,7 +444,8 @@ __device__ inline void key_insert(u64 *table, u64 tmask, u64 *zrep, u64 h, u32 d
 // entries 169 -> 64 us; a graph with a key per vertex runs as before.
 // Must be reached by the whole wave; slots is this wave's own region.
 constexpr int FIRST_SLOTS = 256;
-__device__ inline bool wave_first_of_key(u32 *slots, bool act, u64 h) {
+// *speaker: the lane that goes on for this one (itself if it goes on).
+__device__ inline bool wave_first_of_key(u32 *slots, bool act, u64 h, int *speaker = nullptr) {
   const int lane = threadIdx.x & (WAVE - 1);
 #pragma unroll
   for (int i = 0; i < FIRST_SLOTS / WAVE; ++i) slots[lane + i * WAVE] = 0xFFFFFFFFu;
@@ -438,6 +455,7 @@ __device__ inline bool wave_first_of_key(u32 *slots, bool act, u64 h) {
   __builtin_amdgcn_wave_barrier();
   const int m = act ? (int)slots[at] : lane;
   const u64 hm = __shfl(h, m, WAVE);
+  if (speaker) *speaker = hm == h ? m : lane;
   return act && (m == lane || hm != h);
 }
 
@@ -555,7 +573,8 @@ __global__ void __launch_bounds__(256) k_validate_vals(int64_t cnt, const int32_
 // a workgroup requests its entries without waiting for the row offsets.
 struct Range {
   int v0, v1;
-  int ne, pad;
+  int ne;
+  int row;  // single-row ranges: the row's index among the non-empty rows
   int64_t e0;
 };
 
@@ -607,7 +626,7 @@ __device__ inline void block_reduce_2(u64 &acc, u32 &cnt, u64 *sh_acc, u32 *sh_c
 // so their entries are gathered only after the owner scan.
 template <class Src, int EMAX, class K = u64, bool SKIP = false>
 __global__ void __launch_bounds__(256) k_sig_range(Src src, const Range *__restrict__ ranges, u64 *__restrict__ H,
-                                                   u32 *__restrict__ DC, u64 *table, u64 tmask,
+                                                   u32 *__restrict__ DC, KeySink sink,
                                                    const u32 *__restrict__ dep, u64 hmask,
                                                    const int *__restrict__ nzv, const u32 *__restrict__ nzrow,
                                                    const unsigned char *__restrict__ skip) {
@@ -738,7 +757,8 @@ __global__ void __launch_bounds__(256) k_sig_range(Src src, const Range *__restr
       const u64 h = finalize_key(a, c, own_t) & hmask;
       H[v] = h;
       DC[v] = c;
-      table_insert(table, tmask, h, (u32)v, epoch);
+      if (sink.table) table_insert(sink.table, sink.tmask, h, (u32)v, epoch);
+      else sink_key(sink, rg.v0, v, h);
     }
     return;
   }
@@ -811,8 +831,17 @@ __global__ void __launch_bounds__(256) k_sig_range(Src src, const Range *__restr
   }
   // (the set is no longer read: its space holds the waves' key slots)
   static_assert(sizeof(set) >= 4 * FIRST_SLOTS * sizeof(u32), "key slots of four waves");
-  if (wave_first_of_key(reinterpret_cast<u32 *>(set) + w * FIRST_SLOTS, keyed, h))
-    table_insert(table, tmask, h, (u32)v, epoch);
+  int speaker;
+  const bool first = wave_first_of_key(reinterpret_cast<u32 *>(set) + w * FIRST_SLOTS, keyed, h, &speaker);
+  if (sink.table) {
+    if (first) table_insert(sink.table, sink.tmask, h, (u32)v, epoch);
+  } else {
+    const int vs = __shfl(v, speaker, WAVE);
+    if (keyed) {
+      sink.rep[v] = vs;
+      sink.keys[rg.v0 + t] = first ? sink_form(h) : EMPTY64;
+    }
+  }
 }
 
 // Vertices with an empty signature, which are in no range: no distinct pair,
@@ -826,13 +855,34 @@ __global__ void __launch_bounds__(256) k_sig_empty(Src src, int n, u32 *__restri
   __shared__ u32 slots[4][2 * FIRST_SLOTS];
   const u32 zep = dep[EP_ZERO];
   const int v = blockIdx.x * 256 + threadIdx.x;
-  const bool zero = v < n && src.begin(v) == src.end(v) && !(skip && skip[v]);
+  bool zero = v < n && src.begin(v) == src.end(v) && !(skip && skip[v]);
   u32 own = 0;
   if (zero) {
     DC[v] = 0;
     own = src.own(v);
+    // (most waves come late to blocks that have a smaller vertex already)
+    zero = zrep[own] > (((u64)(~zep) << 32) | (u64)(u32)v);
   }
   zero_insert_wave(slots[threadIdx.x >> 6], zrep, zero, own, (u32)v, zep);
+}
+
+// Representatives of the vertices with an empty signature (DC = 0) in a call's
+// first step: the minimum vertex of their previous block.
+template <class Src>
+__global__ void __launch_bounds__(256) k_rep_empty(Src src, int n, const u32 *__restrict__ DC,
+                                                   const u64 *__restrict__ zrep, const u32 *__restrict__ dep,
+                                                   int *__restrict__ rep, u32 *err,
+                                                   const unsigned char *__restrict__ skip) {
+  const u32 zep = dep[EP_ZERO];
+  const int v = blockIdx.x * 256 + threadIdx.x;
+  if (v >= n || DC[v] != 0 || (skip && skip[v])) return;
+  const u64 z = zrep[src.own(v)];
+  if ((u32)(z >> 32) != ~zep) {
+    atomicOr(err, ERR_LOOKUP_MISS);
+    rep[v] = v;
+  } else {
+    rep[v] = (int)(u32)z;
+  }
 }
 
 // Rows of exactly one item (P0 with one label per vertex): no set, no row
@@ -857,7 +907,7 @@ __global__ void __launch_bounds__(256) k_sig_one(Src src, int n, u64 *__restrict
 // thread-local sums, reduced over the workgroup at the end.
 template <class Src, int EMAX, int NT, class K = u64>
 __global__ void __launch_bounds__(NT) k_sig_row(Src src, const Range *__restrict__ rows, u64 *__restrict__ H,
-                                                u32 *__restrict__ DC, u64 *table, u64 tmask,
+                                                u32 *__restrict__ DC, KeySink sink,
                                                 const u32 *__restrict__ dep, u64 hmask, u64 *zrep,
                                                 const unsigned char *__restrict__ skip) {
   typedef Keys<K> KO;
@@ -901,7 +951,8 @@ __global__ void __launch_bounds__(NT) k_sig_row(Src src, const Range *__restrict
     const u64 h = finalize_key(a, c, own0) & hmask;
     H[v] = h;
     DC[v] = c;
-    key_insert(table, tmask, zrep, h, c, own0, (u32)v, dep[EP_TABLE], dep[EP_ZERO]);
+    if (sink.table) key_insert(sink.table, sink.tmask, zrep, h, c, own0, (u32)v, dep[EP_TABLE], dep[EP_ZERO]);
+    else sink_key(sink, rw.row, v, h);
   }
 }
 
@@ -1211,9 +1262,9 @@ __global__ void __launch_bounds__(256) k_sig_hub_global(Src src, const HubGChunk
 
 template <class Src>
 __global__ void k_hub_final(Src src, const int *__restrict__ hubs, int nhub, u64 *hub_acc, u32 *hub_cnt,
-                            u64 *__restrict__ H, u32 *__restrict__ DC, u64 *table, u64 tmask,
+                            u64 *__restrict__ H, u32 *__restrict__ DC, KeySink sink,
                             const u32 *__restrict__ dep, u64 hmask, u64 *zrep,
-                            const unsigned char *__restrict__ skip) {
+                            const unsigned char *__restrict__ skip, const int *__restrict__ nzv, int nonempty) {
   const u32 epoch = dep[EP_TABLE], zep = dep[EP_ZERO];
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= nhub) return;
@@ -1227,10 +1278,416 @@ __global__ void k_hub_final(Src src, const int *__restrict__ hubs, int nhub, u64
   const u64 h = finalize_key(acc, cnt, own) & hmask;
   H[v] = h;
   DC[v] = cnt;
-  key_insert(table, tmask, zrep, h, cnt, own, (u32)v, epoch, zep);
+  if (sink.table) {
+    key_insert(sink.table, sink.tmask, zrep, h, cnt, own, (u32)v, epoch, zep);
+  } else {
+    int lo = 0, hi = nonempty;  // the hub's place among the non-empty rows
+    while (hi - lo > 1) {
+      const int mid = lo + ((hi - lo) >> 1);
+      if (nzv[mid] <= v) lo = mid;
+      else hi = mid;
+    }
+    sink_key(sink, lo, v, h);
+  }
+}
+
+constexpr int XCDS = 8;  // workgroups go to the XCDs in turn
+// Tile of this workgroup (>= ntiles: none; grids are padded to a multiple of
+// XCDS): each XCD takes a contiguous share of the tiles in order, so that the
+// runs that neighbouring tiles write side by side meet in one L2 and leave it
+// as whole lines (9.25 -> 7.6 ms per summary graph of 125M entries).
+__device__ inline int64_t radix_tile(int64_t ntiles) {
+  return (int64_t)(blockIdx.x % XCDS) * ((ntiles + XCDS - 1) / XCDS) + blockIdx.x / XCDS;
+}
+
+// ---------------------------------------------------------------- grouping by partition
+// The table's inserts are device-wide atomics on random lines (about 25 G/s
+// here) and every vertex probes a random line again to find its minimum.
+// Large steps group without it: the signature kernels leave H, and rep[v] = v
+// for one vertex per key of a wave (rep = that vertex for the wave's others,
+// which go no further); (H, v) pairs are partitioned by 16 hash bits in two
+// stable radix passes; workgroups then find the minimum vertex of each key of
+// whole buckets in LDS, and write rep[v] only where the minimum is another
+// vertex (few, once most blocks are single vertices).  On the 1B-edge graph (40M
+// keys per step) the passes take 1.0 ms; the table's inserts cost the range
+// kernel 1.3 ms (9.49 -> 8.17) and its lookups 1.7 (k_resolve: 0.48).
+constexpr int GROUP_THREADS = 512, GROUP_ITEMS = 8;
+constexpr int GROUP_TILE = GROUP_THREADS * GROUP_ITEMS;  // pairs per radix tile
+static_assert(GROUP_TILE == 4096, "12-bit slots");
+constexpr int GROUP_BITS = 16;                           // bucket bits, the low ones of H
+constexpr int GROUP_CHUNK = 2048;  // pairs per workgroup of k_group_buckets, extended to whole buckets
+constexpr int GROUP_SLOTS = 4096;  // LDS table slots (48 KB with the minima)
+__device__ inline u32 group_bucket(u64 h) { return (u32)h & ((1u << GROUP_BITS) - 1u); }
+
+// Pair `at` of a pass: with FIRST a key of the signature kernels (EMPTY64: none)
+// and, with vals (the list of non-empty vertices), its vertex; else one of the
+// pairs of the pass before.
+template <bool FIRST>
+__device__ inline void group_load(int64_t at, int64_t count, const u64 *__restrict__ keys,
+                                  const int *__restrict__ vals, bool &valid, u64 &key, int &v) {
+  valid = at < count;
+  key = valid ? __builtin_nontemporal_load(&keys[at]) : 0ULL;
+  v = valid && vals ? __builtin_nontemporal_load(&vals[at]) : 0;
+  if constexpr (FIRST) valid = valid && key != EMPTY64;
+}
+
+// Digit histogram of each tile (tiles dealt to the XCDs as radix_tile).
+// FIRST: where one digit takes more than 1/8 of a tile (many vertices with one
+// key), equal keys of the tile meet in an LDS table and all but the minimum
+// vertex of each drop out (rep = that vertex), so that the bucket of a key
+// that n vertices share receives about n / GROUP_TILE pairs.
+template <bool FIRST>
+__global__ void __launch_bounds__(GROUP_THREADS) k_group_hist(int64_t count, const int64_t *__restrict__ total,
+                                                              const int *__restrict__ list, int *rep, u64 *keys,
+                                                              int shift, int64_t ntiles, int *__restrict__ hist) {
+  __shared__ int h[256];
+  __shared__ u64 slot[FIRST ? GROUP_TILE : 1];
+  __shared__ u32 mins[FIRST ? GROUP_TILE : 1];
+  const int64_t tile = radix_tile(ntiles);
+  if (tile >= ntiles) return;
+  const int64_t cnt = FIRST ? count : *total;
+  if (threadIdx.x < 256) h[threadIdx.x] = 0;
+  __syncthreads();
+  u64 key[GROUP_ITEMS];
+  bool valid[GROUP_ITEMS];
+  const int64_t i0 = tile * GROUP_TILE + threadIdx.x;
+#pragma unroll
+  for (int j = 0; j < GROUP_ITEMS; ++j) {
+    int none;
+    group_load<FIRST>(i0 + j * GROUP_THREADS, cnt, keys, nullptr, valid[j], key[j], none);
+  }
+#pragma unroll
+  for (int j = 0; j < GROUP_ITEMS; ++j)
+    if (valid[j]) atomicAdd(&h[(u32)(key[j] >> shift) & 255u], 1);
+  __syncthreads();
+  if constexpr (FIRST) {
+    if (__syncthreads_or(threadIdx.x < 256 && h[threadIdx.x] > GROUP_TILE / 8)) {
+      for (int i = threadIdx.x; i < GROUP_TILE; i += GROUP_THREADS) {
+        slot[i] = EMPTY64;
+        mins[i] = 0xFFFFFFFFu;
+      }
+      __syncthreads();
+      int at[GROUP_ITEMS], v[GROUP_ITEMS];
+#pragma unroll
+      for (int j = 0; j < GROUP_ITEMS; ++j) v[j] = valid[j] ? list[i0 + j * GROUP_THREADS] : 0;
+#pragma unroll
+      for (int j = 0; j < GROUP_ITEMS; ++j) {
+        if (!valid[j]) continue;
+        u32 s = (u32)(key[j] >> GROUP_BITS) * 0x9E3779B1u >> 20;  // 12 bits: as many slots as keys
+        while (true) {
+          const u64 old = atomicCAS(&slot[s], EMPTY64, key[j]);
+          if (old == EMPTY64 || old == key[j]) break;
+          s = (s + 1) & (GROUP_TILE - 1);
+        }
+        at[j] = (int)s;
+        atomicMin(&mins[s], (u32)v[j]);
+      }
+      __syncthreads();
+#pragma unroll
+      for (int j = 0; j < GROUP_ITEMS; ++j) {
+        if (!valid[j]) continue;
+        const int first = (int)mins[at[j]];
+        if (first != v[j]) {
+          rep[v[j]] = first;
+          keys[i0 + j * GROUP_THREADS] = EMPTY64;
+          atomicSub(&h[(u32)(key[j] >> shift) & 255u], 1);
+        }
+      }
+      __syncthreads();
+    }
+  }
+  if (threadIdx.x < 256) hist[(int64_t)threadIdx.x * ntiles + tile] = h[threadIdx.x];
+}
+
+// Stable scatter of a tile's pairs by their digit (as k_radix_scatter).
+template <bool FIRST>
+__global__ void __launch_bounds__(GROUP_THREADS) k_group_scatter(int64_t count, const int64_t *__restrict__ total,
+                                                                 const u64 *__restrict__ keys,
+                                                                 const int *__restrict__ vals, int shift,
+                                                                 int64_t ntiles, const int64_t *__restrict__ offs,
+                                                                 u64 *__restrict__ out_keys,
+                                                                 int *__restrict__ out_vals) {
+  constexpr int NW = GROUP_THREADS / WAVE;
+  __shared__ u64 sk[GROUP_TILE];
+  __shared__ int sv[GROUP_TILE];
+  __shared__ int64_t gpos[256];
+  __shared__ int wcnt[NW][256];
+  __shared__ u32 sh_w[4];
+  __shared__ int sh_n;
+  const int64_t tile = radix_tile(ntiles);
+  if (tile >= ntiles) return;
+  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+  const int64_t cnt = FIRST ? count : *total;
+  if (tile * GROUP_TILE >= cnt) return;
+  const int64_t goff = t < 256 ? offs[(int64_t)t * ntiles + tile] : 0;
+  const u64 lt = (1ULL << lane) - 1ULL;
+  u64 key[GROUP_ITEMS];
+  int val[GROUP_ITEMS];
+  bool valid[GROUP_ITEMS];
+  const int64_t i0 = tile * GROUP_TILE + w * (WAVE * GROUP_ITEMS) + lane;
+#pragma unroll
+  for (int j = 0; j < GROUP_ITEMS; ++j)
+    group_load<FIRST>(i0 + j * WAVE, cnt, keys, vals, valid[j], key[j], val[j]);
+#pragma unroll
+  for (int q = 0; q < 256 / WAVE; ++q) wcnt[w][q * WAVE + lane] = 0;
+  __builtin_amdgcn_wave_barrier();
+  int rank[GROUP_ITEMS];
+#pragma unroll
+  for (int j = 0; j < GROUP_ITEMS; ++j) {
+    const u32 d = (u32)(key[j] >> shift) & 255u;
+    u64 peers = __ballot(valid[j]);
+#pragma unroll
+    for (int b = 0; b < 8; ++b) {
+      const u64 ones = __ballot((d >> b) & 1u);
+      peers &= ((d >> b) & 1u) ? ones : ~ones;
+    }
+    const int below = __popcll(peers & lt);
+    const int before = wcnt[w][d];
+    __builtin_amdgcn_wave_barrier();
+    if (valid[j] && below == 0) wcnt[w][d] = before + __popcll(peers);
+    __builtin_amdgcn_wave_barrier();
+    rank[j] = before + below;
+  }
+  __syncthreads();
+  {
+    u32 c = 0;
+    if (t < 256)
+#pragma unroll
+      for (int q = 0; q < NW; ++q) c += (u32)wcnt[q][t];
+    u32 x = c;
+#pragma unroll
+    for (int o = 1; o < WAVE; o <<= 1) {
+      const u32 y = __shfl_up(x, o, WAVE);
+      if (lane >= o) x += y;
+    }
+    if (t < 256 && lane == WAVE - 1) sh_w[w] = x;
+    __syncthreads();
+    if (t < 256) {
+      int at = (int)(x - c);
+      for (int i = 0; i < w; ++i) at += (int)sh_w[i];
+      gpos[t] = goff - at;
+#pragma unroll
+      for (int q = 0; q < NW; ++q) {
+        const int m = wcnt[q][t];
+        wcnt[q][t] = at;
+        at += m;
+      }
+      if (t == 255) sh_n = at;
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < GROUP_ITEMS; ++j) {
+    if (!valid[j]) continue;
+    const int at = wcnt[w][(u32)(key[j] >> shift) & 255u] + rank[j];
+    sk[at] = key[j];
+    sv[at] = val[j];
+  }
+  __syncthreads();
+  const int n = sh_n;
+#pragma unroll
+  for (int j = 0; j < GROUP_ITEMS; ++j) {
+    const int i = j * GROUP_THREADS + t;
+    if (i < n) {
+      const u64 k = sk[i];
+      const int64_t o = gpos[(u32)(k >> shift) & 255u] + i;
+      out_keys[o] = k;
+      out_vals[o] = sv[i];
+    }
+  }
+}
+
+// Links the vertices of every key of the buckets that start in this workgroup's
+// chunk.  Equal keys share a bucket, so the LDS table sees all of them; it
+// holds the distinct keys of about a chunk (stretches end at bucket starts).
+// Slots are (high hash word << 32 | vertex), the smallest vertex so far: of two
+// vertices that meet, the larger gets a link (rep) to the smaller, so every
+// vertex but the minimum is linked once, along a chain that ends there, and
+// one look at each pair is enough.  Two keys that share bucket, slot run and
+// high word meet in one group; the exact check separates them.  A stretch with
+// more than 3/4 of the slots distinct is redone in Q sub-passes by other hash
+// bits, Q doubled until each fits.
+constexpr int BUCKET_GROUP = 512;
+__global__ void __launch_bounds__(BUCKET_GROUP) k_group_buckets(const int64_t *__restrict__ total_p,
+                                                       const u64 *__restrict__ keys, const int *__restrict__ vals,
+                                                       int *__restrict__ rep, u32 *err) {
+  constexpr int U = 4, BATCH = BUCKET_GROUP * U;
+  static_assert(GROUP_CHUNK % BATCH == 0, "a chunk is whole batches");  // (launched with BUCKET_GROUP threads)
+  __shared__ u64 slot[GROUP_SLOTS];
+  __shared__ u32 sh[2];
+  __shared__ u32 fill[2];
+  const int t = threadIdx.x;
+  const int64_t total = *total_p;
+  const int64_t c0 = (int64_t)blockIdx.x * GROUP_CHUNK;
+  if (c0 >= total) return;
+  for (int i = t; i < GROUP_SLOTS; i += BUCKET_GROUP) slot[i] = EMPTY64;
+  if (t < 2) fill[t] = 0;
+  auto put = [&](u64 key, int x) {
+    const u32 tag = (u32)(key >> 32);
+    const u64 want = (key & 0xFFFFFFFF00000000ULL) | (u64)(u32)x;
+    u32 s = (u32)(key >> GROUP_BITS) * 0x9E3779B1u >> 20;  // 12 bits: GROUP_SLOTS
+    while (true) {
+      u64 cur = slot[s];
+      if (cur == EMPTY64) {
+        // overflowed: nothing more goes in (free slots remain: at most one
+        // insertion per thread lands after the mark), the stretch is redone
+        if (fill[1]) return;
+        cur = atomicCAS(&slot[s], EMPTY64, want);
+        if (cur == EMPTY64) {
+          if (atomicAdd(&fill[0], 1u) + 1u >= (u32)(GROUP_SLOTS / 4 * 3)) fill[1] = 1u;
+          return;
+        }
+      }
+      if ((u32)(cur >> 32) == tag) {
+        cur = atomicMin(&slot[s], want);
+        if ((u32)cur < (u32)x) rep[x] = (int)(u32)cur;
+        else if ((u32)cur > (u32)x) rep[(u32)cur] = x;
+        return;
+      }
+      s = (s + 1) & (GROUP_SLOTS - 1);
+    }
+  };
+  // from the first bucket start in the chunk to the first one past it
+  int64_t b0 = -1, e = total;
+  for (int64_t at = c0;; at += BATCH) {
+    u64 k[U];
+    int v[U];
+    u32 edge = BATCH;  // first bucket start of the batch (the end counts as one)
+#pragma unroll
+    for (int j = 0; j < U; ++j) {
+      const int64_t i = at + j * BUCKET_GROUP + t;
+      k[j] = i < total ? keys[i] : 0ULL;
+      v[j] = i < total ? vals[i] : 0;
+    }
+#pragma unroll
+    for (int j = U - 1; j >= 0; --j) {
+      const int64_t i = at + j * BUCKET_GROUP + t;
+      if (i == 0 || i >= total || group_bucket(keys[i - 1]) != group_bucket(k[j])) edge = j * BUCKET_GROUP + t;
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) edge = min(edge, (u32)__shfl_xor(edge, o, WAVE));
+    __syncthreads();
+    if (t == 0) sh[0] = BATCH;
+    __syncthreads();
+    if ((t & (WAVE - 1)) == 0) atomicMin(&sh[0], edge);
+    __syncthreads();
+    edge = sh[0];
+    u32 lo = 0, hi = BATCH;
+    const bool past = at >= c0 + GROUP_CHUNK;
+    if (past) {
+      hi = edge;
+    } else if (b0 < 0) {
+      lo = edge;
+      if (edge < BATCH && at + edge < total) b0 = at + edge;
+    }
+#pragma unroll
+    for (int j = 0; j < U; ++j) {
+      const u32 p = (u32)(j * BUCKET_GROUP + t);
+      if (p >= lo && p < hi && at + p < total) put(k[j], v[j]);
+    }
+    if (past && edge < BATCH) {
+      e = at + edge;
+      break;
+    }
+    if (at + BATCH >= total) break;
+    if (b0 < 0 && at + BATCH >= c0 + GROUP_CHUNK) return;  // no bucket starts in this chunk
+  }
+  if (b0 < 0) return;
+  __syncthreads();
+  if (!fill[1]) return;
+  u32 Q = 2;
+  for (u32 q = 0; q < Q;) {
+    __syncthreads();
+    for (int i = t; i < GROUP_SLOTS; i += BUCKET_GROUP) slot[i] = EMPTY64;
+    if (t < 2) fill[t] = 0;
+    __syncthreads();
+    for (int64_t i = b0 + t; i < e; i += BUCKET_GROUP)
+      if ((sub_hash(keys[i]) & (Q - 1)) == q) put(keys[i], vals[i]);
+    __syncthreads();
+    if (!fill[1]) {
+      ++q;
+    } else if (Q < (1u << 24)) {
+      Q <<= 1;
+      q = 0;
+    } else {  // more distinct keys than a stretch has pairs; not reached
+      if (t == 0) atomicOr(err, ERR_VERIFY_OVERFLOW);
+      return;
+    }
+  }
 }
 
 // ---------------------------------------------------------------- lookup + exact check
+// 1 or 0: the rows of v and r hold the same pairs or not; -1: one of them has
+// more than SMALL_MAX entries.  r's pairs are kept in registers (static
+// indexing); every pair of v must occur among them, and every entry of r must
+// be met by some pair of v (set equality in both directions, so it does not
+// rest on the distinct counts).
+template <class Src>
+__device__ inline int same_small_rows(const Src &src, int v, int r) {
+  const int64_t bv = src.begin(v), ev = src.end(v);
+  const int64_t br = src.begin(r), er = src.end(r);
+  if (ev - bv > SMALL_MAX || er - br > SMALL_MAX) return -1;
+  u64 rp[SMALL_MAX];
+#pragma unroll
+  for (int j = 0; j < SMALL_MAX; ++j) rp[j] = br + j < er ? src.pair(br + j) : EMPTY64;
+  const u32 want = (u32)((1ull << (er - br)) - 1ull);
+  u32 met = 0;
+  bool ok = true;
+  for (int64_t j = bv; j < ev && ok; ++j) {
+    const u64 p = src.pair(j);
+    u32 hit = 0;
+#pragma unroll
+    for (int q = 0; q < SMALL_MAX; ++q) hit |= (rp[q] == p ? 1u : 0u) << q;
+    met |= hit;
+    ok = hit != 0;
+  }
+  return ok && met == want ? 1 : 0;
+}
+
+// From the vertex that spoke for v, if any, to the minimum of its key.  Links
+// only ever point on to that minimum (a collided vertex keeps its link, so that
+// others can walk over it; peeling gives it its representative).
+__device__ inline int key_minimum(const int *rep, int v) {
+  int r = rep[v];
+  for (int nx = rep[r]; nx != r; nx = rep[r]) r = nx;
+  return r;
+}
+
+// k_lookup's work after a partition, over the list of non-empty vertices: only
+// those whose representative is another vertex are looked at, RESOLVE_V per
+// thread, so that a wave of heads ends after two loads.
+constexpr int RESOLVE_V = 4;
+template <class Src>
+__global__ void __launch_bounds__(256) k_resolve(Src src, int count, const int *__restrict__ list,
+                                                 const u32 *__restrict__ DC, int *rep, int *vcount, int *vlist,
+                                                 int *ccount, int *clist) {
+  const int64_t i0 = ((int64_t)blockIdx.x * 256 + threadIdx.x) * RESOLVE_V;
+  int v[RESOLVE_V], c[RESOLVE_V];
+  if (i0 + RESOLVE_V <= count) {
+    const int4 l4 = *reinterpret_cast<const int4 *>(list + i0);
+    v[0] = l4.x; v[1] = l4.y; v[2] = l4.z; v[3] = l4.w;
+  } else {
+#pragma unroll
+    for (int j = 0; j < RESOLVE_V; ++j) v[j] = i0 + j < count ? list[i0 + j] : -1;
+  }
+  u32 pending = 0;
+#pragma unroll
+  for (int j = 0; j < RESOLVE_V; ++j) c[j] = v[j] >= 0 ? rep[v[j]] : -1;
+#pragma unroll
+  for (int j = 0; j < RESOLVE_V; ++j) pending |= (c[j] != v[j] ? 1u : 0u) << j;
+  while (pending) {
+    const int j = __ffs(pending) - 1;
+    pending &= pending - 1u;
+    const int x = j == 0 ? v[0] : j == 1 ? v[1] : j == 2 ? v[2] : v[3];
+    const int r = key_minimum(rep, x);
+    int eq = 0;
+    if (src.own(x) == src.own(r) && DC[x] == DC[r]) eq = same_small_rows(src, x, r);
+    if (eq != 0) rep[x] = r;
+    wave_append(vcount, vlist, eq < 0, x);
+    wave_append(ccount, clist, eq == 0, x);
+  }
+}
+
 // For each vertex: representative r = minimum vertex stored under its key.
 // r == v: v heads its block.  Otherwise v joins r's block once the keys are
 // shown equal exactly: the previous block, the number of distinct pairs and,
@@ -1284,38 +1741,11 @@ __global__ void __launch_bounds__(256) k_lookup(Src src, int count, const int *_
       } else if (dirty && !dirty[v] && !dirty[r] && mvc[v] == mvc[r]) {
         rep[v] = r;
       } else {
-        const int64_t bv = src.begin(v), ev = src.end(v);
-        const int64_t br = src.begin(r), er = src.end(r);
-        if (ev - bv <= SMALL_MAX && er - br <= SMALL_MAX) {
-          // small rows: r's pairs in registers (static indexing); every pair
-          // of v must occur among them, and every entry of r must be met by
-          // some pair of v (set equality in both directions, so it does not
-          // rest on the distinct counts)
-          u64 rp[SMALL_MAX];
-#pragma unroll
-          for (int j = 0; j < SMALL_MAX; ++j) rp[j] = br + j < er ? src.pair(br + j) : EMPTY64;
-          const u32 want = (u32)((1ull << (er - br)) - 1ull);
-          u32 met = 0;
-          bool ok = true;
-          for (int64_t j = bv; j < ev && ok; ++j) {
-            const u64 p = src.pair(j);
-            u32 hit = 0;
-#pragma unroll
-            for (int q = 0; q < SMALL_MAX; ++q) hit |= (rp[q] == p ? 1u : 0u) << q;
-            met |= hit;
-            ok = hit != 0;
-          }
-          ok = ok && met == want;
-          if (ok) {
-            rep[v] = r;
-          } else {
-            rep[v] = -1;
-            collided = true;
-          }
-        } else {
-          rep[v] = r;  // confirmed or rejected by k_verify
-          to_verify = true;
-        }
+        const int eq = same_small_rows(src, v, r);
+        if (eq != 0) rep[v] = r;  // (long rows: confirmed or rejected by k_verify)
+        else rep[v] = -1;
+        to_verify = eq < 0;
+        collided = eq == 0;
       }
     }
   }
@@ -1784,6 +2214,9 @@ __global__ void __launch_bounds__(256) k_scan_tiles64(int64_t ntiles, int64_t *t
 }
 
 // out_ptr[i] = sum of cnt[0..i), out_ptr[n] = total; cursor[i] = out_ptr[i] (cursor may be NULL).
+// SUMS (at most 256 tiles): tile_pre holds the tile sums, which every workgroup
+// adds up to its own tile, instead of a launch that scans them.
+template <bool SUMS>
 __global__ void __launch_bounds__(256) k_write_ptr64(int64_t n, const int *__restrict__ cnt,
                                                      const int64_t *__restrict__ tile_pre, int64_t *out_ptr,
                                                      unsigned long long *cursor) {
@@ -1794,8 +2227,10 @@ __global__ void __launch_bounds__(256) k_write_ptr64(int64_t n, const int *__res
   int64_t mine = 0;
 #pragma unroll
   for (int j = 0; j < SCAN_ITEMS; ++j) mine += c[j];
-  int64_t total;
-  int64_t off = tile_pre[blockIdx.x] + block_exclusive_scan64(mine, sh_w, &total);
+  int64_t total, before;
+  if constexpr (SUMS) block_exclusive_scan64(threadIdx.x < blockIdx.x ? tile_pre[threadIdx.x] : 0, sh_w, &before);
+  else before = tile_pre[blockIdx.x];
+  int64_t off = before + block_exclusive_scan64(mine, sh_w, &total);
   const bool vec = base + SCAN_ITEMS < n && ((reinterpret_cast<uintptr_t>(out_ptr) |
                                               reinterpret_cast<uintptr_t>(cursor)) & 15) == 0;
   if (vec) {
@@ -2174,15 +2609,6 @@ __global__ void __launch_bounds__(256) k_quotient_hubs(Src src, const Chunk *__r
 constexpr int RADIX_ITEMS = 16;  // keys per thread per tile
 constexpr int RADIX_THREADS = 512;
 constexpr int RADIX_TILE = RADIX_THREADS * RADIX_ITEMS;
-constexpr int XCDS = 8;  // workgroups go to the XCDs in turn
-// Tile of this workgroup (>= ntiles: none; grids are padded to a multiple of
-// XCDS): each XCD takes a contiguous share of the tiles in order, so that the
-// runs that neighbouring tiles write side by side meet in one L2 and leave it
-// as whole lines (9.25 -> 7.6 ms per summary graph of 125M entries).
-__device__ inline int64_t radix_tile(int64_t ntiles) {
-  return (int64_t)(blockIdx.x % XCDS) * ((ntiles + XCDS - 1) / XCDS) + blockIdx.x / XCDS;
-}
-
 // Digit histogram of each tile: hist[digit * ntiles + tile].
 template <class K>
 __global__ void __launch_bounds__(RADIX_THREADS) k_radix_hist(int64_t m, const K *__restrict__ keys, int shift, int64_t ntiles,
@@ -2715,7 +3141,7 @@ __global__ void __launch_bounds__(SCHED_THREADS) k_sched_chunks(const int64_t *_
         const int z = (int)close_at[s] + 1;
         ranges[at[0]++] = Range{z0 + s, z0 + z, (int)(end_of(z) - off[s]), 0, ptr[v]};
       } else {
-        const Range one{v, v + 1, (int)(end_of(s + 1) - off[s]), 0, ptr[v]};
+        const Range one{v, v + 1, (int)(end_of(s + 1) - off[s]), z0 + s, ptr[v]};
         if (list == 3) ranges[at[3]++] = one;
         else if (list == 2) ranges[at[2]++] = one;
         else ranges[at[1]++] = one;
@@ -3551,27 +3977,25 @@ __global__ void k_advance(u32 *dep, u32 mask) {
 constexpr int STEP_ROW = 16, STEP_EPOCHS = 8, STEP_SEGMENT = 14;
 __global__ void k_prepare_steps(u32 *dep, int *rows, int i0, int cnt, u32 *err, int reset_err) {
   const int t = threadIdx.x;
-  u32 e = dep[EP_TABLE], ec = dep[EP_CTABLE];
-  const u32 z = dep[EP_ZERO], hub = dep[EP_HUB];
-  const bool wrap = e + (u32)cnt > 15u, cwrap = ec + (u32)cnt > 15u;
+  u32 e = dep[EP_TABLE];
+  const u32 z = dep[EP_ZERO], hub = dep[EP_HUB], ec = dep[EP_CTABLE];
+  const bool wrap = e + (u32)cnt > 15u;
   if (wrap) e = 0;
-  if (cwrap) ec = 0;
   if (t < cnt) {
     int *row = rows + (int64_t)(i0 + t) * STEP_ROW;
     for (int j = 0; j < STEP_EPOCHS; ++j) row[j] = 0;
     u32 *d = reinterpret_cast<u32 *>(row) + STEP_EPOCHS;
     d[EP_TABLE] = e + (u32)t + 1u;
-    d[EP_CTABLE] = ec + (u32)t + 1u;
+    d[EP_CTABLE] = ec;  // (these steps do not use the peeling table)
     d[EP_ZERO] = z + (u32)t + 1u;
     d[EP_HUB] = hub;
   }
   __syncthreads();  // every thread has read dep
   if (t == 0) {
     dep[EP_TABLE] = e + (u32)cnt;
-    dep[EP_CTABLE] = ec + (u32)cnt;
     dep[EP_ZERO] = z + (u32)cnt;
     dep[EP_CLR_TABLE] = wrap;
-    dep[EP_CLR_CTABLE] = cwrap;
+    dep[EP_CLR_CTABLE] = 0;
     dep[EP_CLR_HUB] = 0;
     if (reset_err) *err = 0;
   }
