@@ -829,13 +829,30 @@ __global__ void __launch_bounds__(256) k_sig_range(Src src, const Range *__restr
     H[v] = h;
     DC[v] = c;
   }
-  // (the set is no longer read: its space holds the waves' key slots)
-  static_assert(sizeof(set) >= 4 * FIRST_SLOTS * sizeof(u32), "key slots of four waves");
-  int speaker;
-  const bool first = wave_first_of_key(reinterpret_cast<u32 *>(set) + w * FIRST_SLOTS, keyed, h, &speaker);
+  // (the set is no longer read: its space holds the key slots)
+  u32 *slots = reinterpret_cast<u32 *>(set);
   if (sink.table) {
-    if (first) table_insert(sink.table, sink.tmask, h, (u32)v, epoch);
+    // One insert per key of the workgroup, as wave_first_of_key: two barriers
+    // more than per wave, but a quarter of the device-wide atomics on keys that
+    // many vertices share (unlabelled graph of 1M vertices: 1.09 -> 1.00 ms per
+    // call; a 10k-vertex graph as before).
+    constexpr int NS = 4 * FIRST_SLOTS;
+    static_assert(sizeof(set) >= NS * sizeof(u32), "key slots of the workgroup");
+    if (keyed) acc[t] = h;
+#pragma unroll
+    for (int i = 0; i < NS / 256; ++i) slots[t + i * 256] = 0xFFFFFFFFu;
+    __syncthreads();
+    const u32 at = (u32)(h >> 20) & (NS - 1);
+    if (keyed) atomicMin(&slots[at], (u32)t);
+    __syncthreads();
+    if (keyed) {
+      const u32 m = slots[at];
+      if (m == (u32)t || acc[m] != h) table_insert(sink.table, sink.tmask, h, (u32)v, epoch);
+    }
   } else {
+    int speaker;
+    static_assert(sizeof(set) >= 4 * FIRST_SLOTS * sizeof(u32), "key slots of four waves");
+    const bool first = wave_first_of_key(slots + w * FIRST_SLOTS, keyed, h, &speaker);
     const int vs = __shfl(v, speaker, WAVE);
     if (keyed) {
       sink.rep[v] = vs;
