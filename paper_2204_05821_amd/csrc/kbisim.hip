@@ -425,7 +425,7 @@ int numbering_words(kbisim_ctx *c, int n, int64_t *count_dev, HeadIds *ids, int 
   return 0;
 }
 
-// Sort the entries of every row of the range and row tiers, and of every
+// Order the entries of every row of the range and row tiers, and of every
 // staged hub chunk, by target rank (results do not depend on the order
 // inside a row).  Separate edge labels move with their entries, in a copy
 // kept in the unused tail of the hub staging region; when the tail is too
@@ -449,12 +449,9 @@ int sort_rows_impl(kbisim_ctx *c, const Schedule &s, u32 *lab) {
     k_sort_rows<ROW_MAX, PAY><<<(unsigned)s.nrow8, 1024, 0, c->stream>>>(g, lab, rows + s.nbig, c->rbits);
     LAUNCH_CHECK();
   }
-  if constexpr (!PAY) {  // rows beyond 8192 entries (32-bit keys): no LDS room for the labels
-    if (s.nrow20) {
-      k_sort_rows<32768, false><<<(unsigned)s.nrow20, 1024, 0, c->stream>>>(g, nullptr, rows + s.nbig + s.nrow8,
-                                                                          c->rbits);
-      LAUNCH_CHECK();
-    }
+  if (s.nrow20) {
+    k_sort_rows<19 * 1024, PAY><<<(unsigned)s.nrow20, 1024, 0, c->stream>>>(g, lab, rows + s.nbig + s.nrow8, c->rbits);
+    LAUNCH_CHECK();
   }
   if (s.nchunks) {
     k_sort_hub_chunks<HUB_CHUNK_MAX, PAY><<<(unsigned)s.nchunks, 1024, 0, c->stream>>>(

@@ -22,7 +22,7 @@ def _tiers(deg, cap, row_max):
 
 @pytest.mark.parametrize("n", [1, 2, 255, 256, 257, CHUNK - 1, CHUNK, CHUNK + 1, 2 * CHUNK + 77])
 @pytest.mark.parametrize("key_bits", [0, 64])
-@pytest.mark.parametrize("form", ["sparse", "dense", "long"])
+@pytest.mark.parametrize("form", ["sparse", "dense", "long", "long_wide_labels"])
 def test_tiers_and_partitions(n, key_bits, form):
     import paper_2204_05821_amd as kb
     print(f"[schedule] n={n} keys={key_bits} {form}", flush=True)
@@ -31,7 +31,7 @@ def test_tiers_and_partitions(n, key_bits, form):
     deg = rng.integers(0, 3, n) if form != "dense" else rng.integers(0, 40, n)
     if form == "sparse":
         deg[: n // 2] = 0
-    if form == "long":
+    if form.startswith("long"):
         special = [cap, cap + 1, 4096, 4097, 8192, 8193, row_max, row_max + 1, cap, 1]
         at = [0, 1, 255, 256, n - 1, n - 2, CHUNK - 1, CHUNK, CHUNK - 2, CHUNK + 1]
         for v, d in zip(at, special):
@@ -40,6 +40,8 @@ def test_tiers_and_partitions(n, key_bits, form):
     src = np.repeat(np.arange(n), deg)
     dst = rng.integers(0, n, len(src))
     lab = rng.integers(0, 3, len(src))
+    if form == "long_wide_labels":  # labels in an array of their own, moved with the ordered entries
+        lab = np.array([0, 12_345, 2**31 - 1])[lab]
     sets = rng.integers(0, 3, n)
     vp = np.concatenate([[0], np.cumsum(sets)])
     g = graphgen.from_edges(n, src, dst, lab, rng.integers(0, 4, int(vp[-1])), vp)
