@@ -879,7 +879,7 @@ int launch_signatures(kbisim_ctx *c, const Src &src, const Schedule &s, bool zfr
   if constexpr (!Src::GRAPH) {
     if (!src.ptr) {  // one label per vertex
       ProfScope ps(c, KBISIM_K_SIG_RANGE);
-      k_sig_one<Src><<<blocks_for(c->g.n, 256), 256, 0, c->stream>>>(src, (int)c->g.n, c->H, c->DC, c->table, tmask,
+      k_sig_one<Src><<<blocks_for(c->g.n, ONE_VERTS), ONE_THREADS, 0, c->stream>>>(src, (int)c->g.n, c->H, c->DC, c->table, tmask,
                                                                     c->cur, c->hmask);
       LAUNCH_CHECK();
       return 0;

@@ -903,19 +903,43 @@ __global__ void __launch_bounds__(256) k_rep_empty(Src src, int n, const u32 *__
 }
 
 // Rows of exactly one item (P0 with one label per vertex): no set, no row
-// offsets, one vertex per thread.
+// offsets.  A workgroup inserts each key of its ONE_VERTS vertices once (they
+// meet in LDS as in wave_first_of_key): labels are few, and their slots were
+// where all waves queued (2M vertices, 32 labels: 180 -> 24 us).
+constexpr int ONE_THREADS = 1024, ONE_ITEMS = 4, ONE_VERTS = ONE_THREADS * ONE_ITEMS;
 template <class Src>
-__global__ void __launch_bounds__(256) k_sig_one(Src src, int n, u64 *__restrict__ H, u32 *__restrict__ DC, u64 *table,
-                                                 u64 tmask, const u32 *__restrict__ dep, u64 hmask) {
-  __shared__ u32 slots[4][FIRST_SLOTS];
-  const int v = blockIdx.x * 256 + threadIdx.x;
-  u64 h = 0;
-  if (v < n) {
-    h = finalize_key(mix_pair(src.pair(v)), 1u, src.own(v)) & hmask;
-    H[v] = h;
+__global__ void __launch_bounds__(ONE_THREADS) k_sig_one(Src src, int n, u64 *__restrict__ H, u32 *__restrict__ DC,
+                                                         u64 *table, u64 tmask, const u32 *__restrict__ dep,
+                                                         u64 hmask) {
+  constexpr int NS = 2 * ONE_VERTS;
+  __shared__ u64 key[ONE_VERTS];
+  __shared__ u32 slots[NS];
+  const u32 epoch = dep[EP_TABLE];
+  const int64_t v0 = (int64_t)blockIdx.x * ONE_VERTS;
+#pragma unroll
+  for (int j = 0; j < NS / ONE_THREADS; ++j) slots[threadIdx.x + j * ONE_THREADS] = 0xFFFFFFFFu;
+  __syncthreads();
+  u64 h[ONE_ITEMS];
+#pragma unroll
+  for (int j = 0; j < ONE_ITEMS; ++j) {
+    const int i = threadIdx.x + j * ONE_THREADS;
+    const int64_t v = v0 + i;
+    h[j] = 0;
+    if (v >= n) continue;
+    h[j] = finalize_key(mix_pair(src.pair(v)), 1u, src.own((int)v)) & hmask;
+    H[v] = h[j];
     DC[v] = 1u;
+    key[i] = h[j];
+    atomicMin(&slots[(u32)(h[j] >> 20) & (NS - 1)], (u32)i);
   }
-  if (wave_first_of_key(slots[threadIdx.x >> 6], v < n, h)) table_insert(table, tmask, h, (u32)v, dep[EP_TABLE]);
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < ONE_ITEMS; ++j) {
+    const int i = threadIdx.x + j * ONE_THREADS;
+    if (v0 + i >= n) continue;
+    const u32 m = slots[(u32)(h[j] >> 20) & (NS - 1)];
+    if (m == (u32)i || key[m] != h[j]) table_insert(table, tmask, h[j], (u32)(v0 + i), epoch);
+  }
 }
 
 // Row tier: one workgroup of NT threads per row of more entries than the
