@@ -2548,8 +2548,8 @@ int kbisim_transpose(int64_t n, int64_t m, const int64_t *row_ptr, const int32_t
 
 namespace {
 struct QuotientPlan {
-  size_t off_a, off_b, off_hist, off_offs, off_tiles, off_flag, off_pos, off_word, off_tgt, total;
-  int64_t rtiles, hist_n, htiles, mtiles;
+  size_t off_a, off_b, off_hist, off_offs, off_tiles, off_count, off_pos, off_word, off_tgt, total;
+  int64_t rtiles, hist_n, htiles, runs;
 };
 QuotientPlan quotient_plan(int64_t n, int64_t m) {
   QuotientPlan p{};
@@ -2563,14 +2563,14 @@ QuotientPlan quotient_plan(int64_t n, int64_t m) {
   p.rtiles = (M + RADIX_TILE - 1) / RADIX_TILE;
   p.hist_n = 256 * p.rtiles;
   p.htiles = (p.hist_n + SCAN_TILE - 1) / SCAN_TILE;
-  p.mtiles = (M + SCAN_TILE - 1) / SCAN_TILE;
+  p.runs = (M + RUN_TILE - 1) / RUN_TILE;  // at most hist_n: their scan fits the sort's tiles
   p.off_a = take(8 * (size_t)M);
   p.off_b = take(8 * (size_t)M);
   p.off_hist = take(4 * (size_t)p.hist_n);
   p.off_offs = take(8 * (size_t)(p.hist_n + 1));
-  p.off_tiles = take(8 * (size_t)std::max(p.htiles, p.mtiles));
-  p.off_flag = take(4 * (size_t)M);
-  p.off_pos = take(8 * (size_t)(M + 1));
+  p.off_tiles = take(8 * (size_t)p.htiles);
+  p.off_count = take(4 * (size_t)p.runs);
+  p.off_pos = take(8 * (size_t)(p.runs + 1));
   p.off_word = take(16);
   p.off_tgt = take(4 * (size_t)std::max<int64_t>(n, 1));
   p.total = at;
@@ -2624,7 +2624,7 @@ int kbisim_quotient(kbisim_ctx *c, const int32_t *src_pid, const int32_t *dst_pi
   u64 *ka = (u64 *)(w + p.off_a), *kb = (u64 *)(w + p.off_b);
   int *hist = (int *)(w + p.off_hist);
   int64_t *offs = (int64_t *)(w + p.off_offs), *tiles = (int64_t *)(w + p.off_tiles);
-  int *flag = (int *)(w + p.off_flag);
+  int *count = (int *)(w + p.off_count);
   int64_t *pos = (int64_t *)(w + p.off_pos);
   u32 *word = (u32 *)(w + p.off_word);  // [0] error bits, [1] max source id, [2] max target id
   int rc = 0;
@@ -2654,13 +2654,12 @@ int kbisim_quotient(kbisim_ctx *c, const int32_t *src_pid, const int32_t *dst_pi
                          tgt, q, ka);
   if (rc) return rc;
   if ((rc = radix_sort(s, m, ka, kb, 0, total_bits, p.rtiles, hist, tiles, offs))) return rc;
-  k_run_starts<<<(unsigned)std::min<int64_t>(blocks_for(m, 256), 65536), 256, 0, s>>>(m, ka, flag);
+  k_run_count<<<(unsigned)p.runs, 256, 0, s>>>(m, ka, count);
   HIP_TRY(hipGetLastError());
-  if ((rc = scan64(s, m, flag, tiles, pos))) return rc;
-  k_quotient_write<<<(unsigned)std::min<int64_t>(blocks_for(m, 256), 65536), 256, 0, s>>>(m, ka, flag, pos, q, out_src,
-                                                                                          out_label, out_dst);
+  if ((rc = scan64(s, p.runs, count, tiles, pos))) return rc;
+  k_quotient_write<<<(unsigned)p.runs, 256, 0, s>>>(m, ka, pos, q, out_src, out_label, out_dst);
   HIP_TRY(hipGetLastError());
-  HIP_TRY(hipMemcpyAsync(out_count, pos + m, 8, hipMemcpyDeviceToHost, s));
+  HIP_TRY(hipMemcpyAsync(out_count, pos + p.runs, 8, hipMemcpyDeviceToHost, s));
   HIP_TRY(hipStreamSynchronize(s));
   return KBISIM_OK;
 }

@@ -3354,23 +3354,69 @@ __global__ void k_rank_from_sorted(int64_t n, const u64 *__restrict__ sorted, co
   }
 }
 
-// flag[i] = 1 where a run of equal keys starts.
-__global__ void k_run_starts(int64_t m, const u64 *__restrict__ keys, int *__restrict__ flag) {
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < m; i += (int64_t)gridDim.x * blockDim.x)
-    flag[i] = (i == 0 || keys[i] != keys[i - 1]) ? 1 : 0;
+// The distinct keys of a sorted array: one kernel counts the run starts of each
+// tile, a scan of the tiles' counts gives each tile its place, and a second
+// kernel finds the same starts again and unpacks them (source block, label,
+// target block) there.  Bound by HBM: both read the keys once and nothing
+// else.  A flag per entry, scanned to a place per entry, moved 28 bytes more an
+// entry (125M entries, nearly all distinct: 1.54 ms; now 0.22 + 0.45).  A wave holds 1024 keys of consecutive positions, 64 at a
+// time, so its starts are ballots and the stores of consecutive starts meet.
+constexpr int RUN_ITEMS = 16;
+constexpr int RUN_TILE = 256 * RUN_ITEMS;
+
+// Bit `lane` of start[j]: key `lane` of the wave's row j starts a run.
+__device__ inline u32 run_starts(int64_t m, const u64 *__restrict__ keys, int64_t base, u64 *k, u64 *start) {
+  const int lane = threadIdx.x & 63;
+#pragma unroll
+  for (int j = 0; j < RUN_ITEMS; ++j) {
+    const int64_t i = base + j * 64 + lane;
+    k[j] = i < m ? keys[i] : 0ull;
+  }
+  u64 before = base > 0 && base < m ? keys[base - 1] : 0ull;  // the key left of the wave's row
+  u32 count = 0;
+#pragma unroll
+  for (int j = 0; j < RUN_ITEMS; ++j) {
+    const int64_t i = base + j * 64 + lane;
+    u64 left = __shfl_up(k[j], 1, WAVE);
+    if (lane == 0) left = before;
+    start[j] = __ballot(i < m && (i == 0 || left != k[j]));
+    before = __shfl(k[j], 63, WAVE);
+    count += (u32)__popcll(start[j]);
+  }
+  return count;
 }
 
-// Unpack the run starts into (source block, label, target block) at their rank.
-__global__ void k_quotient_write(int64_t m, const u64 *__restrict__ keys, const int *__restrict__ flag,
-                                 const int64_t *__restrict__ pos, QKey q, int32_t *out_src, int32_t *out_lab,
-                                 int32_t *out_dst) {
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < m; i += (int64_t)gridDim.x * blockDim.x) {
-    if (!flag[i]) continue;
-    const u64 k = keys[i];
-    const int64_t o = pos[i];
-    out_dst[o] = (int32_t)(k & ((1ULL << q.db) - 1ULL));
-    out_lab[o] = q.lb ? (int32_t)((k >> q.db) & ((1ULL << q.lb) - 1ULL)) : 0;
-    out_src[o] = (int32_t)(k >> (q.db + q.lb));
+__global__ void __launch_bounds__(256) k_run_count(int64_t m, const u64 *__restrict__ keys, int *__restrict__ count) {
+  __shared__ u32 sh[4];
+  const int w = threadIdx.x >> 6;
+  u64 k[RUN_ITEMS], start[RUN_ITEMS];
+  const u32 c = run_starts(m, keys, (int64_t)blockIdx.x * RUN_TILE + w * (RUN_TILE / 4), k, start);
+  if ((threadIdx.x & 63) == 0) sh[w] = c;
+  __syncthreads();
+  if (threadIdx.x == 0) count[blockIdx.x] = (int)(sh[0] + sh[1] + sh[2] + sh[3]);
+}
+
+__global__ void __launch_bounds__(256) k_quotient_write(int64_t m, const u64 *__restrict__ keys,
+                                                        const int64_t *__restrict__ pos, QKey q, int32_t *out_src,
+                                                        int32_t *out_lab, int32_t *out_dst) {
+  __shared__ u32 sh[4];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  u64 k[RUN_ITEMS], start[RUN_ITEMS];
+  const u32 c = run_starts(m, keys, (int64_t)blockIdx.x * RUN_TILE + w * (RUN_TILE / 4), k, start);
+  if (lane == 0) sh[w] = c;
+  __syncthreads();
+  int64_t at = pos[blockIdx.x];
+  for (int i = 0; i < w; ++i) at += sh[i];
+  const u64 below = (1ull << lane) - 1ull;
+#pragma unroll
+  for (int j = 0; j < RUN_ITEMS; ++j) {
+    if ((start[j] >> lane) & 1ull) {
+      const int64_t o = at + __popcll(start[j] & below);
+      out_dst[o] = (int32_t)(k[j] & ((1ULL << q.db) - 1ULL));
+      out_lab[o] = q.lb ? (int32_t)((k[j] >> q.db) & ((1ULL << q.lb) - 1ULL)) : 0;
+      out_src[o] = (int32_t)(k[j] >> (q.db + q.lb));
+    }
+    at += __popcll(start[j]);
   }
 }
 
