@@ -770,9 +770,24 @@ u64 table_mask(const kbisim_ctx *c) {
   return c->plan.tslots - 1;
 }
 
+// Up to two ranges per CU are taken by workgroups of 1024 threads: each is one
+// latency chain, which more threads shorten.  Random graphs of 8 edges a
+// vertex, 10 steps, 256 / 1024 threads: 39 ranges 403 / 338 us, 250 ranges
+// 523 / 469, 500 ranges 599 / 550; but 1000 ranges 721 / 750 and 2000 ranges
+// 1075 / 1120, where 1024 threads leave too few ranges in flight.
+constexpr int FEW_RANGES = 512, FEW_THREADS = 1024;
+
 template <class Src, class K, bool SKIP>
 int launch_range_kernel(kbisim_ctx *c, const Src &src, const Schedule &s, KeySink sink, const unsigned char *skip) {
   ProfScope ps(c, KBISIM_K_SIG_RANGE);
+  if constexpr (!SKIP) {
+    if (s.range_edges == 2048 && s.nranges <= FEW_RANGES) {
+      k_sig_range<Src, 2048, K, false, FEW_THREADS><<<(unsigned)s.nranges, FEW_THREADS, 0, c->stream>>>(
+          src, c->ranges, c->H, c->DC, sink, c->cur, c->hmask, c->nzv, c->nzrow, skip);
+      LAUNCH_CHECK();
+      return 0;
+    }
+  }
   if (s.range_edges == 1024)
     k_sig_range<Src, 1024, K, SKIP><<<(unsigned)s.nranges, 256, 0, c->stream>>>(
         src, c->ranges, c->H, c->DC, sink, c->cur, c->hmask, c->nzv, c->nzrow, skip);

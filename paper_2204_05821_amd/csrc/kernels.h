@@ -624,14 +624,18 @@ __device__ inline void block_reduce_2(u64 &acc, u32 &cnt, u64 *sh_acc, u32 *sh_c
 // SKIP (work-efficient mode): rows of vertices flagged in skip[] (singleton
 // blocks, which cannot split) are left out; the remaining rows are packed,
 // so their entries are gathered only after the owner scan.
-template <class Src, int EMAX, class K = u64, bool SKIP = false>
-__global__ void __launch_bounds__(256) k_sig_range(Src src, const Range *__restrict__ ranges, u64 *__restrict__ H,
+// NT: 256 threads keep the most ranges in flight where ranges are many; where
+// they are few (FEW_RANGES) the chip has room, and 1024 threads walk a range's
+// chain of loads, LDS passes and barriers with 2 entries a thread instead of 8.
+template <class Src, int EMAX, class K = u64, bool SKIP = false, int NT = 256>
+__global__ void __launch_bounds__(NT) k_sig_range(Src src, const Range *__restrict__ ranges, u64 *__restrict__ H,
                                                    u32 *__restrict__ DC, KeySink sink,
                                                    const u32 *__restrict__ dep, u64 hmask,
                                                    const int *__restrict__ nzv, const u32 *__restrict__ nzrow,
                                                    const unsigned char *__restrict__ skip) {
   typedef Keys<K> KO;
-  constexpr int U = EMAX / 256;
+  static_assert(NT >= RANGE_VERTS && (!SKIP || NT == 256), "a thread per vertex; the packing scan has four waves");
+  constexpr int U = EMAX / NT;
   const u32 epoch = dep[EP_TABLE];
   __shared__ K set[2 * EMAX];
   __shared__ u64 acc[RANGE_VERTS];
@@ -639,9 +643,9 @@ __global__ void __launch_bounds__(256) k_sig_range(Src src, const Range *__restr
   __shared__ int roff[RANGE_VERTS + 1];  // CSR row offsets, relative to the range
   __shared__ int coff[SKIP ? RANGE_VERTS + 1 : 1];  // packed offsets (skipped rows empty)
   __shared__ unsigned char owner[EMAX];
-  __shared__ u32 wmax[4];
-  __shared__ u64 sh_acc[4];
-  __shared__ u32 sh_cnt[4];
+  __shared__ u32 wmax[NT / WAVE];
+  __shared__ u64 sh_acc[NT / WAVE];
+  __shared__ u32 sh_cnt[NT / WAVE];
   const int t = threadIdx.x, lane = t & 63, w = t >> 6;
   const Range rg = ranges[blockIdx.x];
   const int V = rg.v1 - rg.v0;
@@ -654,24 +658,24 @@ __global__ void __launch_bounds__(256) k_sig_range(Src src, const Range *__restr
   const u32 b0 = t < V ? nzrow[rg.v0 + t] : 0u;
   const int v = t < V ? nzv[rg.v0 + t] : 0;
   u32 el[U], er[U];
-  if constexpr (!SKIP) src.template entries<U, 256>(eb, t, rg.ne, el, er);
+  if constexpr (!SKIP) src.template entries<U, NT>(eb, t, rg.ne, el, er);
   K pr[U];
   if constexpr (!SKIP) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const K p = KO::from(src, el[u], er[u]);
-      pr[u] = t + u * 256 < rg.ne ? p : KO::EMPTY;
+      pr[u] = t + u * NT < rg.ne ? p : KO::EMPTY;
     }
   }
   const u32 own_t = t < V ? src.own(v) : 0u;
   if (t < V) roff[t] = (int)(b0 - (u32)eb);
   if (t == 0) roff[V] = rg.ne;
-  for (int i = t; i < V; i += 256) {
+  for (int i = t; i < V; i += NT) {
     acc[i] = 0;
     cnt[i] = 0;
   }
   if (!single)
-    for (int i = t; i < EMAX; i += 256) owner[i] = 0;
+    for (int i = t; i < EMAX; i += NT) owner[i] = 0;
   __syncthreads();
   const int *off = roff;  // offsets that place entries and set regions
   bool skipped = false;   // this thread's vertex (t < V) is left out
@@ -686,15 +690,15 @@ __global__ void __launch_bounds__(256) k_sig_range(Src src, const Range *__restr
     off = coff;
   }
   const int E = off[V];
-  for (int i = t; i < 2 * E; i += 256) set[i] = KO::EMPTY;
+  for (int i = t; i < 2 * E; i += NT) set[i] = KO::EMPTY;
   // the row start of every non-empty vertex marks its index; a max-scan then
   // gives the owner of every entry
   if (!single)
-    for (int i = t; i < V; i += 256)
+    for (int i = t; i < V; i += NT)
       if (off[i + 1] > off[i]) owner[off[i]] = (unsigned char)i;
   __syncthreads();
   if (!single) {
-    constexpr int PER = EMAX / 256;
+    constexpr int PER = EMAX / NT;
     u32 run = 0;
     const int j0 = t * PER;
 #pragma unroll
@@ -723,7 +727,7 @@ __global__ void __launch_bounds__(256) k_sig_range(Src src, const Range *__restr
     if (E > 0) {
 #pragma unroll
       for (int u = 0; u < U; ++u) {
-        const int j = min(t + u * 256, E - 1);
+        const int j = min(t + u * NT, E - 1);
         const int lo = single ? 0 : owner[j];
         src.entry(eb + roff[lo] + (j - coff[lo]), l[u], r[u]);
       }
@@ -732,7 +736,7 @@ __global__ void __launch_bounds__(256) k_sig_range(Src src, const Range *__restr
     for (int u = 0; u < U; ++u) {
       K p = KO::EMPTY;
       if (E > 0) p = KO::from(src, l[u], r[u]);
-      pr[u] = t + u * 256 < E ? p : KO::EMPTY;
+      pr[u] = t + u * NT < E ? p : KO::EMPTY;
     }
   }
   if (single) {
@@ -764,7 +768,7 @@ __global__ void __launch_bounds__(256) k_sig_range(Src src, const Range *__restr
   }
 #pragma unroll
   for (int u = 0; u < U; ++u) {
-    const int j = t + u * 256;
+    const int j = t + u * NT;
     if (j < E) {
       const int lo = owner[j];
       const K p = pr[u];
@@ -820,7 +824,7 @@ __global__ void __launch_bounds__(256) k_sig_range(Src src, const Range *__restr
     }
   }
   __syncthreads();
-  // V <= RANGE_VERTS = blockDim: one vertex per thread.
+  // V <= RANGE_VERTS <= NT: one vertex per thread.
   const bool keyed = t < V && !skipped;
   u64 h = 0;
   if (keyed) {
@@ -840,7 +844,7 @@ __global__ void __launch_bounds__(256) k_sig_range(Src src, const Range *__restr
     static_assert(sizeof(set) >= NS * sizeof(u32), "key slots of the workgroup");
     if (keyed) acc[t] = h;
 #pragma unroll
-    for (int i = 0; i < NS / 256; ++i) slots[t + i * 256] = 0xFFFFFFFFu;
+    for (int i = 0; i < NS / NT; ++i) slots[t + i * NT] = 0xFFFFFFFFu;
     __syncthreads();
     const u32 at = (u32)(h >> 20) & (NS - 1);
     if (keyed) atomicMin(&slots[at], (u32)t);
@@ -851,7 +855,7 @@ __global__ void __launch_bounds__(256) k_sig_range(Src src, const Range *__restr
     }
   } else {
     int speaker;
-    static_assert(sizeof(set) >= 4 * FIRST_SLOTS * sizeof(u32), "key slots of four waves");
+    static_assert(sizeof(set) >= NT / WAVE * FIRST_SLOTS * sizeof(u32), "key slots of the waves");
     const bool first = wave_first_of_key(slots + w * FIRST_SLOTS, keyed, h, &speaker);
     const int vs = __shfl(v, speaker, WAVE);
     if (keyed) {
