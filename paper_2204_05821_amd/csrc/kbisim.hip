@@ -706,10 +706,10 @@ int in_degrees(kbisim_ctx *c, int *indeg) {
   return 0;
 }
 
-// Rank vertices by decreasing in-degree (ties by vertex id) and renumber the
+// Rank vertices by decreasing class of in-degree (ties by vertex id) and renumber the
 // targets of every CSR entry: gcol[e] = rank[col[e]].  Vertices no entry
 // names get rank -1: they are never gathered.  A stable LSD radix sort of
-// (in-degree key, vertex) on the device; the grouping tables serve as
+// (class key, vertex) on the device; the grouping tables serve as
 // scratch, so this runs before they are cleared.
 int build_rank(kbisim_ctx *c) {
   const int64_t n = c->g.n, m = c->g.m;
@@ -2061,7 +2061,7 @@ int create_impl(const kbisim_graph *g, int kmax, const kbisim_tuning *tuning, vo
     c->hashed = c->narrow && (c->tune.key_bits == 32 || pb + lb > 31);
   }
 
-  // Gather renumbering: rank vertices by decreasing in-degree (ties by id).
+  // Gather renumbering: rank vertices by decreasing in-degree class (ties by id).
   // Uses the grouping tables as scratch, before they are cleared below.
   if ((rc = build_rank(c))) return fail(rc);
   // Fresh state: tables start empty; empty-signature slots start above any entry.
