@@ -576,11 +576,17 @@ int sched_enqueue(kbisim_ctx *c, const int64_t *ptr, int range_edges, int64_t ro
   const int nch = (int)((n + SCHED_CHUNK_V - 1) / SCHED_CHUNK_V);
   int64_t *sums = reinterpret_cast<int64_t *>(c->vlist);
   int *cnt = reinterpret_cast<int *>(sums + 6 * (size_t)nch);
-  k_sched_chunks<false><<<(unsigned)nch, SCHED_THREADS, 0, c->stream>>>(ptr, n, nch, range_edges, row_max, cnt, sums,
-                                                                        totals, nullptr, nullptr, nullptr, nullptr);
-  k_sched_scan<<<1, 256, 0, c->stream>>>(nch, cnt, sums, totals);
-  k_sched_chunks<true><<<(unsigned)nch, SCHED_THREADS, 0, c->stream>>>(ptr, n, nch, range_edges, row_max, cnt, sums,
-                                                                       totals, c->ranges, c->lists, c->nzv, c->nzrow);
+  if (nch == 1) {
+    k_sched_chunks<SCHED_SINGLE><<<1, SCHED_THREADS, 0, c->stream>>>(ptr, n, 1, range_edges, row_max, nullptr, nullptr,
+                                                                     totals, c->ranges, c->lists, c->nzv, c->nzrow);
+    LAUNCH_CHECK();
+    return 0;
+  }
+  k_sched_chunks<SCHED_COUNT><<<(unsigned)nch, SCHED_THREADS, 0, c->stream>>>(
+      ptr, n, nch, range_edges, row_max, cnt, sums, nullptr, nullptr, nullptr, nullptr, nullptr);
+  k_sched_scan<<<1, SCHED_TOTALS * WAVE, 0, c->stream>>>(nch, cnt, sums, totals);
+  k_sched_chunks<SCHED_WRITE><<<(unsigned)nch, SCHED_THREADS, 0, c->stream>>>(
+      ptr, n, nch, range_edges, row_max, cnt, sums, totals, c->ranges, c->lists, c->nzv, c->nzrow);
   LAUNCH_CHECK();
   return 0;
 }

@@ -3114,11 +3114,15 @@ constexpr int SCHED_PER = SCHED_CHUNK_V / SCHED_THREADS;
 // Totals of a schedule, written by k_sched_scan: rows per list, then the sums.
 constexpr int SCHED_TOTALS = 11;
 
-template <bool WRITE>
+// A graph of one chunk needs no totals of other chunks: one launch does both
+// parts and leaves the totals itself (10k vertices: 30 us; the three launches
+// took 87).
+enum { SCHED_COUNT, SCHED_WRITE, SCHED_SINGLE };
+template <int FORM>
 __global__ void __launch_bounds__(SCHED_THREADS) k_sched_chunks(const int64_t *__restrict__ ptr, int64_t n,
                                                                 int nchunks, int range_edges, int64_t row_max,
                                                                 int *__restrict__ cnt, int64_t *__restrict__ sums,
-                                                                const int64_t *__restrict__ totals,
+                                                                int64_t *__restrict__ totals,
                                                                 Range *__restrict__ ranges, int *__restrict__ hubs,
                                                                 int *__restrict__ nzv, u32 *__restrict__ nzrow) {
   static_assert(SCHED_CHUNK_V <= 65536 && SCHED_PER == 16, "16-bit rows, one start bit per row of a thread");
@@ -3195,6 +3199,7 @@ __global__ void __launch_bounds__(SCHED_THREADS) k_sched_chunks(const int64_t *_
   int next_long = __shfl_down(nl, 1, WAVE);
   if (lane == WAVE - 1) next_long = R;
   for (int i = w + 1; i < SCHED_THREADS / WAVE; ++i) next_long = min(next_long, wl[i]);
+  int last = R;  // end (exclusive) of the range of the row after
   // end of row e - 1: the next non-empty row's start (rows between are empty)
   auto end_of = [&](int e) { return e < R ? off[e] : chunk_end; };
 #pragma unroll
@@ -3204,17 +3209,28 @@ __global__ void __launch_bounds__(SCHED_THREADS) k_sched_chunks(const int64_t *_
     if ((lmask >> j) & 1u) {
       next_long = s;
       close_at[s] = (unsigned short)s;
+      last = s;
       continue;
     }
     // largest e <= lim whose rows [s, e) fit (one row that is not long does);
-    // low words differ exactly, no long row being among them
-    int lo = s + 1, hi = min(s + RANGE_VERTS, next_long);
+    // low words differ exactly, no long row being among them.  It is no larger
+    // than the row after's and mostly a few rows less: looked for from there.
+    int lo = s + 1, hi = min(min(s + RANGE_VERTS, next_long), last);
+    for (int step = 1; lo < hi; step *= 2) {
+      const int at = max(hi - step + 1, lo);
+      if (end_of(at) - off[s] <= (u32)range_edges) {
+        lo = at;
+        break;
+      }
+      hi = at - 1;
+    }
     while (lo < hi) {
       const int mid = (lo + hi + 1) >> 1;
       if (end_of(mid) - off[s] <= (u32)range_edges) lo = mid;
       else hi = mid - 1;
     }
     close_at[s] = (unsigned short)(lo - 1);
+    last = lo;
   }
   __syncthreads();
   if (t == 0)
@@ -3233,7 +3249,7 @@ __global__ void __launch_bounds__(SCHED_THREADS) k_sched_chunks(const int64_t *_
 #pragma unroll
     for (int l = 0; l < 5; ++l) c[l] += list == l;
   }
-  if constexpr (!WRITE) {
+  if constexpr (FORM != SCHED_WRITE) {
 #pragma unroll
     for (int l = 0; l < 6; ++l) {
       const u32 x = wave_sum_u32(l < 5 ? (u32)c[l < 5 ? l : 0] : 0u);
@@ -3251,10 +3267,17 @@ __global__ void __launch_bounds__(SCHED_THREADS) k_sched_chunks(const int64_t *_
         if (t < 5) x += wcnt[t][i];
         y += wsum[t][i];
       }
-      if (t < 5) cnt[(int64_t)t * nchunks + ci] = x;
-      sums[(int64_t)t * nchunks + ci] = y;
+      if constexpr (FORM == SCHED_COUNT) {
+        if (t < 5) cnt[(int64_t)t * nchunks + ci] = x;
+        sums[(int64_t)t * nchunks + ci] = y;
+      } else {
+        if (t < 5) totals[t] = x;
+        totals[5 + t] = y;
+      }
     }
-  } else {
+    __syncthreads();  // wcnt is written again below
+  }
+  if constexpr (FORM != SCHED_COUNT) {
     // exclusive positions inside the chunk, per list
     int at[5];
 #pragma unroll
@@ -3273,14 +3296,21 @@ __global__ void __launch_bounds__(SCHED_THREADS) k_sched_chunks(const int64_t *_
     int64_t base = 0;
 #pragma unroll
     for (int l = 0; l < 5; ++l) {
-      for (int i = 0; i < w; ++i) at[l] += wcnt[l][i];
-      at[l] += cnt[(int64_t)l * nchunks + ci];
+      int64_t whole = 0;  // rows of the list in all chunks
+      for (int i = 0; i < SCHED_THREADS / WAVE; ++i) {
+        if (i < w) at[l] += wcnt[l][i];
+        whole += wcnt[l][i];
+      }
+      if constexpr (FORM == SCHED_WRITE) {
+        at[l] += cnt[(int64_t)l * nchunks + ci];
+        whole = totals[l];
+      }
       if (l < 4) {
         at[l] += (int)base;
-        base += totals[l];
+        base += whole;
       }
     }
-    const int z0 = (int)sums[(int64_t)4 * nchunks + ci];
+    const int z0 = FORM == SCHED_WRITE ? (int)sums[(int64_t)4 * nchunks + ci] : 0;
     for (int i = t; i < R; i += SCHED_THREADS) {
       nzv[z0 + i] = (int)(v0 + row[i]);
       nzrow[z0 + i] = off[i];
@@ -3305,27 +3335,31 @@ __global__ void __launch_bounds__(SCHED_THREADS) k_sched_chunks(const int64_t *_
   }
 }
 
-// One workgroup: in-place exclusive scan of every list's chunk counts and of
-// the non-empty rows (sums[4]), and the totals of all.
-__global__ void __launch_bounds__(256) k_sched_scan(int nchunks, int *__restrict__ cnt, int64_t *__restrict__ sums,
-                                                    int64_t *__restrict__ totals) {
-  __shared__ int64_t sh_w[4];
-  for (int l = 0; l < SCHED_TOTALS; ++l) {
-    int64_t carry = 0;
-    for (int b0 = 0; b0 < nchunks; b0 += 256) {
-      const int i = b0 + threadIdx.x;
-      const int64_t at = (int64_t)(l < 5 ? l : l - 5) * nchunks + i;
-      const int64_t mine = i < nchunks ? (l < 5 ? (int64_t)cnt[at] : sums[at]) : 0;
-      int64_t total;
-      const int64_t ex = carry + block_exclusive_scan64(mine, sh_w, &total);
-      if (i < nchunks) {
-        if (l < 5) cnt[at] = (int)ex;
-        else if (l == 9) sums[at] = ex;
-      }
-      carry += total;
+// One workgroup, a wave per list: in-place exclusive scan of the list's chunk
+// counts and of the non-empty rows (sums[4]), and the totals of all.  (One
+// list after another by the whole workgroup: 9.6 us for a single chunk.)
+__global__ void __launch_bounds__(SCHED_TOTALS *WAVE) k_sched_scan(int nchunks, int *__restrict__ cnt,
+                                                                   int64_t *__restrict__ sums,
+                                                                   int64_t *__restrict__ totals) {
+  const int l = threadIdx.x >> 6, lane = threadIdx.x & (WAVE - 1);
+  int64_t carry = 0;
+  for (int b0 = 0; b0 < nchunks; b0 += WAVE) {
+    const int i = b0 + lane;
+    const int64_t at = (int64_t)(l < 5 ? l : l - 5) * nchunks + i;
+    const int64_t mine = i < nchunks ? (l < 5 ? (int64_t)cnt[at] : sums[at]) : 0;
+    int64_t x = mine;
+#pragma unroll
+    for (int o = 1; o < WAVE; o <<= 1) {
+      const int64_t y = __shfl_up(x, o, WAVE);
+      if (lane >= o) x += y;
     }
-    if (threadIdx.x == 0) totals[l] = carry;
+    if (i < nchunks) {
+      if (l < 5) cnt[at] = (int)(carry + x - mine);
+      else if (l == 9) sums[at] = carry + x - mine;
+    }
+    carry += __shfl(x, WAVE - 1, WAVE);
   }
+  if (lane == 0) totals[l] = carry;
 }
 
 // x on a logarithmic scale: 0 .. 15 exactly, then 8 classes an octave.
