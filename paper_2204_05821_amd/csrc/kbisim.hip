@@ -1044,7 +1044,7 @@ int settle_collisions(kbisim_ctx *c, const Src &src, const Schedule &s, int *cnt
 template <class Src>
 int run_step(kbisim_ctx *c, const Src &src, const Schedule &s, int *out, int64_t *count_dev, int *cnt,
              bool careful, int *gpid_next, bool zfresh, const unsigned char *skip_in = nullptr,
-             unsigned char *single_out = nullptr, int32_t *names_out = nullptr) {
+             unsigned char *single_out = nullptr, int32_t *names_out = nullptr, int *local_out = nullptr) {
   const int n = (int)c->g.n;
   if (n == 0) return 0;
   const u64 tmask = table_mask<Src>(c);
@@ -1094,11 +1094,11 @@ int run_step(kbisim_ctx *c, const Src &src, const Schedule &s, int *out, int64_t
       const unsigned ag = blocks_for((n + ASSIGN_V - 1) / ASSIGN_V, 256);
       const int *rank = gpid_next ? c->rank : nullptr;
       u32 *multi = single_out ? c->multi : nullptr;
-      if (scan_tiles)
-        k_assign<true><<<ag, 256, 0, c->stream>>>(n, c->rep, ids, out, rank, gpid_next, multi, c->cur, scan_tiles,
-                                                  count_dev);
-      else
-        k_assign<false><<<ag, 256, 0, c->stream>>>(n, c->rep, ids, out, rank, gpid_next, multi, c->cur, 0, nullptr);
+      const LocalIds loc{c->gid, c->first, local_out};
+      auto *assign = scan_tiles ? (local_out ? k_assign<true, true> : k_assign<true, false>)
+                                : (local_out ? k_assign<false, true> : k_assign<false, false>);
+      assign<<<ag, 256, 0, c->stream>>>(n, c->rep, ids, out, rank, gpid_next, multi, c->cur, scan_tiles, count_dev,
+                                        loc);
     }
     LAUNCH_CHECK();
     if (single_out) {
@@ -1161,7 +1161,7 @@ int enqueue_steps(kbisim_ctx *c, const int32_t *prev, int i0, int k, int32_t *co
     int32_t *names_out = cache ? c->is.MVc + (size_t)i * (size_t)n : nullptr;
     auto step = [&](auto src) {
       return run_step(c, src, c->sched, dst, &c->dcounts[i], c->counters + CNT_STRIDE * i, careful,
-                      c->gpid[(i + 1) & 1], i == 0, skip_in, single_out, names_out);
+                      c->gpid[(i + 1) & 1], i == 0, skip_in, single_out, names_out, batch ? out[i] : nullptr);
     };
     const int32_t *lab = separate_labels(c) ? sep_labels(c) : nullptr;
     if (c->hashed) {
@@ -1176,8 +1176,6 @@ int enqueue_steps(kbisim_ctx *c, const int32_t *prev, int i0, int k, int32_t *co
     }
     if (rc) return rc;
     if (batch) {
-      k_rebase<<<blocks_for(n, 256), 256, 0, c->stream>>>(n, c->gid, c->first, dst, out[i]);
-      LAUNCH_CHECK();
       k_batch_counts<<<blocks_for(c->num_graphs, 256), 256, 0, c->stream>>>((int)c->num_graphs, c->first, c->next,
                                                                             dst, &c->dcounts[i], cstride, i, c->bcounts);
       LAUNCH_CHECK();
