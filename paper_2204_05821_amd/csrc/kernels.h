@@ -12,9 +12,11 @@
 //               workgroup of its own, and hub rows are split into chunks that
 //               are deduplicated in two passes (chunk, then partition), or,
 //               beyond 4M entries, through a global hash set.
-//   group       every vertex inserts (key hash, v) into an open-addressing
-//               table that keeps the minimum vertex per key; a lookup gives
-//               each vertex its candidate representative.
+//   group       the minimum vertex per key hash becomes the candidate
+//               representative of its vertices.  Few vertices insert (key
+//               hash, v) into an open-addressing table and look theirs up;
+//               many are partitioned by key hash into buckets that one
+//               workgroup groups in LDS.
 //   exact check every vertex whose representative is another vertex is
 //               compared with it exactly: same previous block, same number of
 //               distinct pairs, and every pair of v present in the
