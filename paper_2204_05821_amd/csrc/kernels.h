@@ -144,9 +144,12 @@ struct KeySink {
 // 32-bit set key of a pair (label l, reduced block b).  When every edge label
 // and reduced block id fit together in 31 bits it is exact: fmix32 is one to
 // one, and the one word it takes to 0xFFFFFFFF, the empty marker (0x331DA083),
-// has the top bit clear, which is set here.  Otherwise (HK) it is a 32-bit hash of the pair.  Deduplicating and
-// summing hashed keys gives a function of the signature (equal pair sets give
-// equal key sets), so equal signatures still get equal key hashes; the
+// has the top bit clear, which is set here.  Otherwise (HK) it is a 32-bit hash
+// of the pair, the label spread over the whole word by an odd multiplier: with
+// the label merely rotated above the block, common labels met common blocks
+// past 2^22 often enough that a graph of 2^28 vertices left more collided
+// vertices than a step settles.  Deduplicating and summing hashed keys gives a
+// function of the signature (equal pair sets give equal key sets), so equal signatures still get equal key hashes; the
 // distinct count is then the number of distinct keys, and the exact check
 // compares pair sets in both directions (a key collision inside a row could
 // otherwise make a proper subset look equal).  kmask: the bits kept of hashed
@@ -154,7 +157,7 @@ struct KeySink {
 template <bool HK>
 __device__ inline u32 narrow_key(u32 l, u32 b, u32 pb, u32 kmask) {
   if constexpr (HK) {
-    const u32 k = fmix32(b ^ ((l << 22) | (l >> 10))) & kmask;
+    const u32 k = fmix32(b ^ (l * 0x9E3779B1u)) & kmask;
     return k == 0xFFFFFFFFu ? 0xFFFFFFFEu : k;
   } else {
     return fmix32(0x80000000u | (l << pb) | b);
@@ -1952,8 +1955,9 @@ __global__ void __launch_bounds__(256) k_res_verify(Src src, const int *__restri
 // few (the tags and home slots of 10^8 keys leave a handful), so the minimum
 // vertex of each hash is found by comparing all pairs in LDS.  More than
 // PEEL_MAX of them are passed on whole; the host then redoes the step with
-// k_res_insert and k_res_verify rounds over the whole grid.
-constexpr int PEEL_MAX = 512;
+// k_res_insert and k_res_verify rounds over the whole grid, which costs a call
+// on a large graph as much again, against a few us per collided vertex here.
+constexpr int PEEL_MAX = 4096;
 template <class Src>
 __global__ void __launch_bounds__(256) k_peel_few(Src src, const int *__restrict__ count, const int *__restrict__ list,
                                                   const u64 *__restrict__ H, const u32 *__restrict__ DC,
@@ -1968,16 +1972,23 @@ __global__ void __launch_bounds__(256) k_peel_few(Src src, const int *__restrict
   __shared__ u64 set[BLOCK_SLOTS];
   __shared__ int sh_flag[2];
   __shared__ int vs[PEEL_MAX];
+  __shared__ int first[PEEL_MAX];  // smallest vertex with the hash
   __shared__ u64 hs[PEEL_MAX];
   for (int i = threadIdx.x; i < total; i += 256) {
     vs[i] = list[i];
     hs[i] = H[vs[i]];
   }
   __syncthreads();
+  for (int item = threadIdx.x; item < total; item += 256) {
+    const u64 h = hs[item];
+    int r = vs[item];
+    for (int i = 0; i < total; ++i) r = hs[i] == h ? min(r, vs[i]) : r;
+    first[item] = r;
+  }
+  __syncthreads();
   for (int item = 0; item < total; ++item) {
     const int v = vs[item];
-    int r = v;
-    for (int i = 0; i < total; ++i) r = hs[i] == hs[item] ? min(r, vs[i]) : r;
+    const int r = first[item];
     bool ok;
     if (r == v) ok = true;
     else if (src.own(v) != src.own(r) || DC[v] != DC[r]) ok = false;
