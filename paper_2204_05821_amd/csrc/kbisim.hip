@@ -162,6 +162,7 @@ struct Tuning {
   int hub_parts_cap = HUB_PMAX;  // most partitions per staged hub (a smaller cap is a test knob)
   int scan_items = SCAN_ITEMS;   // vertices per thread in the numbering scan: 8 or 16
   int64_t group_min = GROUP_MIN;  // non-empty rows from which full steps group by partition
+  u32 group_mask = GROUP_MASK;    // bits of the hash that choose a bucket there (fewer: a test knob)
   int gfilter_min = GFILTER_MIN_DIRTY;  // dirty vertices from which update steps use the global filter
 };
 
@@ -978,15 +979,16 @@ int group_by_partition(kbisim_ctx *c, const Schedule &s) {
   const unsigned grid = radix_grid(nt);
   int rc = 0;
   c->table_dirty = true;
-  k_group_hist<true><<<grid, GROUP_THREADS, 0, st>>>(N, nullptr, s.nzv, c->rep, ka, 0, nt, hist);
+  const u32 mask = c->tune.group_mask;
+  k_group_hist<true><<<grid, GROUP_THREADS, 0, st>>>(N, nullptr, s.nzv, c->rep, ka, mask, 0, nt, hist);
   LAUNCH_CHECK();
   if ((rc = scan64(st, hist_n, hist, tiles, offs[0]))) return rc;
-  k_group_scatter<true><<<grid, GROUP_THREADS, 0, st>>>(N, nullptr, ka, s.nzv, 0, nt, offs[0], kb, vb);
-  k_group_hist<false><<<grid, GROUP_THREADS, 0, st>>>(N, total, nullptr, nullptr, kb, 8, nt, hist);
+  k_group_scatter<true><<<grid, GROUP_THREADS, 0, st>>>(N, nullptr, ka, s.nzv, mask, 0, nt, offs[0], kb, vb);
+  k_group_hist<false><<<grid, GROUP_THREADS, 0, st>>>(N, total, nullptr, nullptr, kb, mask, 8, nt, hist);
   LAUNCH_CHECK();
   if ((rc = scan64(st, hist_n, hist, tiles, offs[1]))) return rc;
-  k_group_scatter<false><<<grid, GROUP_THREADS, 0, st>>>(N, total, kb, vb, 8, nt, offs[1], ka, va);
-  k_group_buckets<<<blocks_for(N, GROUP_CHUNK), BUCKET_GROUP, 0, st>>>(total, ka, va, c->rep, c->err);
+  k_group_scatter<false><<<grid, GROUP_THREADS, 0, st>>>(N, total, kb, vb, mask, 8, nt, offs[1], ka, va);
+  k_group_buckets<<<blocks_for(N, GROUP_CHUNK), BUCKET_GROUP, 0, st>>>(total, ka, va, mask, c->rep, c->err);
   LAUNCH_CHECK();
   return 0;
 }
@@ -1981,6 +1983,13 @@ int create_impl(const kbisim_graph *g, int kmax, const kbisim_tuning *tuning, vo
   if (qdbg && *qdbg) {
     const long q = atol(qdbg);
     if (q >= 1) c->tune.group_min = q;
+  }
+  // Test knob: only this many bucket bits, so that small graphs have buckets
+  // of more keys than a workgroup's set holds and take its sub-passes.
+  const char *bdbg = getenv("KBISIM_DEBUG_GROUP_BITS");
+  if (bdbg && *bdbg) {
+    const int b = atoi(bdbg);
+    if (b >= 0 && b < GROUP_BITS) c->tune.group_mask = (1u << b) - 1u;
   }
   // Test knob: update steps use the global dirty-key filter from this many
   // dirty vertices on (at least 1), so that small graphs take that path.

@@ -316,6 +316,19 @@ __device__ inline void load_keys(const Src &src, int64_t first, int t, int count
   }
 }
 
+// ---------------------------------------------------------------- LDS set overflow
+// The overflow mark of an LDS set, set by the insertion that reaches the set's
+// limit and read by all threads between their insertions.  Atomic accesses: a
+// plain read is the compiler's to keep in a register over a whole loop without
+// barriers, where the marks of other threads then go unseen, the set fills up
+// and its probes never end.
+__device__ inline bool set_full(const u32 *mark) {
+  return __hip_atomic_load(mark, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) != 0u;
+}
+__device__ inline void mark_full(u32 *mark) {
+  __hip_atomic_store(mark, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
 // ---------------------------------------------------------------- wave helpers
 __device__ inline u64 sink_form(u64 h) { return h == EMPTY64 ? EMPTY64 - 1ULL : h; }
 __device__ inline void sink_key(const KeySink &s, int row, int v, u64 h) {
@@ -1187,6 +1200,10 @@ __global__ void __launch_bounds__(256) k_hub_reduce(Src src, const HubPart *__re
     u64 pacc = 0;
     u32 pcnt = 0;
     for (int t0 = 0; t0 < T; t0 += 4 * 256) {
+      // One read per batch: the barrier after each batch shows the marks of the
+      // one before, and an unmarked set has room for a whole batch beyond 3/4.
+      static_assert(PS / 4 * 3 - 1 + 4 * 256 < PS, "an empty slot ends every probe");
+      const bool full = set_full(&sh_fill[1]);
       K pr[4];
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
@@ -1211,15 +1228,13 @@ __global__ void __launch_bounds__(256) k_hub_reduce(Src src, const HubPart *__re
           const K cur = set[sl];
           if (cur == p) break;
           if (cur == KO::EMPTY) {
-            // once the pass has overflowed nothing more is inserted (it is redone);
-            // at most one insertion per thread lands after the 3/4 mark, so empty
-            // slots remain and every probe sequence ends
-            if (sh_fill[1]) break;
+            // once the pass has overflowed nothing more is inserted (it is redone)
+            if (full) break;
             const K old = atomicCAS(&set[sl], KO::EMPTY, p);
             if (old == KO::EMPTY) {
               pacc += KO::mix(p);
               ++pcnt;
-              if (atomicAdd(&sh_fill[0], 1u) + 1u >= (u32)(PS / 4 * 3)) sh_fill[1] = 1u;
+              if (atomicAdd(&sh_fill[0], 1u) + 1u >= (u32)(PS / 4 * 3)) mark_full(&sh_fill[1]);
               break;
             }
             if (old == p) break;
@@ -1365,9 +1380,11 @@ constexpr int GROUP_THREADS = 512, GROUP_ITEMS = 8;
 constexpr int GROUP_TILE = GROUP_THREADS * GROUP_ITEMS;  // pairs per radix tile
 static_assert(GROUP_TILE == 4096, "12-bit slots");
 constexpr int GROUP_BITS = 16;                           // bucket bits, the low ones of H
+constexpr u32 GROUP_MASK = (1u << GROUP_BITS) - 1u;      // (the kernels take the mask: a test keeps fewer)
 constexpr int GROUP_CHUNK = 2048;  // pairs per workgroup of k_group_buckets, extended to whole buckets
 constexpr int GROUP_SLOTS = 4096;  // LDS table slots (48 KB with the minima)
-__device__ inline u32 group_bucket(u64 h) { return (u32)h & ((1u << GROUP_BITS) - 1u); }
+// Digit of a pass: 8 bits of the bucket.
+__device__ inline u32 group_digit(u64 h, u32 mask, int shift) { return ((u32)h & mask) >> shift & 255u; }
 
 // Pair `at` of a pass: with FIRST a key of the signature kernels (EMPTY64: none)
 // and, with vals (the list of non-empty vertices), its vertex; else one of the
@@ -1389,7 +1406,8 @@ __device__ inline void group_load(int64_t at, int64_t count, const u64 *__restri
 template <bool FIRST>
 __global__ void __launch_bounds__(GROUP_THREADS) k_group_hist(int64_t count, const int64_t *__restrict__ total,
                                                               const int *__restrict__ list, int *rep, u64 *keys,
-                                                              int shift, int64_t ntiles, int *__restrict__ hist) {
+                                                              u32 mask, int shift, int64_t ntiles,
+                                                              int *__restrict__ hist) {
   __shared__ int h[256];
   __shared__ u64 slot[FIRST ? GROUP_TILE : 1];
   __shared__ u32 mins[FIRST ? GROUP_TILE : 1];
@@ -1408,7 +1426,7 @@ __global__ void __launch_bounds__(GROUP_THREADS) k_group_hist(int64_t count, con
   }
 #pragma unroll
   for (int j = 0; j < GROUP_ITEMS; ++j)
-    if (valid[j]) atomicAdd(&h[(u32)(key[j] >> shift) & 255u], 1);
+    if (valid[j]) atomicAdd(&h[group_digit(key[j], mask, shift)], 1);
   __syncthreads();
   if constexpr (FIRST) {
     if (__syncthreads_or(threadIdx.x < 256 && h[threadIdx.x] > GROUP_TILE / 8)) {
@@ -1440,7 +1458,7 @@ __global__ void __launch_bounds__(GROUP_THREADS) k_group_hist(int64_t count, con
         if (first != v[j]) {
           rep[v[j]] = first;
           keys[i0 + j * GROUP_THREADS] = EMPTY64;
-          atomicSub(&h[(u32)(key[j] >> shift) & 255u], 1);
+          atomicSub(&h[group_digit(key[j], mask, shift)], 1);
         }
       }
       __syncthreads();
@@ -1453,7 +1471,7 @@ __global__ void __launch_bounds__(GROUP_THREADS) k_group_hist(int64_t count, con
 template <bool FIRST>
 __global__ void __launch_bounds__(GROUP_THREADS) k_group_scatter(int64_t count, const int64_t *__restrict__ total,
                                                                  const u64 *__restrict__ keys,
-                                                                 const int *__restrict__ vals, int shift,
+                                                                 const int *__restrict__ vals, u32 mask, int shift,
                                                                  int64_t ntiles, const int64_t *__restrict__ offs,
                                                                  u64 *__restrict__ out_keys,
                                                                  int *__restrict__ out_vals) {
@@ -1484,7 +1502,7 @@ __global__ void __launch_bounds__(GROUP_THREADS) k_group_scatter(int64_t count, 
   int rank[GROUP_ITEMS];
 #pragma unroll
   for (int j = 0; j < GROUP_ITEMS; ++j) {
-    const u32 d = (u32)(key[j] >> shift) & 255u;
+    const u32 d = group_digit(key[j], mask, shift);
     u64 peers = __ballot(valid[j]);
 #pragma unroll
     for (int b = 0; b < 8; ++b) {
@@ -1529,7 +1547,7 @@ __global__ void __launch_bounds__(GROUP_THREADS) k_group_scatter(int64_t count, 
 #pragma unroll
   for (int j = 0; j < GROUP_ITEMS; ++j) {
     if (!valid[j]) continue;
-    const int at = wcnt[w][(u32)(key[j] >> shift) & 255u] + rank[j];
+    const int at = wcnt[w][group_digit(key[j], mask, shift)] + rank[j];
     sk[at] = key[j];
     sv[at] = val[j];
   }
@@ -1540,7 +1558,7 @@ __global__ void __launch_bounds__(GROUP_THREADS) k_group_scatter(int64_t count, 
     const int i = j * GROUP_THREADS + t;
     if (i < n) {
       const u64 k = sk[i];
-      const int64_t o = gpos[(u32)(k >> shift) & 255u] + i;
+      const int64_t o = gpos[group_digit(k, mask, shift)] + i;
       out_keys[o] = k;
       out_vals[o] = sv[i];
     }
@@ -1560,9 +1578,10 @@ __global__ void __launch_bounds__(GROUP_THREADS) k_group_scatter(int64_t count, 
 constexpr int BUCKET_GROUP = 512;
 __global__ void __launch_bounds__(BUCKET_GROUP) k_group_buckets(const int64_t *__restrict__ total_p,
                                                        const u64 *__restrict__ keys, const int *__restrict__ vals,
-                                                       int *__restrict__ rep, u32 *err) {
+                                                       u32 mask, int *__restrict__ rep, u32 *err) {
   constexpr int U = 4, BATCH = BUCKET_GROUP * U;
   static_assert(GROUP_CHUNK % BATCH == 0, "a chunk is whole batches");  // (launched with BUCKET_GROUP threads)
+  static_assert(GROUP_SLOTS / 4 > BUCKET_GROUP, "an empty slot ends every probe");
   __shared__ u64 slot[GROUP_SLOTS];
   __shared__ u32 sh[2];
   __shared__ u32 fill[2];
@@ -1576,15 +1595,16 @@ __global__ void __launch_bounds__(BUCKET_GROUP) k_group_buckets(const int64_t *_
     const u32 tag = (u32)(key >> 32);
     const u64 want = (key & 0xFFFFFFFF00000000ULL) | (u64)(u32)x;
     u32 s = (u32)(key >> GROUP_BITS) * 0x9E3779B1u >> 20;  // 12 bits: GROUP_SLOTS
+    const bool full = set_full(&fill[1]);
     while (true) {
       u64 cur = slot[s];
       if (cur == EMPTY64) {
-        // overflowed: nothing more goes in (free slots remain: at most one
-        // insertion per thread lands after the mark), the stretch is redone
-        if (fill[1]) return;
+        // overflowed: nothing more goes in, the stretch is redone (free slots
+        // remain: at most one insertion per thread lands after the mark)
+        if (full) return;
         cur = atomicCAS(&slot[s], EMPTY64, want);
         if (cur == EMPTY64) {
-          if (atomicAdd(&fill[0], 1u) + 1u >= (u32)(GROUP_SLOTS / 4 * 3)) fill[1] = 1u;
+          if (atomicAdd(&fill[0], 1u) + 1u >= (u32)(GROUP_SLOTS / 4 * 3)) mark_full(&fill[1]);
           return;
         }
       }
@@ -1612,7 +1632,7 @@ __global__ void __launch_bounds__(BUCKET_GROUP) k_group_buckets(const int64_t *_
 #pragma unroll
     for (int j = U - 1; j >= 0; --j) {
       const int64_t i = at + j * BUCKET_GROUP + t;
-      if (i == 0 || i >= total || group_bucket(keys[i - 1]) != group_bucket(k[j])) edge = j * BUCKET_GROUP + t;
+      if (i == 0 || i >= total || (((u32)keys[i - 1] ^ (u32)k[j]) & mask) != 0) edge = j * BUCKET_GROUP + t;
     }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) edge = min(edge, (u32)__shfl_xor(edge, o, WAVE));
@@ -3660,16 +3680,17 @@ __global__ void __launch_bounds__(256) k_sig_list_large(Src src, const int *__re
         const K p = KO::load(src, j);
         if (Q > 1 && (sub_hash((u64)p) & (Q - 1)) != q) continue;
         u32 sl = KO::hash(p) & (PS - 1);
+        const bool full = set_full(&sh_fill[1]);  // at most one insertion per thread lands after the mark
         while (true) {
           const K cur = set[sl];
           if (cur == p) break;
           if (cur == KO::EMPTY) {
-            if (sh_fill[1]) break;  // overflowed: the pass is redone with more sub-partitions
+            if (full) break;  // overflowed: the pass is redone with more sub-partitions
             const K old = atomicCAS(&set[sl], KO::EMPTY, p);
             if (old == KO::EMPTY) {
               pacc += KO::mix(p);
               ++pcnt;
-              if (atomicAdd(&sh_fill[0], 1u) + 1u >= (u32)(PS / 4 * 3)) sh_fill[1] = 1u;
+              if (atomicAdd(&sh_fill[0], 1u) + 1u >= (u32)(PS / 4 * 3)) mark_full(&sh_fill[1]);
               break;
             }
             if (old == p) break;

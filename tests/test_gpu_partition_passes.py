@@ -1,0 +1,42 @@
+"""Grouping by partition (GPU) where a bucket holds more keys than one workgroup's set, against the
+CPU reference: few bucket bits on a small graph put up to 30,000 distinct keys in a bucket (the set
+is marked full at 3,072 of 4,096 slots), so whole passes overflow and are split again and again."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+import graphgen
+import oracle
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+def twins(half, seed):
+    """Rows of two or three labelled entries, nearly all different; row half + i repeats row i."""
+    rng = np.random.default_rng(seed)
+    deg = rng.integers(2, 4, half)
+    src = np.repeat(np.arange(half), deg)
+    dst, lab = rng.integers(0, 2 * half, len(src)), rng.integers(0, 1 << 20, len(src))
+    return graphgen.from_edges(2 * half, np.concatenate([src, src + half]), np.concatenate([dst, dst]),
+                               np.concatenate([lab, lab]), None, name=f"twins_{half}")
+
+
+@pytest.mark.parametrize("bits", [0, 2, 3, 6])
+@pytest.mark.parametrize("half", [6_000, 30_000])
+def test_overflowing_buckets(half, bits, monkeypatch):
+    import paper_2204_05821_amd as kb
+    print(f"[partition passes] half={half} bits={bits}", flush=True)
+    monkeypatch.setenv("KBISIM_DEBUG_GROUP_MIN", "1")
+    monkeypatch.setenv("KBISIM_DEBUG_GROUP_BITS", str(bits))
+    g = twins(half, bits)
+    exp, ec = oracle.refine(g, 3)
+    assert ec[0] > 0.99 * half
+    r = kb.refiner_for(g, kmax=3)
+    ids, counts = r.refine(3)
+    assert counts == ec
+    for a, b in zip(ids, exp):
+        assert np.array_equal(a.cpu().numpy(), b)
+    r.close()
