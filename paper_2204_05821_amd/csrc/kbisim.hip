@@ -163,6 +163,7 @@ struct Tuning {
   int scan_items = SCAN_ITEMS;   // vertices per thread in the numbering scan: 8 or 16
   int64_t group_min = GROUP_MIN;  // non-empty rows from which full steps group by partition
   u32 group_mask = GROUP_MASK;    // bits of the hash that choose a bucket there (fewer: a test knob)
+  int group_mean_bits = GROUP_BITS;  // bucket bits that the sub-passes begun with are planned for
   int gfilter_min = GFILTER_MIN_DIRTY;  // dirty vertices from which update steps use the global filter
 };
 
@@ -988,7 +989,8 @@ int group_by_partition(kbisim_ctx *c, const Schedule &s) {
   LAUNCH_CHECK();
   if ((rc = scan64(st, hist_n, hist, tiles, offs[1]))) return rc;
   k_group_scatter<false><<<grid, GROUP_THREADS, 0, st>>>(N, total, kb, vb, mask, 8, nt, offs[1], ka, va);
-  k_group_buckets<<<blocks_for(N, GROUP_CHUNK), BUCKET_GROUP, 0, st>>>(total, ka, va, mask, c->rep, c->err);
+  k_group_buckets<<<blocks_for(N, GROUP_CHUNK), BUCKET_GROUP, 0, st>>>(total, ka, va, mask, c->tune.group_mean_bits,
+                                                                            c->rep, c->err);
   LAUNCH_CHECK();
   return 0;
 }
@@ -1985,11 +1987,15 @@ int create_impl(const kbisim_graph *g, int kmax, const kbisim_tuning *tuning, vo
     if (q >= 1) c->tune.group_min = q;
   }
   // Test knob: only this many bucket bits, so that small graphs have buckets
-  // of more keys than a workgroup's set holds and take its sub-passes.
+  // of more keys than a workgroup's set holds and take its sub-passes; after
+  // a comma, the bits that their number is planned for (16: planned for one).
   const char *bdbg = getenv("KBISIM_DEBUG_GROUP_BITS");
   if (bdbg && *bdbg) {
     const int b = atoi(bdbg);
     if (b >= 0 && b < GROUP_BITS) c->tune.group_mask = (1u << b) - 1u;
+    const char *comma = strchr(bdbg, ',');
+    const int e = comma ? atoi(comma + 1) : GROUP_BITS;
+    if (e >= 0 && e <= GROUP_BITS) c->tune.group_mean_bits = e;
   }
   // Test knob: update steps use the global dirty-key filter from this many
   // dirty vertices on (at least 1), so that small graphs take that path.

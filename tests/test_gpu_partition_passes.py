@@ -1,6 +1,7 @@
 """Grouping by partition (GPU) where a bucket holds more keys than one workgroup's set, against the
 CPU reference: few bucket bits on a small graph put up to 30,000 distinct keys in a bucket (the set
-is marked full at 3,072 of 4,096 slots), so whole passes overflow and are split again and again."""
+is marked full at 3,072 of 4,096 slots), so whole passes overflow and are split again and again, or
+begin split where that is planned for (the second number: bucket bits of the plan)."""
 from __future__ import annotations
 
 import numpy as np
@@ -24,14 +25,14 @@ def twins(half, seed):
                                np.concatenate([lab, lab]), None, name=f"twins_{half}")
 
 
-@pytest.mark.parametrize("bits", [0, 2, 3, 6])
+@pytest.mark.parametrize("bits", ["0", "2", "3", "6", "0,0", "2,2", "3,1", "2,4", "6,6"])
 @pytest.mark.parametrize("half", [6_000, 30_000])
 def test_overflowing_buckets(half, bits, monkeypatch):
     import paper_2204_05821_amd as kb
     print(f"[partition passes] half={half} bits={bits}", flush=True)
     monkeypatch.setenv("KBISIM_DEBUG_GROUP_MIN", "1")
-    monkeypatch.setenv("KBISIM_DEBUG_GROUP_BITS", str(bits))
-    g = twins(half, bits)
+    monkeypatch.setenv("KBISIM_DEBUG_GROUP_BITS", bits)
+    g = twins(half, len(bits))
     exp, ec = oracle.refine(g, 3)
     assert ec[0] > 0.99 * half
     r = kb.refiner_for(g, kmax=3)
