@@ -1399,10 +1399,15 @@ __device__ inline void group_load(int64_t at, int64_t count, const u64 *__restri
 }
 
 // Digit histogram of each tile (tiles dealt to the XCDs as radix_tile).
-// FIRST: where one digit takes more than 1/8 of a tile (many vertices with one
-// key), equal keys of the tile meet in an LDS table and all but the minimum
-// vertex of each drop out (rep = that vertex), so that the bucket of a key
-// that n vertices share receives about n / GROUP_TILE pairs.
+// FIRST: where a digit has more than GROUP_HOT keys of a tile, the tile's equal
+// keys of that digit meet in an LDS table and all but the minimum vertex of each
+// drop out (rep = that vertex).  The signature kernels leave a key that all rows
+// share once per wave, 64 times a tile, beside 16 keys a digit by chance (more
+// than 40: once in 30,000 tiles); a single workgroup then walks its bucket, of
+// n / 64 pairs.  With the drop the bucket gets n / GROUP_TILE, or at most n / 100
+// of a key below the mark (unlabelled graph of 120M rows, per step: this kernel
+// 0.19 -> 0.44 ms, k_group_buckets 3.73 -> 0.52 ms).
+constexpr int GROUP_HOT = 40;
 template <bool FIRST>
 __global__ void __launch_bounds__(GROUP_THREADS) k_group_hist(int64_t count, const int64_t *__restrict__ total,
                                                               const int *__restrict__ list, int *rep, u64 *keys,
@@ -1429,7 +1434,10 @@ __global__ void __launch_bounds__(GROUP_THREADS) k_group_hist(int64_t count, con
     if (valid[j]) atomicAdd(&h[group_digit(key[j], mask, shift)], 1);
   __syncthreads();
   if constexpr (FIRST) {
-    if (__syncthreads_or(threadIdx.x < 256 && h[threadIdx.x] > GROUP_TILE / 8)) {
+    if (__syncthreads_or(threadIdx.x < 256 && h[threadIdx.x] > GROUP_HOT)) {
+#pragma unroll
+      for (int j = 0; j < GROUP_ITEMS; ++j)  // (keys of the other digits take no part)
+        valid[j] = valid[j] && h[group_digit(key[j], mask, shift)] > GROUP_HOT;
       for (int i = threadIdx.x; i < GROUP_TILE; i += GROUP_THREADS) {
         slot[i] = EMPTY64;
         mins[i] = 0xFFFFFFFFu;
@@ -1441,7 +1449,7 @@ __global__ void __launch_bounds__(GROUP_THREADS) k_group_hist(int64_t count, con
 #pragma unroll
       for (int j = 0; j < GROUP_ITEMS; ++j) {
         if (!valid[j]) continue;
-        u32 s = (u32)(key[j] >> GROUP_BITS) * 0x9E3779B1u >> 20;  // 12 bits: as many slots as keys
+        u32 s = (u32)(key[j] >> GROUP_BITS) * 0x9E3779B1u >> 20;  // 12 bits: no fewer slots than keys
         while (true) {
           const u64 old = atomicCAS(&slot[s], EMPTY64, key[j]);
           if (old == EMPTY64 || old == key[j]) break;

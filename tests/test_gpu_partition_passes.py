@@ -41,3 +41,26 @@ def test_overflowing_buckets(half, bits, monkeypatch):
     for a, b in zip(ids, exp):
         assert np.array_equal(a.cpu().numpy(), b)
     r.close()
+
+
+@pytest.mark.parametrize("n", [4_095, 4_097, 20_011])  # rows; a tile is 4,096 of them
+@pytest.mark.parametrize("shared", [1.0, 0.5])
+@pytest.mark.parametrize("hash_bits", [None, 12])
+def test_key_shared_by_a_tile(n, shared, hash_bits, monkeypatch):
+    """One key for many rows: at least one per wave of 64 is left, over 40 a tile, and all but one of
+    those drop out of the tile.  With 12 hash bits other keys drop out too, and collide."""
+    import paper_2204_05821_amd as kb
+    print(f"[shared key] n={n} shared={shared} bits={hash_bits}", flush=True)
+    monkeypatch.setenv("KBISIM_DEBUG_GROUP_MIN", "1")
+    if hash_bits is not None:
+        monkeypatch.setenv("KBISIM_DEBUG_HASH_BITS", str(hash_bits))
+    rng = np.random.default_rng(n)
+    lab = np.where(rng.random(n) < shared, 0, rng.integers(1, 1 << 20, n))
+    g = graphgen.from_edges(n, np.arange(n), rng.integers(0, n, n), lab, None, name=f"shared_{n}_{shared}")
+    exp, ec = oracle.refine(g, 3)
+    r = kb.refiner_for(g, kmax=3)
+    ids, counts = r.refine(3)
+    assert counts == ec
+    for a, b in zip(ids, exp):
+        assert np.array_equal(a.cpu().numpy(), b)
+    r.close()
