@@ -2042,11 +2042,9 @@ int create_impl(const kbisim_graph *g, int kmax, const kbisim_tuning *tuning, vo
         hipMemcpyAsync(c->next, nxt.data(), 8 * (size_t)num_graphs, hipMemcpyHostToDevice, c->stream) != hipSuccess)
       return fail(KBISIM_EHIP);
     if (n > 0) {
-      // workgroups per graph: all of them for few graphs, no more than there is work for
-      const int share = (int)std::max<int64_t>(
-          1, std::min<int64_t>(GRAPH_GRID / num_graphs, blocks_for(std::max(n, m), 1024)));
-      k_graph_ids<<<(unsigned)(share * std::min<int64_t>(num_graphs, GRAPH_GRID)), 256, 0, c->stream>>>(
-          num_graphs, share, m, c->first, g->row_ptr, g->col, c->gid, c->err);
+      const unsigned vchunks = blocks_for(n, GRAPH_CHUNK);
+      k_graph_ids<<<vchunks + blocks_for(m, GRAPH_CHUNK), 256, 0, c->stream>>>(num_graphs, n, m, vchunks, c->first,
+                                                                             g->row_ptr, g->col, c->gid, c->err);
       if (hipGetLastError() != hipSuccess) return fail(KBISIM_EHIP);
     }
   }
