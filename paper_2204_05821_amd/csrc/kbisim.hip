@@ -1022,7 +1022,7 @@ int settle_collisions(kbisim_ctx *c, const Src &src, const Schedule &s, int *cnt
   }
   if (!careful) {
     ProfScope ps(c, KBISIM_K_PEEL);
-    k_peel_few<Src><<<1, 256, 0, c->stream>>>(src, &cnt[1], c->clA, c->H, c->DC, c->rep, &cnt[2], c->clB, c->err);
+    k_peel_few<Src><<<1, 256, 0, c->stream>>>(src, &cnt[1], c->clA, c->H, c->DC, c->rep, &cnt[2], c->err);
     LAUNCH_CHECK();
   } else {
     if ((rc = peel_round(c, src, &cnt[1], c->clA, &cnt[2], c->clB))) return rc;

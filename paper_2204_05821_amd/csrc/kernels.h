@@ -2017,55 +2017,77 @@ __global__ void __launch_bounds__(256) k_res_verify(Src src, const int *__restri
   }
 }
 
-// The one peeling round inside a step, by one workgroup: collided vertices are
-// few (the tags and home slots of 10^8 keys leave a handful), so the minimum
-// vertex of each hash is found by comparing all pairs in LDS.  More than
-// PEEL_MAX of them are passed on whole; the host then redoes the step with
+// The one peeling round inside a step, by one workgroup: tags and home slots of
+// 10^8 exact keys leave a handful of collided vertices; 32-bit hashes of pairs
+// some hundred to a few thousand on the largest graphs.  The vertices of one hash
+// meet in an LDS table that keeps the smallest; then a thread each compares rows
+// of at most SMALL_MAX entries, and only longer ones go through the workgroup's
+// check one after another (all of them that way: ten steps on 40,000 vertices of
+// one or two entries, hashes cut to 20 bits, 84.9 ms; now 2.6).  With more than PEEL_MAX of them, or some left over, the host redoes the step with
 // k_res_insert and k_res_verify rounds over the whole grid, which costs a call
-// on a large graph as much again, against a few us per collided vertex here.
+// on a large graph as much again: here they are only counted.
 constexpr int PEEL_MAX = 4096;
+static_assert(2 * PEEL_MAX <= BLOCK_SLOTS && PEEL_MAX <= 65536, "slots for twice the hashes, 16-bit places");
 template <class Src>
 __global__ void __launch_bounds__(256) k_peel_few(Src src, const int *__restrict__ count, const int *__restrict__ list,
                                                   const u64 *__restrict__ H, const u32 *__restrict__ DC,
-                                                  int *__restrict__ rep, int *next_count, int *next_list, u32 *err) {
+                                                  int *__restrict__ rep, int *next_count, u32 *err) {
   const int total = *count;
   if (total == 0) return;
   if (total > PEEL_MAX) {
-    for (int i = threadIdx.x; i < total; i += 256) next_list[i] = list[i];
     if (threadIdx.x == 0) *next_count = total;
     return;
   }
   __shared__ u64 set[BLOCK_SLOTS];
-  __shared__ int sh_flag[2];
+  __shared__ u32 mins[BLOCK_SLOTS];
   __shared__ int vs[PEEL_MAX];
-  __shared__ int first[PEEL_MAX];  // smallest vertex with the hash
-  __shared__ u64 hs[PEEL_MAX];
+  __shared__ unsigned short at[PEEL_MAX];     // slot of the vertex's hash
+  __shared__ unsigned short longs[PEEL_MAX];  // places of the vertices whose rows are too long for a thread
+  __shared__ int sh_flag[2];
+  __shared__ int sh_long, sh_left;
+  for (int i = threadIdx.x; i < BLOCK_SLOTS; i += 256) {
+    set[i] = EMPTY64;
+    mins[i] = 0xFFFFFFFFu;
+  }
+  if (threadIdx.x == 0) sh_long = sh_left = 0;
+  __syncthreads();
   for (int i = threadIdx.x; i < total; i += 256) {
-    vs[i] = list[i];
-    hs[i] = H[vs[i]];
+    const int v = list[i];
+    const u64 h = sink_form(H[v]);
+    u32 s = ((u32)h ^ (u32)(h >> 32)) * 0x9E3779B1u >> 19;  // 13 bits: BLOCK_SLOTS
+    while (true) {
+      const u64 old = atomicCAS(&set[s], EMPTY64, h);
+      if (old == EMPTY64 || old == h) break;
+      s = (s + 1) & (BLOCK_SLOTS - 1);
+    }
+    atomicMin(&mins[s], (u32)v);
+    vs[i] = v;
+    at[i] = (unsigned short)s;
   }
   __syncthreads();
-  for (int item = threadIdx.x; item < total; item += 256) {
-    const u64 h = hs[item];
-    int r = vs[item];
-    for (int i = 0; i < total; ++i) r = hs[i] == h ? min(r, vs[i]) : r;
-    first[item] = r;
+  for (int i = threadIdx.x; i < total; i += 256) {
+    const int v = vs[i], r = (int)mins[at[i]];
+    int eq = 1;
+    if (r != v) {
+      if (src.own(v) != src.own(r) || DC[v] != DC[r]) eq = 0;
+      else if (DC[v] != 0) eq = same_small_rows(src, v, r);
+    }
+    if (eq > 0) rep[v] = r;
+    else if (eq == 0) atomicAdd(&sh_left, 1);
+    else longs[atomicAdd(&sh_long, 1)] = (unsigned short)i;
   }
   __syncthreads();
-  for (int item = 0; item < total; ++item) {
-    const int v = vs[item];
-    const int r = first[item];
-    bool ok;
-    if (r == v) ok = true;
-    else if (src.own(v) != src.own(r) || DC[v] != DC[r]) ok = false;
-    else if (DC[v] == 0) ok = true;
-    else ok = wg_subset(src, v, r, DC[r], set, sh_flag, err);
+  const int nlong = sh_long;
+  for (int i = 0; i < nlong; ++i) {
+    const int v = vs[longs[i]], r = (int)mins[at[longs[i]]];
+    const bool ok = wg_subset(src, v, r, DC[r], set, sh_flag, err);
     if (threadIdx.x == 0) {
       if (ok) rep[v] = r;
-      else next_list[(*next_count)++] = v;
+      else ++sh_left;
     }
-    __syncthreads();
   }
+  __syncthreads();
+  if (threadIdx.x == 0) *next_count = sh_left;
 }
 
 // ---------------------------------------------------------------- numbering
