@@ -203,7 +203,7 @@ struct kbisim_ctx {
   u64 hmask = ~0ULL;
   u32 kmask = 0xFFFFFFFFu;  // bits kept of hashed set keys (test knob)
   u64 tmask_steps = 0;   // grouping-table mask of refinement steps (sized by vertices with edges)
-  bool table_dirty = false;  // the grouping table's space was used by partitioned steps
+  size_t table_dirty = 0;  // bytes at the start of the grouping table's space used by partitioned steps
   bool work_eff = false;  // skip singleton blocks, stop at the fixpoint
   int we_steps = 0;       // steps computed by the last work-efficient call
   unsigned char *single[2] = {nullptr, nullptr};  // singleton flags of the last two partitions
@@ -955,31 +955,49 @@ int launch_signatures(kbisim_ctx *c, const Src &src, const Schedule &s, bool zfr
 // k_group_hist).  The signature kernels left the keys at the start of the
 // grouping table's space; pairs go to the list space (vlist, clA, clB: 12 n
 // bytes, free until the lookup), then back to the table's space, which also
-// holds the histograms.  It is cleared before the table is next used
-// (table_dirty).
+// holds the histograms.  What it used there is cleared before the table is next
+// used (table_dirty).
+struct GroupPlan {
+  int64_t nt, hist_n;  // tiles, histogram counters
+  size_t off_ka, off_va, off_hist, off_offs[2], off_tiles, total;
+};
+GroupPlan group_plan(int64_t N) {
+  GroupPlan p{};
+  size_t at = 0;
+  auto take = [&](size_t bytes) {
+    size_t o = at;
+    at = align_up(at + bytes);
+    return o;
+  };
+  p.nt = (N + GROUP_TILE - 1) / GROUP_TILE;
+  p.hist_n = 256 * p.nt;
+  p.off_ka = take(8 * (size_t)N);
+  p.off_va = take(4 * (size_t)N);
+  p.off_hist = take(4 * (size_t)p.hist_n);
+  p.off_offs[0] = take(8 * (size_t)(p.hist_n + 1));
+  p.off_offs[1] = take(8 * (size_t)(p.hist_n + 1));
+  p.off_tiles = take(8 * (size_t)(p.hist_n / SCAN_TILE + 1));
+  p.total = at;
+  return p;
+}
 int group_by_partition(kbisim_ctx *c, const Schedule &s) {
   ProfScope ps(c, KBISIM_K_LOOKUP);
   hipStream_t st = c->stream;
-  const int64_t N = s.nonempty, nt = (N + GROUP_TILE - 1) / GROUP_TILE, hist_n = 256 * nt;
+  const int64_t N = s.nonempty;
+  const GroupPlan p = group_plan(N);
+  if (p.total > 8 * c->plan.tslots) return KBISIM_EINTERNAL;
+  const int64_t nt = p.nt, hist_n = p.hist_n;
   char *w = (char *)c->table;
-  size_t at = 0;
-  auto take = [&](size_t bytes) {
-    char *p = w + at;
-    at = align_up(at + bytes);
-    return p;
-  };
-  u64 *ka = (u64 *)take(8 * (size_t)N);
-  int *va = (int *)take(4 * (size_t)N);
-  int *hist = (int *)take(4 * (size_t)hist_n);
-  int64_t *offs[2] = {(int64_t *)take(8 * (size_t)(hist_n + 1)), (int64_t *)take(8 * (size_t)(hist_n + 1))};
-  int64_t *tiles = (int64_t *)take(8 * (size_t)(hist_n / SCAN_TILE + 1));
-  if (at > 8 * c->plan.tslots) return KBISIM_EINTERNAL;
+  u64 *ka = (u64 *)(w + p.off_ka);
+  int *va = (int *)(w + p.off_va), *hist = (int *)(w + p.off_hist);
+  int64_t *offs[2] = {(int64_t *)(w + p.off_offs[0]), (int64_t *)(w + p.off_offs[1])};
+  int64_t *tiles = (int64_t *)(w + p.off_tiles);
   u64 *kb = (u64 *)c->vlist;
   int *vb = (int *)(kb + N);
   const int64_t *total = offs[0] + hist_n;  // pairs after the first pass
   const unsigned grid = radix_grid(nt);
   int rc = 0;
-  c->table_dirty = true;
+  c->table_dirty = p.total;
   const u32 mask = c->tune.group_mask;
   k_group_hist<true><<<grid, GROUP_THREADS, 0, st>>>(N, nullptr, s.nzv, c->rep, ka, mask, 0, nt, hist);
   LAUNCH_CHECK();
@@ -995,11 +1013,12 @@ int group_by_partition(kbisim_ctx *c, const Schedule &s) {
   return 0;
 }
 
-// The grouping table empty again after partitioned steps used its space.
+// The grouping table empty again after partitioned steps used its space: only
+// as far as they did (3.5M rows of an 8.4M-vertex graph: 47 MB of 134).
 int clean_table(kbisim_ctx *c) {
-  if (!c->table_dirty) return 0;
-  c->table_dirty = false;
-  return fill_u64(c, c->table, (int64_t)c->plan.tslots, 0);
+  const size_t dirty = c->table_dirty;
+  c->table_dirty = 0;
+  return dirty ? fill_u64(c, c->table, (int64_t)(dirty / sizeof(u64)), 0) : 0;
 }
 
 // Whether full steps of this schedule group by partition.
@@ -1311,7 +1330,7 @@ int refine_impl(kbisim_ctx *c, const int32_t *start, int k, int32_t *const *out,
       if (e != hipSuccess) return hip_fail(e);
       it = c->graphs.emplace(key, exec).first;
     }
-    if (by_partition(c, c->sched)) c->table_dirty = true;  // as the captured steps leave it
+    if (by_partition(c, c->sched)) c->table_dirty = group_plan(c->sched.nonempty).total;  // by the captured steps
     HIP_TRY(hipGraphLaunch(it->second, c->stream));
   } else {
     if ((rc = enqueue_steps(c, p0, 0, k, out, false, k, true, true))) return rc;

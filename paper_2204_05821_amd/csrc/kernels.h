@@ -2023,9 +2023,10 @@ __global__ void __launch_bounds__(256) k_res_verify(Src src, const int *__restri
 // meet in an LDS table that keeps the smallest; then a thread each compares rows
 // of at most SMALL_MAX entries, and only longer ones go through the workgroup's
 // check one after another (all of them that way: ten steps on 40,000 vertices of
-// one or two entries, hashes cut to 20 bits, 84.9 ms; now 2.6).  With more than PEEL_MAX of them, or some left over, the host redoes the step with
-// k_res_insert and k_res_verify rounds over the whole grid, which costs a call
-// on a large graph as much again: here they are only counted.
+// one or two entries, hashes cut to 20 bits, 84.9 ms; now 2.6).  With more than
+// PEEL_MAX of them, or some left over, the host redoes the step with k_res_insert
+// and k_res_verify rounds over the whole grid, which costs a call on a large graph
+// as much again: here they are only counted.
 constexpr int PEEL_MAX = 4096;
 static_assert(2 * PEEL_MAX <= BLOCK_SLOTS && PEEL_MAX <= 65536, "slots for twice the hashes, 16-bit places");
 template <class Src>
