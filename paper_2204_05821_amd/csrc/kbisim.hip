@@ -659,13 +659,16 @@ int radix_sort(hipStream_t s, int64_t m, K *&ka, K *&kb, int lo, int hi, int64_t
 }
 // Entries per target of the context's graph into indeg.  Graphs of at least
 // INDEG_SORT_MIN entries partition the targets first (k_bucket_count): 24M
-// entries 0.95 -> 0.17 ms, 40M 1.65 -> 0.27.  Scratch: the hub-set space, not yet in use.
-constexpr int64_t INDEG_SORT_MIN = (int64_t)1 << 21;
+// entries 0.95 -> 0.17 ms, 40M 1.65 -> 0.27.  Not those of at most INDEG_FEW
+// vertices, where a chunk adds to so few counters that its atomics are cheap
+// (200M entries, create without / with the partition: 2 vertices 3.8 / 7.9 ms,
+// 4: 6.0 / 7.6, 8: 10.3 / 7.3).  Scratch: the hub-set space, not yet in use.
+constexpr int64_t INDEG_SORT_MIN = (int64_t)1 << 21, INDEG_FEW = 4;
 int in_degrees(kbisim_ctx *c, int *indeg) {
   const int64_t n = c->g.n, m = c->g.m;
   hipStream_t s = c->stream;
   int rc = 0;
-  if (m < INDEG_SORT_MIN) {
+  if (m < INDEG_SORT_MIN || n <= INDEG_FEW) {
     if ((rc = fill_i32(c, indeg, n, 0))) return rc;
     if (m > 0) {
       k_indegree<<<(unsigned)std::min<int64_t>(blocks_for(m, INDEG_CHUNK), 1 << 16), 256, 0, s>>>(m, c->g.col, indeg);
@@ -701,8 +704,11 @@ int in_degrees(kbisim_ctx *c, int *indeg) {
     to = next;  // radix_sort left the result in `from`
   }
   if ((rc = fill_i32(c, rest, 1, 0))) return rc;
-  // a bucket of several times the mean is finished by the whole grid
-  const int64_t cap = std::max<int64_t>(1 << 16, 8 * (m / nb));
+  // A bucket of several times the mean is finished by the whole grid (the mean
+  // over 256 buckets at least: a graph of few vertices has fewer, and the cap
+  // then let one workgroup count up to all entries; 200M entries of 40 vertices:
+  // create 7.0 -> 5.7 ms, of two: 98.6 -> 7.9).
+  const int64_t cap = std::max<int64_t>(1 << 16, 8 * (m / std::max<int64_t>(nb, 256)));
   if (shift <= 13)
     k_bucket_count<13><<<(unsigned)nb, BUCKET_THREADS, 0, s>>>(m, n, from, (u32)shift, cap, indeg, starts, rest);
   else
