@@ -224,14 +224,16 @@ int kbisim_batch_destroy(kbisim_batch *b);
  *   out_row_ptr  device int64 [n+1]
  *   out_col      device int32 [m]
  *   out_elabel   device int32 [m] or NULL (zeros when elabel is NULL)
- *   workspace    device, kbisim_transpose_workspace_bytes(n, m) bytes (the
- *                entries are then sorted, 16 bytes of keys each), or at least
- *                kbisim_transpose_workspace_bytes(n, 0): scattered one by one,
- *                several times slower
+ *   workspace    device, at least kbisim_transpose_workspace_bytes(n, m) bytes
+ *                (entries scattered one by one), or
+ *                kbisim_transpose_sort_bytes(n, m): the entries are then
+ *                sorted, several times faster, with 16 bytes more for each of
+ *                them (for 2^20 to 2^31 entries; otherwise the same number)
  * The order of entries inside an output row is unspecified; refinement does
  * not depend on it.  Validates the input first; synchronises `stream`.
  * Errors: EINVAL, ERANGE, ENOSPACE, EGRAPH (invalid input), EHIP.           */
 int kbisim_transpose_workspace_bytes(int64_t n, int64_t m, size_t *bytes);
+int kbisim_transpose_sort_bytes(int64_t n, int64_t m, size_t *bytes);
 int kbisim_transpose(int64_t n, int64_t m, const int64_t *row_ptr, const int32_t *col, const int32_t *elabel,
                      int64_t *out_row_ptr, int32_t *out_col, int32_t *out_elabel, void *workspace, size_t ws_bytes,
                      void *stream);

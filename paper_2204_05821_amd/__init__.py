@@ -79,8 +79,9 @@ def _lib():
     lib.kbisim_batch_create.argtypes = [ctypes.POINTER(_Graph), i64, vp, i32, ctypes.POINTER(Tuning), vp, sz, vp,
                                         ctypes.POINTER(vp)]
     lib.kbisim_batch_refine.argtypes = [vp, i32, ctypes.POINTER(vp), vp]
-    lib.kbisim_transpose_workspace_bytes.argtypes = [i64, i64, ctypes.POINTER(sz)]
-    lib.kbisim_transpose_workspace_bytes.restype = i32
+    for f in (lib.kbisim_transpose_workspace_bytes, lib.kbisim_transpose_sort_bytes):
+        f.argtypes = [i64, i64, ctypes.POINTER(sz)]
+        f.restype = i32
     lib.kbisim_transpose.argtypes = [i64, i64, vp, vp, vp, vp, vp, vp, vp, sz, vp]
     lib.kbisim_transpose.restype = i32
     lib.kbisim_quotient_workspace_bytes.argtypes = [vp, ctypes.POINTER(sz)]
@@ -432,9 +433,9 @@ def transpose(row_ptr: torch.Tensor, col: torch.Tensor, elabel: Optional[torch.T
     elabel = _check(elabel, torch.int32, "elabel", dev)
     n, m = int(row_ptr.numel()) - 1, int(col.numel())
     nbytes = ctypes.c_size_t(0)
-    rc = lib.kbisim_transpose_workspace_bytes(n, m, ctypes.byref(nbytes))
+    rc = lib.kbisim_transpose_sort_bytes(n, m, ctypes.byref(nbytes))
     if rc:
-        raise KbisimError(rc, "kbisim_transpose_workspace_bytes")
+        raise KbisimError(rc, "kbisim_transpose_sort_bytes")
     with torch.cuda.device(dev):
         out_rp = torch.empty(n + 1, dtype=torch.int64, device=dev)
         out_col = torch.empty(max(m, 0), dtype=torch.int32, device=dev)
@@ -443,7 +444,7 @@ def transpose(row_ptr: torch.Tensor, col: torch.Tensor, elabel: Optional[torch.T
             ws = torch.empty(int(nbytes.value), dtype=torch.uint8, device=dev)
         except torch.cuda.OutOfMemoryError:
             # no room for sort keys: the smaller workspace of the entry-by-entry scatter
-            lib.kbisim_transpose_workspace_bytes(n, 0, ctypes.byref(nbytes))
+            lib.kbisim_transpose_workspace_bytes(n, m, ctypes.byref(nbytes))
             ws = torch.empty(int(nbytes.value), dtype=torch.uint8, device=dev)
         torch.cuda.current_stream().synchronize()
         rc = lib.kbisim_transpose(n, m, _ptr(row_ptr), _ptr(col), _ptr(elabel), _ptr(out_rp), _ptr(out_col),

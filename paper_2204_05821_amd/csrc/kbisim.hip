@@ -2542,6 +2542,13 @@ TransposePlan transpose_plan(int64_t n, int64_t m) {
 int kbisim_transpose_workspace_bytes(int64_t n, int64_t m, size_t *bytes) {
   if (!bytes || n < 0 || m < 0) return KBISIM_EINVAL;
   if (n >= (int64_t(1) << 31)) return KBISIM_ERANGE;
+  *bytes = transpose_plan(n, m).total;
+  return KBISIM_OK;
+}
+
+int kbisim_transpose_sort_bytes(int64_t n, int64_t m, size_t *bytes) {
+  if (!bytes || n < 0 || m < 0) return KBISIM_EINVAL;
+  if (n >= (int64_t(1) << 31)) return KBISIM_ERANGE;
   *bytes = transpose_plan(n, m).sort_total;
   return KBISIM_OK;
 }
