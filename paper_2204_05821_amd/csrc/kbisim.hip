@@ -1097,7 +1097,7 @@ int run_step(kbisim_ctx *c, const Src &src, const Schedule &s, int *out, int64_t
     }
     const int count = s.nzv ? (int)s.nonempty : n;
     if (partition) {
-      k_resolve<Src><<<blocks_for(blocks_for(count, RESOLVE_V), 256), 256, 0, c->stream>>>(
+      k_resolve<Src><<<blocks_for(count, 4 * RESOLVE_V), 256, 0, c->stream>>>(
           src, count, s.nzv, c->DC, c->rep, &cnt[0], c->vlist, &cnt[1], c->clA);
     } else if (count) {
       k_lookup<Src><<<blocks_for(count, 256), 256, 0, c->stream>>>(
