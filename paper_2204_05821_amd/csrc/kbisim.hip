@@ -1000,21 +1000,21 @@ int group_by_partition(kbisim_ctx *c, const Schedule &s) {
   int64_t *tiles = (int64_t *)(w + p.off_tiles);
   u64 *kb = (u64 *)c->vlist;
   int *vb = (int *)(kb + N);
-  const int64_t *total = offs[0] + hist_n;  // pairs after the first pass
+  const int64_t *total = offs[0] + hist_n, *left = offs[1] + hist_n;  // pairs after each pass
   const unsigned grid = radix_grid(nt);
   int rc = 0;
   c->table_dirty = p.total;
   const u32 mask = c->tune.group_mask;
-  k_group_hist<true><<<grid, GROUP_THREADS, 0, st>>>(N, nullptr, s.nzv, c->rep, ka, mask, 0, nt, hist);
+  k_group_hist<false><<<grid, GROUP_THREADS, 0, st>>>(N, nullptr, nullptr, nullptr, ka, mask, 0, nt, hist);
   LAUNCH_CHECK();
   if ((rc = scan64(st, hist_n, hist, tiles, offs[0]))) return rc;
-  k_group_scatter<true><<<grid, GROUP_THREADS, 0, st>>>(N, nullptr, ka, s.nzv, mask, 0, nt, offs[0], kb, vb);
-  k_group_hist<false><<<grid, GROUP_THREADS, 0, st>>>(N, total, nullptr, nullptr, kb, mask, 8, nt, hist);
+  k_group_scatter<<<grid, GROUP_THREADS, 0, st>>>(N, nullptr, ka, s.nzv, mask, 0, offs[0], kb, vb);
+  k_group_hist<true><<<grid, GROUP_THREADS, 0, st>>>(N, total, vb, c->rep, kb, mask, 8, nt, hist);
   LAUNCH_CHECK();
   if ((rc = scan64(st, hist_n, hist, tiles, offs[1]))) return rc;
-  k_group_scatter<false><<<grid, GROUP_THREADS, 0, st>>>(N, total, kb, vb, mask, 8, nt, offs[1], ka, va);
-  k_group_buckets<<<blocks_for(N, GROUP_CHUNK), BUCKET_GROUP, 0, st>>>(total, ka, va, mask, c->tune.group_mean_bits,
-                                                                            c->rep, c->err);
+  k_group_scatter<<<grid, GROUP_THREADS, 0, st>>>(N, total, kb, vb, mask, 8, offs[1], ka, va);
+  k_group_buckets<<<blocks_for(N, GROUP_CHUNK), BUCKET_GROUP, 0, st>>>(left, ka, va, mask, c->tune.group_mean_bits,
+                                                                       c->rep, c->err);
   LAUNCH_CHECK();
   return 0;
 }

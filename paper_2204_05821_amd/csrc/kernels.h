@@ -1401,39 +1401,54 @@ constexpr int GROUP_SLOTS = 4096;  // LDS table slots (48 KB with the minima)
 // Digit of a pass: 8 bits of the bucket.
 __device__ inline u32 group_digit(u64 h, u32 mask, int shift) { return ((u32)h & mask) >> shift & 255u; }
 
-// Pair `at` of a pass: with FIRST a key of the signature kernels (EMPTY64: none)
-// and, with vals (the list of non-empty vertices), its vertex; else one of the
-// pairs of the pass before.
-template <bool FIRST>
+// Pairs of a pass (the first: all rows; the second: what the first left), and
+// this workgroup's tile of them (>= the number of tiles: none).  The tiles that
+// hold pairs are dealt to the XCDs as in radix_tile, and their histograms lie
+// together: dealt out over the rows, the pairs of a step with few keys all fell
+// to the first XCD (unlabelled graph of 120M rows: the second histogram 415 -> 134
+// us, the scatters 241 -> 201 on average).
+__device__ inline int64_t group_tiles(int64_t count, const int64_t *total, int64_t &pairs, int64_t &tile) {
+  pairs = total ? *total : count;
+  const int64_t nt = (pairs + GROUP_TILE - 1) / GROUP_TILE;
+  tile = (int64_t)(blockIdx.x / XCDS) < (nt + XCDS - 1) / XCDS ? radix_tile(nt) : nt;
+  return nt;
+}
+
+// Pair `at` of a pass: its key (EMPTY64: none) and, with vals, its vertex.
 __device__ inline void group_load(int64_t at, int64_t count, const u64 *__restrict__ keys,
                                   const int *__restrict__ vals, bool &valid, u64 &key, int &v) {
-  valid = at < count;
-  key = valid ? __builtin_nontemporal_load(&keys[at]) : 0ULL;
-  v = valid && vals ? __builtin_nontemporal_load(&vals[at]) : 0;
-  if constexpr (FIRST) valid = valid && key != EMPTY64;
+  const bool in = at < count;
+  key = in ? __builtin_nontemporal_load(&keys[at]) : EMPTY64;
+  v = in && vals ? __builtin_nontemporal_load(&vals[at]) : 0;
+  valid = key != EMPTY64;
 }
 
 // Digit histogram of each tile (tiles dealt to the XCDs as radix_tile).
-// FIRST: where a digit has more than GROUP_HOT keys of a tile, the tile's equal
-// keys of that digit meet in an LDS table and all but the minimum vertex of each
-// drop out (rep = that vertex).  The signature kernels leave a key that all rows
-// share once per wave, 64 times a tile, beside 16 keys a digit by chance (more
-// than 40: once in 30,000 tiles); a single workgroup then walks its bucket, of
-// n / 64 pairs.  With the drop the bucket gets n / GROUP_TILE, or at most n / 100
-// of a key below the mark (unlabelled graph of 120M rows, per step: this kernel
-// 0.19 -> 0.44 ms, k_group_buckets 3.73 -> 0.52 ms).
+// DROP (second pass): keys that many rows share drop out, all but one per tile,
+// which a single workgroup would otherwise walk in the key's bucket.  A tile now
+// holds one digit or two of the first pass, so the pairs of such a key (one per
+// wave of rows) lie together: where a digit has more than GROUP_HOT keys of a tile
+// (16 are there by chance, more than 40 once in 30,000 tiles), its equal keys meet
+// in an LDS table and all but the minimum vertex of each drop out (rep = that
+// vertex).  A bucket gets at most about n / 26,000 pairs of one key (dropped in the
+// first pass, by the same mark, where rows lie as they come: n / 100).  Unlabelled
+// graphs, per step, k_group_buckets with drops in the first pass and in the second:
+// 4.8M entries 38 / 14 us, 24M 173 / 37; both histograms together 22 / 27, 82 / 108.
 constexpr int GROUP_HOT = 40;
-template <bool FIRST>
+template <bool DROP>
 __global__ void __launch_bounds__(GROUP_THREADS) k_group_hist(int64_t count, const int64_t *__restrict__ total,
-                                                              const int *__restrict__ list, int *rep, u64 *keys,
-                                                              u32 mask, int shift, int64_t ntiles,
+                                                              const int *__restrict__ vals, int *rep, u64 *keys,
+                                                              u32 mask, int shift, int64_t max_tiles,
                                                               int *__restrict__ hist) {
   __shared__ int h[256];
-  __shared__ u64 slot[FIRST ? GROUP_TILE : 1];
-  __shared__ u32 mins[FIRST ? GROUP_TILE : 1];
-  const int64_t tile = radix_tile(ntiles);
+  __shared__ u64 slot[DROP ? GROUP_TILE : 1];
+  __shared__ u32 mins[DROP ? GROUP_TILE : 1];
+  int64_t cnt, tile;
+  const int64_t ntiles = group_tiles(count, total, cnt, tile);
+  // (the scan goes over the counters of max_tiles tiles: zeros past those used)
+  if (blockIdx.x >= ntiles && blockIdx.x < max_tiles && threadIdx.x < 256)
+    hist[(int64_t)blockIdx.x * 256 + threadIdx.x] = 0;
   if (tile >= ntiles) return;
-  const int64_t cnt = FIRST ? count : *total;
   if (threadIdx.x < 256) h[threadIdx.x] = 0;
   __syncthreads();
   u64 key[GROUP_ITEMS];
@@ -1442,13 +1457,13 @@ __global__ void __launch_bounds__(GROUP_THREADS) k_group_hist(int64_t count, con
 #pragma unroll
   for (int j = 0; j < GROUP_ITEMS; ++j) {
     int none;
-    group_load<FIRST>(i0 + j * GROUP_THREADS, cnt, keys, nullptr, valid[j], key[j], none);
+    group_load(i0 + j * GROUP_THREADS, cnt, keys, nullptr, valid[j], key[j], none);
   }
 #pragma unroll
   for (int j = 0; j < GROUP_ITEMS; ++j)
     if (valid[j]) atomicAdd(&h[group_digit(key[j], mask, shift)], 1);
   __syncthreads();
-  if constexpr (FIRST) {
+  if constexpr (DROP) {
     if (__syncthreads_or(threadIdx.x < 256 && h[threadIdx.x] > GROUP_HOT)) {
 #pragma unroll
       for (int j = 0; j < GROUP_ITEMS; ++j)  // (keys of the other digits take no part)
@@ -1460,18 +1475,19 @@ __global__ void __launch_bounds__(GROUP_THREADS) k_group_hist(int64_t count, con
       __syncthreads();
       int at[GROUP_ITEMS], v[GROUP_ITEMS];
 #pragma unroll
-      for (int j = 0; j < GROUP_ITEMS; ++j) v[j] = valid[j] ? list[i0 + j * GROUP_THREADS] : 0;
+      for (int j = 0; j < GROUP_ITEMS; ++j) v[j] = valid[j] ? vals[i0 + j * GROUP_THREADS] : 0;
 #pragma unroll
       for (int j = 0; j < GROUP_ITEMS; ++j) {
         if (!valid[j]) continue;
         u32 s = (u32)(key[j] >> GROUP_BITS) * 0x9E3779B1u >> 20;  // 12 bits: no fewer slots than keys
         while (true) {
-          const u64 old = atomicCAS(&slot[s], EMPTY64, key[j]);
+          u64 old = slot[s];
+          if (old == EMPTY64) old = atomicCAS(&slot[s], EMPTY64, key[j]);
           if (old == EMPTY64 || old == key[j]) break;
           s = (s + 1) & (GROUP_TILE - 1);
         }
         at[j] = (int)s;
-        atomicMin(&mins[s], (u32)v[j]);
+        if (mins[s] > (u32)v[j]) atomicMin(&mins[s], (u32)v[j]);
       }
       __syncthreads();
 #pragma unroll
@@ -1491,11 +1507,10 @@ __global__ void __launch_bounds__(GROUP_THREADS) k_group_hist(int64_t count, con
 }
 
 // Stable scatter of a tile's pairs by their digit (as k_radix_scatter).
-template <bool FIRST>
 __global__ void __launch_bounds__(GROUP_THREADS) k_group_scatter(int64_t count, const int64_t *__restrict__ total,
                                                                  const u64 *__restrict__ keys,
                                                                  const int *__restrict__ vals, u32 mask, int shift,
-                                                                 int64_t ntiles, const int64_t *__restrict__ offs,
+                                                                 const int64_t *__restrict__ offs,
                                                                  u64 *__restrict__ out_keys,
                                                                  int *__restrict__ out_vals) {
   constexpr int NW = GROUP_THREADS / WAVE;
@@ -1505,11 +1520,10 @@ __global__ void __launch_bounds__(GROUP_THREADS) k_group_scatter(int64_t count, 
   __shared__ int wcnt[NW][256];
   __shared__ u32 sh_w[4];
   __shared__ int sh_n;
-  const int64_t tile = radix_tile(ntiles);
+  int64_t cnt, tile;
+  const int64_t ntiles = group_tiles(count, total, cnt, tile);
   if (tile >= ntiles) return;
   const int t = threadIdx.x, lane = t & 63, w = t >> 6;
-  const int64_t cnt = FIRST ? count : *total;
-  if (tile * GROUP_TILE >= cnt) return;
   const int64_t goff = t < 256 ? offs[(int64_t)t * ntiles + tile] : 0;
   const u64 lt = (1ULL << lane) - 1ULL;
   u64 key[GROUP_ITEMS];
@@ -1518,7 +1532,7 @@ __global__ void __launch_bounds__(GROUP_THREADS) k_group_scatter(int64_t count, 
   const int64_t i0 = tile * GROUP_TILE + w * (WAVE * GROUP_ITEMS) + lane;
 #pragma unroll
   for (int j = 0; j < GROUP_ITEMS; ++j)
-    group_load<FIRST>(i0 + j * WAVE, cnt, keys, vals, valid[j], key[j], val[j]);
+    group_load(i0 + j * WAVE, cnt, keys, vals, valid[j], key[j], val[j]);
 #pragma unroll
   for (int q = 0; q < 256 / WAVE; ++q) wcnt[w][q * WAVE + lane] = 0;
   __builtin_amdgcn_wave_barrier();
@@ -1807,7 +1821,8 @@ __global__ void __launch_bounds__(256) k_resolve(Src src, int count, const int *
     int eq = 0;
     if (act) {
       const int r = key_minimum(rep, x);
-      if (src.own(x) == src.own(r) && DC[x] == DC[r]) eq = same_small_rows(src, x, r);
+      if (src.own(x) == src.own(r)) eq = same_small_rows(src, x, r);
+      if (eq < 0 && DC[x] != DC[r]) eq = 0;  // (equal short rows need no look at their counts)
       if (eq != 0) rep[x] = r;
     }
     __builtin_amdgcn_wave_barrier();  // (places up to b + 63 have been read)

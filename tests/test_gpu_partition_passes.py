@@ -47,8 +47,8 @@ def test_overflowing_buckets(half, bits, monkeypatch):
 @pytest.mark.parametrize("shared", [1.0, 0.5])
 @pytest.mark.parametrize("hash_bits", [None, 12])
 def test_key_shared_by_a_tile(n, shared, hash_bits, monkeypatch):
-    """One key for many rows: at least one per wave of 64 is left, over 40 a tile, and all but one of
-    those drop out of the tile.  With 12 hash bits other keys drop out too, and collide."""
+    """One key for many rows: at least one per wave of 64 reaches the second pass, over 40 a tile, and
+    all but one of a tile drop out.  With 12 hash bits other keys drop out too, and collide."""
     import paper_2204_05821_amd as kb
     print(f"[shared key] n={n} shared={shared} bits={hash_bits}", flush=True)
     monkeypatch.setenv("KBISIM_DEBUG_GROUP_MIN", "1")
