@@ -132,7 +132,7 @@ __device__ inline u64 finalize_key(u64 acc, u32 dc, u32 own) {
 
 // Where a key goes: into the grouping table, or (table NULL) to the partition
 // (k_group_*): keys[i] for non-empty row i, EMPTY64 where another vertex of the
-// wave speaks for this one, and rep[v] = that vertex (or v itself).
+// range speaks for this one, and rep[v] = that vertex (or v itself).
 struct KeySink {
   u64 *table;
   u64 tmask;
@@ -477,8 +477,7 @@ __device__ inline void key_insert(u64 *table, u64 tmask, u64 *zrep, u64 h, u32 d
 // entries 169 -> 64 us; a graph with a key per vertex runs as before.
 // Must be reached by the whole wave; slots is this wave's own region.
 constexpr int FIRST_SLOTS = 256;
-// *speaker: the lane that goes on for this one (itself if it goes on).
-__device__ inline bool wave_first_of_key(u32 *slots, bool act, u64 h, int *speaker = nullptr) {
+__device__ inline bool wave_first_of_key(u32 *slots, bool act, u64 h) {
   const int lane = threadIdx.x & (WAVE - 1);
 #pragma unroll
   for (int i = 0; i < FIRST_SLOTS / WAVE; ++i) slots[lane + i * WAVE] = 0xFFFFFFFFu;
@@ -488,7 +487,6 @@ __device__ inline bool wave_first_of_key(u32 *slots, bool act, u64 h, int *speak
   __builtin_amdgcn_wave_barrier();
   const int m = act ? (int)slots[at] : lane;
   const u64 hm = __shfl(h, m, WAVE);
-  if (speaker) *speaker = hm == h ? m : lane;
   return act && (m == lane || hm != h);
 }
 
@@ -866,35 +864,32 @@ __global__ void __launch_bounds__(NT) k_sig_range(Src src, const Range *__restri
     H[v] = h;
     DC[v] = c;
   }
-  // (the set is no longer read: its space holds the key slots)
+  // One key of the workgroup goes on, as in wave_first_of_key: two barriers more
+  // than per wave, but a quarter of the pairs or device-wide atomics of keys that
+  // many vertices share (unlabelled graphs, ten steps: table, 1M vertices 1.09 ->
+  // 1.00 ms; partition, 4.8M entries 3.32 -> 3.27, 72M 49.0 -> 47.9).  The set is no
+  // longer read: its space holds the slots.
+  constexpr int NS = 4 * FIRST_SLOTS;
+  static_assert(sizeof(set) >= NS * sizeof(u32), "key slots of the workgroup");
   u32 *slots = reinterpret_cast<u32 *>(set);
-  if (sink.table) {
-    // One insert per key of the workgroup, as wave_first_of_key: two barriers
-    // more than per wave, but a quarter of the device-wide atomics on keys that
-    // many vertices share (unlabelled graph of 1M vertices: 1.09 -> 1.00 ms per
-    // call; a 10k-vertex graph as before).
-    constexpr int NS = 4 * FIRST_SLOTS;
-    static_assert(sizeof(set) >= NS * sizeof(u32), "key slots of the workgroup");
-    if (keyed) acc[t] = h;
+  if (keyed) {
+    acc[t] = h;
+    cnt[t] = (u32)v;
+  }
 #pragma unroll
-    for (int i = 0; i < NS / NT; ++i) slots[t + i * NT] = 0xFFFFFFFFu;
-    __syncthreads();
-    const u32 at = (u32)(h >> 20) & (NS - 1);
-    if (keyed) atomicMin(&slots[at], (u32)t);
-    __syncthreads();
-    if (keyed) {
-      const u32 m = slots[at];
-      if (m == (u32)t || acc[m] != h) table_insert(sink.table, sink.tmask, h, (u32)v, epoch);
-    }
-  } else {
-    int speaker;
-    static_assert(sizeof(set) >= NT / WAVE * FIRST_SLOTS * sizeof(u32), "key slots of the waves");
-    const bool first = wave_first_of_key(slots + w * FIRST_SLOTS, keyed, h, &speaker);
-    const int vs = __shfl(v, speaker, WAVE);
-    if (keyed) {
-      sink.rep[v] = vs;
-      sink.keys[rg.v0 + t] = first ? sink_form(h) : EMPTY64;
-    }
+  for (int i = 0; i < NS / NT; ++i) slots[t + i * NT] = 0xFFFFFFFFu;
+  __syncthreads();
+  const u32 at = (u32)(h >> 20) & (NS - 1);
+  if (keyed) atomicMin(&slots[at], (u32)t);
+  __syncthreads();
+  if (!keyed) return;
+  u32 m = slots[at];
+  if (acc[m] != h) m = (u32)t;
+  if (!sink.table) {
+    sink.rep[v] = (int)cnt[m];
+    sink.keys[rg.v0 + t] = m == (u32)t ? sink_form(h) : EMPTY64;
+  } else if (m == (u32)t) {
+    table_insert(sink.table, sink.tmask, h, (u32)v, epoch);
   }
 }
 
@@ -1384,7 +1379,7 @@ __device__ inline int64_t radix_tile(int64_t ntiles) {
 // The table's inserts are device-wide atomics on random lines (about 25 G/s
 // here) and every vertex probes a random line again to find its minimum.
 // Large steps group without it: the signature kernels leave H, and rep[v] = v
-// for one vertex per key of a wave (rep = that vertex for the wave's others,
+// for one vertex per key of a workgroup (rep = that vertex for its others,
 // which go no further); (H, v) pairs are partitioned by 16 hash bits in two
 // stable radix passes; workgroups then find the minimum vertex of each key of
 // whole buckets in LDS, and write rep[v] only where the minimum is another
@@ -1427,7 +1422,7 @@ __device__ inline void group_load(int64_t at, int64_t count, const u64 *__restri
 // DROP (second pass): keys that many rows share drop out, all but one per tile,
 // which a single workgroup would otherwise walk in the key's bucket.  A tile now
 // holds one digit or two of the first pass, so the pairs of such a key (one per
-// wave of rows) lie together: where a digit has more than GROUP_HOT keys of a tile
+// range of rows) lie together: where a digit has more than GROUP_HOT keys of a tile
 // (16 are there by chance, more than 40 once in 30,000 tiles), its equal keys meet
 // in an LDS table and all but the minimum vertex of each drop out (rep = that
 // vertex).  A bucket gets at most about n / 26,000 pairs of one key (dropped in the

@@ -43,12 +43,12 @@ def test_overflowing_buckets(half, bits, monkeypatch):
     r.close()
 
 
-@pytest.mark.parametrize("n", [4_095, 4_097, 20_011])  # rows; a tile is 4,096 of them
+@pytest.mark.parametrize("n", [4_097, 10_240, 10_241, 30_011])  # rows, in ranges of 256
 @pytest.mark.parametrize("shared", [1.0, 0.5])
 @pytest.mark.parametrize("hash_bits", [None, 12])
 def test_key_shared_by_a_tile(n, shared, hash_bits, monkeypatch):
-    """One key for many rows: at least one per wave of 64 reaches the second pass, over 40 a tile, and
-    all but one of a tile drop out.  With 12 hash bits other keys drop out too, and collide."""
+    """One key for many rows: one per range reaches the second pass, and where that makes over 40 in a
+    tile of 4,096 pairs all but one of them drop out.  With 12 hash bits other keys collide with it."""
     import paper_2204_05821_amd as kb
     print(f"[shared key] n={n} shared={shared} bits={hash_bits}", flush=True)
     monkeypatch.setenv("KBISIM_DEBUG_GROUP_MIN", "1")
