@@ -2573,12 +2573,14 @@ int kbisim_transpose(int64_t n, int64_t m, const int64_t *row_ptr, const int32_t
     HIP_TRY(hipStreamSynchronize(s));
     return KBISIM_OK;
   }
-  // validate the input (row offsets monotone from 0 to m, targets in range)
+  // validate the input (row offsets monotone from 0 to m, targets in range); the
+  // largest label is asked for only where entries may be sorted (it takes 5 us)
+  const bool sortable = p.sort_total > p.total && ws_bytes >= p.sort_total;
   k_fill_i32<<<1, 64, 0, s>>>((int *)err, 2, 0);
   k_validate_rows<<<blocks_for(n + 1, 256), 256, 0, s>>>(n, m, row_ptr, err, ERR_GRAPH_ROWPTR);
   if (m > 0) {
     validate_vals(s, m, col, n, err, ERR_GRAPH_COL);
-    if (elabel) validate_vals(s, m, elabel, -1, err, ERR_GRAPH_ELABEL, err + 1);
+    if (elabel) validate_vals(s, m, elabel, -1, err, ERR_GRAPH_ELABEL, sortable ? err + 1 : nullptr);
   }
   HIP_TRY(hipGetLastError());
   u32 bad[2] = {0, 0};
@@ -2592,7 +2594,7 @@ int kbisim_transpose(int64_t n, int64_t m, const int64_t *row_ptr, const int32_t
   // against 6.1).
   const u32 sb = (u32)std::max(1, bit_width((uint64_t)(n - 1)));
   const u32 lb = elabel && out_elabel ? (u32)bit_width(bad[1]) : 0u;
-  if (m > 0 && p.sort_total > p.total && ws_bytes >= p.sort_total && 2 * sb + lb <= 64) {
+  if (sortable && 2 * sb + lb <= 64) {
     u64 *ka = (u64 *)(w + p.off_ka), *kb = (u64 *)(w + p.off_kb);
     k_transpose_keys<<<blocks_for(m, TKEY_CHUNK), 256, 0, s>>>(n, m, row_ptr, col, lb ? elabel : nullptr, sb, lb, ka);
     HIP_TRY(hipGetLastError());
