@@ -916,7 +916,8 @@ int launch_signatures(kbisim_ctx *c, const Src &src, const Schedule &s, bool zfr
   }
   if (zfresh && range_tier && s.nonempty < c->g.n) {
     ProfScope ps(c, KBISIM_K_LOOKUP);  // it forms representatives; a launch of the range kernel holds entries
-    k_sig_empty<Src><<<blocks_for(c->g.n, 256), 256, 0, c->stream>>>(src, (int)c->g.n, c->DC, c->zrep, c->cur, skip_in);
+    k_sig_empty<Src><<<blocks_for(c->g.n, EMPTY_VERTS), EMPTY_THREADS, 0, c->stream>>>(src, (int)c->g.n, c->DC,
+                                                                                       c->zrep, c->cur, skip_in);
     LAUNCH_CHECK();
   }
   if ((rc = launch_ranges(c, src, s, sink, skip_in, range_tier))) return rc;
