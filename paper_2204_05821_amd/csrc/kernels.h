@@ -1787,50 +1787,46 @@ __device__ inline void four_pairs(const Src &src, int64_t first, int count, u64 
   for (int u = 0; u < 4; ++u) p[u] = u < count ? p[u] : EMPTY64;
 }
 
-// Whether rows of dv and dr entries (1 .. N each) hold the same pairs.  r's
-// pairs are kept in registers (static indexing); every pair of v must occur
-// among them, and every entry of r must be met by some pair of v (set equality
-// in both directions, so it does not rest on the distinct counts).
-template <int N, class Src>
-__device__ inline bool same_rows(const Src &src, int64_t bv, int dv, int64_t br, int dr) {
-  u64 rp[N];
-#pragma unroll
-  for (int g = 0; g < N; g += 4) {
-    if (g < dr) four_pairs(src, br + g, dr - g, rp + g);
-    else rp[g] = rp[g + 1] = rp[g + 2] = rp[g + 3] = EMPTY64;
-  }
-  const u32 want = (u32)((1ull << dr) - 1ull);
-  u32 met = 0;
-  bool ok = true;
-  for (int g = 0; g < dv && ok; g += 4) {
-    u64 p[4];
-    four_pairs(src, bv + g, dv - g, p);
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      u32 hit = 0;
-#pragma unroll
-      for (int q = 0; q < N; ++q) hit |= (rp[q] == p[u] ? 1u : 0u) << q;
-      met |= hit;
-      ok = ok && (hit != 0 || g + u >= dv);
-    }
-  }
-  return ok && (met & want) == want;
-}
-
 // 1 or 0: the rows of v and r hold the same pairs or not; -1: one of them has
-// more than SMALL_MAX entries.  Loads are what bounds it, so four entries of a row
-// are in flight at a time (one after the other: unlabelled graphs of 20M vertices
-// and 160M entries, ten steps 64.3 -> 60.0 ms; 60M and 72M entries, 47.9 -> 46.5;
-// 1M vertices, through k_lookup, 0.99 -> 0.96).
+// more than SMALL_MAX entries.  Every pair of v must occur in r and every pair of
+// r in v (set equality in both directions, so it does not rest on the distinct
+// counts).  Loads are what bounds it, so four entries of a row are in flight at a
+// time, and RU pairs of r are held, v being read again for each RU of them: with
+// all 16 held, lookups of mostly heads have too few waves in flight, and with 4,
+// rows of 5 to 8 entries are read twice.  Ten steps, entry by entry / 16 held / 8 /
+// 4: unlabelled graphs of 20M vertices and 160M entries 64.3 / 59.6 / 62.9 / 82.5
+// ms, 60M and 72M 47.9 / 46.5 / 46.4 / 46.7, 1M and 1.2M (k_lookup) 0.99 / 0.94 /
+// 0.91 / 0.91; work-efficient call on 250M entries 8.29 / 8.42 / 8.32 / 8.31.
 template <class Src>
 __device__ inline int same_small_rows(const Src &src, int v, int r) {
+  constexpr int RU = Src::GRAPH ? 8 : 4;  // (label sets are short)
   const int64_t bv = src.begin(v), lv = src.end(v) - bv;
   const int64_t br = src.begin(r), lr = src.end(r) - br;
   if (lv > SMALL_MAX || lr > SMALL_MAX) return -1;
   const int dv = (int)lv, dr = (int)lr;
-  if (dv == 0 || dr == 0) return dv == dr;
-  if (max(dv, dr) <= 4) return same_rows<4>(src, bv, dv, br, dr);
-  return same_rows<SMALL_MAX>(src, bv, dv, br, dr);
+  u32 in_r = 0, in_v = 0;  // entries of v found in r, and of r found in v
+  for (int g = 0; g < dr; g += RU) {
+    u64 rp[RU];
+#pragma unroll
+    for (int q = 0; q < RU; q += 4) {
+      if (q == 0 || g + q < dr) four_pairs(src, br + g + q, dr - g - q, rp + q);
+      else rp[q] = rp[q + 1] = rp[q + 2] = rp[q + 3] = EMPTY64;
+    }
+    for (int i = 0; i < dv; i += 4) {
+      u64 p[4];
+      four_pairs(src, bv + i, dv - i, p);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        u32 hit = 0;
+#pragma unroll
+        for (int q = 0; q < RU; ++q) hit |= (rp[q] == p[u] ? 1u : 0u) << q;
+        in_v |= hit << g;
+        in_r |= (hit != 0 ? 1u : 0u) << (i + u);
+      }
+    }
+  }
+  const u32 all_v = (1u << dv) - 1u, all_r = (1u << dr) - 1u;
+  return (in_r & all_v) == all_v && (in_v & all_r) == all_r ? 1 : 0;
 }
 
 // From the vertex that spoke for v, if any, to the minimum of its key.  Links
