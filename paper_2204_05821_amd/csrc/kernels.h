@@ -1791,12 +1791,13 @@ __device__ inline void four_pairs(const Src &src, int64_t first, int count, u64 
 // more than SMALL_MAX entries.  Every pair of v must occur in r and every pair of
 // r in v (set equality in both directions, so it does not rest on the distinct
 // counts).  Loads are what bounds it, so four entries of a row are in flight at a
-// time, and RU pairs of r are held, v being read again for each RU of them: with
-// all 16 held, lookups of mostly heads have too few waves in flight, and with 4,
-// rows of 5 to 8 entries are read twice.  Ten steps, entry by entry / 16 held / 8 /
-// 4: unlabelled graphs of 20M vertices and 160M entries 64.3 / 59.6 / 62.9 / 82.5
-// ms, 60M and 72M 47.9 / 46.5 / 46.4 / 46.7, 1M and 1.2M (k_lookup) 0.99 / 0.94 /
-// 0.91 / 0.91; work-efficient call on 250M entries 8.29 / 8.42 / 8.32 / 8.31.
+// time, and RU pairs of v are held, r (the row that many lanes may share) being read
+// again for each RU of them: with all 16 held, lookups of mostly heads have too few
+// waves in flight.  Ten steps, entry by entry / 16 pairs of r held / 8 of r / 8 of v:
+// unlabelled graphs of 20M vertices and 160M entries 64.3 / 59.6 / 63.3 / 60.6 ms,
+// 60M and 72M 47.9 / 46.5 / 46.4 / 46.4, 1M and 1.2M (k_lookup) 0.99 / 0.94 / 0.91 /
+// 0.91; work-efficient calls on 250M entries 8.3 / 8.4 / 8.3 / 8.3, on 50M entries of
+// 9 a row that share their keys 3.48 / - / 3.61 / 3.37.
 template <class Src>
 __device__ inline int same_small_rows(const Src &src, int v, int r) {
   constexpr int RU = Src::GRAPH ? 8 : 4;  // (label sets are short)
@@ -1805,23 +1806,23 @@ __device__ inline int same_small_rows(const Src &src, int v, int r) {
   if (lv > SMALL_MAX || lr > SMALL_MAX) return -1;
   const int dv = (int)lv, dr = (int)lr;
   u32 in_r = 0, in_v = 0;  // entries of v found in r, and of r found in v
-  for (int g = 0; g < dr; g += RU) {
-    u64 rp[RU];
+  for (int g = 0; g < dv; g += RU) {
+    u64 vp[RU];
 #pragma unroll
     for (int q = 0; q < RU; q += 4) {
-      if (q == 0 || g + q < dr) four_pairs(src, br + g + q, dr - g - q, rp + q);
-      else rp[q] = rp[q + 1] = rp[q + 2] = rp[q + 3] = EMPTY64;
+      if (q == 0 || g + q < dv) four_pairs(src, bv + g + q, dv - g - q, vp + q);
+      else vp[q] = vp[q + 1] = vp[q + 2] = vp[q + 3] = EMPTY64;
     }
-    for (int i = 0; i < dv; i += 4) {
+    for (int i = 0; i < dr; i += 4) {
       u64 p[4];
-      four_pairs(src, bv + i, dv - i, p);
+      four_pairs(src, br + i, dr - i, p);
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
         u32 hit = 0;
 #pragma unroll
-        for (int q = 0; q < RU; ++q) hit |= (rp[q] == p[u] ? 1u : 0u) << q;
-        in_v |= hit << g;
-        in_r |= (hit != 0 ? 1u : 0u) << (i + u);
+        for (int q = 0; q < RU; ++q) hit |= (vp[q] == p[u] ? 1u : 0u) << q;
+        in_r |= hit << g;
+        in_v |= (hit != 0 ? 1u : 0u) << (i + u);
       }
     }
   }
