@@ -1170,10 +1170,11 @@ int enqueue_steps(kbisim_ctx *c, const int32_t *prev, int i0, int k, int32_t *co
     if (ahead) {
       if ((i - i0) % STEP_SEGMENT == 0) {
         ProfScope ps(c, KBISIM_K_FILL);
-        k_prepare_steps<<<1, 64, 0, c->stream>>>(c->dep, c->counters, i, std::min(STEP_SEGMENT, k - i), c->err,
+        const bool table = c->work_eff || !by_partition(c, c->sched);
+        k_prepare_steps<<<1, 64, 0, c->stream>>>(c->dep, c->counters, i, std::min(STEP_SEGMENT, k - i), table, c->err,
                                                  reset_err && i == i0 ? 1 : 0);
         LAUNCH_CHECK();
-        if (c->work_eff || !by_partition(c, c->sched)) {
+        if (table) {
           k_clear_if<<<CLEAR_GRID, 256, 0, c->stream>>>(c->dep, c->table, (int64_t)c->plan.tslots, nullptr, 0, nullptr,
                                                         0);
           LAUNCH_CHECK();

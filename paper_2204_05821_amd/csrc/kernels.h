@@ -4499,26 +4499,28 @@ __global__ void k_advance(u32 *dep, u32 mask) {
 // all of them: row i of `rows` (STEP_ROW words) gets zeroed counters and, from
 // STEP_EPOCHS on, the step's own epochs, so a step launches nothing for them.
 // Epochs that would wrap inside the segment start again from 1, and the table
-// is cleared before it (k_clear_if).  reset_err: also clear the error word.
+// is cleared before it (k_clear_if).  Without `table` (steps that group by
+// partition) the table's epoch stays: slots that such steps do not overwrite must
+// not meet their epoch again.  reset_err: also clear the error word.
 constexpr int STEP_ROW = 16, STEP_EPOCHS = 8, STEP_SEGMENT = 14;
-__global__ void k_prepare_steps(u32 *dep, int *rows, int i0, int cnt, u32 *err, int reset_err) {
+__global__ void k_prepare_steps(u32 *dep, int *rows, int i0, int cnt, int table, u32 *err, int reset_err) {
   const int t = threadIdx.x;
   u32 e = dep[EP_TABLE];
   const u32 z = dep[EP_ZERO], hub = dep[EP_HUB], ec = dep[EP_CTABLE];
-  const bool wrap = e + (u32)cnt > 15u;
+  const bool wrap = table && e + (u32)cnt > 15u;
   if (wrap) e = 0;
   if (t < cnt) {
     int *row = rows + (int64_t)(i0 + t) * STEP_ROW;
     for (int j = 0; j < STEP_EPOCHS; ++j) row[j] = 0;
     u32 *d = reinterpret_cast<u32 *>(row) + STEP_EPOCHS;
-    d[EP_TABLE] = e + (u32)t + 1u;
+    d[EP_TABLE] = table ? e + (u32)t + 1u : e;
     d[EP_CTABLE] = ec;  // (these steps do not use the peeling table)
     d[EP_ZERO] = z + (u32)t + 1u;
     d[EP_HUB] = hub;
   }
   __syncthreads();  // every thread has read dep
   if (t == 0) {
-    dep[EP_TABLE] = e + (u32)cnt;
+    dep[EP_TABLE] = table ? e + (u32)cnt : e;
     dep[EP_ZERO] = z + (u32)cnt;
     dep[EP_CLR_TABLE] = wrap;
     dep[EP_CLR_CTABLE] = 0;

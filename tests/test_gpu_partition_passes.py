@@ -64,3 +64,39 @@ def test_key_shared_by_a_tile(n, shared, hash_bits, monkeypatch):
     for a, b in zip(ids, exp):
         assert np.array_equal(a.cpu().numpy(), b)
     r.close()
+
+
+@pytest.mark.parametrize("n", [9_000, 40_000])
+def test_table_calls_between_partitioned_ones(n, monkeypatch):
+    """The table, cleared only where partitioned steps wrote, over many epochs: work-efficient calls and
+    updates among refine calls of odd lengths, each against the reference."""
+    import paper_2204_05821_amd as kb
+    from tests.test_gpu_incremental import edited
+    print(f"[table between] n={n}", flush=True)
+    monkeypatch.setenv("KBISIM_DEBUG_GROUP_MIN", "1")
+    rng = np.random.default_rng(n)
+    src, dst = graphgen.uniform_edges(n, n + n // 4, 5)
+    g = graphgen.from_edges(n, src, dst, None, rng.integers(0, 3, n), name=f"sparse_{n}")
+    chain = [oracle.refine(g, k) for k in range(1, 10)]
+    r = kb.refiner_for(g, kmax=9)
+    for turn in range(12):
+        for k, mode in ((1 + turn % 9, True), (9 - turn % 5, False), (3 + turn % 4, False), (1 + turn % 3, True)):
+            r.work_efficient(mode)
+            ids, counts = r.refine(k)
+            exp, ec = chain[k - 1]
+            assert counts == ec, (turn, k, mode)
+            for a, b in zip(ids, exp):
+                assert np.array_equal(a.cpu().numpy(), b)
+    r.work_efficient(False)
+    r.incremental()
+    for turn in range(6):
+        ids, counts = r.refine(9)
+        assert counts == chain[8][1]
+        g2, rows = edited(g, rng, 5, 5)
+        e2, c2 = oracle.refine(g2, 9)
+        rp, col, el, _, _ = kb.to_device(g2)
+        ids, counts = r.update(rp, col, el, torch.from_numpy(rows).cuda(), 9)
+        assert counts == c2
+        for a, b in zip(ids, e2):
+            assert np.array_equal(a.cpu().numpy(), b)
+    r.close()
