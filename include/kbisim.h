@@ -114,7 +114,9 @@ typedef struct {
 int kbisim_workspace_bytes(const kbisim_graph *g, int kmax, size_t *bytes);
 
 /* Validate the graph, compute P_0 and the static degree schedule, and bind a
- * context to `stream`.  Synchronises `stream` once (to report validation).
+ * context to `stream`.  Synchronises `stream` twice (validation, then P_0 and
+ * the totals of the schedule), once more for label sets and twice more where
+ * rows are long enough to be hubs.
  * kmax >= 0 bounds k in later calls.  On success *out receives the context.
  * Errors: EINVAL, ERANGE, ENOSPACE, EGRAPH, EHIP.                           */
 int kbisim_create(const kbisim_graph *g, int kmax, void *workspace, size_t ws_bytes, void *stream,
@@ -260,13 +262,17 @@ int kbisim_quotient(kbisim_ctx *c, const int32_t *src_pid, const int32_t *dst_pi
 
 /* ---- tracing and measurement -------------------------------------------- */
 
-/* Kernel kinds reported by the per-kernel profiler. */
+/* Kernel kinds reported by the per-kernel profiler.  A launch count is the
+ * number of timed scopes, which hold one kernel or several: K_LOOKUP's are the
+ * lookups, the two kernels of empty signatures in a call's first step, and the
+ * whole partition (its passes and buckets) where steps group by one, so its
+ * time per scope averages over unlike ones.                                 */
 #define KBISIM_K_SIG_RANGE 0   /* signatures of runs of low-degree vertices        */
 #define KBISIM_K_SIG_BLOCK 1   /* signatures, one workgroup per row (1k-8k entries) */
 #define KBISIM_K_HUB_STAGE 2   /* hub rows: chunk dedupe and partitioned staging   */
 #define KBISIM_K_HUB_REDUCE 3  /* hub rows: per-partition dedupe and sums          */
 #define KBISIM_K_HUB_FINAL 4   /* hub key hashes (and very large hubs)             */
-#define KBISIM_K_LOOKUP 5      /* representative lookup + small exact checks       */
+#define KBISIM_K_LOOKUP 5      /* grouping: partition or lookup, small exact checks */
 #define KBISIM_K_VERIFY 6      /* exact checks of larger rows                      */
 #define KBISIM_K_PEEL 7        /* collision peeling rounds                         */
 #define KBISIM_K_SCAN 8        /* first-vertex numbering scan                      */

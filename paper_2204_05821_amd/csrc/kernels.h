@@ -1423,7 +1423,7 @@ static_assert(GROUP_TILE == 4096, "12-bit slots");
 constexpr int GROUP_BITS = 16;                           // bucket bits, the low ones of H
 constexpr u32 GROUP_MASK = (1u << GROUP_BITS) - 1u;      // (the kernels take the mask: a test keeps fewer)
 constexpr int GROUP_CHUNK = 2048;  // pairs per workgroup of k_group_buckets, extended to whole buckets
-constexpr int GROUP_SLOTS = 4096;  // LDS table slots (48 KB with the minima)
+constexpr int GROUP_SLOTS = 4096;  // slots of the set of k_group_buckets (32 KB)
 // Digit of a pass: 8 bits of the bucket.
 __device__ inline u32 group_digit(u64 h, u32 mask, int shift) { return ((u32)h & mask) >> shift & 255u; }
 
@@ -2596,7 +2596,7 @@ __global__ void k_remap(int64_t m, const int *__restrict__ col, const int *__res
 // logarithmic scale (8 per octave, at most ORDER_BUCKETS) and rows ordered by
 // bucket with a counting sort in LDS, instead of a full sort: the bitonic
 // networks that did that took 66 barriers per range, 0.9 ms on a graph of 23M
-// entries (now 0.15), for the same gather rate.
+// entries (now 0.15), and calls are as fast (100M-edge graph 8.73 / 8.78 ms).
 constexpr int ORDER_BUCKETS = 256;
 __device__ inline u32 order_bucket(u32 rank) {
   const u32 x = (rank >> 5) + 8u;  // lines of 32 ids; the first 8 exactly
@@ -3041,7 +3041,7 @@ __global__ void __launch_bounds__(256) k_quotient_hubs(Src src, const Chunk *__r
 // Tiles of 8192 keys: the 32 keys a digit gets on average leave as whole
 // lines.  A summary graph of 125M entries (7 passes): 8.5 ms with 8192-key
 // tiles against 9.25 with 4096; 16384 leave one workgroup per CU (8.6
-// against 7.6 ms, both with the mapping below).
+// against 7.6 ms, both with the mapping of radix_tile).
 constexpr int RADIX_ITEMS = 16;  // keys per thread per tile
 constexpr int RADIX_THREADS = 512;
 constexpr int RADIX_TILE = RADIX_THREADS * RADIX_ITEMS;
