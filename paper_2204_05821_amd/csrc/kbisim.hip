@@ -1016,8 +1016,12 @@ int group_by_partition(kbisim_ctx *c, const Schedule &s) {
   LAUNCH_CHECK();
   if ((rc = scan64(st, hist_n, hist, tiles, offs[1]))) return rc;
   k_group_scatter<<<grid, GROUP_THREADS, 0, st>>>(N, total, kb, vb, mask, 8, offs[1], ka, va);
-  k_group_buckets<<<blocks_for(N, GROUP_CHUNK), BUCKET_GROUP, 0, st>>>(left, ka, va, mask, c->tune.group_mean_bits,
-                                                                       c->rep, c->err);
+  auto buckets = [&](auto kernel, int u) {
+    kernel<<<blocks_for(N, u * BUCKET_GROUP), BUCKET_GROUP, 0, st>>>(left, ka, va, mask, c->tune.group_mean_bits, c->rep,
+                                                                     c->err);
+  };
+  if ((N >> c->tune.group_mean_bits) < BUCKET_WIDE) buckets(k_group_buckets<2>, 2);
+  else buckets(k_group_buckets<4>, 4);
   LAUNCH_CHECK();
   return 0;
 }

@@ -1422,7 +1422,6 @@ constexpr int GROUP_TILE = GROUP_THREADS * GROUP_ITEMS;  // pairs per radix tile
 static_assert(GROUP_TILE == 4096, "12-bit slots");
 constexpr int GROUP_BITS = 16;                           // bucket bits, the low ones of H
 constexpr u32 GROUP_MASK = (1u << GROUP_BITS) - 1u;      // (the kernels take the mask: a test keeps fewer)
-constexpr int GROUP_CHUNK = 2048;  // pairs per workgroup of k_group_buckets, extended to whole buckets
 constexpr int GROUP_SLOTS = 4096;  // slots of the set of k_group_buckets (32 KB)
 // Digit of a pass: 8 bits of the bucket.
 __device__ inline u32 group_digit(u64 h, u32 mask, int shift) { return ((u32)h & mask) >> shift & 255u; }
@@ -1639,25 +1638,29 @@ __global__ void __launch_bounds__(GROUP_THREADS) k_group_scatter(int64_t count, 
 // more than 3/4 of the slots distinct is redone in Q sub-passes by other hash
 // bits, Q doubled until each fits.  From about 185M pairs on the mean bucket is
 // longer than that by itself and says how many sub-passes to begin with, so that
-// none is walked in vain (mean_bits: bucket bits of that estimate): 200M rows
-// 3.56 -> 2.60 ms.  Between 100M and 134M, where only stretches of two buckets
-// are too long (fewer and fewer of them), redoing those costs less than two
-// passes over all (120M rows: 2.15 ms).
+// none is walked in vain (mean_bits: bucket bits of that estimate).
+// U: pairs in flight per thread; a chunk is one round of them.  With 2 (chunks of
+// 1,024) a stretch holds one bucket of up to 2,048 pairs; two in a stretch of 2,048
+// overflow from 100M rows on.  From BUCKET_WIDE pairs a bucket, of which every
+// stretch holds one at most, 4 in flight read it faster.  Distinct keys, U = 2 / 4,
+// ms per step: 4M rows 0.036 / 0.052, 40M 0.34 / 0.39, 90M 0.81 / 1.03, 110M 1.05 /
+// 2.03, 130M 1.38 / 2.06, 160M 2.02 / 1.72, 200M 2.70 / 2.21.
+constexpr int64_t BUCKET_WIDE = 2048;
 constexpr int BUCKET_GROUP = 512;
 constexpr u32 BUCKET_FIT = GROUP_SLOTS / 16 * 11;  // mean pairs of a planned pass: 3/4 less 5 standard deviations
+template <int U>
 __global__ void __launch_bounds__(BUCKET_GROUP) k_group_buckets(const int64_t *__restrict__ total_p,
                                                        const u64 *__restrict__ keys, const int *__restrict__ vals,
                                                        u32 mask, int mean_bits, int *__restrict__ rep,
                                                        u32 *err) {
-  constexpr int U = 4, BATCH = BUCKET_GROUP * U;
-  static_assert(GROUP_CHUNK % BATCH == 0, "a chunk is whole batches");  // (launched with BUCKET_GROUP threads)
+  constexpr int BATCH = BUCKET_GROUP * U;  // a chunk, and the pairs in flight (launched with BUCKET_GROUP threads)
   static_assert(GROUP_SLOTS / 4 > BUCKET_GROUP, "an empty slot ends every probe");
   __shared__ u64 slot[GROUP_SLOTS];
   __shared__ u32 sh[2];
   __shared__ u32 fill[2];
   const int t = threadIdx.x;
   const int64_t total = *total_p;
-  const int64_t c0 = (int64_t)blockIdx.x * GROUP_CHUNK;
+  const int64_t c0 = (int64_t)blockIdx.x * BATCH;
   if (c0 >= total) return;
   u32 Q = 1;
   while ((u32)(total >> mean_bits) / Q > BUCKET_FIT) Q <<= 1;
@@ -1715,7 +1718,7 @@ __global__ void __launch_bounds__(BUCKET_GROUP) k_group_buckets(const int64_t *_
     __syncthreads();
     edge = sh[0];
     u32 lo = 0, hi = BATCH;
-    const bool past = at >= c0 + GROUP_CHUNK;
+    const bool past = at >= c0 + BATCH;
     if (past) {
       hi = edge;
     } else if (b0 < 0) {
@@ -1732,7 +1735,7 @@ __global__ void __launch_bounds__(BUCKET_GROUP) k_group_buckets(const int64_t *_
       break;
     }
     if (at + BATCH >= total) break;
-    if (b0 < 0 && at + BATCH >= c0 + GROUP_CHUNK) return;  // no bucket starts in this chunk
+    if (b0 < 0 && at + BATCH >= c0 + BATCH) return;  // no bucket starts in this chunk
   }
   if (b0 < 0) return;
   __syncthreads();
