@@ -41,12 +41,13 @@ constexpr int MIN_RANGE_EDGES = 1024;  // smallest tunable range capacity
 constexpr int MIN_HUB_CHUNK = 2048;    // smallest tunable hub chunk
 // Non-empty rows from which a full step groups by partition (9 launches more,
 // no device-wide atomics) instead of through the table.  k = 10 calls, table /
-// partition, in ms: nearly distinct keys, rows of 8 entries 0.5M 0.97 / 1.10, 1.0M
-// 1.57 / 1.51, 1.8M 2.85 / 2.45, rows of 24 1.0M 2.38 / 2.26; RMAT rows of 25 1.0M
-// 2.79 / 2.99, 1.85M 4.83 / 4.77, 3.5M (the 100M-edge graph) 9.31 / 8.62; RDF 11M
-// 31.2 / 27.7.  Rows that share keys (unlabelled sparse graphs) stay ahead in the
-// table: 1.4M 1.44 / 1.77, 2.8M 2.66 / 3.05, 42M 43.2 / 46.5; how many do is only
-// known step by step on the device.  The line lies where RMAT rows break even.
+// partition, in ms: nearly distinct keys, rows of 8 entries 0.5M 0.96 / 1.00, 1.0M
+// 1.55 / 1.35, 1.8M 2.87 / 2.29, rows of 24 1.0M 2.38 / 2.14; RMAT rows of 25 1.0M
+// 2.80 / 2.90, 1.85M 4.82 / 4.63, 3.5M (the 100M-edge graph) 9.31 / 8.48; RDF 11M
+// 31.2 / 27.4.  Rows that share keys (unlabelled sparse graphs) stay ahead in the
+// table: 1.4M 1.42 / 1.73, 2.8M 2.68 / 3.04, 42M 43.2 / 46.4; how many do is only
+// known step by step, on the device.  The line lies between: distinct keys would
+// gain from 0.8M on, RMAT rows from 1.4M, shared keys lose less the more rows.
 constexpr int64_t GROUP_MIN = 1800000;
 constexpr int MAX_GRAPH_CACHE = 8;
 constexpr size_t READBACK_MAX = 1 << 16;  // bytes of counters and counts copied back at once

@@ -1415,8 +1415,8 @@ __device__ inline int64_t radix_tile(int64_t ntiles) {
 // stable radix passes; workgroups then find the minimum vertex of each key of
 // whole buckets in LDS, and write rep[v] only where the minimum is another
 // vertex (few, once most blocks are single vertices).  On the 1B-edge graph (40M
-// keys per step) the passes take 1.0 ms; the table's inserts cost the range
-// kernel 1.3 ms (9.49 -> 8.17) and its lookups 1.7 (k_resolve: 0.48).
+// keys per step) the passes and buckets take 0.9 ms; the table's inserts cost the
+// range kernel 1.3 ms (9.49 -> 8.17) and its lookups 1.7 (k_resolve: 0.39).
 constexpr int GROUP_THREADS = 512, GROUP_ITEMS = 8;
 constexpr int GROUP_TILE = GROUP_THREADS * GROUP_ITEMS;  // pairs per radix tile
 static_assert(GROUP_TILE == 4096, "12-bit slots");
